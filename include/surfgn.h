@@ -36,9 +36,10 @@
  *   - The context owns a descriptor table of fixed capacity (SGN_MAX_BATCH
  *     keyframes or keyframe pairs and SGN_MAX_BATCH_FRAMES neighbour frames
  *     per call; about 2 MB on the device and four times that in pinned host
- *     staging memory), the work-queue counters, timing events and captured
- *     HIP graphs.  sgn_create allocates all of it; no other call allocates
- *     device or pinned memory.
+ *     staging memory), the work-queue counters and timing events.  sgn_create
+ *     allocates all of it; no other call allocates device or pinned memory.
+ *     A call for one keyframe (or keyframe pair) passes its descriptors in
+ *     its kernels' arguments and uses no table.
  *   - Calls that need scratch memory (re-gridding, disc render and
  *     placement, the autotuner's state snapshot) take a caller-provided
  *     workspace `ws` of `ws_bytes` bytes: device memory, 256-byte aligned, at
@@ -239,8 +240,7 @@ sgn_status sgn_render_inverse_depth(sgn_ctx* ctx, const sgn_keyframe* kf,
 /* The whole per-keyframe update for many keyframes at once: initialisation
  * of new surfels, the Gauss-Newton iterations in one fused kernel launch
  * (persistent, or one wavefront per work item as the plan says), and the
- * inverse-depth render; the setup + initialisation and render parts (and a
- * persistent GN launch) are replayed from captured HIP graphs.  All
+ * inverse-depth render.  All
  * items must share patch and image dtype.  Results equal those of the
  * per-keyframe calls for the same plan (each surfel is reduced in a fixed
  * order that does not depend on the batch). */

@@ -1,5 +1,5 @@
 // Host side of the surfgn C ABI: argument validation, descriptor tables,
-// launch sequencing, HIP graph capture/replay and the plan autotuner.
+// launch sequencing and the plan autotuner.
 // See include/surfgn.h for the contract of every entry point.
 #include <hip/hip_runtime.h>
 
@@ -9,9 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <map>
 #include <string>
-#include <tuple>
 #include <vector>
 
 #include "../../include/surfgn.h"
@@ -44,15 +42,6 @@ size_t dtype_size(int dt) { return dt == SGN_F32 ? 4 : dt == SGN_F16 ? 2 : 1; }
 constexpr int kRingSlots = 4;
 constexpr int kTimingRing = 64;
 
-struct GraphKey {
-    int dtype, patch, tx, ty, lds, persistent, grid, part, do_init, groups, frames_cap, by_row;
-    bool operator<(const GraphKey& o) const {
-        return std::tie(dtype, patch, tx, ty, lds, persistent, grid, part, do_init, groups, frames_cap, by_row) <
-               std::tie(o.dtype, o.patch, o.tx, o.ty, o.lds, o.persistent, o.grid, o.part, o.do_init,
-                        o.groups, o.frames_cap, o.by_row);
-    }
-};
-
 }  // namespace
 
 struct sgn_ctx {
@@ -70,22 +59,21 @@ struct sgn_ctx {
     uint32_t* counters = nullptr;
     // this device's copy of the static scratch (sgn_transfer_surfels_static)
     void* static_scratch = nullptr;
-    // timing of the last GN kernel
     // timing of the GN kernels: a ring of event pairs, the last kTimingRing
     // launches; gn_start/gn_end point at the latest pair
     hipEvent_t gn_ring[2][kTimingRing] = {};
     int64_t gn_launches = 0;
     hipEvent_t gn_start = nullptr, gn_end = nullptr;
     bool gn_timed = false;
-    // graphs
-    bool use_graphs = true;
-    std::map<GraphKey, hipGraphExec_t> graphs;
 };
 
 namespace {
 
+// The device table: header, keyframes, then frames.  Its staging slot holds
+// the header and keyframes as they are and, from fr_off on, the frames'
+// inputs (host_total bytes).
 struct TableLayout {
-    size_t hdr_off, kf_off, fr_off, total;
+    size_t hdr_off, kf_off, fr_off, total, host_total;
 };
 
 TableLayout layout_for(int n_kf, int n_frames) {
@@ -95,6 +83,7 @@ TableLayout layout_for(int n_kf, int n_frames) {
     L.kf_off = align(sizeof(BatchHeader));
     L.fr_off = align(L.kf_off + sizeof(KfDev) * (size_t)std::max(n_kf, 1));
     L.total = align(L.fr_off + sizeof(FrameDev) * (size_t)std::max(n_frames, 1));
+    L.host_total = align(L.fr_off + sizeof(FrameIn) * (size_t)std::max(n_frames, 1));
     return L;
 }
 
@@ -102,7 +91,8 @@ TableLayout layout_for(int n_kf, int n_frames) {
 // may describe (SGN_MAX_BATCH keyframes or keyframe pairs, SGN_MAX_BATCH_FRAMES
 // neighbour frames), fixed at sgn_create so that no call allocates.
 size_t table_bytes_needed() {
-    size_t b = layout_for(SGN_MAX_BATCH, SGN_MAX_BATCH_FRAMES).total;
+    const TableLayout L = layout_for(SGN_MAX_BATCH, SGN_MAX_BATCH_FRAMES);
+    const size_t b = std::max(L.total, L.host_total);
     const size_t per_pair = std::max(std::max(sizeof(RegridArgs), sizeof(DiscRenderItem)),
                                      std::max(sizeof(DiscPlaceArgs), sizeof(DiscTransferArgs)));
     return std::max(b, per_pair * (size_t)SGN_MAX_BATCH);
@@ -171,6 +161,59 @@ void next_timing_slot(sgn_ctx* c) {
     c->gn_start = c->gn_ring[0][slot];
     c->gn_end = c->gn_ring[1][slot];
     ++c->gn_launches;
+}
+
+// A staging slot whose previous upload has completed.
+sgn_status take_slot(sgn_ctx* c, int& slot) {
+    slot = c->ring_next;
+    c->ring_next = (c->ring_next + 1) % kRingSlots;
+    if (c->ring_used[slot]) SGN_HIP(hipEventSynchronize(c->ring_ev[slot]));
+    return SGN_OK;
+}
+
+// Upload of a filled slot (bytes to copy, frames to form) on the context's stream.
+sgn_status stage(sgn_ctx* c, int slot, size_t bytes, const FrameIn* in, FrameDev* frames, int n_frames) {
+    const hipError_t e = launch_stage(c->host_ring[slot], c->dev_table, (int)((bytes + 15) / 16), in, frames,
+                                      n_frames, c->counters, c->stream);
+    if (e != hipSuccess) return hip_fail(e, "table upload launch");
+    SGN_HIP(hipEventRecord(c->ring_ev[slot], c->stream));
+    c->ring_used[slot] = true;
+    return SGN_OK;
+}
+
+// Geometry, intrinsics and image fields common to tile and disc keyframes.
+void describe_keyframe(const sgn_keyframe& kf, const sgn_surfels& s, KfDev& D) {
+    D.kf_img = kf.kf.data;
+    D.inv_depth = s.inv_depth;
+    D.nx = s.nx; D.ny = s.ny; D.nz = s.nz;
+    D.flags = s.flags;
+    D.cost = s.cost;
+    D.nvalid = s.nvalid;
+    D.last_update = s.last_update;
+    D.width = kf.kf.width;
+    D.height = kf.kf.height;
+    D.kf_pitch = kf.kf.pitch;
+    D.n_nbr = kf.n_nbr;
+    D.nbr_pitch_b = kf.n_nbr > 0 ? kf.nbr[0].pitch * (int32_t)dtype_size(kf.kf.dtype) : 0;
+    D.fx = (float)kf.K.fx; D.fy = (float)kf.K.fy; D.cx = (float)kf.K.cx; D.cy = (float)kf.K.cy;
+    D.fx_d = kf.K.fx; D.fy_d = kf.K.fy; D.cx_d = kf.K.cx; D.cy_d = kf.K.cy;
+    D.kf_scale = kf.kf.scale;
+    D.img_scale = kf.n_nbr > 0 ? kf.nbr[0].scale : 1.f;
+}
+
+// The frames' inputs; the neighbour images of one keyframe share scale and pitch.
+sgn_status describe_frames(const sgn_keyframe& kf, FrameIn* F) {
+    for (int f = 0; f < kf.n_nbr; ++f) {
+        if (kf.nbr[f].scale != kf.nbr[0].scale)
+            return fail(SGN_E_UNSUPPORTED, "neighbour images of one keyframe must share a scale");
+        if (kf.nbr[f].pitch != kf.nbr[0].pitch)
+            return fail(SGN_E_UNSUPPORTED, "neighbour images of one keyframe must share a pitch");
+        F[f].img = kf.nbr[f].data;
+        F[f].K[0] = kf.K.fx; F[f].K[1] = kf.K.fy; F[f].K[2] = kf.K.cx; F[f].K[3] = kf.K.cy;
+        std::memcpy(F[f].R, kf.pose[f].R, sizeof(F[f].R));
+        std::memcpy(F[f].t, kf.pose[f].t, sizeof(F[f].t));
+    }
+    return SGN_OK;
 }
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -397,19 +440,26 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
                   (int)rows_by_index(items, n)};
     if (fl.gn && !gn_variant_supported(var)) return fail(SGN_E_UNSUPPORTED, "plan not supported for this patch");
 
+    // one keyframe's table travels with each launch; several, or a work queue
+    // to clear, take a staging slot and an upload
+    const bool lone = n == 1 && !(fl.gn && plan.persistent);
+    LoneBatch one{};
+    FrameIn one_in[kMaxNbr];
     TableLayout L = layout_for(n, total_frames);
-    st = check_table(c, L.total);
-    if (st) return st;
-    // pick a staging slot whose previous upload has completed
-    int slot = c->ring_next;
-    c->ring_next = (c->ring_next + 1) % kRingSlots;
-    if (c->ring_used[slot]) SGN_HIP(hipEventSynchronize(c->ring_ev[slot]));
-    char* host = (char*)c->host_ring[slot];
+    int slot = 0;
+    char* host = nullptr;
     char* dev = (char*)c->dev_table;
-    BatchHeader* H = (BatchHeader*)(host + L.hdr_off);
-    KfDev* kfs = (KfDev*)(host + L.kf_off);
-    FrameDev* frs = (FrameDev*)(host + L.fr_off);
-    std::memset(host, 0, L.total);
+    if (!lone) {
+        st = check_table(c, std::max(L.total, L.host_total));
+        if (st) return st;
+        st = take_slot(c, slot);
+        if (st) return st;
+        host = (char*)c->host_ring[slot];
+        std::memset(host, 0, L.fr_off);
+    }
+    BatchHeader* H = lone ? &one.one.hdr : (BatchHeader*)(host + L.hdr_off);
+    KfDev* kfs = lone ? &one.one.kf : (KfDev*)(host + L.kf_off);
+    FrameIn* frs = lone ? one_in : (FrameIn*)(host + L.fr_off);
 
     // keyframe order: longest work items first, grouped by XCD queue
     const ItemGeo geo = fl.gn ? item_geo(patch, plan.tiles_x, plan.tiles_y, plan.groups)
@@ -441,24 +491,13 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         const sgn_batch_item& it = items[i];
         const sgn_keyframe& kf = it.kf;
         KfDev& D = kfs[oi];
-        D.kf_img = kf.kf.data;
-        D.inv_depth = it.surfels.inv_depth;
-        D.nx = it.surfels.nx; D.ny = it.surfels.ny; D.nz = it.surfels.nz;
-        D.flags = it.surfels.flags;
-        D.cost = it.surfels.cost;
-        D.nvalid = it.surfels.nvalid;
-        D.last_update = it.surfels.last_update;
+        describe_keyframe(kf, it.surfels, D);
         D.is_new = fl.init ? it.is_new : nullptr;
         D.inv_depth_out = fl.render ? it.inv_depth_out : nullptr;
         D.index_out = fl.render ? it.index_out : nullptr;
-        D.width = kf.kf.width;
-        D.height = kf.kf.height;
-        D.kf_pitch = kf.kf.pitch;
-        D.n_nbr = kf.n_nbr;
         D.gw = kf.kf.width / kf.patch;
         D.gh = kf.kf.height / kf.patch;
         D.patch = kf.patch;
-        D.nbr_pitch_b = kf.n_nbr > 0 ? kf.nbr[0].pitch * (int32_t)dtype_size(kf.kf.dtype) : 0;
         D.frame_base = frame_base;
         D.groups_x = (D.gw + geo.ab - 1) / geo.ab;            // anchor blocks per row
         const int blocks_y = (D.gh + geo.ab - 1) / geo.ab;
@@ -467,21 +506,8 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         D.surfel_base = surfel_base;
         D.pixel_base = pixel_base;
         D.queue = queue_of[i];
-        D.fx = (float)kf.K.fx; D.fy = (float)kf.K.fy; D.cx = (float)kf.K.cx; D.cy = (float)kf.K.cy;
-        D.fx_d = kf.K.fx; D.fy_d = kf.K.fy; D.cx_d = kf.K.cx; D.cy_d = kf.K.cy;
-        D.kf_scale = kf.kf.scale;
-        D.img_scale = kf.n_nbr > 0 ? kf.nbr[0].scale : 1.f;
-        for (int f = 0; f < kf.n_nbr; ++f) {
-            if (kf.nbr[f].scale != D.img_scale)
-                return fail(SGN_E_UNSUPPORTED, "neighbour images of one keyframe must share a scale");
-            if (kf.nbr[f].pitch != kf.nbr[0].pitch)
-                return fail(SGN_E_UNSUPPORTED, "neighbour images of one keyframe must share a pitch");
-            FrameDev& F = frs[frame_base + f];
-            F.img = kf.nbr[f].data;
-            F.pitch = kf.nbr[f].pitch;
-            std::memcpy(F.R, kf.pose[f].R, sizeof(F.R));
-            std::memcpy(F.t, kf.pose[f].t, sizeof(F.t));
-        }
+        st = describe_frames(kf, frs + frame_base);
+        if (st) return st;
         if (D.queue != cur_q) {
             H->queues[D.queue].begin = item_base;
             cur_q = D.queue;
@@ -514,13 +540,15 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     H->do_render = fl.render && any_render;
     H->n_queues = nq;
 
-    SGN_HIP(hipMemcpyAsync(dev, host, L.total, hipMemcpyHostToDevice, c->stream));
-    SGN_HIP(hipEventRecord(c->ring_ev[slot], c->stream));
-    c->ring_used[slot] = true;
-
-    const BatchHeader* dH = (const BatchHeader*)(dev + L.hdr_off);
-    const int frames_cap = (int)((c->table_cap - L.fr_off) / sizeof(FrameDev));
-    const int aux_grid = std::max(1, c->cus) * 8;
+    const BatchHeader* dH = nullptr;
+    if (lone) {
+        if (fl.gn)
+            for (int f = 0; f < total_frames; ++f) frame_constants(one_in[f], one.frames[f]);
+    } else {
+        st = stage(c, slot, L.fr_off, (const FrameIn*)(host + L.fr_off), (FrameDev*)(dev + L.fr_off), total_frames);
+        if (st) return st;
+        dH = (const BatchHeader*)(dev + L.hdr_off);
+    }
     // one wavefront per work item, four per workgroup; with one share per
     // XCD, workgroup b serves share b % kXcds, so the grid covers the largest
     // share kXcds times
@@ -533,101 +561,34 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         np_blocks = kXcds * widest;
     }
     const int gn_grid = plan.persistent ? persistent_grid(c, var, plan) : std::max(1, np_blocks);
-    const bool do_init = H->do_init, do_render = H->do_render;
-    // Kernel sequence in three parts (pre: setup + init, gn, post: render),
-    // each replayed from its own captured graph when the launch shape
-    // repeats; the GN part is bracketed by the context's timing events.
-    auto enqueue_pre = [&](hipStream_t s) -> hipError_t {
-        hipError_t e = launch_setup(dH, c->counters, frames_cap, s);
-        if (e == hipSuccess && do_init) e = launch_init(dH, aux_grid, s);
-        return e;
-    };
-    auto enqueue_gn = [&](hipStream_t s) -> hipError_t {
-        return launch_gn(var, dH, c->counters, plan.persistent, gn_grid, s);
-    };
-    // render: one segment per thread for the larger batches (runs of 256
-    // segments per block, so blocks past the batch's segments return at once)
-    const int render_grid = std::max(1, c->cus) * 32;
-    auto enqueue_post = [&](hipStream_t s) -> hipError_t { return launch_render(dH, render_grid, s); };
-    const bool run_gn = fl.gn && item_base > 0;
-    const bool graph_ok = c->use_graphs && (plan.persistent || !run_gn);
-    auto run_part = [&](int part, bool needed, auto&& enq) -> sgn_status {
-        if (!needed) return SGN_OK;
-        if (!graph_ok) {
-            hipError_t e = enq(c->stream);
-            return e == hipSuccess ? SGN_OK : hip_fail(e, "kernel launch");
-        }
-        GraphKey key{dtype, patch, plan.tiles_x, plan.tiles_y, plan.lds_stage, plan.persistent,
-                     part == 1 ? gn_grid : aux_grid, part, (int)do_init, plan.groups, frames_cap, var.by_row};
-        auto found = c->graphs.find(key);
-        if (found == c->graphs.end()) {
-            hipStream_t cap = nullptr;
-            SGN_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-            hipGraph_t g = nullptr;
-            hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-            if (e == hipSuccess) {
-                hipError_t e2 = enq(cap);
-                e = hipStreamEndCapture(cap, &g);
-                if (e2 != hipSuccess) e = e2;
-            }
-            (void)hipStreamDestroy(cap);
-            if (e != hipSuccess) {
-                if (g) (void)hipGraphDestroy(g);
-                return hip_fail(e, "graph capture");
-            }
-            hipGraphExec_t ex = nullptr;
-            e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(g);
-            if (e != hipSuccess) return hip_fail(e, "graph instantiate");
-            found = c->graphs.emplace(key, ex).first;
-        }
-        SGN_HIP(hipGraphLaunch(found->second, c->stream));
-        return SGN_OK;
-    };
-    st = run_part(0, true, enqueue_pre);
-    if (st) return st;
-    if (run_gn) {
+    hipError_t e = hipSuccess;
+    if (H->do_init) e = launch_init(one.one, dH, std::max(1, c->cus) * 8, c->stream);
+    if (e == hipSuccess && fl.gn && item_base > 0) {
         next_timing_slot(c);
-        SGN_HIP(hipEventRecord(c->gn_start, c->stream));
-        st = run_part(1, true, enqueue_gn);
-        if (st) return st;
-        SGN_HIP(hipEventRecord(c->gn_end, c->stream));
-        c->gn_timed = true;
+        e = launch_gn(var, one, dH, c->counters, plan.persistent, gn_grid, c->stream, c->gn_start, c->gn_end);
+        if (e == hipSuccess) c->gn_timed = true;
     }
-    return run_part(2, do_render, enqueue_post);
+    // one segment per thread for the larger batches (runs of 256 segments per
+    // block, so blocks past the batch's segments return at once)
+    if (e == hipSuccess && H->do_render) e = launch_render(one.one, dH, std::max(1, c->cus) * 32, c->stream);
+    return e == hipSuccess ? SGN_OK : hip_fail(e, "kernel launch");
 }
 
-// Upload a table of n entries through the staging ring into the device
-// table (asynchronous on the context's stream).
-template <class T>
-sgn_status upload_table(sgn_ctx* c, const std::vector<T>& tab) {
-    const size_t bytes = sizeof(T) * tab.size();
-    sgn_status st = check_table(c, bytes);
-    if (st) return st;
-    const int slot = c->ring_next;
-    c->ring_next = (c->ring_next + 1) % kRingSlots;
-    if (c->ring_used[slot]) SGN_HIP(hipEventSynchronize(c->ring_ev[slot]));
-    std::memcpy(c->host_ring[slot], tab.data(), bytes);
-    SGN_HIP(hipMemcpyAsync(c->dev_table, c->host_ring[slot], bytes, hipMemcpyHostToDevice, c->stream));
-    SGN_HIP(hipEventRecord(c->ring_ev[slot], c->stream));
-    c->ring_used[slot] = true;
-    return SGN_OK;
-}
-
-// upload_table for a caller's array (no container, no allocation)
+// Upload of a caller's table of n entries: *dev is its device copy, or null
+// for a single entry, which travels with the launch.
 template <typename T>
-sgn_status upload_array(sgn_ctx* c, const T* tab, int n) {
+sgn_status upload_table(sgn_ctx* c, const T* tab, int n, const T** dev) {
+    *dev = nullptr;
+    if (n == 1) return SGN_OK;
     const size_t bytes = sizeof(T) * (size_t)n;
     sgn_status st = check_table(c, bytes);
     if (st) return st;
-    const int slot = c->ring_next;
-    c->ring_next = (c->ring_next + 1) % kRingSlots;
-    if (c->ring_used[slot]) SGN_HIP(hipEventSynchronize(c->ring_ev[slot]));
+    int slot;
+    st = take_slot(c, slot);
+    if (st) return st;
     std::memcpy(c->host_ring[slot], tab, bytes);
-    SGN_HIP(hipMemcpyAsync(c->dev_table, c->host_ring[slot], bytes, hipMemcpyHostToDevice, c->stream));
-    SGN_HIP(hipEventRecord(c->ring_ev[slot], c->stream));
-    c->ring_used[slot] = true;
-    return SGN_OK;
+    *dev = (const T*)c->dev_table;
+    return stage(c, slot, bytes, nullptr, nullptr, 0);
 }
 
 sgn_status check_disc_item(const sgn_disc_item* it, bool need_nbr) {
@@ -667,18 +628,24 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
     sgn_status st = check_params(prm);
     if (st) return st;
     SGN_HIP(hipSetDevice(c->device));
+    const bool lone = n == 1;             // as in run_batch
+    LoneBatch one{};
+    FrameIn one_in[kMaxNbr];
     TableLayout L = layout_for(n, total_frames);
-    st = check_table(c, L.total);
-    if (st) return st;
-    int slot = c->ring_next;
-    c->ring_next = (c->ring_next + 1) % kRingSlots;
-    if (c->ring_used[slot]) SGN_HIP(hipEventSynchronize(c->ring_ev[slot]));
-    char* host = (char*)c->host_ring[slot];
+    int slot = 0;
+    char* host = nullptr;
     char* dev = (char*)c->dev_table;
-    BatchHeader* H = (BatchHeader*)(host + L.hdr_off);
-    KfDev* kfs = (KfDev*)(host + L.kf_off);
-    FrameDev* frs = (FrameDev*)(host + L.fr_off);
-    std::memset(host, 0, L.total);
+    if (!lone) {
+        st = check_table(c, std::max(L.total, L.host_total));
+        if (st) return st;
+        st = take_slot(c, slot);
+        if (st) return st;
+        host = (char*)c->host_ring[slot];
+        std::memset(host, 0, L.fr_off);
+    }
+    BatchHeader* H = lone ? &one.one.hdr : (BatchHeader*)(host + L.hdr_off);
+    KfDev* kfs = lone ? &one.one.kf : (KfDev*)(host + L.kf_off);
+    FrameIn* frs = lone ? one_in : (FrameIn*)(host + L.fr_off);
     // batches of eight keyframes or more: the keyframes split into one share
     // per XCD, balanced by work (surfels x neighbour frames), and workgroup b
     // takes the items of XCD b % kXcds's share in order; within a share (or
@@ -699,41 +666,17 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
         const sgn_disc_item& it = items[order[oi]];
         const sgn_keyframe& kf = it.kf;
         KfDev& D = kfs[oi];
-        D.kf_img = kf.kf.data;
-        D.inv_depth = it.surfels.inv_depth;
-        D.nx = it.surfels.nx; D.ny = it.surfels.ny; D.nz = it.surfels.nz;
-        D.flags = it.surfels.flags;
-        D.cost = it.surfels.cost;
-        D.nvalid = it.surfels.nvalid;
-        D.last_update = it.surfels.last_update;
-        D.width = kf.kf.width;
-        D.height = kf.kf.height;
-        D.kf_pitch = kf.kf.pitch;
-        D.n_nbr = kf.n_nbr;
-        D.nbr_pitch_b = kf.n_nbr > 0 ? kf.nbr[0].pitch * (int32_t)dtype_size(kf.kf.dtype) : 0;
+        describe_keyframe(kf, it.surfels, D);
         D.frame_base = frame_base;
         D.item_base = item_base;
         D.n_items = (it.count + disc_surfels_per_wave(dtype) - 1) / disc_surfels_per_wave(dtype);
         D.surfel_base = surfel_base;
         D.disc_count = it.count;
-        D.fx = (float)kf.K.fx; D.fy = (float)kf.K.fy; D.cx = (float)kf.K.cx; D.cy = (float)kf.K.cy;
-        D.fx_d = kf.K.fx; D.fy_d = kf.K.fy; D.cx_d = kf.K.cx; D.cy_d = kf.K.cy;
-        D.kf_scale = kf.kf.scale;
-        D.img_scale = kf.n_nbr > 0 ? kf.nbr[0].scale : 1.f;
         D.disc_ux = it.ux;
         D.disc_uy = it.uy;
         D.disc_r = it.radius;
-        for (int f = 0; f < kf.n_nbr; ++f) {
-            if (kf.nbr[f].scale != D.img_scale)
-                return fail(SGN_E_UNSUPPORTED, "neighbour images of one keyframe must share a scale");
-            if (kf.nbr[f].pitch != kf.nbr[0].pitch)
-                return fail(SGN_E_UNSUPPORTED, "neighbour images of one keyframe must share a pitch");
-            FrameDev& F = frs[frame_base + f];
-            F.img = kf.nbr[f].data;
-            F.pitch = kf.nbr[f].pitch;
-            std::memcpy(F.R, kf.pose[f].R, sizeof(F.R));
-            std::memcpy(F.t, kf.pose[f].t, sizeof(F.t));
-        }
+        st = describe_frames(kf, frs + frame_base);
+        if (st) return st;
         const int q = share_of[order[oi]];
         if (q != cur_q) {
             H->queues[q].begin = item_base;
@@ -759,16 +702,16 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
     H->lm_lambda = prm->lm_lambda;
     H->do_gn = 1;
     H->n_queues = nq;
-    SGN_HIP(hipMemcpyAsync(dev, host, L.total, hipMemcpyHostToDevice, c->stream));
-    SGN_HIP(hipEventRecord(c->ring_ev[slot], c->stream));
-    c->ring_used[slot] = true;
-    const BatchHeader* dH = (const BatchHeader*)(dev + L.hdr_off);
-    const int frames_cap = (int)((c->table_cap - L.fr_off) / sizeof(FrameDev));
-    hipError_t e = launch_setup(dH, c->counters, frames_cap, c->stream);
-    if (e != hipSuccess) return hip_fail(e, "setup launch");
+    const BatchHeader* dH = nullptr;
+    if (lone) {
+        for (int f = 0; f < total_frames; ++f) frame_constants(one_in[f], one.frames[f]);
+    } else {
+        st = stage(c, slot, L.fr_off, (const FrameIn*)(host + L.fr_off), (FrameDev*)(dev + L.fr_off), total_frames);
+        if (st) return st;
+        dH = (const BatchHeader*)(dev + L.hdr_off);
+    }
     if (item_base > 0) {
         next_timing_slot(c);
-        SGN_HIP(hipEventRecord(c->gn_start, c->stream));
         // neighbour rows read by index unless a row pitch exceeds the
         // descriptor's stride field
         bool by_row = true;
@@ -786,9 +729,9 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
                 widest = std::max(widest, (H->queues[q].end - H->queues[q].begin + wpb - 1) / wpb);
             blocks = kXcds * widest;
         }
-        e = launch_disc_gn(dtype, dH, item_base, std::max(1, blocks), by_row, c->stream);
+        const hipError_t e = launch_disc_gn(dtype, one, dH, item_base, std::max(1, blocks), by_row, c->stream,
+                                            c->gn_start, c->gn_end);
         if (e != hipSuccess) return hip_fail(e, "disc Gauss-Newton launch");
-        SGN_HIP(hipEventRecord(c->gn_end, c->stream));
         c->gn_timed = true;
     }
     return SGN_OK;
@@ -855,11 +798,11 @@ sgn_status sgn_create(sgn_ctx** out, int32_t device, void* hip_stream) {
     if (static_scratch_on(device, &c->static_scratch) != hipSuccess)
         return give_up(SGN_E_DEVICE, "static scratch lookup failed");
     for (int i = 0; i < kRingSlots; ++i)
-        if (hipEventCreateWithFlags(&c->ring_ev[i], hipEventDisableTiming) != hipSuccess)
+        if (hipEventCreateWithFlags(&c->ring_ev[i], hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess)
             return give_up(SGN_E_DEVICE, "event creation failed");
     for (int k = 0; k < 2; ++k)
         for (int i = 0; i < kTimingRing; ++i)
-            if (hipEventCreate(&c->gn_ring[k][i]) != hipSuccess)
+            if (hipEventCreateWithFlags(&c->gn_ring[k][i], hipEventDisableSystemFence) != hipSuccess)
                 return give_up(SGN_E_DEVICE, "event creation failed");
     c->gn_start = c->gn_ring[0][0];
     c->gn_end = c->gn_ring[1][0];
@@ -873,7 +816,6 @@ sgn_status sgn_create(sgn_ctx** out, int32_t device, void* hip_stream) {
             return give_up(SGN_E_NOMEM, "pinned staging allocation failed");
     if (hipMalloc(&c->dev_table, cap) != hipSuccess) return give_up(SGN_E_NOMEM, "device table allocation failed");
     c->table_cap = cap;
-    if (const char* g = std::getenv("SGN_NO_GRAPHS")) c->use_graphs = !(g[0] == '1');
     *out = c;
     return SGN_OK;
 }
@@ -882,7 +824,6 @@ sgn_status sgn_destroy(sgn_ctx* c) {
     if (!c) return SGN_OK;
     hipSetDevice(c->device);
     hipStreamSynchronize(c->stream);
-    for (auto& kv : c->graphs) hipGraphExecDestroy(kv.second);
     for (int i = 0; i < kRingSlots; ++i) {
         if (c->host_ring[i]) hipHostFree(c->host_ring[i]);
         if (c->ring_ev[i]) hipEventDestroy(c->ring_ev[i]);
@@ -1073,9 +1014,10 @@ static sgn_status transfer_impl(sgn_ctx* c, int32_t n, const sgn_grid* src_grids
         tab[k].best = best + tab[k].dst_base;
         tab[k].win = win + tab[k].dst_base;
     }
-    st = upload_array(c, tab, n);
+    const RegridArgs* dtab;
+    st = upload_table(c, tab, n, &dtab);
     if (st) return st;
-    hipError_t e = launch_regrid((const RegridArgs*)c->dev_table, n, (int)src_waves, (int)dst_waves, c->stream);
+    hipError_t e = launch_regrid(tab[0], dtab, n, (int)src_waves, (int)dst_waves, c->stream);
     if (e != hipSuccess) return hip_fail(e, "re-gridding launch");
     return SGN_OK;
 }
@@ -1163,7 +1105,8 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     if (st) return st;
     if (!c) return fail(SGN_E_INVALID, "null context");
     SGN_HIP(hipSetDevice(c->device));
-    st = upload_table(c, tab);
+    const DiscRenderItem* dtab;
+    st = upload_table(c, tab.data(), n, &dtab);
     if (st) return st;
     DiscRenderScratch w;
     w.rec = (DiscRaster*)((char*)ws + lw.rec_off);
@@ -1171,8 +1114,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     w.start = (int32_t*)((char*)ws + lw.start_off);
     w.block_sum = (int32_t*)((char*)ws + lw.block_off);
     w.list = (int32_t*)((char*)ws + lw.list_off);
-    hipError_t e = launch_disc_render((const DiscRenderItem*)c->dev_table, n, (int)total_surfels,
-                                      (int)total_tiles, w, c->stream);
+    hipError_t e = launch_disc_render(tab[0], dtab, n, (int)total_surfels, (int)total_tiles, w, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc render launch");
     return SGN_OK;
 }
@@ -1242,10 +1184,10 @@ sgn_status sgn_disc_place_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t 
     if (!c) return fail(SGN_E_INVALID, "null context");
     SGN_HIP(hipSetDevice(c->device));
     for (int i = 0; i < n; ++i) tab[i].cand_flag = (uint8_t*)ws + tab[i].cand_base;
-    st = upload_table(c, tab);
+    const DiscPlaceArgs* dtab;
+    st = upload_table(c, tab.data(), n, &dtab);
     if (st) return st;
-    hipError_t e = launch_disc_place((const DiscPlaceArgs*)c->dev_table, n, (int)total_cands, (int)total_init,
-                                     c->stream);
+    hipError_t e = launch_disc_place(tab[0], dtab, n, (int)total_cands, (int)total_init, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc placement launch");
     return SGN_OK;
 }
@@ -1306,9 +1248,10 @@ sgn_status sgn_disc_transfer_batch(sgn_ctx* c, int32_t n, const sgn_disc_item* s
         a.counts = counts_outs[k];
     }
     SGN_HIP(hipSetDevice(c->device));
-    sgn_status st = upload_table(c, tab);
+    const DiscTransferArgs* dtab;
+    sgn_status st = upload_table(c, tab.data(), n, &dtab);
     if (st) return st;
-    hipError_t e = launch_disc_transfer((const DiscTransferArgs*)c->dev_table, n, c->stream);
+    hipError_t e = launch_disc_transfer(tab[0], dtab, n, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc transfer launch");
     return SGN_OK;
 }

@@ -44,26 +44,56 @@ struct KfDev {
     int32_t disc_count;           // surfels of the keyframe (an item is a run of them)
 };
 
-// Per-neighbour-frame descriptor.  R and t are the caller's pose in double;
-// hm/kt are written on the device by the setup kernel.
+// Per-neighbour-frame constants of Eq. 6, in device memory or in a lone
+// keyframe's kernel arguments.
 struct FrameDev {
     float zrow[4];  // hm[6], hm[7], kt[2] rounded to float (the q_z row), pad
     const void* img;  // next to zrow: one scalar load per frame fetches both
-    int32_t pitch, pad0;
-    double R[9];
-    double t[3];
     double hm[9];   // K R K^-1
     double kt[3];   // K t
 };
+// What FrameDev is formed from: the caller's pose and the keyframe's
+// intrinsics (fx, fy, cx, cy).
+struct FrameIn {
+    const void* img;
+    double K[4];
+    double R[9];
+    double t[3];
+};
+// K R K^-1 and K t (Eq. 6) in double, the q_z row rounded once to float.  A
+// lone keyframe's frames are formed on the host and a batch's on the device:
+// every operation is an IEEE one and the fused ones are written out, so both
+// give the same bits.
+__host__ __device__ inline void frame_constants(const FrameIn& in, FrameDev& F) {
+#pragma clang fp contract(off)
+    const double fx = in.K[0], fy = in.K[1], cx = in.K[2], cy = in.K[3];
+    for (int r = 0; r < 3; ++r) {
+        // row r of K R
+        const double f = r == 0 ? fx : fy, o = r == 0 ? cx : cy;
+        double k[3];
+        for (int c = 0; c < 3; ++c) k[c] = r == 2 ? in.R[6 + c] : fma(f, in.R[3 * r + c], o * in.R[6 + c]);
+        // times K^-1 = [[1/fx, 0, -cx/fx], [0, 1/fy, -cy/fy], [0, 0, 1]]
+        F.hm[3 * r + 0] = k[0] / fx;
+        F.hm[3 * r + 1] = k[1] / fy;
+        F.hm[3 * r + 2] = k[2] - k[0] * cx / fx - k[1] * cy / fy;
+    }
+    F.kt[0] = fma(fx, in.t[0], cx * in.t[2]);
+    F.kt[1] = fma(fy, in.t[1], cy * in.t[2]);
+    F.kt[2] = in.t[2];
+    F.zrow[0] = (float)F.hm[6];
+    F.zrow[1] = (float)F.hm[7];
+    F.zrow[2] = (float)F.kt[2];
+    F.zrow[3] = 0.f;
+    F.img = in.img;
+}
 
 // Work queue q covers the global item range [begin, end).
 struct QueueDev {
     int32_t begin, end;
 };
 
-// Header of one batch, in device memory, read by every kernel.  All per-call
-// values live here (not in kernel arguments) so that a captured graph can be
-// replayed for any batch.
+// Header of one batch: every per-call value of the kernels, in device memory
+// for a batch, in the kernel arguments for a lone keyframe.
 struct BatchHeader {
     KfDev* kfs;
     FrameDev* frames;
@@ -90,6 +120,20 @@ enum : uint32_t {
     F_UNINIT = 1u << 5,
     F_GN_BITS = F_DEGENERATE | F_FEW_SAMPLES | F_SOLVE_FAIL | F_REJECTED | F_FP64_SOLVE,
 };
+
+// A lone keyframe's whole table, passed by value as the first kernel
+// argument (kernels that need no frames take it up to kf): no upload, no
+// staging slot.  hdr.kfs and hdr.frames are not used.  Kernel arguments hold
+// 4 KB.
+struct LoneKf {
+    BatchHeader hdr;
+    KfDev kf;
+};
+struct LoneBatch {
+    LoneKf one;
+    FrameDev frames[kMaxNbr];
+};
+static_assert(sizeof(LoneBatch) <= 3072, "kernel arguments of a lone keyframe");
 
 // Kernel variants.
 struct GnVariant {
@@ -149,23 +193,31 @@ struct RegridArgs {
 };
 
 // Launchers implemented in sgn_kernels.hip.  All return hipError_t of the
+// launch.  `one` (host memory) or `hdr` (device memory) gives the table: hdr
+// null means the lone keyframe of `one`, whose contents are copied into the
 // launch.
-hipError_t launch_setup(const BatchHeader* hdr, uint32_t* counters, int n_frames_cap,
-                        hipStream_t s);
-hipError_t launch_init(const BatchHeader* hdr, int grid, hipStream_t s);
-hipError_t launch_render(const BatchHeader* hdr, int grid, hipStream_t s);
-hipError_t launch_gn(const GnVariant& v, const BatchHeader* hdr, uint32_t* counters,
-                     int persistent, int grid_blocks, hipStream_t s);
+//
+// Table upload: n16 16-byte words from pinned host memory to the device
+// table, the constants of n_frames frames formed from `in` (pinned host
+// memory), and the work-queue counters cleared.
+hipError_t launch_stage(const void* host, void* dev, int n16, const FrameIn* in, FrameDev* frames, int n_frames,
+                        uint32_t* counters, hipStream_t s);
+hipError_t launch_init(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s);
+hipError_t launch_render(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s);
+// The kernel's own start and end go to the two events.
+hipError_t launch_gn(const GnVariant& v, const LoneBatch& one, const BatchHeader* hdr, uint32_t* counters,
+                     int persistent, int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 // Device address of the static scratch array on `device` (which must be the
 // current device), looked up on the first call for that device and kept.
 hipError_t static_scratch_on(int device, void** out);
-// Re-gridding of a device table of n_pairs keyframe pairs.  A wavefront
+// Re-gridding of n_pairs keyframe pairs: a device table, or (table null) the
+// one entry `one`.  A wavefront
 // never spans two pairs: pair k's sources run over the
 // wavefronts from src_wave on (surfel i at lane i % 64 of wavefront
 // src_wave + i / 64), likewise its tiles from dst_wave; src_waves and
 // dst_waves are the totals.
-hipError_t launch_regrid(const RegridArgs* table, int n_pairs, int src_waves, int dst_waves,
-                         hipStream_t s);
+hipError_t launch_regrid(const RegridArgs& one, const RegridArgs* table, int n_pairs, int src_waves,
+                         int dst_waves, hipStream_t s);
 
 // Disc surfels (Eq. 4).
 constexpr float kDiscMaxRadius = 12.f;
@@ -178,8 +230,8 @@ constexpr int disc_surfels_per_wave(int dtype) { return dtype == 0 ? 1 : 2; }
 // ceil(disc_count / that), item_base their prefix).
 // grid_blocks workgroups of four wavefronts, one work item each (with one
 // share per XCD in the header, workgroup b serves share b % kXcds)
-hipError_t launch_disc_gn(int dtype, const BatchHeader* hdr, int total_items, int grid_blocks, bool by_row,
-                          hipStream_t s);
+hipError_t launch_disc_gn(int dtype, const LoneBatch& one, const BatchHeader* hdr, int total_items,
+                          int grid_blocks, bool by_row, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 // Depth-buffered render of the discs of several keyframes: one table entry
 // per keyframe (device memory); the scratch holds one 64-bit depth key and
 // one index per pixel of every keyframe, keyframe after keyframe.
@@ -217,8 +269,8 @@ struct DiscRenderScratch {
     int32_t* block_sum;
     int32_t* list;
 };
-hipError_t launch_disc_render(const DiscRenderItem* table, int n_items, int total_surfels, int total_tiles,
-                              const DiscRenderScratch& w, hipStream_t s);
+hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items, int total_surfels,
+                              int total_tiles, const DiscRenderScratch& w, hipStream_t s);
 // The search for empty areas on the lattice (spacing/2 + i spacing, ...),
 // placement of the qualifying candidates as surfels first .. and their
 // neighbour initialisation from the index map.
@@ -246,8 +298,8 @@ struct DiscPlaceArgs {
 // Placement for a device table of n_items keyframes: search (one wavefront
 // per candidate), compaction (one workgroup per keyframe), initialisation
 // (one wavefront per new-surfel slot).
-hipError_t launch_disc_place(const DiscPlaceArgs* table, int n_items, int total_cands, int total_init,
-                             hipStream_t s);
+hipError_t launch_disc_place(const DiscPlaceArgs& one, const DiscPlaceArgs* table, int n_items,
+                             int total_cands, int total_init, hipStream_t s);
 // Eq. 10 for disc surfels: each usable source surfel moves to p' = R p + t,
 // n' = R n, and is re-centred at K_dst pi(p'); those landing in the
 // destination image are written in source order.
@@ -269,8 +321,9 @@ struct DiscTransferArgs {
     int32_t* src_index;           // may be null
     int32_t* counts;              // device [2]: written, landed
 };
-// One workgroup per entry of a device table of n_pairs keyframe pairs.
-hipError_t launch_disc_transfer(const DiscTransferArgs* table, int n_pairs, hipStream_t s);
+// One workgroup per keyframe pair.
+hipError_t launch_disc_transfer(const DiscTransferArgs& one, const DiscTransferArgs* table, int n_pairs,
+                                hipStream_t s);
 hipError_t launch_quantize(const float* src, int src_pitch, void* dst, int dst_pitch,
                            int width, int height, int dtype, float scale, hipStream_t s);
 // Workgroups of 256 threads of the chosen GN variant that fit on one CU.

@@ -4,7 +4,8 @@
 // Dondo Gazzano, Sosa Paez), Proposed Approach section, Eq. 1-10.
 //
 // Kernels
-//   setup_kernel   per-frame constants H = K R K^-1 and K t (Eq. 6) in
+//   stage_kernel   table upload: descriptors copied from pinned host memory,
+//                  per-frame constants H = K R K^-1 and K t (Eq. 6) formed in
 //                  double; clears the work queues.
 //   init_kernel    neighbour-plane initialisation (Surfel Initialization).
 //   gn_kernel      the fused Gauss-Newton iterations.  A work item is a set
@@ -49,7 +50,9 @@ namespace sgn {
 // Pointers into the constant address space: the descriptor tables are not
 // written while a kernel runs, so uniform reads become scalar loads.
 template <class T>
-using cptr = const T __attribute__((address_space(4)))*;
+using carg = const T __attribute__((address_space(4)));
+template <class T>
+using cptr = carg<T>*;
 // Global-address-space pointers (global_load with a scalar base).
 template <class T>
 using gptr = const T __attribute__((address_space(1)))*;
@@ -158,7 +161,7 @@ __device__ __forceinline__ int find_kf(cptr<KfDev> kfs, int n_kf, int item, int 
 
 // Next work item of a persistent wavefront: take one from queue q, moving on
 // to the next queue when q is exhausted; `total` when every queue is empty.
-__device__ __forceinline__ int pull_item(const BatchHeader* __restrict__ hdr, uint32_t* counters,
+__device__ __forceinline__ int pull_item(cptr<BatchHeader> hdr, uint32_t* counters,
                                          int& q, int& q_left, int lane, int total) {
     while (q_left > 0) {
         int got = 0;
@@ -172,49 +175,52 @@ __device__ __forceinline__ int pull_item(const BatchHeader* __restrict__ hdr, ui
     return total;
 }
 
-// ------------------------------------------------------------ setup kernel --
+// ------------------------------------------------------------ stage kernel --
 
-// One thread per neighbour frame: H = K R K^-1 and K t in double, rounded
-// once to float (Eq. 6).  Thread 0 also clears the work-queue heads.
-__global__ void setup_kernel(const BatchHeader* __restrict__ hdr, uint32_t* __restrict__ counters) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+// The call's table from pinned host memory to the device table, 16 bytes per
+// thread, one thread per neighbour frame forming its constants, and the
+// work-queue heads cleared.  A few hundred KB at most: bound by the latency
+// of one read over the host link.  A copy command (on the DMA engine for the
+// larger tables) and a kernel for the constants after it took 40 us from the
+// copy's start to the first working kernel of a 64-keyframe update, this
+// launch 19; 30 and 10 us for a 64-pair transfer, which has no constants.
+__global__ __launch_bounds__(256) void stage_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst,
+                                                    int n16, const FrameIn* __restrict__ in,
+                                                    FrameDev* __restrict__ frames, int n_frames,
+                                                    uint32_t* __restrict__ counters) {
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
     if (i < kNumCounters) counters[i] = 0u;
-    if (i >= hdr->n_frames) return;
-    FrameDev& F = hdr->frames[i];
-    // the owning keyframe carries K
-    int k = 0;
-    {
-        int lo = 0, hi = hdr->n_kf - 1;
-        while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if (hdr->kfs[mid].frame_base <= i) lo = mid; else hi = mid - 1;
-        }
-        k = lo;
+    const int n_copy = (n16 + 255) & ~255;             // frames start a workgroup of their own
+    if (i < n16) dst[i] = src[i];
+    if (i >= n_copy && i - n_copy < n_frames) {
+        const FrameIn f = in[i - n_copy];
+        frame_constants(f, frames[i - n_copy]);
     }
-    const KfDev& K = hdr->kfs[k];
-    const double fx = K.fx_d, fy = K.fy_d, cx = K.cx_d, cy = K.cy_d;
-    const double* R = F.R;
-    // K R
-    double KR[9];
-    for (int c = 0; c < 3; ++c) {
-        KR[0 * 3 + c] = fx * R[0 * 3 + c] + cx * R[2 * 3 + c];
-        KR[1 * 3 + c] = fy * R[1 * 3 + c] + cy * R[2 * 3 + c];
-        KR[2 * 3 + c] = R[2 * 3 + c];
+}
+
+// A table is read through the constant address space (scalar loads): from
+// device memory, or, when its pointer is null, from the launch's own
+// arguments, where a lone entry is passed by value as the first parameter.
+template <class T>
+__device__ __forceinline__ cptr<T> lone_arg() {
+    return (cptr<T>)__builtin_amdgcn_kernarg_segment_ptr();
+}
+template <class T>
+__device__ __forceinline__ cptr<T> table_or_arg(const T* tab) {
+    return tab ? (cptr<T>)tab : lone_arg<T>();
+}
+struct BatchView {
+    cptr<BatchHeader> hdr;
+    cptr<KfDev> kfs;
+    cptr<FrameDev> frames;
+};
+__device__ __forceinline__ BatchView batch_view(const BatchHeader* hdr) {
+    if (hdr) {
+        const cptr<BatchHeader> h = (cptr<BatchHeader>)hdr;
+        return {h, (cptr<KfDev>)h->kfs, (cptr<FrameDev>)h->frames};
     }
-    // (K R) K^-1, K^-1 = [[1/fx, 0, -cx/fx], [0, 1/fy, -cy/fy], [0, 0, 1]]
-    for (int r = 0; r < 3; ++r) {
-        double a = KR[r * 3 + 0], b = KR[r * 3 + 1], c = KR[r * 3 + 2];
-        F.hm[r * 3 + 0] = a / fx;
-        F.hm[r * 3 + 1] = b / fy;
-        F.hm[r * 3 + 2] = c - a * cx / fx - b * cy / fy;
-    }
-    F.kt[0] = fx * F.t[0] + cx * F.t[2];
-    F.kt[1] = fy * F.t[1] + cy * F.t[2];
-    F.kt[2] = F.t[2];
-    F.zrow[0] = (float)F.hm[6];
-    F.zrow[1] = (float)F.hm[7];
-    F.zrow[2] = (float)F.kt[2];
-    F.zrow[3] = 0.f;
+    const cptr<LoneBatch> a = lone_arg<LoneBatch>();
+    return {&a->one.hdr, &a->one.kf, a->frames};
 }
 
 // ------------------------------------------------------------- init kernel --
@@ -224,20 +230,23 @@ __global__ void setup_kernel(const BatchHeader* __restrict__ hdr, uint32_t* __re
 // id_s = mean of Eq. 3 of each neighbour's plane at r_s; new n_s = mean of
 // the sign-aligned neighbour normals, renormalised.  Neighbours are visited
 // in index order.
-__global__ void init_kernel(const BatchHeader* __restrict__ hdr) {
+__global__ void init_kernel(LoneKf, const BatchHeader* __restrict__ hdr_) {
+    const BatchView view = batch_view(hdr_);
+    const cptr<BatchHeader> hdr = view.hdr;
+    const cptr<KfDev> kfs = view.kfs;
     const int total = hdr->total_surfels;
     int hint = 0;
     for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < total; s += gridDim.x * blockDim.x) {
         int lo = 0, hi = hdr->n_kf - 1;
-        if (!(s >= hdr->kfs[hint].surfel_base &&
-              s < hdr->kfs[hint].surfel_base + hdr->kfs[hint].gw * hdr->kfs[hint].gh)) {
+        if (!(s >= kfs[hint].surfel_base &&
+              s < kfs[hint].surfel_base + kfs[hint].gw * kfs[hint].gh)) {
             while (lo < hi) {
                 int mid = (lo + hi + 1) >> 1;
-                if (hdr->kfs[mid].surfel_base <= s) lo = mid; else hi = mid - 1;
+                if (kfs[mid].surfel_base <= s) lo = mid; else hi = mid - 1;
             }
             hint = lo;
         }
-        const KfDev& K = hdr->kfs[hint];
+        const carg<KfDev>& K = kfs[hint];
         if (!K.is_new) continue;
         const int S = K.patch;
         const int i = s - K.surfel_base;
@@ -386,10 +395,10 @@ enum : int {
 // The pair words of every neighbour frame for the anchor point (qbx, qby),
 // one frame per lane (lanes below nf), formed in double and rounded once,
 // into the wavefront's LDS words.
-__device__ __forceinline__ void stage_pair_words(const FrameDev* frames, int nf, int lane,
+__device__ __forceinline__ void stage_pair_words(cptr<FrameDev> frames, int nf, int lane,
                                                  double qbx, double qby, float* pairs) {
     if (lane < nf) {
-        const gptr<FrameDev> F = (gptr<FrameDev>)(frames + lane);
+        const gptr<FrameDev> F = (gptr<FrameDev>)(uint64_t)(frames + lane);
         const gptr<double> hm = F->hm;
         const gptr<double> kt = F->kt;
         const double Qx = fma(hm[0], qbx, fma(hm[1], qby, hm[2]));
@@ -953,7 +962,8 @@ template <int S, int K>
 constexpr int gn_waves() { return K == 1 ? 7 : (S == 8 ? 6 : 5); }
 
 template <typename T, int S, int TX, int TY, int K, bool BY_ROW>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(gn_waves<S, K>(), 8))) void gn_kernel(const BatchHeader* __restrict__ hdr_,
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(gn_waves<S, K>(), 8))) void gn_kernel(LoneBatch,
+                                                           const BatchHeader* __restrict__ hdr_,
                                                            uint32_t* __restrict__ counters,
                                                            int persistent) {
     constexpr ItemGeo G = item_geo(S, TX, TY, K);
@@ -967,7 +977,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     static_assert(PPL == 1 || LANES % S == 0, "a lane's pixels share a column");
     static_assert(NS <= kMaxItemSurfels && K <= LANES, "surfels per item");
     static_assert(G.ix <= G.ab && G.iy <= G.ab, "a work item lies in one anchor block");
-    const cptr<BatchHeader> hdr = (cptr<BatchHeader>)hdr_;
+    const BatchView view = batch_view(hdr_);
+    const cptr<BatchHeader> hdr = view.hdr;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = threadIdx.x >> 6;
     // pixel role: slot r of a group; pixels p + LANES j (j < PPL) of that surfel
@@ -999,7 +1010,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     const uint32_t stamp = hdr->stamp;
     const float lm0 = hdr->lm_lambda;
     const bool lm = lm0 > 0.f;
-    const cptr<KfDev> kfs = (cptr<KfDev>)hdr->kfs;
+    const cptr<KfDev> kfs = view.kfs;
 
     __shared__ float4 s_pairs[kBlockThreads / kWaveSize][kMaxNbr * kPairWords / 4];
     __shared__ float4 s_state[kBlockThreads / kWaveSize][kMaxItemSurfels * ST_WORDS / 4];
@@ -1013,7 +1024,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     int hint = 0;
     int item;
     if (persistent) {
-        item = pull_item(hdr_, counters, q, q_left, lane, total);
+        item = pull_item(hdr, counters, q, q_left, lane, total);
     } else if (hdr->n_queues == kXcds) {
         // one share of the work items per XCD: the hardware hands the
         // workgroups to the XCDs in turn, so workgroup b runs on XCD
@@ -1028,7 +1039,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
         item = blockIdx.x * (kBlockThreads / kWaveSize) + wave;
     }
     for (; item < total;
-         item = persistent ? pull_item(hdr_, counters, q, q_left, lane, total) : total) {
+         item = persistent ? pull_item(hdr, counters, q, q_left, lane, total) : total) {
         item = __builtin_amdgcn_readfirstlane(item);
         const int kidx = find_kf(kfs, n_kf, item, hint);
         hint = kidx;
@@ -1057,12 +1068,12 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
             // warp constants of every frame for this anchor block, one frame
             // per lane, in double
             wave_sync();
-            stage_pair_words(hdr->frames + Kd->frame_base, nf, lane,
+            stage_pair_words(view.frames + Kd->frame_base, nf, lane,
                              (double)bpx + 0.5 * (double)(G.ab * S - 1),
                              (double)bpy + 0.5 * (double)(G.ab * S - 1), pairs);
         }
         // the frame table pointer is wave-uniform: keep it in SGPRs
-        const uint64_t fr_bits = (uint64_t)(const void*)(hdr->frames + Kd->frame_base);
+        const uint64_t fr_bits = (uint64_t)(view.frames + Kd->frame_base);
         const uint32_t fr_lo = __builtin_amdgcn_readfirstlane((uint32_t)fr_bits);
         const uint32_t fr_hi = __builtin_amdgcn_readfirstlane((uint32_t)(fr_bits >> 32));
         const cptr<FrameDev> fr = (cptr<FrameDev>)(((uint64_t)fr_hi << 32) | fr_lo);
@@ -1516,9 +1527,10 @@ __device__ __forceinline__ int render_owner(cptr<KfDev> kfs, int n_kf, int64_t g
     return lo;
 }
 
-__global__ __launch_bounds__(256) void render_kernel(const BatchHeader* __restrict__ hdr_) {
-    const cptr<BatchHeader> hdr = (cptr<BatchHeader>)hdr_;
-    const cptr<KfDev> kfs = (cptr<KfDev>)hdr->kfs;
+__global__ __launch_bounds__(256) void render_kernel(LoneKf, const BatchHeader* __restrict__ hdr_) {
+    const BatchView view = batch_view(hdr_);
+    const cptr<BatchHeader> hdr = view.hdr;
+    const cptr<KfDev> kfs = view.kfs;
     const int n_kf = hdr->n_kf;
     const int64_t total = hdr->total_pixels;           // render segments
     __shared__ int s_kf;
@@ -1631,7 +1643,7 @@ struct Land {
     int tile;
 };
 
-__device__ __forceinline__ bool regrid_land(const RegridArgs& a, int i, Land& L) {
+__device__ __forceinline__ bool regrid_land(const carg<RegridArgs>& a, int i, Land& L) {
 #pragma clang fp contract(off)
     const int S0 = a.src_patch, gw0 = a.src_w / S0;
     if (a.src.flags[i] & (F_DEGENERATE | F_UNINIT)) return false;
@@ -1641,7 +1653,7 @@ __device__ __forceinline__ bool regrid_land(const RegridArgs& a, int i, Land& L)
     const double rs0 = (usx - a.src_K[2]) / a.src_K[0], rs1 = (usy - a.src_K[3]) / a.src_K[1];
     const double p00 = rs0 / id, p01 = rs1 / id, p02 = 1.0 / id;          // Eq. 1
     const double n0 = a.src.nx[i], n1 = a.src.ny[i], n2 = a.src.nz[i];
-    const double* R = a.R;
+    const cptr<double> R = a.R;
     const double p10 = R[0] * p00 + R[1] * p01 + R[2] * p02 + a.t[0];
     const double p11 = R[3] * p00 + R[4] * p01 + R[5] * p02 + a.t[1];
     const double p12 = R[6] * p00 + R[7] * p01 + R[8] * p02 + a.t[2];
@@ -1666,7 +1678,7 @@ __device__ __forceinline__ bool regrid_land(const RegridArgs& a, int i, Land& L)
 // the last whose first wavefront is <= the wavefront's number.  It is found
 // and read with wavefront-uniform (scalar) loads.
 template <bool DST>
-__device__ __forceinline__ int regrid_entry_of_wave(const RegridArgs* __restrict__ tab, int n, int wv) {
+__device__ __forceinline__ int regrid_entry_of_wave(cptr<RegridArgs> tab, int n, int wv) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -1682,11 +1694,12 @@ __device__ __forceinline__ int grid_wave() {
 }
 __device__ __forceinline__ int grid_waves() { return (int)gridDim.x * 4; }
 
-__global__ __launch_bounds__(256) void regrid_clear_kernel(const RegridArgs* __restrict__ tab, int n_pairs,
+__global__ __launch_bounds__(256) void regrid_clear_kernel(RegridArgs, const RegridArgs* __restrict__ tab_, int n_pairs,
                                                            int dst_waves) {
+    const cptr<RegridArgs> tab = table_or_arg(tab_);
     const int lane = threadIdx.x & 63;
     for (int wv = grid_wave(); wv < dst_waves; wv += grid_waves()) {
-        const RegridArgs& a = tab[regrid_entry_of_wave<true>(tab, n_pairs, wv)];
+        const carg<RegridArgs>& a = tab[regrid_entry_of_wave<true>(tab, n_pairs, wv)];
         const int j = (wv - a.dst_wave) * 64 + lane;
         if (j < a.dst_count) {
             a.best[j] = 0ull;
@@ -1697,11 +1710,12 @@ __global__ __launch_bounds__(256) void regrid_clear_kernel(const RegridArgs* __r
 
 // pass 0: closest landing per tile (1/p'_z > 0, so its bits order like the
 // value); pass 1: the lowest source index among the closest
-__global__ __launch_bounds__(256) void regrid_scatter_kernel(const RegridArgs* __restrict__ tab, int n_pairs,
+__global__ __launch_bounds__(256) void regrid_scatter_kernel(RegridArgs, const RegridArgs* __restrict__ tab_, int n_pairs,
                                                              int src_waves, int pass) {
+    const cptr<RegridArgs> tab = table_or_arg(tab_);
     const int lane = threadIdx.x & 63;
     for (int wv = grid_wave(); wv < src_waves; wv += grid_waves()) {
-        const RegridArgs& a = tab[regrid_entry_of_wave<false>(tab, n_pairs, wv)];
+        const carg<RegridArgs>& a = tab[regrid_entry_of_wave<false>(tab, n_pairs, wv)];
         const int i = (wv - a.src_wave) * 64 + lane;
         Land L;
         if (i >= a.src_count || !regrid_land(a, i, L)) continue;
@@ -1713,12 +1727,13 @@ __global__ __launch_bounds__(256) void regrid_scatter_kernel(const RegridArgs* _
     }
 }
 
-__global__ __launch_bounds__(256) void regrid_gather_kernel(const RegridArgs* __restrict__ tab, int n_pairs,
+__global__ __launch_bounds__(256) void regrid_gather_kernel(RegridArgs, const RegridArgs* __restrict__ tab_, int n_pairs,
                                                             int dst_waves) {
 #pragma clang fp contract(off)
+    const cptr<RegridArgs> tab = table_or_arg(tab_);
     const int lane = threadIdx.x & 63;
     for (int wv = grid_wave(); wv < dst_waves; wv += grid_waves()) {
-        const RegridArgs& a = tab[regrid_entry_of_wave<true>(tab, n_pairs, wv)];
+        const carg<RegridArgs>& a = tab[regrid_entry_of_wave<true>(tab, n_pairs, wv)];
         const int j = (wv - a.dst_wave) * 64 + lane;
         if (j >= a.dst_count) continue;
         const int S1 = a.dst_patch, gw1 = a.dst_w / S1;
@@ -1753,19 +1768,19 @@ __global__ __launch_bounds__(256) void regrid_gather_kernel(const RegridArgs* __
     }
 }
 
-hipError_t launch_regrid(const RegridArgs* table, int n_pairs, int src_waves, int dst_waves,
-                         hipStream_t s) {
+hipError_t launch_regrid(const RegridArgs& one, const RegridArgs* table, int n_pairs, int src_waves,
+                         int dst_waves, hipStream_t s) {
     // four wavefronts per workgroup
     auto blocks = [](int waves) { return std::max(1, std::min(65536, (waves + 3) / 4)); };
-    hipLaunchKernelGGL(regrid_clear_kernel, dim3(blocks(dst_waves)), dim3(256), 0, s, table, n_pairs,
+    hipLaunchKernelGGL(regrid_clear_kernel, dim3(blocks(dst_waves)), dim3(256), 0, s, one, table, n_pairs,
                        dst_waves);
     if (src_waves > 0) {
-        hipLaunchKernelGGL(regrid_scatter_kernel, dim3(blocks(src_waves)), dim3(256), 0, s, table, n_pairs,
+        hipLaunchKernelGGL(regrid_scatter_kernel, dim3(blocks(src_waves)), dim3(256), 0, s, one, table, n_pairs,
                            src_waves, 0);
-        hipLaunchKernelGGL(regrid_scatter_kernel, dim3(blocks(src_waves)), dim3(256), 0, s, table, n_pairs,
+        hipLaunchKernelGGL(regrid_scatter_kernel, dim3(blocks(src_waves)), dim3(256), 0, s, one, table, n_pairs,
                            src_waves, 1);
     }
-    hipLaunchKernelGGL(regrid_gather_kernel, dim3(blocks(dst_waves)), dim3(256), 0, s, table, n_pairs,
+    hipLaunchKernelGGL(regrid_gather_kernel, dim3(blocks(dst_waves)), dim3(256), 0, s, one, table, n_pairs,
                        dst_waves);
     return hipGetLastError();
 }
@@ -1819,20 +1834,21 @@ hipError_t static_scratch_on(int device, void** out) {
 
 // ---------------------------------------------------------------- launchers --
 
-hipError_t launch_setup(const BatchHeader* hdr, uint32_t* counters, int n_frames_cap, hipStream_t s) {
-    int n = n_frames_cap > kNumCounters ? n_frames_cap : kNumCounters;
-    int blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(setup_kernel, dim3(blocks), dim3(256), 0, s, hdr, counters);
+hipError_t launch_stage(const void* host, void* dev, int n16, const FrameIn* in, FrameDev* frames, int n_frames,
+                        uint32_t* counters, hipStream_t s) {
+    const int blocks = (n16 + 255) / 256 + (n_frames + 255) / 256;
+    hipLaunchKernelGGL(stage_kernel, dim3(blocks), dim3(256), 0, s, (const uint4*)host, (uint4*)dev, n16, in,
+                       frames, n_frames, counters);
     return hipGetLastError();
 }
 
-hipError_t launch_init(const BatchHeader* hdr, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(init_kernel, dim3(grid), dim3(256), 0, s, hdr);
+hipError_t launch_init(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s) {
+    hipLaunchKernelGGL(init_kernel, dim3(grid), dim3(256), 0, s, one, hdr);
     return hipGetLastError();
 }
 
-hipError_t launch_render(const BatchHeader* hdr, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(render_kernel, dim3(grid), dim3(256), 0, s, hdr);
+hipError_t launch_render(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s) {
+    hipLaunchKernelGGL(render_kernel, dim3(grid), dim3(256), 0, s, one, hdr);
     return hipGetLastError();
 }
 
@@ -1895,12 +1911,22 @@ int gn_blocks_per_cu(const GnVariant& v) {
     return n;
 }
 
-hipError_t launch_gn(const GnVariant& v, const BatchHeader* hdr, uint32_t* counters, int persistent,
-                     int grid_blocks, hipStream_t s) {
+// A kernel between the two timing events.  Recorded events: the launch that
+// carries its own (hipExtLaunchKernel) took 6-7 us longer alone.
+static hipError_t launch_timed(void* f, int grid_blocks, void** args, hipStream_t s, hipEvent_t start,
+                               hipEvent_t stop) {
+    hipError_t e = hipEventRecord(start, s);
+    if (e == hipSuccess) e = hipLaunchKernel(f, dim3(grid_blocks), dim3(kBlockThreads), args, 0, s);
+    if (e == hipSuccess) e = hipEventRecord(stop, s);
+    return e;
+}
+
+hipError_t launch_gn(const GnVariant& v, const LoneBatch& one, const BatchHeader* hdr, uint32_t* counters,
+                     int persistent, int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
     void* f = gn_select(v);
     if (!f) return hipErrorInvalidValue;
-    void* args[] = {(void*)&hdr, (void*)&counters, (void*)&persistent};
-    return hipLaunchKernel(f, dim3(grid_blocks), dim3(kBlockThreads), args, 0, s);
+    void* args[] = {(void*)&one, (void*)&hdr, (void*)&counters, (void*)&persistent};
+    return launch_timed(f, grid_blocks, args, s, start, stop);
 }
 
 // ------------------------------------------------------------ disc surfels --
@@ -2018,13 +2044,14 @@ __device__ __forceinline__ void disc_pixel(const DiscRows& d, const int* row_x0,
 // step once per iteration or by its double-precision fallback only.
 template <typename T, int SPW, bool BY_ROW>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) void disc_gn_kernel(
-    const BatchHeader* __restrict__ hdr_, int total) {
+    LoneBatch, const BatchHeader* __restrict__ hdr_, int total) {
     constexpr int LANES = kWaveSize / SPW;        // lanes per surfel
     constexpr int PPL = kDiscPPL * SPW;           // pixel slots per lane
     constexpr int WPB = kBlockThreads / kWaveSize;
     constexpr bool packed = DiscSlot<T>::packed;
     static_assert(kDiscMaxRows <= LANES, "a disc row per lane");
-    const cptr<BatchHeader> hdr = (cptr<BatchHeader>)hdr_;
+    const BatchView view = batch_view(hdr_);
+    const cptr<BatchHeader> hdr = view.hdr;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = threadIdx.x >> 6;
     const int h = lane / LANES, hl = lane % LANES;       // surfel of the wave, lane within it
@@ -2050,7 +2077,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
     int* const row_x0 = s_rows[wave][h];
     int* const row_start = s_rows[wave][h] + kDiscMaxRows;
 
-    const cptr<KfDev> kfs = (cptr<KfDev>)hdr->kfs;
+    const cptr<KfDev> kfs = view.kfs;
     const int kidx = find_kf(kfs, hdr->n_kf, item, 0);
     const cptr<KfDev> Kd = kfs + kidx;
     const int sidx = (item - Kd->item_base) * SPW + h;
@@ -2081,8 +2108,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
     // warp coordinates)
     const int ax = (int)rint(fmin(fmax((double)ux, -1e6), 1e6));
     const int ay = (int)rint(fmin(fmax((double)uy, -1e6), 1e6));
-    stage_pair_words(hdr->frames + Kd->frame_base, nf, hl, (double)ax, (double)ay, pairs);
-    const uint64_t fr_bits = (uint64_t)(const void*)(hdr->frames + Kd->frame_base);
+    stage_pair_words(view.frames + Kd->frame_base, nf, hl, (double)ax, (double)ay, pairs);
+    const uint64_t fr_bits = (uint64_t)(view.frames + Kd->frame_base);
     const uint32_t fr_lo = __builtin_amdgcn_readfirstlane((uint32_t)fr_bits);
     const uint32_t fr_hi = __builtin_amdgcn_readfirstlane((uint32_t)(fr_bits >> 32));
     const cptr<FrameDev> fr = (cptr<FrameDev>)(((uint64_t)fr_hi << 32) | fr_lo);
@@ -2301,7 +2328,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
 
 // Table entry of global surfel g (largest surfel_base <= g among entries
 // with surfels) or of global tile t (by tile_base).
-__device__ __forceinline__ int render_item_of_surfel(const DiscRenderItem* tab, int n, int g) {
+__device__ __forceinline__ int render_item_of_surfel(cptr<DiscRenderItem> tab, int n, int g) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -2309,7 +2336,7 @@ __device__ __forceinline__ int render_item_of_surfel(const DiscRenderItem* tab, 
     }
     return lo;        // entries without surfels share the next base and are never the largest
 }
-__device__ __forceinline__ int render_item_of_tile(const DiscRenderItem* tab, int n, int t) {
+__device__ __forceinline__ int render_item_of_tile(cptr<DiscRenderItem> tab, int n, int t) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -2326,15 +2353,16 @@ __global__ void fill_int_kernel(int32_t* __restrict__ p, int n, int32_t v) {
 // and stores its raster record; pass 1 (after the scan) writes it into those
 // tiles' lists.  One thread per surfel.
 template <int PASS>
-__global__ __launch_bounds__(256) void disc_bin_kernel(const DiscRenderItem* __restrict__ tab, int n_items,
+__global__ __launch_bounds__(256) void disc_bin_kernel(DiscRenderItem, const DiscRenderItem* __restrict__ tab_, int n_items,
                                                        int total, DiscRaster* __restrict__ rec,
                                                        int32_t* __restrict__ count,
                                                        const int32_t* __restrict__ start,
                                                        int32_t* __restrict__ list) {
 #pragma clang fp contract(off)
+    const cptr<DiscRenderItem> tab = table_or_arg(tab_);
     const int g = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (g >= total) return;
-    const DiscRenderItem& a = tab[render_item_of_surfel(tab, n_items, g)];
+    const carg<DiscRenderItem>& a = tab[render_item_of_surfel(tab, n_items, g)];
     const int s = g - a.surfel_base;
     if (a.flags[s] & (F_DEGENERATE | F_UNINIT)) return;
     const double cx = (double)a.ux[s], cy = (double)a.uy[s], r = (double)a.radius;
@@ -2426,14 +2454,15 @@ __global__ __launch_bounds__(1024) void bin_scan_add_kernel(int32_t* __restrict_
 // loads in flight at once), so the per-pixel walk reads LDS instead of
 // waiting on a dependent pair of loads per entry.
 __global__ __launch_bounds__(kRenderTile * kRenderTile) void disc_raster_kernel(
-    const DiscRenderItem* __restrict__ tab, int n_items, const DiscRaster* __restrict__ rec,
+    DiscRenderItem, const DiscRenderItem* __restrict__ tab_, int n_items, const DiscRaster* __restrict__ rec,
     const int32_t* __restrict__ start, const int32_t* __restrict__ list) {
 #pragma clang fp contract(off)
+    const cptr<DiscRenderItem> tab = table_or_arg(tab_);
     constexpr int kChunk = kRenderTile * kRenderTile;
     __shared__ DiscRaster s_rec[kChunk];
     __shared__ int s_idx[kChunk];
     const int t = (int)blockIdx.x;
-    const DiscRenderItem& a = tab[render_item_of_tile(tab, n_items, t)];
+    const carg<DiscRenderItem>& a = tab[render_item_of_tile(tab, n_items, t)];
     const int lt = t - a.tile_base;
     const int ty = lt / a.tiles_x, tx = lt - ty * a.tiles_x;
     const int x = tx * kRenderTile + (int)(threadIdx.x % kRenderTile);
@@ -2480,7 +2509,7 @@ __global__ __launch_bounds__(kRenderTile * kRenderTile) void disc_raster_kernel(
 // numbered keyframe after keyframe (cand_base, init_base); the entry owning
 // number g is the last whose base is <= g (entries with none share the next
 // base and are never the last).
-__device__ __forceinline__ int place_entry_of_cand(const DiscPlaceArgs* tab, int n, int g) {
+__device__ __forceinline__ int place_entry_of_cand(cptr<DiscPlaceArgs> tab, int n, int g) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -2488,7 +2517,7 @@ __device__ __forceinline__ int place_entry_of_cand(const DiscPlaceArgs* tab, int
     }
     return lo;
 }
-__device__ __forceinline__ int place_entry_of_init(const DiscPlaceArgs* tab, int n, int g) {
+__device__ __forceinline__ int place_entry_of_init(cptr<DiscPlaceArgs> tab, int n, int g) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -2502,13 +2531,14 @@ __device__ __forceinline__ int place_entry_of_init(const DiscPlaceArgs* tab, int
 // spacing), its lanes sharing the window of pixels within alpha r; the
 // candidate qualifies when no non-empty pixel of the index map lies within
 // alpha r (integer squared distance against (alpha r)^2 in double).
-__global__ __launch_bounds__(kBlockThreads) void disc_search_kernel(const DiscPlaceArgs* __restrict__ tab,
+__global__ __launch_bounds__(kBlockThreads) void disc_search_kernel(DiscPlaceArgs, const DiscPlaceArgs* __restrict__ tab_,
                                                                     int n_items, int total) {
+    const cptr<DiscPlaceArgs> tab = table_or_arg(tab_);
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int g = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kBlockThreads / kWaveSize) +
                                                  (int)(threadIdx.x >> 6));
     if (g >= total) return;
-    const DiscPlaceArgs& a = tab[place_entry_of_cand(tab, n_items, g)];
+    const carg<DiscPlaceArgs>& a = tab[place_entry_of_cand(tab, n_items, g)];
     const int c = g - a.cand_base;
     const int cx = a.spacing / 2 + (c % a.cand_x) * a.spacing;
     const int cy = a.spacing / 2 + (c / a.cand_x) * a.spacing;
@@ -2537,8 +2567,9 @@ __global__ __launch_bounds__(kBlockThreads) void disc_search_kernel(const DiscPl
 // first, first + 1, ... (as many as there is room for); counts[0] = placed,
 // counts[1] = qualifying.  One workgroup per keyframe scans its flags in
 // chunks.
-__global__ __launch_bounds__(1024) void disc_compact_kernel(const DiscPlaceArgs* __restrict__ tab) {
-    const DiscPlaceArgs& a = tab[blockIdx.x];
+__global__ __launch_bounds__(1024) void disc_compact_kernel(DiscPlaceArgs, const DiscPlaceArgs* __restrict__ tab_) {
+    const cptr<DiscPlaceArgs> tab = table_or_arg(tab_);
+    const carg<DiscPlaceArgs>& a = tab[blockIdx.x];
     __shared__ int s_wave[1024 / kWaveSize + 1];
     const int n = a.cand_x * a.cand_y;
     const int lane = threadIdx.x & (kWaveSize - 1);
@@ -2590,13 +2621,14 @@ __device__ __forceinline__ int wave_min(int v) {
 // index each round); id = mean of Eq. 3 of their planes at the new ray,
 // n = mean of their normals sign-aligned to the first, renormalised; none
 // usable: UNINIT with id 0 and n = (0, 0, -1).
-__global__ __launch_bounds__(kWaveSize) void disc_init_kernel(const DiscPlaceArgs* __restrict__ tab,
+__global__ __launch_bounds__(kWaveSize) void disc_init_kernel(DiscPlaceArgs, const DiscPlaceArgs* __restrict__ tab_,
                                                               int n_items) {
+    const cptr<DiscPlaceArgs> tab = table_or_arg(tab_);
     // the window's surfel indices (those within beta r, below `first`), or -1
     __shared__ int s_win[(2 * kDiscMaxWindowReach + 1) * (2 * kDiscMaxWindowReach + 1)];
     const int lane = threadIdx.x;
     const int g = __builtin_amdgcn_readfirstlane((int)blockIdx.x);
-    const DiscPlaceArgs& a = tab[place_entry_of_init(tab, n_items, g)];
+    const carg<DiscPlaceArgs>& a = tab[place_entry_of_init(tab, n_items, g)];
     const int w = g - a.init_base;
     if (w >= a.counts[0]) return;
     const int i = a.first + w;
@@ -2678,9 +2710,10 @@ __global__ __launch_bounds__(kWaveSize) void disc_init_kernel(const DiscPlaceArg
 // and writes them; every landing is computed in double in the oracle's
 // order, so the kept set and the order are the same.
 constexpr int kDiscXferSub = 4;
-__global__ __launch_bounds__(1024) void disc_transfer_kernel(const DiscTransferArgs* __restrict__ tab) {
+__global__ __launch_bounds__(1024) void disc_transfer_kernel(DiscTransferArgs, const DiscTransferArgs* __restrict__ tab_) {
 #pragma clang fp contract(off)
-    const DiscTransferArgs& a = tab[blockIdx.x];          // one workgroup per keyframe pair
+    const cptr<DiscTransferArgs> tab = table_or_arg(tab_);
+    const carg<DiscTransferArgs>& a = tab[blockIdx.x];          // one workgroup per keyframe pair
     constexpr int kWaves = 1024 / kWaveSize;
     constexpr int kSlots = kDiscXferSub * kWaves;         // (chunk, wavefront) in source order
     static_assert(kSlots <= kWaveSize, "one wavefront scans the slots");
@@ -2765,57 +2798,54 @@ __global__ __launch_bounds__(1024) void disc_transfer_kernel(const DiscTransferA
     }
 }
 
-hipError_t launch_disc_transfer(const DiscTransferArgs* table, int n_pairs, hipStream_t s) {
-    disc_transfer_kernel<<<n_pairs, 1024, 0, s>>>(table);
+hipError_t launch_disc_transfer(const DiscTransferArgs& one, const DiscTransferArgs* table, int n_pairs,
+                                hipStream_t s) {
+    disc_transfer_kernel<<<n_pairs, 1024, 0, s>>>(one, table);
     return hipGetLastError();
 }
 
 template <bool R>
-static void launch_disc_gn_rows(int dtype, const BatchHeader* hdr, int total_items, dim3 grid, hipStream_t s) {
-    if (dtype == 0)
-        disc_gn_kernel<float, disc_surfels_per_wave(0), R><<<grid, kBlockThreads, 0, s>>>(hdr, total_items);
-    else if (dtype == 1)
-        disc_gn_kernel<_Float16, disc_surfels_per_wave(1), R><<<grid, kBlockThreads, 0, s>>>(hdr, total_items);
-    else
-        disc_gn_kernel<uint8_t, disc_surfels_per_wave(2), R><<<grid, kBlockThreads, 0, s>>>(hdr, total_items);
+static void* disc_gn_ptr(int dtype) {
+    return dtype == 0   ? (void*)&disc_gn_kernel<float, disc_surfels_per_wave(0), R>
+           : dtype == 1 ? (void*)&disc_gn_kernel<_Float16, disc_surfels_per_wave(1), R>
+                        : (void*)&disc_gn_kernel<uint8_t, disc_surfels_per_wave(2), R>;
 }
 
-hipError_t launch_disc_gn(int dtype, const BatchHeader* hdr, int total_items, int grid_blocks, bool by_row,
-                          hipStream_t s) {
+hipError_t launch_disc_gn(int dtype, const LoneBatch& one, const BatchHeader* hdr, int total_items,
+                          int grid_blocks, bool by_row, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
     if (total_items <= 0) return hipSuccess;
-    const dim3 grid(grid_blocks);
-    if (by_row) launch_disc_gn_rows<true>(dtype, hdr, total_items, grid, s);
-    else launch_disc_gn_rows<false>(dtype, hdr, total_items, grid, s);
-    return hipGetLastError();
+    void* args[] = {(void*)&one, (void*)&hdr, (void*)&total_items};
+    return launch_timed(by_row ? disc_gn_ptr<true>(dtype) : disc_gn_ptr<false>(dtype), grid_blocks, args, s, start,
+                        stop);
 }
 
-hipError_t launch_disc_render(const DiscRenderItem* table, int n_items, int total_surfels, int total_tiles,
-                              const DiscRenderScratch& w, hipStream_t s) {
+hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items,
+                              int total_surfels, int total_tiles, const DiscRenderScratch& w, hipStream_t s) {
     const int nb = (total_tiles + 1023) / 1024;
     fill_int_kernel<<<std::min((total_tiles + 255) / 256, 4096), 256, 0, s>>>(w.count, total_tiles, 0);
     const int sblocks = (total_surfels + 255) / 256;
     if (total_surfels > 0)
-        disc_bin_kernel<0><<<sblocks, 256, 0, s>>>(table, n_items, total_surfels, w.rec, w.count, w.start,
+        disc_bin_kernel<0><<<sblocks, 256, 0, s>>>(one, table, n_items, total_surfels, w.rec, w.count, w.start,
                                                    w.list);
     bin_scan_block_kernel<<<nb, 1024, 0, s>>>(w.count, w.start, w.block_sum, total_tiles);
     bin_scan_top_kernel<<<1, 1024, 0, s>>>(w.block_sum, nb, w.start, total_tiles);
     bin_scan_add_kernel<<<nb, 1024, 0, s>>>(w.start, w.block_sum, total_tiles);
     if (total_surfels > 0)
-        disc_bin_kernel<1><<<sblocks, 256, 0, s>>>(table, n_items, total_surfels, w.rec, w.count, w.start,
+        disc_bin_kernel<1><<<sblocks, 256, 0, s>>>(one, table, n_items, total_surfels, w.rec, w.count, w.start,
                                                    w.list);
-    disc_raster_kernel<<<total_tiles, kRenderTile * kRenderTile, 0, s>>>(table, n_items, w.rec, w.start,
+    disc_raster_kernel<<<total_tiles, kRenderTile * kRenderTile, 0, s>>>(one, table, n_items, w.rec, w.start,
                                                                          w.list);
     return hipGetLastError();
 }
 
-hipError_t launch_disc_place(const DiscPlaceArgs* table, int n_items, int total_cands, int total_init,
-                             hipStream_t s) {
+hipError_t launch_disc_place(const DiscPlaceArgs& one, const DiscPlaceArgs* table, int n_items,
+                             int total_cands, int total_init, hipStream_t s) {
     const int waves = kBlockThreads / kWaveSize;
     if (total_cands > 0)
-        disc_search_kernel<<<(total_cands + waves - 1) / waves, kBlockThreads, 0, s>>>(table, n_items,
+        disc_search_kernel<<<(total_cands + waves - 1) / waves, kBlockThreads, 0, s>>>(one, table, n_items,
                                                                                         total_cands);
-    disc_compact_kernel<<<n_items, 1024, 0, s>>>(table);
-    if (total_init > 0) disc_init_kernel<<<total_init, kWaveSize, 0, s>>>(table, n_items);
+    disc_compact_kernel<<<n_items, 1024, 0, s>>>(one, table);
+    if (total_init > 0) disc_init_kernel<<<total_init, kWaveSize, 0, s>>>(one, table, n_items);
     return hipGetLastError();
 }
 
