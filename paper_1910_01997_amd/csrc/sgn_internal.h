@@ -62,23 +62,26 @@ struct FrameIn {
 };
 // K R K^-1 and K t (Eq. 6) in double, the q_z row rounded once to float.  A
 // lone keyframe's frames are formed on the host and a batch's on the device:
-// every operation is an IEEE one and the fused ones are written out, so both
-// give the same bits.
+// every operation is an IEEE one, and which product of a fused pair is
+// rounded by itself is written out, so both give the same bits (an ulp here
+// moves the last bits of a few warp constants, and with them the path of
+// some weakly determined surfels).
 __host__ __device__ inline void frame_constants(const FrameIn& in, FrameDev& F) {
 #pragma clang fp contract(off)
     const double fx = in.K[0], fy = in.K[1], cx = in.K[2], cy = in.K[3];
+    const double* R = in.R;
+    // K R
+    const double k[9] = {fma(fx, R[0], cx * R[6]), fma(fx, R[1], cx * R[7]), fma(fx, R[2], cx * R[8]),
+                         fma(cy, R[6], fy * R[3]), fma(fy, R[4], cy * R[7]), fma(cy, R[8], fy * R[5]),
+                         R[6],                     R[7],                     R[8]};
     for (int r = 0; r < 3; ++r) {
-        // row r of K R
-        const double f = r == 0 ? fx : fy, o = r == 0 ? cx : cy;
-        double k[3];
-        for (int c = 0; c < 3; ++c) k[c] = r == 2 ? in.R[6 + c] : fma(f, in.R[3 * r + c], o * in.R[6 + c]);
         // times K^-1 = [[1/fx, 0, -cx/fx], [0, 1/fy, -cy/fy], [0, 0, 1]]
-        F.hm[3 * r + 0] = k[0] / fx;
-        F.hm[3 * r + 1] = k[1] / fy;
-        F.hm[3 * r + 2] = k[2] - k[0] * cx / fx - k[1] * cy / fy;
+        F.hm[3 * r + 0] = k[3 * r] / fx;
+        F.hm[3 * r + 1] = k[3 * r + 1] / fy;
+        F.hm[3 * r + 2] = k[3 * r + 2] - k[3 * r] * cx / fx - k[3 * r + 1] * cy / fy;
     }
     F.kt[0] = fma(fx, in.t[0], cx * in.t[2]);
-    F.kt[1] = fma(fy, in.t[1], cy * in.t[2]);
+    F.kt[1] = fma(cy, in.t[2], fy * in.t[1]);
     F.kt[2] = in.t[2];
     F.zrow[0] = (float)F.hm[6];
     F.zrow[1] = (float)F.hm[7];
