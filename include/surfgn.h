@@ -162,12 +162,15 @@ typedef struct {
                                    S = 8 and 16: 1x1, an S = 16 surfel giving each lane
                                    four pixels).  Plans with the same pixels per lane
                                    give bitwise-equal results */
-    int32_t persistent;         /* 1: persistent grid pulling work items from a
-                                   device queue; 0: one wavefront per work item */
-    int32_t waves_per_cu;       /* persistent grid size per compute unit (0: occupancy) */
+    int32_t persistent;         /* with waves_per_cu > 0: a persistent grid pulling work
+                                   items from device queues, for a caller that gives the
+                                   call part of the device only.  Otherwise one wavefront
+                                   per work item (never slower where the whole device is
+                                   free) */
+    int32_t waves_per_cu;       /* persistent grid size per compute unit (0: not bounded) */
     int32_t lds_stage;          /* 1: stage neighbour-frame footprints in LDS */
-    int32_t xcd_queues;         /* 1: keyframes bound to an XCD, balanced by work: with
-                                   persistent, one device queue per XCD; without, the
+    int32_t xcd_queues;         /* 1: keyframes bound to an XCD, balanced by work: in a
+                                   persistent grid, one device queue per XCD; else the
                                    workgroups the hardware gives XCD x (every eighth,
                                    from x) take XCD x's share of the work items in
                                    order (batches of eight keyframes or more; fewer
@@ -238,8 +241,8 @@ sgn_status sgn_render_inverse_depth(sgn_ctx* ctx, const sgn_keyframe* kf,
                                     int32_t* index_out);
 
 /* The whole per-keyframe update for many keyframes at once: initialisation
- * of new surfels, the Gauss-Newton iterations in one fused kernel launch
- * (persistent, or one wavefront per work item as the plan says), and the
+ * of new surfels, the Gauss-Newton iterations in one fused kernel launch,
+ * and the
  * inverse-depth render.  All
  * items must share patch and image dtype.  Results equal those of the
  * per-keyframe calls for the same plan (each surfel is reduced in a fixed
@@ -248,8 +251,8 @@ sgn_status sgn_optimize_batch(sgn_ctx* ctx, const sgn_batch_item* items, int32_t
                               const sgn_params* params, const sgn_plan* plan /* NULL: default */);
 
 /* Time candidate plans on a sample batch and return the fastest in *out
- * (host): every tile layout with its group counts, persistent or not, XCD
- * queues or shares or not; each timed as the fastest of three runs after a warm-up
+ * (host): every tile layout with its group counts, XCD shares or not; each
+ * timed as the fastest of three runs after a warm-up
  * run.  When the default plan is within 1 % of the fastest it is returned
  * instead (a tie at the timer's resolution), so a batch gets the same plan
  * from run to run.  The surfel state is snapshotted into the workspace

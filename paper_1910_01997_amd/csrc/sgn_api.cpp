@@ -359,10 +359,33 @@ sgn_plan default_plan(int patch) {
     if (patch == 4) { p.tiles_x = 4; p.tiles_y = 4; }
     else { p.tiles_x = 1; p.tiles_y = 1; }
     p.groups = default_groups(patch, p.tiles_x, p.tiles_y);
-    p.persistent = patch == 4 ? 0 : 1;
+    p.persistent = 0;
     p.waves_per_cu = 0;
     p.lds_stage = 0;
     p.xcd_queues = 1;
+    return p;
+}
+
+// Work items of a batch under a tile layout.
+int64_t count_items(const sgn_batch_item* items, int n, const ItemGeo& geo) {
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) {
+        const sgn_keyframe& kf = items[i].kf;
+        const int64_t bx = (kf.kf.width / kf.patch + geo.ab - 1) / geo.ab, by = (kf.kf.height / kf.patch + geo.ab - 1) / geo.ab;
+        total += bx * by * geo.ipb;
+    }
+    return total;
+}
+
+// The default plan of a batch.  8 x 8 surfels take four groups per wavefront
+// (the solves of four surfels issued once) only where that still leaves the
+// chip eight wavefronts per SIMD: 96 us against 189 with four groups at
+// 4,800 surfels, 285 against 305 at 19,200, 423 against 397 at 38,400.
+sgn_plan default_plan_for(const sgn_ctx* c, const sgn_batch_item* items, int n) {
+    const int patch = items[0].kf.patch;
+    sgn_plan p = default_plan(patch);
+    if (patch == 8 && count_items(items, n, item_geo(8, 1, 1, 1)) < 32 * (int64_t)std::max(1, c->cus) * 4)
+        p.groups = 1;
     return p;
 }
 
@@ -413,6 +436,45 @@ std::vector<int> share_order(int nq, const std::vector<int64_t>& work, const std
     return order;
 }
 
+// The form of a four-pixels-per-lane kernel (the 4x4 layout of 4x4 surfels,
+// 16 x 16 surfels) for the batch's number of work items; every form adds the
+// same terms in the same order, so results do not depend on it.  w = items
+// per SIMD:
+//   w <= 0.65  a column's pixels on four lanes, four frames in flight: a lone
+//              wavefront's time is its instructions' latency, and the chip
+//              has room for four times the wavefronts.  61 us against 108 for
+//              the plain form at 300 items (6 neighbours, f16), 82 at 910.
+//   w <= 1.75  on two lanes, two frames: 87 us against 113 at 1,200 items
+//              and 117 at 1,530 (four lanes: 104 and 121).
+//   w <= 3     unsplit, two frames: 100 us against 120 at 1,900, 125 against
+//              144 at 3,072 (two lanes: 103 and 151).
+//   w <= 24, or f32
+//              one frame in flight at five wavefronts per SIMD: 180 us
+//              against 200 at 4,200, 308 against 327 at 8,295, 550 against
+//              545 at 16,950 (whole calls 583 against 624: fewer resident
+//              wavefronts leave a shorter tail); on the 64-keyframe f32 batch
+//              4.25 ms against 4.79.
+//   otherwise  one sample at a time at seven wavefronts per SIMD: f16 batch
+//              4.23 ms against 4.29, u8 4.17 against 4.44.
+// The damped variant sums a candidate's cost along a column's pixels in
+// turn, so it is not split.
+void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_params* prm, GnVariant& v) {
+    const bool four_px = v.patch == 16 || (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4);
+    if (!four_px || v.persistent) return;
+    const int64_t total = count_items(items, n, item_geo(v.patch, v.tiles_x, v.tiles_y, v.groups));
+    const double w = (double)total / (4.0 * std::max(1, c->cus));
+    const bool can_split = v.patch == 4 && !(prm->lm_lambda > 0.f);
+    if (can_split && w <= 0.65) {
+        v.split = 4; v.deep = 4; v.tiles_x = 2; v.tiles_y = 2;
+    } else if (can_split && w <= 1.75) {
+        v.split = 2; v.deep = 2; v.tiles_x = 4; v.tiles_y = 2;
+    } else if (w <= 3.0) {
+        v.deep = 2;
+    } else if (w <= 24.0 || v.dtype == SGN_F32) {
+        v.deep = 1;
+    }
+}
+
 // Build the descriptor table for a batch, upload it and enqueue the kernels.
 sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_params* prm,
                      const sgn_plan* plan_in, RunFlags fl) {
@@ -433,12 +495,19 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         return fail(SGN_E_UNSUPPORTED, "batch larger than SGN_MAX_BATCH keyframes or SGN_MAX_BATCH_FRAMES frames");
     sgn_status st = check_params(prm);
     if (st) return st;
-    sgn_plan plan = plan_in ? *plan_in : default_plan(patch);
-    if (plan.tiles_x == 0 && plan.tiles_y == 0) plan = default_plan(patch);
+    sgn_plan plan = plan_in ? *plan_in : default_plan_for(c, items, n);
+    if (plan.tiles_x == 0 && plan.tiles_y == 0) plan = default_plan_for(c, items, n);
     if (plan.groups == 0) plan.groups = default_groups(patch, plan.tiles_x, plan.tiles_y);
+    // A grid of fixed size runs only where the plan bounds it: handing the
+    // items out from device queues took 1.6-4 times the hardware dispatcher's
+    // time at every measured size (300 to 104,000 items).
+    plan.persistent = plan.persistent && plan.waves_per_cu > 0;
     GnVariant var{dtype, patch, plan.tiles_x, plan.tiles_y, plan.lds_stage, plan.groups,
-                  (int)rows_by_index(items, n)};
+                  (int)rows_by_index(items, n), 0, 1, plan.persistent};
     if (fl.gn && !gn_variant_supported(var)) return fail(SGN_E_UNSUPPORTED, "plan not supported for this patch");
+    if (fl.gn) choose_form(c, items, n, prm, var);
+    plan.tiles_x = var.tiles_x;
+    plan.tiles_y = var.tiles_y;
 
     // one keyframe's table travels with each launch; several, or a work queue
     // to clear, take a staging slot and an upload
@@ -565,7 +634,7 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     if (H->do_init) e = launch_init(one.one, dH, std::max(1, c->cus) * 8, c->stream);
     if (e == hipSuccess && fl.gn && item_base > 0) {
         next_timing_slot(c);
-        e = launch_gn(var, one, dH, c->counters, plan.persistent, gn_grid, c->stream, c->gn_start, c->gn_end);
+        e = launch_gn(var, one, dH, c->counters, gn_grid, c->stream, c->gn_start, c->gn_end);
         if (e == hipSuccess) c->gn_timed = true;
     }
     // one segment per thread for the larger batches (runs of 256 segments per
@@ -864,9 +933,7 @@ sgn_status sgn_optimize_keyframe(sgn_ctx* c, const sgn_keyframe* kf, const sgn_s
     sgn_batch_item it{};
     it.kf = *kf;
     if (s) it.surfels = *s;
-    sgn_plan pl = plan ? *plan : default_plan(kf->patch);
-    if (!plan) pl.persistent = 0;   // one keyframe: one wavefront per work item
-    return run_batch(c, &it, 1, p, &pl, RunFlags{false, true, false});
+    return run_batch(c, &it, 1, p, plan, RunFlags{false, true, false});
 }
 
 sgn_status sgn_render_inverse_depth(sgn_ctx* c, const sgn_keyframe* kf, const sgn_surfels* s,
@@ -1314,31 +1381,30 @@ sgn_status sgn_autotune(sgn_ctx* c, const sgn_batch_item* items, int32_t n, cons
     const std::vector<int> group_counts = patch == 16 ? std::vector<int>{1} : std::vector<int>{1, 2, 4};
     for (auto sh : shapes)
         for (int groups : group_counts)
-            for (int pers = 0; pers <= 1; ++pers)
-                for (int xq = 0; xq <= 1; ++xq) {
-                    // under eight keyframes the one-wavefront-per-item grid
-                    // ignores xcd_queues: the same launch as xq = 0
-                    if (!pers && xq && n < kXcds) continue;
-                    sgn_plan pl{};
-                    pl.tiles_x = sh.first;
-                    pl.tiles_y = sh.second;
-                    pl.groups = groups;
-                    pl.persistent = pers;
-                    pl.xcd_queues = xq;
-                    pl.lds_stage = 0;
-                    pl.waves_per_cu = 0;
-                    cands.push_back(pl);
-                }
+            for (int xq = 0; xq <= 1; ++xq) {
+                // under eight keyframes the grid ignores xcd_queues: the
+                // same launch as xq = 0
+                if (xq && n < kXcds) continue;
+                sgn_plan pl{};
+                pl.tiles_x = sh.first;
+                pl.tiles_y = sh.second;
+                pl.groups = groups;
+                pl.persistent = 0;
+                pl.xcd_queues = xq;
+                pl.lds_stage = 0;
+                pl.waves_per_cu = 0;
+                cands.push_back(pl);
+            }
     float best = 1e30f;
-    sgn_plan best_plan = default_plan(patch);
+    sgn_plan best_plan = default_plan_for(c, items, n);
     const char* log_env = std::getenv("SGN_AUTOTUNE_LOG");    // set to 1: print every trial
     const bool log = log_env && log_env[0] == '1';
     sgn_status result = SGN_OK;
-    const sgn_plan dflt = default_plan(patch);
+    const sgn_plan dflt = default_plan_for(c, items, n);
     float dflt_ms = 1e30f;
     for (const sgn_plan& pl : cands) {
         GnVariant v{items[0].kf.kf.dtype, patch, pl.tiles_x, pl.tiles_y, pl.lds_stage, pl.groups,
-                    (int)rows_by_index(items, n)};
+                    (int)rows_by_index(items, n), 0, 1, 0};
         if (!gn_variant_supported(v)) continue;
         float tmin = 1e30f;
         bool ok = true;

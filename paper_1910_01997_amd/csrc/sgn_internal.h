@@ -146,6 +146,9 @@ struct GnVariant {
     int lds;        // stage footprints in LDS
     int groups;     // surfel groups per work item (1, 2 or 4)
     int by_row;     // neighbour rows read by index (every row pitch below kMaxRowStride)
+    int deep;       // frames whose taps are in flight at once (0: one sample at a time)
+    int split;      // lanes per pixel column of the 4x4 layout (1, 2 or 4)
+    int persistent; // a grid of fixed size pulling items from device queues
 };
 // Row pitch (bytes) up to which neighbour images are read through a
 // structured buffer, the row as the index: the descriptor's stride field holds
@@ -209,7 +212,7 @@ hipError_t launch_init(const LoneKf& one, const BatchHeader* hdr, int grid, hipS
 hipError_t launch_render(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s);
 // The kernel's own start and end go to the two events.
 hipError_t launch_gn(const GnVariant& v, const LoneBatch& one, const BatchHeader* hdr, uint32_t* counters,
-                     int persistent, int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+                     int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 // Device address of the static scratch array on `device` (which must be the
 // current device), looked up on the first call for that device and kept.
 hipError_t static_scratch_on(int device, void** out);

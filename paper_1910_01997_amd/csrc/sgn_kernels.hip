@@ -164,8 +164,15 @@ __device__ __forceinline__ int find_kf(cptr<KfDev> kfs, int n_kf, int item, int 
 __device__ __forceinline__ int pull_item(cptr<BatchHeader> hdr, uint32_t* counters,
                                          int& q, int& q_left, int lane, int total) {
     while (q_left > 0) {
+        // a plain read of the head first: once a queue is empty every
+        // wavefront of the grid comes by, and an atomic from each, one after
+        // another on the same word, costs more than the work of a small batch
         int got = 0;
-        if (lane == 0) got = (int)atomicAdd(&counters[q], 1u);
+        if (lane == 0) {
+            const int size = hdr->queues[q].end - hdr->queues[q].begin;
+            got = (int)__hip_atomic_load(&counters[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (got < size) got = (int)atomicAdd(&counters[q], 1u);
+        }
         got = __builtin_amdgcn_readfirstlane(got);
         const int it = hdr->queues[q].begin + got;
         if (it < hdr->queues[q].end) return it;
@@ -477,23 +484,31 @@ __device__ __forceinline__ void load_row_pair(__amdgpu_buffer_rsrc_t rs, unsigne
         b = __builtin_amdgcn_raw_buffer_load_b64(rs, o, pitch_b, 0);
     }
 }
-template <typename T, bool BY_ROW>
-__device__ __forceinline__ Taps load_taps(__amdgpu_buffer_rsrc_t rs, unsigned row, unsigned col,
-                                          unsigned pitch_b) {
-    Taps t;
+// The loaded words of a sample's two tap rows, and their decoding.
+struct TapWords {
     u32x2 a, b;
+};
+template <typename T, bool BY_ROW>
+__device__ __forceinline__ TapWords load_words(__amdgpu_buffer_rsrc_t rs, unsigned row, unsigned col,
+                                               unsigned pitch_b) {
+    TapWords w;
+    if constexpr (std::is_same<T, float>::value) load_row_pair<BY_ROW>(rs, row, col, pitch_b, w.a, w.b);
+    else load_row_pair<BY_ROW>(rs, row, col & ~3u, pitch_b, w.a, w.b);
+    return w;
+}
+template <typename T>
+__device__ __forceinline__ Taps decode_taps(const TapWords& w, unsigned col) {
+    Taps t;
     if constexpr (std::is_same<T, float>::value) {
-        load_row_pair<BY_ROW>(rs, row, col, pitch_b, a, b);
-        t.i00 = __uint_as_float(a.x);
-        t.i01 = __uint_as_float(a.y);
-        t.i10 = __uint_as_float(b.x);
-        t.i11 = __uint_as_float(b.y);
+        t.i00 = __uint_as_float(w.a.x);
+        t.i01 = __uint_as_float(w.a.y);
+        t.i10 = __uint_as_float(w.b.x);
+        t.i11 = __uint_as_float(w.b.y);
     } else {
         // u8: the byte shift of v_alignbyte is its third operand mod 4 (the
         // pitch is a multiple of 4, so col's shift is the address's)
-        load_row_pair<BY_ROW>(rs, row, col & ~3u, pitch_b, a, b);
-        const unsigned pa = __builtin_amdgcn_alignbyte(a.y, a.x, col);
-        const unsigned pb = __builtin_amdgcn_alignbyte(b.y, b.x, col);
+        const unsigned pa = __builtin_amdgcn_alignbyte(w.a.y, w.a.x, col);
+        const unsigned pb = __builtin_amdgcn_alignbyte(w.b.y, w.b.x, col);
         t.i00 = (float)(pa & 0xffu);
         t.i01 = (float)((pa >> 8) & 0xffu);
         t.i10 = (float)(pb & 0xffu);
@@ -511,18 +526,6 @@ struct Lerp {
     float d0, top, d1, bot;
 };
 
-template <typename T, bool BY_ROW>
-__device__ __forceinline__ Lerp lerp_rows(__amdgpu_buffer_rsrc_t rs, unsigned row, unsigned col, unsigned pitch_b,
-                                          float ax) {
-    const Taps t = load_taps<T, BY_ROW>(rs, row, col, pitch_b);
-    Lerp l;
-    l.d0 = t.i01 - t.i00;
-    l.d1 = t.i11 - t.i10;
-    l.top = fmaf(ax, l.d0, t.i00);
-    l.bot = fmaf(ax, l.d1, t.i10);
-    return l;
-}
-
 // hi - lo of a packed pair of halves, in float
 __device__ __forceinline__ float half_pair_diff(unsigned pk) {
     float r;
@@ -536,28 +539,32 @@ __device__ __forceinline__ float half_lo_fma(float a, float b, unsigned pk) {
     return r;
 }
 
-template <bool BY_ROW>
-__device__ __forceinline__ Lerp lerp_rows_f16(__amdgpu_buffer_rsrc_t rs, unsigned row, unsigned col,
-                                              unsigned pitch_b, float ax) {
-    // pitch_b is a multiple of 4; the byte funnel shift (v_alignbyte) takes
-    // its amount mod 4, so col gives the address's shift
-    u32x2 va, vb;
-    load_row_pair<BY_ROW>(rs, row, col & ~3u, pitch_b, va, vb);
-    const unsigned a = __builtin_amdgcn_alignbyte(va.y, va.x, col);  // (I(x0), I(x0+1)) of row y0
-    const unsigned b = __builtin_amdgcn_alignbyte(vb.y, vb.x, col);  // of row y0 + 1
+template <typename T>
+__device__ __forceinline__ Lerp lerp_words(const TapWords& w, unsigned col, float ax) {
     Lerp l;
-    l.d0 = half_pair_diff(a);
-    l.d1 = half_pair_diff(b);
-    l.top = half_lo_fma(ax, l.d0, a);
-    l.bot = half_lo_fma(ax, l.d1, b);
+    if constexpr (std::is_same<T, _Float16>::value) {
+        // the byte funnel shift (v_alignbyte) takes its amount mod 4, so col
+        // gives the address's shift (the pitch is a multiple of 4)
+        const unsigned a = __builtin_amdgcn_alignbyte(w.a.y, w.a.x, col);  // (I(x0), I(x0+1)) of row y0
+        const unsigned b = __builtin_amdgcn_alignbyte(w.b.y, w.b.x, col);  // of row y0 + 1
+        l.d0 = half_pair_diff(a);
+        l.d1 = half_pair_diff(b);
+        l.top = half_lo_fma(ax, l.d0, a);
+        l.bot = half_lo_fma(ax, l.d1, b);
+    } else {
+        const Taps t = decode_taps<T>(w, col);
+        l.d0 = t.i01 - t.i00;
+        l.d1 = t.i11 - t.i10;
+        l.top = fmaf(ax, l.d0, t.i00);
+        l.bot = fmaf(ax, l.d1, t.i10);
+    }
     return l;
 }
 
 template <typename T, bool BY_ROW>
 __device__ __forceinline__ Lerp sample_rows(__amdgpu_buffer_rsrc_t rs, unsigned row, unsigned col,
                                             unsigned pitch_b, float ax) {
-    if constexpr (std::is_same<T, _Float16>::value) return lerp_rows_f16<BY_ROW>(rs, row, col, pitch_b, ax);
-    else return lerp_rows<T, BY_ROW>(rs, row, col, pitch_b, ax);
+    return lerp_words<T>(load_words<T, BY_ROW>(rs, row, col, pitch_b), col, ax);
 }
 
 // floor(x) converted to int in one instruction (v_cvt_flr_i32_f32).
@@ -648,49 +655,61 @@ __device__ __forceinline__ void frame_loop(const float* __restrict__ pc, cptr<Fr
 }
 
 // One sample from its homogeneous warp q = (nxq, nyq, qz) in local
-// coordinates (see the pair words): validity on the integer corner, the
-// bilinear value and exact gradient, residual, Huber IRLS weight and chain
-// factor; accumulates A, B, the valid count and (LAST) the Huber cost.
-template <typename T, bool LAST, bool BY_ROW>
-__device__ __forceinline__ void sample_at(float nxq, float nyq, float qz, const float4& c0, const float4& c1,
-                                          const float4& c2, float k2, __amdgpu_buffer_rsrc_t rs, bool pix_ok,
-                                          unsigned pitch_b, unsigned wm1, unsigned hm1, float ikf, float hk,
-                                          float img_scale, float& A, float& B, float& cst, unsigned& nvl,
-                                          unsigned one = 1u) {
-    constexpr bool SCALED = std::is_same<T, uint8_t>::value;
-    const float rq = rcp_fast(qz);
-    const float fx = nxq * rq;                            // x_p - X0
-    const float fy = nyq * rq;                            // y_p - Y0
-    const int flx = cvt_floor(fx), fly = cvt_floor(fy);
+// coordinates (see the pair words).  sample_warp: projection and validity on
+// the integer corner; sample_load: the tap words of a valid sample;
+// sample_use: bilinear value and exact gradient, residual, Huber IRLS weight
+// and chain factor, accumulating A, B, the valid count and (LAST) the Huber
+// cost.
+struct Sample {
+    float fx, fy, rq;           // x_p - X0, y_p - Y0, 1 / q_z
+    unsigned row, col;          // tap corner: row y0, byte column of x0
+    bool v;
+};
+template <typename T>
+__device__ __forceinline__ Sample sample_warp(float nxq, float nyq, float qz, const float4& c2, bool pix_ok,
+                                              unsigned wm1, unsigned hm1) {
+    Sample s;
+    s.rq = rcp_fast(qz);
+    s.fx = nxq * s.rq;                                    // x_p - X0
+    s.fy = nyq * s.rq;                                    // y_p - Y0
+    const int flx = cvt_floor(s.fx), fly = cvt_floor(s.fy);
     // unsigned wrap-around: out-of-range (or saturated) corners fail the test
     const unsigned ix = __float_as_uint(c2.y) + (unsigned)flx;
     const unsigned iy = __float_as_uint(c2.z) + (unsigned)fly;
-    if (pix_ok & (qz > 0.f) & (ix < wm1) & (iy < hm1)) {
-        const float ax = __builtin_amdgcn_fractf(fx);
-        const float ay = __builtin_amdgcn_fractf(fy);
-        const Lerp l = sample_rows<T, BY_ROW>(rs, iy, ix * (unsigned)sizeof(T), pitch_b, ax);
-        // bilinear value and the exact gradient of the interpolant
-        const float gy = l.bot - l.top;
-        const float val = fmaf(ay, gy, l.top);
-        const float gx = fmaf(ay, l.d1 - l.d0, l.d0);
-        // residual (Eq. 5) and Huber IRLS weight w = min(1, k/|r|) (Eq. 8)
-        const float r = SCALED ? fmaf(val, img_scale, -ikf) : val - ikf;
-        const float ar = fabsf(r);
-        // (the clamp to [0, 1] folds into the multiply; it maps a NaN weight
-        // to 0 where min(1, NaN) gives 1, which changes nothing the update
-        // reports: B = sum w a r is NaN either way)
-        const float wt = fminf(fmaxf(hk * rcp_fast(ar), 0.f), 1.f);
-        // dr/did_u = grad I . dpi/dq . K t  (Eq. 8 with dq/did_u = K t):
-        // (k0 - x_p k2) = kx - (x_p - X0) k2, likewise for y
-        const float tx_ = fmaf(-fx, k2, c0.z);
-        const float ty_ = fmaf(-fy, k2, c1.z);
-        const float a = fmaf(gx, tx_, gy * ty_) * (SCALED ? rq * img_scale : rq);
-        const float wa = wt * a;
-        A = fmaf(wa, a, A);
-        B = fmaf(wa, r, B);
-        nvl += one;
-        if constexpr (LAST) cst += (ar <= hk) ? 0.5f * r * r : hk * (ar - 0.5f * hk);
-    }
+    s.v = pix_ok & (qz > 0.f) & (ix < wm1) & (iy < hm1);
+    s.row = iy;
+    s.col = ix * (unsigned)sizeof(T);
+    return s;
+}
+template <typename T, bool LAST>
+__device__ __forceinline__ void sample_use(const Sample& s, const TapWords& tw, const float4& c0, const float4& c1,
+                                           float k2, float ikf, float hk, float img_scale, float& A, float& B,
+                                           float& cst, unsigned& nvl, unsigned one) {
+    constexpr bool SCALED = std::is_same<T, uint8_t>::value;
+    const float ax = __builtin_amdgcn_fractf(s.fx);
+    const float ay = __builtin_amdgcn_fractf(s.fy);
+    const Lerp l = lerp_words<T>(tw, s.col, ax);
+    // bilinear value and the exact gradient of the interpolant
+    const float gy = l.bot - l.top;
+    const float val = fmaf(ay, gy, l.top);
+    const float gx = fmaf(ay, l.d1 - l.d0, l.d0);
+    // residual (Eq. 5) and Huber IRLS weight w = min(1, k/|r|) (Eq. 8)
+    const float r = SCALED ? fmaf(val, img_scale, -ikf) : val - ikf;
+    const float ar = fabsf(r);
+    // (the clamp to [0, 1] folds into the multiply; it maps a NaN weight
+    // to 0 where min(1, NaN) gives 1, which changes nothing the update
+    // reports: B = sum w a r is NaN either way)
+    const float wt = fminf(fmaxf(hk * rcp_fast(ar), 0.f), 1.f);
+    // dr/did_u = grad I . dpi/dq . K t  (Eq. 8 with dq/did_u = K t):
+    // (k0 - x_p k2) = kx - (x_p - X0) k2, likewise for y
+    const float tx_ = fmaf(-s.fx, k2, c0.z);
+    const float ty_ = fmaf(-s.fy, k2, c1.z);
+    const float a = fmaf(gx, tx_, gy * ty_) * (SCALED ? s.rq * img_scale : s.rq);
+    const float wa = wt * a;
+    A = fmaf(wa, a, A);
+    B = fmaf(wa, r, B);
+    nvl += one;
+    if constexpr (LAST) cst += (ar <= hk) ? 0.5f * r * r : hk * (ar - 0.5f * hk);
 }
 
 // The frame loop for the NP pixels of one lane at once: for each neighbour
@@ -702,38 +721,92 @@ __device__ __forceinline__ void sample_at(float nxq, float nyq, float qz, const 
 // homography's y column plus didu times K t.  Accumulates A, B and the cost
 // per pixel as frame_loop does; the valid counts of the pixels are packed
 // one per byte of nvp (pixel j in byte j; at most 16 frames each).
-template <typename T, bool LAST, int NP, bool BY_ROW>
+//
+// DEEP = 0: each pixel's taps are loaded and used before the next pixel's
+// warp, which takes the fewest registers: with seven wavefronts per SIMD the
+// others' arithmetic covers each wait.  DEEP = D > 0: the taps of all the
+// lane's pixels in D frames are loaded before the first is used, for grids
+// that leave a SIMD a wavefront or two and each wait uncovered.  The samples
+// and the order of every sum are the same.
+//
+// SPLIT > 1: a column's pixels are dealt to SPLIT lanes, this lane taking
+// rows row0, row0 + SPLIT, ...; (dx, dy) and idu0 are the column's first
+// pixel's, and the lane walks the same chain of steps to its own rows.
+template <typename T, bool LAST, int NP, bool BY_ROW, int DEEP, int SPLIT>
 __device__ __forceinline__ void frame_loop_px(const float* __restrict__ pc, cptr<FrameDev> fr, int nf,
-                                              float dx, float dy, float dyr, float idu0, float didu,
+                                              float dx, float dy, float dyr, float idu0, float didu, int row0,
                                               const bool (&pix_ok)[NP],
-                                              unsigned pitch_b, unsigned img_bytes, unsigned wm1,
+                                              unsigned pitch_b, unsigned wm1,
                                               unsigned hm1, const float (&ikf)[NP], float hk, float img_scale,
                                               float (&A)[NP], float (&B)[NP], float (&cst)[NP],
                                               unsigned& nvp) {
     static_assert(NP <= 4, "four byte counters");
-    for (int f = 0; f < nf; ++f) {
-        const float4 c0 = *(const float4*)(pc + f * kPairWords);
-        const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
-        const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
-        const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
-        const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
-        // Eq. 6 in local coordinates
-        float nxq = fmaf(c0.x, dx, fmaf(c0.y, dy, fmaf(c0.z, idu0, c0.w)));
-        float nyq = fmaf(c1.x, dx, fmaf(c1.y, dy, fmaf(c1.z, idu0, c1.w)));
-        float qz = fmaf(h6, dx, fmaf(h7, dy, fmaf(k2, idu0, c2.x)));
-        sample_at<T, LAST, BY_ROW>(nxq, nyq, qz, c0, c1, c2, k2, rs, pix_ok[0], pitch_b, wm1, hm1, ikf[0], hk,
-                           img_scale, A[0], B[0], cst[0], nvp, 1u);
-        if constexpr (NP > 1) {
-            const float sx = fmaf(c0.z, didu, c0.y * dyr);
-            const float sy = fmaf(c1.z, didu, c1.y * dyr);
-            const float sz = fmaf(k2, didu, c2.w * dyr);     // c2.w = h7
+    constexpr int D = DEEP > 0 ? DEEP : 1;
+    for (int f0 = 0; f0 < nf; f0 += D) {
+        Sample sm[D][NP];
+        TapWords tw[D][NP];
 #pragma unroll
-            for (int j = 1; j < NP; ++j) {
-                nxq += sx;
-                nyq += sy;
-                qz += sz;
-                sample_at<T, LAST, BY_ROW>(nxq, nyq, qz, c0, c1, c2, k2, rs, pix_ok[j], pitch_b, wm1, hm1, ikf[j],
-                                   hk, img_scale, A[j], B[j], cst[j], nvp, 1u << (8 * j));
+        for (int d = 0; d < D; ++d) {
+            const int f = f0 + d;
+            if (D > 1 && f >= nf) break;               // wave-uniform
+            const float4 c0 = *(const float4*)(pc + f * kPairWords);
+            const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
+            const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
+            const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
+            const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
+            // Eq. 6 in local coordinates
+            float nxq = fmaf(c0.x, dx, fmaf(c0.y, dy, fmaf(c0.z, idu0, c0.w)));
+            float nyq = fmaf(c1.x, dx, fmaf(c1.y, dy, fmaf(c1.z, idu0, c1.w)));
+            float qz = fmaf(h6, dx, fmaf(h7, dy, fmaf(k2, idu0, c2.x)));
+            // the step to the column's next pixel (formed where it is first
+            // used: registers)
+            float sx = 0.f, sy = 0.f, sz = 0.f;
+            auto step = [&]() {
+                sx = fmaf(c0.z, didu, c0.y * dyr);
+                sy = fmaf(c1.z, didu, c1.y * dyr);
+                sz = fmaf(k2, didu, c2.w * dyr);     // c2.w = h7
+            };
+            if constexpr (SPLIT > 1) {
+                step();
+#pragma unroll
+                for (int m = 1; m < SPLIT; ++m) {
+                    nxq += row0 >= m ? sx : 0.f;
+                    nyq += row0 >= m ? sy : 0.f;
+                    qz += row0 >= m ? sz : 0.f;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                if (SPLIT == 1 && j == 1) step();
+#pragma unroll
+                for (int m = 0; m < (j > 0 ? SPLIT : 0); ++m) {
+                    nxq += sx;
+                    nyq += sy;
+                    qz += sz;
+                }
+                Sample& s = sm[d][j];
+                s = sample_warp<T>(nxq, nyq, qz, c2, pix_ok[j], wm1, hm1);
+                if (s.v) {
+                    tw[d][j] = load_words<T, BY_ROW>(rs, s.row, s.col, pitch_b);
+                    if constexpr (DEEP == 0)
+                        sample_use<T, LAST>(s, tw[d][j], c0, c1, k2, ikf[j], hk, img_scale, A[j], B[j], cst[j], nvp,
+                                            1u << (8 * j));
+                }
+            }
+        }
+        if constexpr (DEEP > 0) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int f = f0 + d;
+                if (D > 1 && f >= nf) break;
+                const float4 c0 = *(const float4*)(pc + f * kPairWords);
+                const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
+                const float k2 = fr[f].zrow[2];
+#pragma unroll
+                for (int j = 0; j < NP; ++j)
+                    if (sm[d][j].v)
+                        sample_use<T, LAST>(sm[d][j], tw[d][j], c0, c1, k2, ikf[j], hk, img_scale, A[j], B[j], cst[j],
+                                            nvp, 1u << (8 * j));
             }
         }
     }
@@ -742,27 +815,48 @@ __device__ __forceinline__ void frame_loop_px(const float* __restrict__ pc, cptr
 // Huber cost (Eq. 5) and valid-sample count of one pixel at a candidate
 // state, over all neighbour frames (no Jacobian): the Levenberg-Marquardt
 // acceptance test.
-template <typename T, bool BY_ROW>
+// (DEEP as in frame_loop_px: the taps of that many frames in flight.)
+template <typename T, bool BY_ROW, int DEEP>
 __device__ __forceinline__ void frame_cost(const float* __restrict__ pc, cptr<FrameDev> fr, int nf,
                                            float dx, float dy, float idu, bool pix_ok,
-                                           unsigned pitch_b, unsigned img_bytes, unsigned wm1,
+                                           unsigned pitch_b, unsigned wm1,
                                            unsigned hm1, float ikf, float hk, float img_scale,
                                            float& cst, int& nvl) {
     constexpr bool SCALED = std::is_same<T, uint8_t>::value;
-    for (int f = 0; f < nf; ++f) {
-        const float4 c0 = *(const float4*)(pc + f * kPairWords);
-        const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
-        const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
-        const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
-        const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
-        const Warp w = warp_sample<T>(c0, c1, c2, h6, h7, k2, dx, dy, idu, pix_ok, wm1, hm1, pitch_b);
-        if (w.v) {
-            const Lerp l = sample_rows<T, BY_ROW>(rs, w.row, w.col, pitch_b, w.ax);
-            const float val = fmaf(w.ay, l.bot - l.top, l.top);
-            const float r = SCALED ? fmaf(val, img_scale, -ikf) : val - ikf;
-            const float ar = fabsf(r);
-            cst += (ar <= hk) ? 0.5f * r * r : hk * (ar - 0.5f * hk);
-            ++nvl;
+    constexpr int D = DEEP > 0 ? DEEP : 1;
+    auto use = [&](const Sample& s, const TapWords& w) {
+        const Lerp l = lerp_words<T>(w, s.col, __builtin_amdgcn_fractf(s.fx));
+        const float val = fmaf(__builtin_amdgcn_fractf(s.fy), l.bot - l.top, l.top);
+        const float r = SCALED ? fmaf(val, img_scale, -ikf) : val - ikf;
+        const float ar = fabsf(r);
+        cst += (ar <= hk) ? 0.5f * r * r : hk * (ar - 0.5f * hk);
+        ++nvl;
+    };
+    for (int f0 = 0; f0 < nf; f0 += D) {
+        Sample sm[D];
+        TapWords tw[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int f = f0 + d;
+            if (D > 1 && f >= nf) break;               // wave-uniform
+            const float4 c0 = *(const float4*)(pc + f * kPairWords);
+            const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
+            const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
+            const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
+            const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
+            const float nxq = fmaf(c0.x, dx, fmaf(c0.y, dy, fmaf(c0.z, idu, c0.w)));
+            const float nyq = fmaf(c1.x, dx, fmaf(c1.y, dy, fmaf(c1.z, idu, c1.w)));
+            const float qz = fmaf(h6, dx, fmaf(h7, dy, fmaf(k2, idu, c2.x)));
+            sm[d] = sample_warp<T>(nxq, nyq, qz, c2, pix_ok, wm1, hm1);
+            if (sm[d].v) {
+                tw[d] = load_words<T, BY_ROW>(rs, sm[d].row, sm[d].col, pitch_b);
+                if constexpr (DEEP == 0) use(sm[d], tw[d]);
+            }
+        }
+        if constexpr (DEEP > 0) {
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+                if (f0 + d < nf && sm[d].v) use(sm[d], tw[d]);
         }
     }
 }
@@ -958,21 +1052,28 @@ __device__ __forceinline__ bool lm_accept(float cost2, int nv2, float cost_here,
 // 4.30 at five, 3.94 at six and 3.76 at seven (its 11-12 spilled words are
 // stored and reloaded once per work item, or in the damped variant's
 // branches); at eight, with spills inside the iteration loop, 4.05 ms.
-template <int S, int K>
-constexpr int gn_waves() { return K == 1 ? 7 : (S == 8 ? 6 : 5); }
+// The DEEP forms keep more samples in registers: two frames of four pixels
+// take 144 VGPRs (three wavefronts), one frame 96 (five, 23 spilled words),
+// the SPLIT forms 102.
+template <int S, int K, int DEEP, int SPLIT>
+constexpr int gn_waves() {
+    return SPLIT > 1 ? 4 : DEEP == 2 ? 2 : DEEP == 1 ? 5 : K == 1 ? 7 : (S == 8 ? 6 : 5);
+}
 
-template <typename T, int S, int TX, int TY, int K, bool BY_ROW>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(gn_waves<S, K>(), 8))) void gn_kernel(LoneBatch,
+template <typename T, int S, int TX, int TY, int K, bool BY_ROW, int DEEP, int SPLIT, bool PERSIST>
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(gn_waves<S, K, DEEP, SPLIT>(), 8))) void gn_kernel(LoneBatch,
                                                            const BatchHeader* __restrict__ hdr_,
-                                                           uint32_t* __restrict__ counters,
-                                                           int persistent) {
+                                                           uint32_t* __restrict__ counters) {
     constexpr ItemGeo G = item_geo(S, TX, TY, K);
     constexpr int PIX = S * S;                                // pixels per surfel
     constexpr int SLOTS = TX * TY;                            // surfels per group
     constexpr int LANES = kWaveSize / SLOTS;                  // lanes per surfel
     constexpr int PPL = PIX / LANES;                          // pixels per lane
     constexpr int NS = K * SLOTS;                             // surfels per work item
-    constexpr float DYR = (float)(LANES / S);                 // rows between a lane's pixels
+    constexpr int RL = LANES / SPLIT;                         // lanes that join in a surfel's sums
+    // rows from one pixel of a column's chain to the next
+    constexpr float DYR = SPLIT > 1 ? 1.f : (float)(LANES / S);
+    static_assert(SPLIT == 1 || (S == 4 && K == 1 && PPL * SPLIT == 4 && LANES == S * SPLIT), "split columns");
     static_assert(PPL * LANES == PIX, "a group fills the wavefront");
     static_assert(PPL == 1 || LANES % S == 0, "a lane's pixels share a column");
     static_assert(NS <= kMaxItemSurfels && K <= LANES, "surfels per item");
@@ -985,6 +1086,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     const int r = lane / LANES;
     const int p = lane % LANES;
     const float half = 0.5f * (float)(S - 1);
+    const int row0 = SPLIT > 1 ? p / S : 0;      // the lane's first row in its column's chain
     int pxs[PPL], pys[PPL];
     float dxp[PPL], dyp[PPL];                    // offsets from u_s (exact)
 #pragma unroll
@@ -1019,11 +1121,11 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     float* const lst = (float*)s_state[wave];
     float* const lsm = (float*)s_sums[wave];
 
-    int q = persistent ? (int)(blockIdx.x % (unsigned)kXcds) % hdr->n_queues : 0;
+    int q = PERSIST ? (int)(blockIdx.x % (unsigned)kXcds) % hdr->n_queues : 0;
     int q_left = hdr->n_queues;
     int hint = 0;
     int item;
-    if (persistent) {
+    if constexpr (PERSIST) {
         item = pull_item(hdr, counters, q, q_left, lane, total);
     } else if (hdr->n_queues == kXcds) {
         // one share of the work items per XCD: the hardware hands the
@@ -1038,8 +1140,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     } else {
         item = blockIdx.x * (kBlockThreads / kWaveSize) + wave;
     }
-    for (; item < total;
-         item = persistent ? pull_item(hdr, counters, q, q_left, lane, total) : total) {
+    for (; item < total; item = PERSIST ? pull_item(hdr, counters, q, q_left, lane, total) : total) {
         item = __builtin_amdgcn_readfirstlane(item);
         const int kidx = find_kf(kfs, n_kf, item, hint);
         hint = kidx;
@@ -1055,12 +1156,11 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
         const int nf = Kd->n_nbr;
         const float img_scale = Kd->img_scale;
         const unsigned pitch_b = (unsigned)Kd->nbr_pitch_b;
-        const unsigned img_bytes = pitch_b * (unsigned)Kd->height;
         const unsigned wm1 = (unsigned)(Kd->width - 1), hm1 = (unsigned)(Kd->height - 1);
         const float fxk = Kd->fx, fyk = Kd->fy, cxk = Kd->cx, cyk = Kd->cy;
         // r_u - r_s of the lane's first pixel; its later pixels lie DYR rows
         // apart in the same column, dyr_f apart in r
-        const float drx0 = dxp[0] / fxk, dry0 = dyp[0] / fyk;
+        const float drx0 = dxp[0] / fxk, dry0 = (SPLIT > 1 ? -half : dyp[0]) / fyk;
         const float dyr_f = DYR / fyk;
         // anchor block centre (pixels)
         const int bpx = bx * G.ab * S, bpy = by * G.ab * S;
@@ -1173,25 +1273,26 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                 const float didu = sid * dsig;
 #pragma unroll
                 for (int j = 0; j < PPL; ++j) {
-                    const float sig = j == 0 ? sig0 : fmaf((float)j, dsig, sig0);
+                    const int row = row0 + SPLIT * j;
+                    const float sig = row == 0 ? sig0 : fmaf((float)row, dsig, sig0);
                     pix_ok[j] = salive && (fmaf(sid, sig, sid) > 0.f);
                 }
                 // the first pixel's offset from the anchor block centre; the
                 // lane's later pixels lie DYR rows apart in the same column
                 const float bdx = (float)(S * tx + pxs[0] - bpx) - 0.5f * (float)(G.ab * S - 1);
-                const float bdy = (float)(S * ty + pys[0] - bpy) - 0.5f * (float)(G.ab * S - 1);
-                float A[PPL], B[PPL], cst[PPL];
+                const float bdy = (float)(S * ty + (SPLIT > 1 ? 0 : pys[0]) - bpy) - 0.5f * (float)(G.ab * S - 1);
+                float Ap[PPL], Bp[PPL], cp[PPL];
                 unsigned nvp = 0u;
 #pragma unroll
                 for (int j = 0; j < PPL; ++j) {
-                    A[j] = 0.f; B[j] = 0.f; cst[j] = 0.f;
+                    Ap[j] = 0.f; Bp[j] = 0.f; cp[j] = 0.f;
                 }
                 if (with_cost)
-                    frame_loop_px<T, true, PPL, BY_ROW>(pairs, fr, nf, bdx, bdy, DYR, idu0, didu, pix_ok, pitch_b,
-                                                img_bytes, wm1, hm1, ikf[k], hk, img_scale, A, B, cst, nvp);
+                    frame_loop_px<T, true, PPL, BY_ROW, DEEP, SPLIT>(pairs, fr, nf, bdx, bdy, DYR, idu0, didu, row0, pix_ok, pitch_b,
+                                                wm1, hm1, ikf[k], hk, img_scale, Ap, Bp, cp, nvp);
                 else
-                    frame_loop_px<T, false, PPL, BY_ROW>(pairs, fr, nf, bdx, bdy, DYR, idu0, didu, pix_ok, pitch_b,
-                                                 img_bytes, wm1, hm1, ikf[k], hk, img_scale, A, B, cst, nvp);
+                    frame_loop_px<T, false, PPL, BY_ROW, DEEP, SPLIT>(pairs, fr, nf, bdx, bdy, DYR, idu0, didu, row0, pix_ok, pitch_b,
+                                                 wm1, hm1, ikf[k], hk, img_scale, Ap, Bp, cp, nvp);
                 // the surfel's state and tangent basis, read again from LDS
                 // after the frame loop rather than held in registers through it
                 __asm__ volatile("" ::: "memory");
@@ -1220,7 +1321,29 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                 const float g20 = fmaf(-psig0, q2, fmaf(k2y, dry0, k2x * drx0));
                 const float dg1 = fmaf(-pdsig, q1, k1y * dyr_f);
                 const float dg2 = fmaf(-pdsig, q2, k2y * dyr_f);
-                if constexpr (PPL == 4) {
+                // the lane's valid samples: the byte counters summed (v_sad_u8)
+                unsigned nvs = __builtin_amdgcn_sad_u8(nvp, 0u, 0u);
+                // the column's sums, brought to the lane of its first row
+                constexpr int NC = PPL * SPLIT;
+                float A[NC], B[NC], cst[NC];
+#pragma unroll
+                for (int j = 0; j < PPL; ++j) {
+                    A[SPLIT * j] = Ap[j]; B[SPLIT * j] = Bp[j]; cst[SPLIT * j] = cp[j];
+                    if constexpr (SPLIT >= 2) {
+                        A[SPLIT * j + 1] = dpp_f<0x104>(Ap[j]);      // row_shl:4 (lane i takes lane i + 4)
+                        B[SPLIT * j + 1] = dpp_f<0x104>(Bp[j]);
+                        cst[SPLIT * j + 1] = dpp_f<0x104>(cp[j]);
+                    }
+                    if constexpr (SPLIT == 4) {
+                        A[2] = dpp_f<0x108>(Ap[j]); A[3] = dpp_f<0x10C>(Ap[j]);
+                        B[2] = dpp_f<0x108>(Bp[j]); B[3] = dpp_f<0x10C>(Bp[j]);
+                        cst[2] = dpp_f<0x108>(cp[j]); cst[3] = dpp_f<0x10C>(cp[j]);
+                    }
+                }
+                if constexpr (SPLIT == 2) nvs += (unsigned)dpp_i<0x104>((int)nvs);
+                if constexpr (SPLIT == 4)
+                    nvs += (unsigned)(dpp_i<0x104>((int)nvs) + dpp_i<0x108>((int)nvs) + dpp_i<0x10C>((int)nvs));
+                if constexpr (NC == 4) {
                     // sum_j A_j g_j g_j^T and sum_j B_j g_j with g_j = ga + j gb,
                     // through the lane's moments S_m = sum_j j^m A_j and
                     // T_m = sum_j j^m B_j: with u = S0 ga + S1 gb and
@@ -1261,8 +1384,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                         pcs = (j == 0) ? cst[j] : pcs + cst[j];
                     }
                 }
-                // the lane's valid samples: the byte counters summed (v_sad_u8)
-                pnv = (float)__builtin_amdgcn_sad_u8(nvp, 0u, 0u);
+                pnv = (float)nvs;
                 // reduced two at a time: lane 0 of the surfel ends with words
                 // 0, 2, 4, 6, 8 and lane 1 with words 1, 3, 5, 7, 9 (the valid
                 // count as an exact float)
@@ -1273,24 +1395,24 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                     // on which lane forms them.
 #pragma clang fp contract(off)
                     const bool odd = (p & 1) != 0;
-                    s0 = pair_sum<LANES>(ph[0], ph[1], odd);     // H00 | H01
-                    s1 = pair_sum<LANES>(ph[2], ph[3], odd);     // H02 | H11
-                    s2 = pair_sum<LANES>(ph[4], ph[5], odd);     // H12 | H22
-                    s3 = pair_sum<LANES>(ph[6], ph[7], odd);     // b0  | b1
-                    s4 = pair_sum<LANES>(ph[8], pnv, odd);       // b2  | nv
+                    s0 = pair_sum<RL>(ph[0], ph[1], odd);     // H00 | H01
+                    s1 = pair_sum<RL>(ph[2], ph[3], odd);     // H02 | H11
+                    s2 = pair_sum<RL>(ph[4], ph[5], odd);     // H12 | H22
+                    s3 = pair_sum<RL>(ph[6], ph[7], odd);     // b0  | b1
+                    s4 = pair_sum<RL>(ph[8], pnv, odd);       // b2  | nv
                 }
                 // In a 4-lane surfel lanes 2 and 3 end with the sums of lanes 0
                 // and 1, formed from the same two partial sums (the adds
                 // commute), so they store the same words: no branch, and the
                 // last butterfly add stays a DPP add over the whole wavefront.
                 float* const o = lsm + (k * SLOTS + r) * SM_WORDS;
-                if (LANES == 4 || p < 2) {
+                if (LANES == 4 || p < (RL == 4 ? 4 : 2)) {
                     const int w = p & 1;
                     o[w] = s0; o[w + 2] = s1; o[w + 4] = s2; o[w + 6] = s3; o[w + 8] = s4;
                 }
                 if (with_cost) {
-                    const float cs = group_sum<LANES>(pcs);    // 4 lanes: the same in each
-                    if (LANES == 4 || p == 0) o[SM_COST] = cs;
+                    const float cs = group_sum<RL>(pcs);       // 4 lanes: the same in each
+                    if (LANES == 4 || p < (RL == 4 ? 4 : 1)) o[SM_COST] = cs;
                 }
             }
             wave_sync();
@@ -1425,7 +1547,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                 }
                 // owner_step body end
             }
-            if (lm) {
+            if (SPLIT == 1 && lm) {
                 // Levenberg-Marquardt: the candidate's cost over the pixels,
                 // then the acceptance test (lm_accept)
                 float inv_cc = 0.f;
@@ -1467,8 +1589,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                         // formed here, not kept from the item's start through the
                         // iterations (registers)
                         __asm__ volatile("" : "+v"(bdx), "+v"(bdy));
-                        frame_cost<T, BY_ROW>(pairs, fr, nf, bdx, bdy, idu_c, calive && (idu_c > 0.f), pitch_b,
-                                      img_bytes, wm1, hm1, ikf[k][j], hk, img_scale, cst2, nv2l);
+                        frame_cost<T, BY_ROW, DEEP ? 4 : 0>(pairs, fr, nf, bdx, bdy, idu_c, calive && (idu_c > 0.f),
+                                                           pitch_b, wm1, hm1, ikf[k][j], hk, img_scale, cst2, nv2l);
                     }
                     const float c2 = group_sum<LANES>(cst2);
                     const int n2 = group_sum<LANES>(nv2l);
@@ -1863,41 +1985,60 @@ hipError_t launch_quantize(const float* src, int src_pitch, void* dst, int dst_p
     return hipGetLastError();
 }
 
-template <typename T, int S, int TX, int TY, int K, bool R>
+template <typename T, int S, int TX, int TY, int K, bool R, bool P, int D = 0, int SPLIT = 1>
 static void* gn_ptr() {
-    return (void*)&gn_kernel<T, S, TX, TY, K, R>;
+    return (void*)&gn_kernel<T, S, TX, TY, K, R, D, SPLIT, P>;
 }
 
-template <typename T, int S, int TX, int TY, bool R, int KMAX = 4>
+template <typename T, int S, int TX, int TY, bool R, bool P, int KMAX = 4>
 static void* gn_pick_groups(int groups) {
-    if (groups == 1) return gn_ptr<T, S, TX, TY, 1, R>();
-    if (groups == 2) return gn_ptr<T, S, TX, TY, 2, R>();
+    if (groups == 1) return gn_ptr<T, S, TX, TY, 1, R, P>();
+    if (groups == 2) return gn_ptr<T, S, TX, TY, 2, R, P>();
     if constexpr (KMAX >= 4)
-        if (groups == 4) return gn_ptr<T, S, TX, TY, 4, R>();
+        if (groups == 4) return gn_ptr<T, S, TX, TY, 4, R, P>();
     return nullptr;
 }
 
-template <typename T, bool R>
+template <typename T, bool R, bool P>
 static void* gn_pick(const GnVariant& v) {
-    if (v.patch == 8 && v.tiles_x == 1 && v.tiles_y == 1) return gn_pick_groups<T, 8, 1, 1, R>(v.groups);
+    if (v.patch == 8 && v.tiles_x == 1 && v.tiles_y == 1) return gn_pick_groups<T, 8, 1, 1, R, P>(v.groups);
     // a 16 x 16 surfel is its own anchor block: one group per item
-    if (v.patch == 16 && v.tiles_x == 1 && v.tiles_y == 1 && v.groups == 1) return gn_ptr<T, 16, 1, 1, 1, R>();
-    if (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 1) return gn_pick_groups<T, 4, 4, 1, R>(v.groups);
-    if (v.patch == 4 && v.tiles_x == 2 && v.tiles_y == 2) return gn_pick_groups<T, 4, 2, 2, R>(v.groups);
-    if (v.patch == 4 && v.tiles_x == 1 && v.tiles_y == 4) return gn_pick_groups<T, 4, 1, 4, R>(v.groups);
+    if (v.patch == 16 && v.tiles_x == 1 && v.tiles_y == 1 && v.groups == 1) return gn_ptr<T, 16, 1, 1, 1, R, P>();
+    if (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 1) return gn_pick_groups<T, 4, 4, 1, R, P>(v.groups);
+    if (v.patch == 4 && v.tiles_x == 2 && v.tiles_y == 2) return gn_pick_groups<T, 4, 2, 2, R, P>(v.groups);
+    if (v.patch == 4 && v.tiles_x == 1 && v.tiles_y == 4) return gn_pick_groups<T, 4, 1, 4, R, P>(v.groups);
     // eight 4 x 4 surfels per wavefront, two pixels per lane: one or two groups
-    if (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 2) return gn_pick_groups<T, 4, 4, 2, R, 2>(v.groups);
-    if (v.patch == 4 && v.tiles_x == 2 && v.tiles_y == 4) return gn_pick_groups<T, 4, 2, 4, R, 2>(v.groups);
+    if (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 2) return gn_pick_groups<T, 4, 4, 2, R, P, 2>(v.groups);
+    if (v.patch == 4 && v.tiles_x == 2 && v.tiles_y == 4) return gn_pick_groups<T, 4, 2, 4, R, P, 2>(v.groups);
     // sixteen 4 x 4 surfels (a whole anchor block) per wavefront, four pixels per lane
-    if (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4 && v.groups == 1) return gn_ptr<T, 4, 4, 4, 1, R>();
+    if (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4 && v.groups == 1) return gn_ptr<T, 4, 4, 4, 1, R, P>();
     return nullptr;
+}
+
+// the forms for grids that leave the chip short of wavefronts (four pixels
+// per lane: the 4x4 layout of 4x4 surfels, and 16 x 16 surfels)
+template <typename T, bool R>
+static void* gn_pick_deep(const GnVariant& v) {
+    if (v.split == 4) return gn_ptr<T, 4, 2, 2, 1, R, false, 4, 4>();
+    if (v.split == 2) return gn_ptr<T, 4, 4, 2, 1, R, false, 2, 2>();
+    if (v.patch == 16) return v.deep == 2 ? gn_ptr<T, 16, 1, 1, 1, R, false, 2>() : gn_ptr<T, 16, 1, 1, 1, R, false, 1>();
+    return v.deep == 2 ? gn_ptr<T, 4, 4, 4, 1, R, false, 2>() : gn_ptr<T, 4, 4, 4, 1, R, false, 1>();
+}
+
+template <typename T>
+static void* gn_pick_rows(const GnVariant& v) {
+    // a persistent grid reads rows by offset whatever the pitch (bitwise the
+    // same; it exists for plans that take only part of the device)
+    if (v.persistent) return gn_pick<T, false, true>(v);
+    if (v.deep) return v.by_row ? gn_pick_deep<T, true>(v) : gn_pick_deep<T, false>(v);
+    return v.by_row ? gn_pick<T, true, false>(v) : gn_pick<T, false, false>(v);
 }
 
 static void* gn_select(const GnVariant& v) {
     if (v.lds) return nullptr;
-    if (v.dtype == 0) return v.by_row ? gn_pick<float, true>(v) : gn_pick<float, false>(v);
-    if (v.dtype == 1) return v.by_row ? gn_pick<_Float16, true>(v) : gn_pick<_Float16, false>(v);
-    if (v.dtype == 2) return v.by_row ? gn_pick<uint8_t, true>(v) : gn_pick<uint8_t, false>(v);
+    if (v.dtype == 0) return gn_pick_rows<float>(v);
+    if (v.dtype == 1) return gn_pick_rows<_Float16>(v);
+    if (v.dtype == 2) return gn_pick_rows<uint8_t>(v);
     return nullptr;
 }
 
@@ -1922,10 +2063,10 @@ static hipError_t launch_timed(void* f, int grid_blocks, void** args, hipStream_
 }
 
 hipError_t launch_gn(const GnVariant& v, const LoneBatch& one, const BatchHeader* hdr, uint32_t* counters,
-                     int persistent, int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+                     int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
     void* f = gn_select(v);
     if (!f) return hipErrorInvalidValue;
-    void* args[] = {(void*)&one, (void*)&hdr, (void*)&counters, (void*)&persistent};
+    void* args[] = {(void*)&one, (void*)&hdr, (void*)&counters};
     return launch_timed(f, grid_blocks, args, s, start, stop);
 }
 
@@ -2280,8 +2421,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
                     const float drx = (bdx + fox) * ifx, dry = (bdy + foy) * ify;
                     const float sig = fmaf(sa.z * inv_c, dry, (sa.y * inv_c) * drx);
                     const float idu_c = fmaf(sa.x, sig, sa.x);
-                    frame_cost<T, BY_ROW>(pairs, fr, nf, bdx, bdy, idu_c, calive && pv && (idu_c > 0.f), pitch_b,
-                                  img_bytes, wm1, hm1, ikf, hk, img_scale, cst2, nv2l);
+                    frame_cost<T, BY_ROW, 0>(pairs, fr, nf, bdx, bdy, idu_c, calive && pv && (idu_c > 0.f), pitch_b,
+                                             wm1, hm1, ikf, hk, img_scale, cst2, nv2l);
                 }
                 const float c2 = group_sum<LANES>(cst2);
                 const int n2 = group_sum<LANES>(nv2l);
