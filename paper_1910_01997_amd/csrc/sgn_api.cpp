@@ -409,16 +409,13 @@ int persistent_grid(sgn_ctx* c, const GnVariant& v, const sgn_plan& plan) {
     return std::max(1, c->cus) * per_cu;
 }
 
-// Keyframes bound to nq shares (one per XCD) by greedy load balance: the
-// biggest work to the least loaded share.  Returns the keyframe order: by
-// share, and within one by neighbour count, longest first (share_of[i] is
-// keyframe i's share).
-std::vector<int> share_order(int nq, const std::vector<int64_t>& work, const std::vector<int>& n_nbr,
-                             std::vector<int>& share_of) {
+// Keyframe order of a batch: bound to nq shares by greedy load balance (the
+// biggest work to the least loaded share), share after share, and within one
+// by neighbour count, longest first, so the short items fill the tail.
+std::vector<int> share_order(int nq, const std::vector<int64_t>& work, const std::vector<int>& n_nbr) {
     const int n = (int)work.size();
-    std::vector<int> order(n);
+    std::vector<int> order(n), share_of(n, 0);
     for (int i = 0; i < n; ++i) order[i] = i;
-    share_of.assign(n, 0);
     if (nq > 1) {
         std::vector<int> bysize(order);
         std::stable_sort(bysize.begin(), bysize.end(), [&](int a, int b) { return work[a] > work[b]; });
@@ -434,6 +431,46 @@ std::vector<int> share_order(int nq, const std::vector<int64_t>& work, const std
         return n_nbr[a] > n_nbr[b];
     });
     return order;
+}
+
+// Cuts the items of the table's keyframes (in share_order) into nq runs of
+// equal work, one per XCD: a run reads one part of the images through one
+// L2, and no XCD waits for another.  An item's work is its neighbour frames
+// plus what does not depend on them (about `fixed` frames' worth).  Whole
+// keyframes per XCD keep the same locality but leave XCDs idle where few or
+// unequal keyframes do not divide by eight: the Gauss-Newton of 16 mixed
+// disc keyframes took 2.95 ms so, the heaviest share holding 1.5 times the
+// mean, and 1.82-1.97 ms cut.  (Ordered by neighbour count alone, so that each
+// XCD has items of one length, the 64-keyframe tile batch took 8 % longer:
+// an error of the work estimate then adds up over a whole XCD.)
+void cut_shares(int nq, const KfDev* kfs, int n, double fixed, QueueDev* queues) {
+    double total = 0.0;
+    for (int i = 0; i < n; ++i) total += (double)kfs[i].n_items * (kfs[i].n_nbr + fixed);
+    int k = 0, end = 0;
+    double before = 0.0;                       // work of the keyframes before k
+    for (int q = 0; q < nq; ++q) {
+        queues[q].begin = end;
+        const double want = total * (q + 1) / nq;
+        while (k < n && before + (double)kfs[k].n_items * (kfs[k].n_nbr + fixed) <= want) {
+            before += (double)kfs[k].n_items * (kfs[k].n_nbr + fixed);
+            ++k;
+        }
+        const int last = n > 0 ? kfs[n - 1].item_base + kfs[n - 1].n_items : 0;
+        int at = k < n ? kfs[k].item_base + (int)((want - before) / (kfs[k].n_nbr + fixed)) : last;
+        if (q == nq - 1) at = last;
+        end = std::min(last, std::max(end, at));
+        queues[q].end = end;
+    }
+}
+
+// Workgroups of a one-wavefront-per-item grid: workgroup b serves share
+// b % kXcds, so with shares the grid covers the largest one kXcds times.
+int item_blocks(int nq, const QueueDev* queues, int items) {
+    constexpr int wpb = kBlockThreads / kWaveSize;    // wavefronts per workgroup
+    if (nq != kXcds) return std::max(1, (items + wpb - 1) / wpb);
+    int widest = 1;
+    for (int q = 0; q < kXcds; ++q) widest = std::max(widest, (queues[q].end - queues[q].begin + wpb - 1) / wpb);
+    return kXcds * widest;
 }
 
 // The form of a four-pixels-per-lane kernel (the 4x4 layout of 4x4 surfels,
@@ -533,28 +570,19 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     // keyframe order: longest work items first, grouped by XCD queue
     const ItemGeo geo = fl.gn ? item_geo(patch, plan.tiles_x, plan.tiles_y, plan.groups)
                               : item_geo(patch, patch == 4 ? 4 : 1, 1, 1);
+    int nq = fl.gn && plan.xcd_queues ? kXcds : 1;
     std::vector<int64_t> work(n);
+    std::vector<int> n_nbr(n);
     for (int i = 0; i < n; ++i) {
         const sgn_keyframe& kf = items[i].kf;
-        int64_t gw = kf.kf.width / kf.patch, gh = kf.kf.height / kf.patch;
-        work[i] = gw * gh * std::max(1, kf.n_nbr);
+        work[i] = (int64_t)(kf.kf.width / kf.patch) * (kf.kf.height / kf.patch) * std::max(1, kf.n_nbr);
+        n_nbr[i] = kf.n_nbr;
     }
-    // XCD-bound keyframes: a persistent grid pulls from one queue per XCD
-    // (as many as there are keyframes); a one-wavefront-per-item grid maps
-    // its workgroups onto the eight XCDs' shares, so it needs all eight
-    const int nq = !(fl.gn && plan.xcd_queues) ? 1
-                   : plan.persistent ? std::min(kXcds, n)
-                   : (n >= kXcds ? kXcds : 1);
-    std::vector<int> n_nbr(n);
-    for (int i = 0; i < n; ++i) n_nbr[i] = items[i].kf.n_nbr;
-    std::vector<int> queue_of;
-    const std::vector<int> order = share_order(nq, work, n_nbr, queue_of);
+    const std::vector<int> order = share_order(nq, work, n_nbr);
 
     int frame_base = 0, item_base = 0, surfel_base = 0;
     int64_t pixel_base = 0;
     bool any_init = false, any_render = false;
-    for (int q = 0; q < kNumCounters; ++q) H->queues[q].begin = H->queues[q].end = 0;
-    int cur_q = -1;
     for (int oi = 0; oi < n; ++oi) {
         const int i = order[oi];
         const sgn_batch_item& it = items[i];
@@ -574,16 +602,10 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         D.item_base = item_base;
         D.surfel_base = surfel_base;
         D.pixel_base = pixel_base;
-        D.queue = queue_of[i];
         st = describe_frames(kf, frs + frame_base);
         if (st) return st;
-        if (D.queue != cur_q) {
-            H->queues[D.queue].begin = item_base;
-            cur_q = D.queue;
-        }
         frame_base += kf.n_nbr;
         item_base += D.n_items;
-        H->queues[D.queue].end = item_base;
         surfel_base += D.gw * D.gh;
         if (D.inv_depth_out)     // render segments: rows x tile columns
             pixel_base += (int64_t)D.height * ((D.width + D.patch - 1) / D.patch);
@@ -607,7 +629,13 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     H->do_init = fl.init && any_init;
     H->do_gn = fl.gn;
     H->do_render = fl.render && any_render;
+    // fewer items than SIMDs are all in flight at once whatever their order:
+    // no cut (160x120, 300 items: 32.6 us a call against 34.4)
+    if (!plan.persistent && item_base < 4 * c->cus) nq = 1;
     H->n_queues = nq;
+    // (64 mixed f16 keyframes: 4.18 ms with 0.5-1.5 frames, 4.23 with 2;
+    // f32 4.13 with 1, 4.20 with 0.5 and 1.5)
+    cut_shares(nq, kfs, n, 1.0, H->queues);
 
     const BatchHeader* dH = nullptr;
     if (lone) {
@@ -618,18 +646,7 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         if (st) return st;
         dH = (const BatchHeader*)(dev + L.hdr_off);
     }
-    // one wavefront per work item, four per workgroup; with one share per
-    // XCD, workgroup b serves share b % kXcds, so the grid covers the largest
-    // share kXcds times
-    constexpr int wpb = kBlockThreads / kWaveSize;    // wavefronts per workgroup
-    int np_blocks = (item_base + wpb - 1) / wpb;
-    if (!plan.persistent && nq == kXcds) {
-        int widest = 0;
-        for (int q = 0; q < kXcds; ++q)
-            widest = std::max(widest, (H->queues[q].end - H->queues[q].begin + wpb - 1) / wpb);
-        np_blocks = kXcds * widest;
-    }
-    const int gn_grid = plan.persistent ? persistent_grid(c, var, plan) : std::max(1, np_blocks);
+    const int gn_grid = plan.persistent ? persistent_grid(c, var, plan) : item_blocks(nq, H->queues, item_base);
     hipError_t e = hipSuccess;
     if (H->do_init) e = launch_init(one.one, dH, std::max(1, c->cus) * 8, c->stream);
     if (e == hipSuccess && fl.gn && item_base > 0) {
@@ -715,21 +732,14 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
     BatchHeader* H = lone ? &one.one.hdr : (BatchHeader*)(host + L.hdr_off);
     KfDev* kfs = lone ? &one.one.kf : (KfDev*)(host + L.kf_off);
     FrameIn* frs = lone ? one_in : (FrameIn*)(host + L.fr_off);
-    // batches of eight keyframes or more: the keyframes split into one share
-    // per XCD, balanced by work (surfels x neighbour frames), and workgroup b
-    // takes the items of XCD b % kXcds's share in order; within a share (or
-    // the one share of a smaller batch) longest work first (most neighbour
-    // frames), so the short surfels fill the tail
-    const int nq = n >= kXcds ? kXcds : 1;
+    const int nq = kXcds;
     std::vector<int64_t> work(n);
-    std::vector<int> n_nbr(n), share_of;
+    std::vector<int> n_nbr(n);
     for (int i = 0; i < n; ++i) {
         work[i] = (int64_t)items[i].count * std::max(1, items[i].kf.n_nbr);
         n_nbr[i] = items[i].kf.n_nbr;
     }
-    const std::vector<int> order = share_order(nq, work, n_nbr, share_of);
-    for (int q = 0; q < kNumCounters; ++q) H->queues[q].begin = H->queues[q].end = 0;
-    int cur_q = -1;
+    const std::vector<int> order = share_order(nq, work, n_nbr);
     int frame_base = 0, surfel_base = 0, item_base = 0;
     for (int oi = 0; oi < n; ++oi) {
         const sgn_disc_item& it = items[order[oi]];
@@ -746,15 +756,9 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
         D.disc_r = it.radius;
         st = describe_frames(kf, frs + frame_base);
         if (st) return st;
-        const int q = share_of[order[oi]];
-        if (q != cur_q) {
-            H->queues[q].begin = item_base;
-            cur_q = q;
-        }
         frame_base += kf.n_nbr;
         surfel_base += it.count;
         item_base += D.n_items;
-        H->queues[q].end = item_base;
     }
     H->kfs = (KfDev*)(dev + L.kf_off);
     H->frames = (FrameDev*)(dev + L.fr_off);
@@ -771,6 +775,7 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
     H->lm_lambda = prm->lm_lambda;
     H->do_gn = 1;
     H->n_queues = nq;
+    cut_shares(nq, kfs, n, 0.5, H->queues);    // 16 mixed keyframes: 1.82 ms; 1.90 with 0, 1.96 with 1
     const BatchHeader* dH = nullptr;
     if (lone) {
         for (int f = 0; f < total_frames; ++f) frame_constants(one_in[f], one.frames[f]);
@@ -788,17 +793,7 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
             const sgn_keyframe& kf = items[i].kf;
             if (kf.n_nbr > 0 && (size_t)kf.nbr[0].pitch * dtype_size(kf.kf.dtype) >= kMaxRowStride) by_row = false;
         }
-        // one wavefront per item, four per workgroup; with shares the grid
-        // covers the largest share once per XCD
-        constexpr int wpb = kBlockThreads / kWaveSize;
-        int blocks = (item_base + wpb - 1) / wpb;
-        if (nq == kXcds) {
-            int widest = 0;
-            for (int q = 0; q < kXcds; ++q)
-                widest = std::max(widest, (H->queues[q].end - H->queues[q].begin + wpb - 1) / wpb);
-            blocks = kXcds * widest;
-        }
-        const hipError_t e = launch_disc_gn(dtype, one, dH, item_base, std::max(1, blocks), by_row, c->stream,
+        const hipError_t e = launch_disc_gn(dtype, one, dH, item_base, item_blocks(nq, H->queues, item_base), by_row, c->stream,
                                             c->gn_start, c->gn_end);
         if (e != hipSuccess) return hip_fail(e, "disc Gauss-Newton launch");
         c->gn_timed = true;
@@ -1382,9 +1377,6 @@ sgn_status sgn_autotune(sgn_ctx* c, const sgn_batch_item* items, int32_t n, cons
     for (auto sh : shapes)
         for (int groups : group_counts)
             for (int xq = 0; xq <= 1; ++xq) {
-                // under eight keyframes the grid ignores xcd_queues: the
-                // same launch as xq = 0
-                if (xq && n < kXcds) continue;
                 sgn_plan pl{};
                 pl.tiles_x = sh.first;
                 pl.tiles_y = sh.second;

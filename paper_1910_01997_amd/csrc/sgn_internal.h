@@ -30,7 +30,7 @@ struct KfDev {
     int32_t* index_out;           // may be null
     int32_t width, height, kf_pitch, n_nbr;
     int32_t gw, gh, frame_base, item_base;      // frames: [frame_base, frame_base + n_nbr)
-    int32_t groups_x, n_items, surfel_base, queue;  // anchor blocks per row; work items
+    int32_t groups_x, n_items, surfel_base, pad_q;  // anchor blocks per row; work items
     int64_t pixel_base;                          // prefix over render segments (row x tile column)
     int32_t patch, nbr_pitch_b;                   // neighbour-image row pitch in bytes
     double fx_d, fy_d, cx_d, cy_d;               // intrinsics as given (double)
