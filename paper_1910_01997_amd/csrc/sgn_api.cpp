@@ -465,8 +465,7 @@ void cut_shares(int nq, const KfDev* kfs, int n, double fixed, QueueDev* queues)
 
 // Workgroups of a one-wavefront-per-item grid: workgroup b serves share
 // b % kXcds, so with shares the grid covers the largest one kXcds times.
-int item_blocks(int nq, const QueueDev* queues, int items) {
-    constexpr int wpb = kBlockThreads / kWaveSize;    // wavefronts per workgroup
+int item_blocks(int nq, const QueueDev* queues, int items, int wpb) {
     if (nq != kXcds) return std::max(1, (items + wpb - 1) / wpb);
     int widest = 1;
     for (int q = 0; q < kXcds; ++q) widest = std::max(widest, (queues[q].end - queues[q].begin + wpb - 1) / wpb);
@@ -646,7 +645,7 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         if (st) return st;
         dH = (const BatchHeader*)(dev + L.hdr_off);
     }
-    const int gn_grid = plan.persistent ? persistent_grid(c, var, plan) : item_blocks(nq, H->queues, item_base);
+    const int gn_grid = plan.persistent ? persistent_grid(c, var, plan) : item_blocks(nq, H->queues, item_base, kBlockThreads / kWaveSize);
     hipError_t e = hipSuccess;
     if (H->do_init) e = launch_init(one.one, dH, std::max(1, c->cus) * 8, c->stream);
     if (e == hipSuccess && fl.gn && item_base > 0) {
@@ -690,6 +689,40 @@ sgn_status check_disc_item(const sgn_disc_item* it, bool need_nbr) {
         if (st) return st;
     }
     return SGN_OK;
+}
+
+// The disc kernel's form for the batch's number of work items, w = items per
+// SIMD (times: 15 iterations, 6 neighbours, f16 with two discs per item unless
+// f32 is said, with one):
+//   w <= 0.25  sixteen wavefronts per item, one workgroup per CU: 79 us at
+//              187 items against 97 with eight and 316 with one.
+//   w <= 0.45  eight: 107 us at 424 items (sixteen 152, four 131).
+//   w <= 1.7, f32 1.0
+//              four: 142 us at 755 items (eight 201, one with four frames in
+//              flight 271), 266 against 290 at 1,716; f32 96 against 149 at
+//              848, but 170 against 158 at 1,510.
+//   w <= 4     one, four frames in flight (four wavefronts per SIMD): 320 us
+//              at 2,267 items (one sample at a time 363).
+//   w <= 5     two frames at five per SIMD: f32 233 us at 4,533 (305 and 250).
+//   w <= 6     one sample at a time, all resident at six: 545 us at 5,192
+//              (two frames 618, four 582).
+//   w <= 8     four frames again, two full rounds: 648 us at 6,800 (753).
+//   beyond     one sample at a time (2.09 ms at 27,200; two frames 2.12, four
+//              2.25), f32 two frames (2.15 ms at 54,400; 2.20, 2.39).
+// The damped variant's cost sums run over the slots in turn: one wavefront.
+DiscForm choose_disc_form(const sgn_ctx* c, int items, int dtype, const sgn_params* prm) {
+    const bool f32 = dtype == SGN_F32;
+    const double w = (double)items / (4.0 * std::max(1, c->cus));
+    if (!(prm->lm_lambda > 0.f)) {
+        if (w <= 0.25) return {16, 4};
+        if (w <= 0.45) return {8, 4};
+        if (w <= (f32 ? 1.0 : 1.7)) return {4, 4};
+    }
+    if (w <= 4.0) return {1, 4};
+    if (w <= 5.0) return {1, 2};
+    if (w <= 6.0) return {1, 0};
+    if (w <= 8.0) return {1, 4};
+    return {1, f32 ? 2 : 0};
 }
 
 // Disc surfels: descriptor table (one KfDev per keyframe; its items are runs
@@ -793,8 +826,10 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
             const sgn_keyframe& kf = items[i].kf;
             if (kf.n_nbr > 0 && (size_t)kf.nbr[0].pitch * dtype_size(kf.kf.dtype) >= kMaxRowStride) by_row = false;
         }
-        const hipError_t e = launch_disc_gn(dtype, one, dH, item_base, item_blocks(nq, H->queues, item_base), by_row, c->stream,
-                                            c->gn_start, c->gn_end);
+        const DiscForm form = choose_disc_form(c, item_base, dtype, prm);
+        const int blocks = item_blocks(nq, H->queues, item_base, form.waves > 1 ? 1 : kBlockThreads / kWaveSize);
+        const hipError_t e = launch_disc_gn(dtype, form, one, dH, item_base, blocks, by_row, c->stream, c->gn_start,
+                                            c->gn_end);
         if (e != hipSuccess) return hip_fail(e, "disc Gauss-Newton launch");
         c->gn_timed = true;
     }

@@ -231,13 +231,21 @@ constexpr float kDiscMaxRadius = 12.f;
 // (0 f32, 1 f16, 2 u8): two (32 lanes each) where a pixel's LDS slot packs
 // into one word, one for f32 images.
 constexpr int disc_surfels_per_wave(int dtype) { return dtype == 0 ? 1 : 2; }
-// Gauss-Newton over the disc surfels of a batch: one wavefront per work item
-// of disc_surfels_per_wave(dtype) surfels of one keyframe (KfDev::n_items =
+// How the disc kernel runs: wavefronts per item (1, 4, 8 or 16) and frames
+// whose taps are in flight at once (4 with several wavefronts, else 0, 2 or
+// 4).  Results do not depend on it.
+struct DiscForm {
+    int waves, deep;
+};
+// Gauss-Newton over the disc surfels of a batch: work items of
+// disc_surfels_per_wave(dtype) surfels of one keyframe (KfDev::n_items =
 // ceil(disc_count / that), item_base their prefix).
-// grid_blocks workgroups of four wavefronts, one work item each (with one
-// share per XCD in the header, workgroup b serves share b % kXcds)
-hipError_t launch_disc_gn(int dtype, const LoneBatch& one, const BatchHeader* hdr, int total_items,
-                          int grid_blocks, bool by_row, hipStream_t s, hipEvent_t start, hipEvent_t stop);
+// grid_blocks workgroups of four items of one wavefront or of one item of
+// several (with one share per XCD in the header, workgroup b serves share
+// b % kXcds)
+hipError_t launch_disc_gn(int dtype, const DiscForm& form, const LoneBatch& one, const BatchHeader* hdr,
+                          int total_items, int grid_blocks, bool by_row, hipStream_t s, hipEvent_t start,
+                          hipEvent_t stop);
 // Depth-buffered render of the discs of several keyframes: one table entry
 // per keyframe (device memory); the scratch holds one 64-bit depth key and
 // one index per pixel of every keyframe, keyframe after keyframe.

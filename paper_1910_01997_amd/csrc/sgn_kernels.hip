@@ -574,86 +574,6 @@ __device__ __forceinline__ int cvt_floor(float x) {
     return r;
 }
 
-// Warp of one sample into frame f in local coordinates (see the pair words):
-// returns validity; on success the integer tap corner (row, col) and the
-// bilinear fractions.  Valid iff q_z > 0 and 0 <= x_p < W-1, 0 <= y_p < H-1,
-// decided exactly on the integer corner X0 + floor(x_p - X0).
-struct Warp {
-    float fx, fy, rq, ax, ay;
-    unsigned row, col;          // tap corner: row y0, byte column of x0
-    bool v;
-};
-
-template <typename T>
-__device__ __forceinline__ Warp warp_sample(const float4& c0, const float4& c1, const float4& c2,
-                                            float h6, float h7, float k2, float dx, float dy,
-                                            float idu, bool pix_ok, unsigned wm1, unsigned hm1,
-                                            unsigned pitch_b) {
-    Warp w;
-    const float nxq = fmaf(c0.x, dx, fmaf(c0.y, dy, fmaf(c0.z, idu, c0.w)));
-    const float nyq = fmaf(c1.x, dx, fmaf(c1.y, dy, fmaf(c1.z, idu, c1.w)));
-    const float qz = fmaf(h6, dx, fmaf(h7, dy, fmaf(k2, idu, c2.x)));
-    w.rq = rcp_fast(qz);
-    w.fx = nxq * w.rq;                                   // x_p - X0
-    w.fy = nyq * w.rq;                                   // y_p - Y0
-    const int flx = cvt_floor(w.fx), fly = cvt_floor(w.fy);
-    // unsigned wrap-around: out-of-range (or saturated) corners fail the test
-    const unsigned ix = __float_as_uint(c2.y) + (unsigned)flx;
-    const unsigned iy = __float_as_uint(c2.z) + (unsigned)fly;
-    w.v = pix_ok & (qz > 0.f) & (ix < wm1) & (iy < hm1);
-    w.ax = __builtin_amdgcn_fractf(w.fx);
-    w.ay = __builtin_amdgcn_fractf(w.fy);
-    w.row = iy; w.col = ix * (unsigned)sizeof(T);
-    return w;
-}
-
-// The frame loop of one Gauss-Newton iteration for one pixel (lane): warp
-// into every neighbour frame, bilinear sample with gradient, Huber-weighted
-// residual, and the scalar chain factor a = dr/did_u.  Accumulates
-// A = sum w a^2 and B = sum w a r (the per-pixel Jacobian g is applied after
-// the loop, hoisted as the paper suggests).  LAST also sums the Huber cost.
-template <typename T, bool LAST, bool BY_ROW>
-__device__ __forceinline__ void frame_loop(const float* __restrict__ pc, cptr<FrameDev> fr, int nf,
-                                           float dx, float dy, float idu, bool pix_ok,
-                                           unsigned pitch_b, unsigned img_bytes, unsigned wm1,
-                                           unsigned hm1, float ikf, float hk, float img_scale,
-                                           float& A, float& B, float& cst, int& nvl) {
-    constexpr bool SCALED = std::is_same<T, uint8_t>::value;
-    for (int f = 0; f < nf; ++f) {
-        const float4 c0 = *(const float4*)(pc + f * kPairWords);
-        const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
-        const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
-        const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
-        const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
-        // Eq. 6 in local coordinates
-        const Warp w = warp_sample<T>(c0, c1, c2, h6, h7, k2, dx, dy, idu, pix_ok, wm1, hm1, pitch_b);
-        if (w.v) {
-            const Lerp l = sample_rows<T, BY_ROW>(rs, w.row, w.col, pitch_b, w.ax);
-            // bilinear value and the exact gradient of the interpolant
-            const float gy = l.bot - l.top;
-            const float val = fmaf(w.ay, gy, l.top);
-            const float gx = fmaf(w.ay, l.d1 - l.d0, l.d0);
-            // residual (Eq. 5) and Huber IRLS weight w = min(1, k/|r|) (Eq. 8)
-            const float r = SCALED ? fmaf(val, img_scale, -ikf) : val - ikf;
-            const float ar = fabsf(r);
-            // (the clamp to [0, 1] folds into the multiply; it maps a NaN
-            // weight to 0 where min(1, NaN) gives 1, which changes nothing
-            // the update reports: B = sum w a r is NaN either way)
-            const float wt = fminf(fmaxf(hk * rcp_fast(ar), 0.f), 1.f);
-            // dr/did_u = grad I . dpi/dq . K t  (Eq. 8 with dq/did_u = K t):
-            // (k0 - x_p k2) = kx - (x_p - X0) k2, likewise for y
-            const float tx_ = fmaf(-w.fx, k2, c0.z);
-            const float ty_ = fmaf(-w.fy, k2, c1.z);
-            const float a = fmaf(gx, tx_, gy * ty_) * (SCALED ? w.rq * img_scale : w.rq);
-            const float wa = wt * a;
-            A = fmaf(wa, a, A);
-            B = fmaf(wa, r, B);
-            ++nvl;
-            if constexpr (LAST) cst += (ar <= hk) ? 0.5f * r * r : hk * (ar - 0.5f * hk);
-        }
-    }
-}
-
 // One sample from its homogeneous warp q = (nxq, nyq, qz) in local
 // coordinates (see the pair words).  sample_warp: projection and validity on
 // the integer corner; sample_load: the tap words of a valid sample;
@@ -719,7 +639,8 @@ __device__ __forceinline__ void sample_use(const Sample& s, const TapWords& tw, 
 // below pixel j-1 of the same surfel and its id_u is didu larger (id_u is
 // affine along the column), so its q adds the frame's step, dyr times the
 // homography's y column plus didu times K t.  Accumulates A, B and the cost
-// per pixel as frame_loop does; the valid counts of the pixels are packed
+// per pixel: A = sum w a^2 and B = sum w a r (the per-pixel Jacobian g is
+// applied after the loop, hoisted as the paper suggests); the valid counts of the pixels are packed
 // one per byte of nvp (pixel j in byte j; at most 16 frames each).
 //
 // DEEP = 0: each pixel's taps are loaded and used before the next pixel's
@@ -2054,10 +1975,10 @@ int gn_blocks_per_cu(const GnVariant& v) {
 
 // A kernel between the two timing events.  Recorded events: the launch that
 // carries its own (hipExtLaunchKernel) took 6-7 us longer alone.
-static hipError_t launch_timed(void* f, int grid_blocks, void** args, hipStream_t s, hipEvent_t start,
+static hipError_t launch_timed(void* f, int grid_blocks, int threads, void** args, hipStream_t s, hipEvent_t start,
                                hipEvent_t stop) {
     hipError_t e = hipEventRecord(start, s);
-    if (e == hipSuccess) e = hipLaunchKernel(f, dim3(grid_blocks), dim3(kBlockThreads), args, 0, s);
+    if (e == hipSuccess) e = hipLaunchKernel(f, dim3(grid_blocks), dim3(threads), args, 0, s);
     if (e == hipSuccess) e = hipEventRecord(stop, s);
     return e;
 }
@@ -2067,7 +1988,7 @@ hipError_t launch_gn(const GnVariant& v, const LoneBatch& one, const BatchHeader
     void* f = gn_select(v);
     if (!f) return hipErrorInvalidValue;
     void* args[] = {(void*)&one, (void*)&hdr, (void*)&counters};
-    return launch_timed(f, grid_blocks, args, s, start, stop);
+    return launch_timed(f, grid_blocks, kBlockThreads, args, s, start, stop);
 }
 
 // ------------------------------------------------------------ disc surfels --
@@ -2183,18 +2104,39 @@ __device__ __forceinline__ void disc_pixel(const DiscRows& d, const int* row_x0,
 // reductions span 32 lanes.  Six wavefronts per SIMD (80 VGPRs, and the LDS
 // of six workgroups per CU): the few values that spill are read by the owner
 // step once per iteration or by its double-precision fallback only.
-template <typename T, int SPW, bool BY_ROW>
-__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) void disc_gn_kernel(
+//
+// WAVES > 1: a workgroup of that many wavefronts per item, dealing out the
+// pixel slots; each slot's A, B and cost go through LDS and every sum then runs
+// over the slots in order, a pair of sums per wavefront, so the results are
+// those of one wavefront.  DEEP as in frame_loop_px.  A lone wavefront takes
+// about 22 us per iteration over a disc of radius 10 and six frames whatever
+// the chip has free (640x480, 1,510 discs in 755 wavefronts: 324 us for 15
+// iterations); four of them take 142 us, with the taps of four frames in
+// flight.
+constexpr int disc_threads(int waves) { return waves == 1 ? kBlockThreads : waves * kWaveSize; }
+template <int WAVES, int DEEP>
+constexpr int disc_waves() { return WAVES > 1 ? 4 : DEEP == 4 ? 4 : DEEP ? 5 : 6; }
+
+template <typename T, int SPW, bool BY_ROW, int WAVES, int DEEP>
+__global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_per_eu(disc_waves<WAVES, DEEP>(), 8))) void disc_gn_kernel(
     LoneBatch, const BatchHeader* __restrict__ hdr_, int total) {
     constexpr int LANES = kWaveSize / SPW;        // lanes per surfel
     constexpr int PPL = kDiscPPL * SPW;           // pixel slots per lane
-    constexpr int WPB = kBlockThreads / kWaveSize;
+    constexpr int NWAVE = disc_threads(WAVES) / kWaveSize;
+    constexpr int WPB = NWAVE / WAVES;            // items per workgroup
+    static_assert(WAVES == 1 || WAVES == NWAVE, "an item takes a wavefront or a workgroup");
     constexpr bool packed = DiscSlot<T>::packed;
     static_assert(kDiscMaxRows <= LANES, "a disc row per lane");
     const BatchView view = batch_view(hdr_);
     const cptr<BatchHeader> hdr = view.hdr;
     const int lane = threadIdx.x & (kWaveSize - 1);
-    const int wave = threadIdx.x >> 6;
+    const int wave_ = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wave = WAVES == 1 ? wave_ : 0;             // item of the workgroup
+    const int part = WAVES == 1 ? 0 : wave_;             // wavefront of the item
+    auto sync = [] {
+        if constexpr (WAVES == 1) wave_sync();
+        else __syncthreads();
+    };
     const int h = lane / LANES, hl = lane % LANES;       // surfel of the wave, lane within it
     int item_ = (int)blockIdx.x * WPB + wave;
     if (hdr->n_queues == kXcds) {
@@ -2208,15 +2150,19 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
     __shared__ float4 s_pairs[WPB][SPW][kMaxNbr * kPairWords / 4];
     __shared__ float4 s_state[WPB][SPW][ST_WORDS / 4];
     __shared__ float4 s_sums[WPB][SPW][SM_WORDS / 4];
-    __shared__ int s_rows[WPB][SPW][kDiscRowWords];
+    __shared__ int s_rows[NWAVE][SPW][kDiscRowWords];
     // each lane's pixels: offsets from the anchor and keyframe values
     __shared__ uint32_t s_pix[WPB][PPL][kWaveSize];
     __shared__ float s_val[WPB][packed ? 1 : PPL][kWaveSize];
+    // each slot's sums over the frames, and each wavefront's valid counts
+    __shared__ float2 s_ab[WAVES > 1 ? PPL : 1][WAVES > 1 ? kWaveSize : 1];
+    __shared__ float s_cst[WAVES > 1 ? PPL : 1][WAVES > 1 ? kWaveSize : 1];
+    __shared__ int s_nv[WAVES > 1 ? NWAVE : 1][WAVES > 1 ? kWaveSize : 1];
     float* const pairs = (float*)s_pairs[wave][h];
     float* const lst = (float*)s_state[wave][h];
     float* const lsm = (float*)s_sums[wave][h];
-    int* const row_x0 = s_rows[wave][h];
-    int* const row_start = s_rows[wave][h] + kDiscMaxRows;
+    int* const row_x0 = s_rows[wave_][h];
+    int* const row_start = s_rows[wave_][h] + kDiscMaxRows;
 
     const cptr<KfDev> kfs = view.kfs;
     const int kidx = find_kf(kfs, hdr->n_kf, item, 0);
@@ -2233,13 +2179,12 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
     const int nf = Kd->n_nbr;
     const float img_scale = Kd->img_scale;
     const unsigned pitch_b = (unsigned)Kd->nbr_pitch_b;
-    const unsigned img_bytes = pitch_b * (unsigned)H;
     const unsigned wm1 = (unsigned)(W - 1), hm1 = (unsigned)(H - 1);
     const float fxk = Kd->fx, fyk = Kd->fy, cxk = Kd->cx, cyk = Kd->cy;
     const float ux = have ? ((gptr<float>)Kd->disc_ux)[sidx] : __builtin_nanf("");
     const float uy = have ? ((gptr<float>)Kd->disc_uy)[sidx] : __builtin_nanf("");
 
-    wave_sync();
+    wave_sync();                                     // (rows: each wavefront its own)
     const DiscRows d = disc_rows<LANES>(ux, uy, Kd->disc_r, W, H, hl, row_x0, row_start);
     // slot count: the larger of the wavefront's surfels, so the loop is uniform
     int nslots = (d.total + LANES - 1) / LANES;
@@ -2249,7 +2194,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
     // warp coordinates)
     const int ax = (int)rint(fmin(fmax((double)ux, -1e6), 1e6));
     const int ay = (int)rint(fmin(fmax((double)uy, -1e6), 1e6));
-    stage_pair_words(view.frames + Kd->frame_base, nf, hl, (double)ax, (double)ay, pairs);
+    if (part == 0) stage_pair_words(view.frames + Kd->frame_base, nf, hl, (double)ax, (double)ay, pairs);
     const uint64_t fr_bits = (uint64_t)(view.frames + Kd->frame_base);
     const uint32_t fr_lo = __builtin_amdgcn_readfirstlane((uint32_t)fr_bits);
     const uint32_t fr_hi = __builtin_amdgcn_readfirstlane((uint32_t)(fr_bits >> 32));
@@ -2259,7 +2204,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
     // holds one pixel's terms in registers at a time
     const gptr<T> kimg = (gptr<T>)Kd->kf_img;
     const float kf_scale = Kd->kf_scale;
-    for (int j = 0; j < nslots; ++j) {
+    for (int j = part; j < nslots; j += WAVES) {
         const int k = hl + LANES * j;
         uint32_t pk = 0u;
         float v = 0.f;
@@ -2278,7 +2223,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
     const float ifx = 1.f / fxk, ify = 1.f / fyk;
 
     // owner (lane 0 of each surfel): the surfel's state
-    const bool owner = hl == 0;
+    const bool owner = hl == 0 && part == 0;
     const float rsx = (ux - cxk) / fxk, rsy = (uy - cyk) / fyk;
     float id = 0.f, nx = 0.f, ny = 0.f, nz = -1.f;
     uint32_t flags = 0u;
@@ -2313,7 +2258,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
             lst[ST_RSX] = rsx; lst[ST_RSY] = rsy;
             lst[ST_ALIVE] = alive ? 1.f : 0.f;
         }
-        wave_sync();
+        sync();
         {
             const float4 sa = *(const float4*)(lst + 0);
             const float4 sb = *(const float4*)(lst + 4);
@@ -2333,55 +2278,103 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
             const float q2 = kk * fmaf(sb2x, srsx, fmaf(sb2y, srsy, sb2z));
             float ph[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             float pnv = 0.f, pcs = 0.f;
-            for (int j = 0; j < nslots; ++j) {
+            const bool with_cost = last || lm;
+            // one slot's pixel: offsets from the anchor, sigma_u and g_u
+            struct Pixel {
+                float bdx, bdy, sigma, g0, g1, g2;
+            };
+            auto pixel = [&](uint32_t pk) {
+                Pixel x;
+                x.bdx = (float)(int8_t)(pk & 0xffu);
+                x.bdy = (float)(int8_t)((pk >> 8) & 0xffu);
+                const float drx = (x.bdx + fox) * ifx, dry = (x.bdy + foy) * ify;
+                x.sigma = fmaf(cny, dry, cnx * drx);
+                x.g0 = 1.f + x.sigma;
+                x.g1 = fmaf(-x.sigma, q1, fmaf(k1y, dry, k1x * drx));
+                x.g2 = fmaf(-x.sigma, q2, fmaf(k2y, dry, k2x * drx));
+                return x;
+            };
+            for (int j = part; j < nslots; j += WAVES) {
                 const uint32_t pk = s_pix[wave][j][lane];
-                const float bdx = (float)(int8_t)(pk & 0xffu), bdy = (float)(int8_t)((pk >> 8) & 0xffu);
-                const float ikf = packed ? slot_value<T>(pk) * kf_scale : s_val[wave][packed ? 0 : j][lane];
+                const Pixel x = pixel(pk);
+                const float ikf[1] = {packed ? slot_value<T>(pk) * kf_scale : s_val[wave][packed ? 0 : j][lane]};
                 const bool pv = hl + LANES * j < d.total;
-                const float drx = (bdx + fox) * ifx, dry = (bdy + foy) * ify;
-                const float sigma = fmaf(cny, dry, cnx * drx);
-                const float idu = fmaf(sid, sigma, sid);
-                const float g0 = 1.f + sigma;
-                const float g1 = fmaf(-sigma, q1, fmaf(k1y, dry, k1x * drx));
-                const float g2 = fmaf(-sigma, q2, fmaf(k2y, dry, k2x * drx));
-                const bool pix_ok = salive && pv && (idu > 0.f);
-                float A = 0.f, B = 0.f, cst = 0.f;
-                int nvl = 0;
-                if (last || lm)
-                    frame_loop<T, true, BY_ROW>(pairs, fr, nf, bdx, bdy, idu, pix_ok, pitch_b, img_bytes, wm1, hm1,
-                                        ikf, hk, img_scale, A, B, cst, nvl);
+                const float idu = fmaf(sid, x.sigma, sid);
+                const bool pix_ok[1] = {salive && pv && (idu > 0.f)};
+                float A[1] = {0.f}, B[1] = {0.f}, cst[1] = {0.f};
+                unsigned nvl = 0u;
+                if (with_cost)
+                    frame_loop_px<T, true, 1, BY_ROW, DEEP, 1>(pairs, fr, nf, x.bdx, x.bdy, 0.f, idu, 0.f, 0, pix_ok,
+                                                               pitch_b, wm1, hm1, ikf, hk, img_scale, A, B, cst, nvl);
                 else
-                    frame_loop<T, false, BY_ROW>(pairs, fr, nf, bdx, bdy, idu, pix_ok, pitch_b, img_bytes, wm1, hm1,
-                                         ikf, hk, img_scale, A, B, cst, nvl);
-                {
-                    const float ag0 = A * g0, ag1 = A * g1, ag2 = A * g2;
-                    ph[0] = fmaf(ag0, g0, ph[0]); ph[1] = fmaf(ag0, g1, ph[1]);
-                    ph[2] = fmaf(ag0, g2, ph[2]); ph[3] = fmaf(ag1, g1, ph[3]);
-                    ph[4] = fmaf(ag1, g2, ph[4]); ph[5] = fmaf(ag2, g2, ph[5]);
-                    ph[6] = fmaf(B, g0, ph[6]); ph[7] = fmaf(B, g1, ph[7]); ph[8] = fmaf(B, g2, ph[8]);
-                    pnv += (float)nvl;
-                    pcs += cst;
+                    frame_loop_px<T, false, 1, BY_ROW, DEEP, 1>(pairs, fr, nf, x.bdx, x.bdy, 0.f, idu, 0.f, 0, pix_ok,
+                                                                pitch_b, wm1, hm1, ikf, hk, img_scale, A, B, cst, nvl);
+                pnv += (float)nvl;
+                if constexpr (WAVES == 1) {
+                    const float ag0 = A[0] * x.g0, ag1 = A[0] * x.g1, ag2 = A[0] * x.g2;
+                    ph[0] = fmaf(ag0, x.g0, ph[0]); ph[1] = fmaf(ag0, x.g1, ph[1]);
+                    ph[2] = fmaf(ag0, x.g2, ph[2]); ph[3] = fmaf(ag1, x.g1, ph[3]);
+                    ph[4] = fmaf(ag1, x.g2, ph[4]); ph[5] = fmaf(ag2, x.g2, ph[5]);
+                    ph[6] = fmaf(B[0], x.g0, ph[6]); ph[7] = fmaf(B[0], x.g1, ph[7]); ph[8] = fmaf(B[0], x.g2, ph[8]);
+                    pcs += cst[0];
+                } else {
+                    s_ab[j][lane] = make_float2(A[0], B[0]);
+                    if (with_cost) s_cst[j][lane] = cst[0];
                 }
             }
-            float s0, s1, s2, s3, s4;
-            {
+            const bool odd = (hl & 1) != 0;
+            if constexpr (WAVES == 1) {
 #pragma clang fp contract(off)
-                const bool odd = (hl & 1) != 0;
-                s0 = pair_sum<LANES>(ph[0], ph[1], odd);
-                s1 = pair_sum<LANES>(ph[2], ph[3], odd);
-                s2 = pair_sum<LANES>(ph[4], ph[5], odd);
-                s3 = pair_sum<LANES>(ph[6], ph[7], odd);
-                s4 = pair_sum<LANES>(ph[8], pnv, odd);
-            }
-            float cs = 0.f;
-            if (last || lm) cs = group_sum<LANES>(pcs);
-            if (hl < 2) {
-                float* o = lsm + hl;
-                o[0] = s0; o[2] = s1; o[4] = s2; o[6] = s3; o[8] = s4;
-                if (hl == 0) o[SM_COST] = cs;
+                const float s0 = pair_sum<LANES>(ph[0], ph[1], odd);
+                const float s1 = pair_sum<LANES>(ph[2], ph[3], odd);
+                const float s2 = pair_sum<LANES>(ph[4], ph[5], odd);
+                const float s3 = pair_sum<LANES>(ph[6], ph[7], odd);
+                const float s4 = pair_sum<LANES>(ph[8], pnv, odd);
+                float cs = 0.f;
+                if (with_cost) cs = group_sum<LANES>(pcs);
+                if (hl < 2) {
+                    float* o = lsm + hl;
+                    o[0] = s0; o[2] = s1; o[4] = s2; o[6] = s3; o[8] = s4;
+                    if (hl == 0) o[SM_COST] = cs;
+                }
+            } else {
+                s_nv[part][lane] = (int)pnv;
+                sync();
+                // wavefront p takes sums 2p and 2p + 1 (H00 H01, H02 H11, H12 H22,
+                // b0 b1); the first also b2 and the count, the last the cost
+                float e0 = 0.f, e1 = 0.f, e2 = 0.f;
+                for (int j = 0; j < (part < 4 ? nslots : 0); ++j) {
+                    const Pixel x = pixel(s_pix[0][j][lane]);
+                    const float2 ab = s_ab[j][lane];
+                    // the pair's factors: u0 v0 and u1 v1, u a product A g or B
+                    const float ga = part < 2 ? x.g0 : part == 2 ? x.g1 : x.g0;
+                    const float u0 = part == 3 ? ab.y : ab.x * ga;
+                    const float v0 = part == 0 ? x.g0 : part == 3 ? x.g0 : x.g2;
+                    const float u1 = part == 0 ? ab.x * x.g0 : part == 1 ? ab.x * x.g1
+                                     : part == 2 ? ab.x * x.g2 : ab.y;
+                    const float v1 = part == 2 ? x.g2 : x.g1;
+                    e0 = fmaf(u0, v0, e0);
+                    e1 = fmaf(u1, v1, e1);
+                    if (part == 0) e2 = fmaf(ab.y, x.g2, e2);
+                    if (part == 3 && with_cost) e2 += s_cst[j][lane];
+                }
+                const float se = pair_sum<LANES>(e0, e1, odd);
+                if (hl < 2 && part < 4) lsm[2 * part + hl] = se;
+                if (part == 0) {
+                    int nvs = 0;
+#pragma unroll
+                    for (int w = 0; w < NWAVE; ++w) nvs += s_nv[w][lane];
+                    const float s4 = pair_sum<LANES>(e2, (float)nvs, odd);
+                    if (hl < 2) lsm[8 + hl] = s4;
+                }
+                if (part == 3) {
+                    float cs = 0.f;
+                    if (with_cost) cs = group_sum<LANES>(e2);
+                    if (hl == 0) lsm[SM_COST] = cs;
+                }
             }
         }
-        wave_sync();
+        sync();
         bool cand = false;
         float id_c = 0.f, nx_c = 0.f, ny_c = 0.f, nz_c = 0.f, cost_here = 0.f;
         int nv = 0;
@@ -2389,7 +2382,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
             cand = owner_step(lsm, alive, last, depth_only, lm, kap2, lam, id, nx, ny, nz, b1x, b1y, b1z,
                               b2x, b2y, b2z, flags, cost_out, nv_out, nv, cost_here, id_c, nx_c, ny_c,
                               nz_c);
-        if (lm) {
+        if (WAVES == 1 && lm) {
             float inv_cc = 0.f;
             bool cand_ok = cand;
             if (owner && cand) {
@@ -2421,8 +2414,8 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(6
                     const float drx = (bdx + fox) * ifx, dry = (bdy + foy) * ify;
                     const float sig = fmaf(sa.z * inv_c, dry, (sa.y * inv_c) * drx);
                     const float idu_c = fmaf(sa.x, sig, sa.x);
-                    frame_cost<T, BY_ROW, 0>(pairs, fr, nf, bdx, bdy, idu_c, calive && pv && (idu_c > 0.f), pitch_b,
-                                             wm1, hm1, ikf, hk, img_scale, cst2, nv2l);
+                    frame_cost<T, BY_ROW, DEEP>(pairs, fr, nf, bdx, bdy, idu_c, calive && pv && (idu_c > 0.f), pitch_b,
+                                                wm1, hm1, ikf, hk, img_scale, cst2, nv2l);
                 }
                 const float c2 = group_sum<LANES>(cst2);
                 const int n2 = group_sum<LANES>(nv2l);
@@ -2945,19 +2938,29 @@ hipError_t launch_disc_transfer(const DiscTransferArgs& one, const DiscTransferA
     return hipGetLastError();
 }
 
+template <typename T, bool R>
+static void* disc_gn_pick(const DiscForm& f) {
+    constexpr int SPW = disc_surfels_per_wave(std::is_same<T, float>::value ? 0 : 1);
+    return f.waves == 16  ? (void*)&disc_gn_kernel<T, SPW, R, 16, 4>
+           : f.waves == 8 ? (void*)&disc_gn_kernel<T, SPW, R, 8, 4>
+           : f.waves == 4 ? (void*)&disc_gn_kernel<T, SPW, R, 4, 4>
+           : f.deep == 4  ? (void*)&disc_gn_kernel<T, SPW, R, 1, 4>
+           : f.deep == 2  ? (void*)&disc_gn_kernel<T, SPW, R, 1, 2>
+                          : (void*)&disc_gn_kernel<T, SPW, R, 1, 0>;
+}
 template <bool R>
-static void* disc_gn_ptr(int dtype) {
-    return dtype == 0   ? (void*)&disc_gn_kernel<float, disc_surfels_per_wave(0), R>
-           : dtype == 1 ? (void*)&disc_gn_kernel<_Float16, disc_surfels_per_wave(1), R>
-                        : (void*)&disc_gn_kernel<uint8_t, disc_surfels_per_wave(2), R>;
+static void* disc_gn_ptr(int dtype, const DiscForm& f) {
+    return dtype == 0 ? disc_gn_pick<float, R>(f) : dtype == 1 ? disc_gn_pick<_Float16, R>(f)
+                                                               : disc_gn_pick<uint8_t, R>(f);
 }
 
-hipError_t launch_disc_gn(int dtype, const LoneBatch& one, const BatchHeader* hdr, int total_items,
-                          int grid_blocks, bool by_row, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+hipError_t launch_disc_gn(int dtype, const DiscForm& form, const LoneBatch& one, const BatchHeader* hdr,
+                          int total_items, int grid_blocks, bool by_row, hipStream_t s, hipEvent_t start,
+                          hipEvent_t stop) {
     if (total_items <= 0) return hipSuccess;
     void* args[] = {(void*)&one, (void*)&hdr, (void*)&total_items};
-    return launch_timed(by_row ? disc_gn_ptr<true>(dtype) : disc_gn_ptr<false>(dtype), grid_blocks, args, s, start,
-                        stop);
+    return launch_timed(by_row ? disc_gn_ptr<true>(dtype, form) : disc_gn_ptr<false>(dtype, form), grid_blocks,
+                        disc_threads(form.waves), args, s, start, stop);
 }
 
 hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items,
