@@ -250,20 +250,21 @@ TransferWs transfer_ws(int64_t total_dst) {
     return w;
 }
 
-// Disc render workspace: raster records [surfels], tile counts [tiles], list
-// starts [tiles + 1], scan block sums [ceil(tiles / 1024)], tile lists
-// [kDiscMaxTilesPerSurfel * surfels].
+// Disc render workspace: raster records [surfels], tile counts [tiles] and the
+// list's cursor, list starts [tiles], tile lists [kDiscMaxTilesPerSurfel *
+// surfels].
 struct DiscRenderWs {
-    size_t rec_off, count_off, start_off, block_off, list_off, total;
+    size_t rec_off, count_off, start_off, list_off, total;
 };
 DiscRenderWs disc_render_ws(int64_t surfels, int64_t tiles) {
     DiscRenderWs w;
-    const size_t n_blocks = (size_t)((tiles + 1023) / 1024);
     w.rec_off = 0;
     w.count_off = align256(sizeof(DiscRaster) * (size_t)surfels);
-    w.start_off = w.count_off + align256(sizeof(int32_t) * (size_t)tiles);
-    w.block_off = w.start_off + align256(sizeof(int32_t) * ((size_t)tiles + 1));
-    w.list_off = w.block_off + align256(sizeof(int32_t) * n_blocks);
+    w.start_off = w.count_off + align256(sizeof(int32_t) * ((size_t)tiles + 1));
+    // (one word per 1024 tiles is spare: the size that callers keep for these
+    // arguments stays what it was)
+    w.list_off = w.start_off + align256(sizeof(int32_t) * (size_t)tiles) +
+                 align256(sizeof(int32_t) * (size_t)((tiles + 1023) / 1024));
     w.total = w.list_off + align256(sizeof(int32_t) * (size_t)kDiscMaxTilesPerSurfel * (size_t)surfels);
     return w;
 }
@@ -1171,6 +1172,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     if (n > SGN_MAX_BATCH) return fail(SGN_E_UNSUPPORTED, "more keyframes than SGN_MAX_BATCH");
     std::vector<DiscRenderItem> tab(n);
     int64_t total_surfels = 0, total_pixels = 0, total_tiles = 0;
+    bool bin_lds = true;
     for (int i = 0; i < n; ++i) {
         const sgn_disc_item* it = &items[i];
         sgn_status st = check_disc_item(it, false);
@@ -1193,7 +1195,9 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
         r.tile_base = (int32_t)total_tiles;
         total_surfels += it->count;
         total_pixels += (int64_t)r.width * r.height;
-        total_tiles += (int64_t)r.tiles_x * ((r.height + kRenderTile - 1) / kRenderTile);
+        const int64_t tiles = (int64_t)r.tiles_x * ((r.height + kRenderTile - 1) / kRenderTile);
+        total_tiles += tiles;
+        bin_lds &= tiles <= kBinTiles && it->count <= kBinSurfels;
     }
     if (total_surfels > (int64_t)INT32_MAX / (2 * kDiscMaxTilesPerSurfel) || total_tiles > (int64_t)INT32_MAX / 2)
         return fail(SGN_E_UNSUPPORTED, "too many surfels or pixels in one batch");
@@ -1209,9 +1213,8 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     w.rec = (DiscRaster*)((char*)ws + lw.rec_off);
     w.count = (int32_t*)((char*)ws + lw.count_off);
     w.start = (int32_t*)((char*)ws + lw.start_off);
-    w.block_sum = (int32_t*)((char*)ws + lw.block_off);
     w.list = (int32_t*)((char*)ws + lw.list_off);
-    hipError_t e = launch_disc_render(tab[0], dtab, n, (int)total_surfels, (int)total_tiles, w, c->stream);
+    hipError_t e = launch_disc_render(tab[0], dtab, n, (int)total_surfels, (int)total_tiles, bin_lds, w, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc render launch");
     return SGN_OK;
 }

@@ -272,19 +272,21 @@ constexpr int kRenderTile = 16;
 struct DiscRaster {
     double cx, cy, n0, n1, n2, den;
 };
-// The render's scratch: raster records [surfels], tile counts [tiles], list
-// starts [tiles + 1], scan block sums [ceil(tiles / 1024)], tile lists
+// The render's scratch: raster records [surfels], tile counts [tiles] and
+// after them the list's cursor, list starts [tiles], tile lists
 // [kDiscMaxTilesPerSurfel * surfels].
 constexpr int kDiscMaxTilesPerSurfel = 9;     // a box of <= 2 r + 1 <= 25 pixels meets <= 3 x 3 tiles
 struct DiscRenderScratch {
     DiscRaster* rec;
     int32_t* count;
     int32_t* start;
-    int32_t* block_sum;
     int32_t* list;
 };
+// Largest keyframe that one workgroup bins in LDS.
+constexpr int kBinTiles = 15360;
+constexpr int kBinSurfels = 16384;
 hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items, int total_surfels,
-                              int total_tiles, const DiscRenderScratch& w, hipStream_t s);
+                              int total_tiles, bool bin_lds, const DiscRenderScratch& w, hipStream_t s);
 // The search for empty areas on the lattice (spacing/2 + i spacing, ...),
 // placement of the qualifying candidates as surfels first .. and their
 // neighbour initialisation from the index map.

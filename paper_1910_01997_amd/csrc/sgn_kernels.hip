@@ -2454,11 +2454,18 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
 //
 // The render works in screen tiles of kRenderTile x kRenderTile pixels.  The
 // usable surfels are binned to the tiles their disc's bounding box meets (a
-// count, an exclusive scan of the counts over the tiles of the whole batch,
-// a fill); then one workgroup per tile gives each pixel to a thread, which
-// walks the tile's list keeping the largest value and the lowest index that
-// reaches it.  The outcome does not depend on the list order, so the fill's
-// atomics leave it deterministic, and the depth test needs no atomics.
+// count per tile, a range of the list for each, a fill); then one workgroup
+// per tile gives each pixel to a thread, which walks the tile's list keeping
+// the largest value and the lowest index that reaches it.  The outcome does
+// not depend on the list order, so the fill's atomics leave it
+// deterministic, and the depth test needs no atomics.
+//
+// Binning takes one launch where a workgroup's LDS holds a keyframe's tile
+// counts (disc_bin_lds_kernel: up to kBinTiles tiles and kBinSurfels surfels,
+// images to about 2000 x 2000), else four (clear, count, ranges, fill).  The
+// work is a few microseconds either way; what counts is the launches, about
+// 4.7 us each: a 640x480 keyframe's render took 35 us with seven (three of
+// them a scan of the counts) and takes 17 with two.
 
 // Table entry of global surfel g (largest surfel_base <= g among entries
 // with surfels) or of global tile t (by tile_base).
@@ -2483,50 +2490,68 @@ __global__ void fill_int_kernel(int32_t* __restrict__ p, int n, int32_t v) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
 }
 
-// Pass 0 counts a usable surfel in each tile its disc's bounding box meets
-// and stores its raster record; pass 1 (after the scan) writes it into those
-// tiles' lists.  One thread per surfel.
-template <int PASS>
-__global__ __launch_bounds__(256) void disc_bin_kernel(DiscRenderItem, const DiscRenderItem* __restrict__ tab_, int n_items,
-                                                       int total, DiscRaster* __restrict__ rec,
-                                                       int32_t* __restrict__ count,
-                                                       const int32_t* __restrict__ start,
-                                                       int32_t* __restrict__ list) {
+// The tiles that surfel s's disc (its bounding box inside the image) meets.
+struct TileBox {
+    int tx0, tx1, ty0, ty1;
+};
+__device__ __forceinline__ bool disc_box(const carg<DiscRenderItem>& a, int s, TileBox& b) {
+    const double cx = (double)a.ux[s], cy = (double)a.uy[s], r = (double)a.radius;
+    if (!isfinite(cx) || !isfinite(cy)) return false;
+    const double xlo = fmax(0.0, ceil(cx - r)), xhi = fmin((double)(a.width - 1), floor(cx + r));
+    const double ylo = fmax(0.0, ceil(cy - r)), yhi = fmin((double)(a.height - 1), floor(cy + r));
+    if (!(xlo <= xhi) || !(ylo <= yhi)) return false;
+    b.tx0 = (int)xlo / kRenderTile; b.tx1 = (int)xhi / kRenderTile;
+    b.ty0 = (int)ylo / kRenderTile; b.ty1 = (int)yhi / kRenderTile;
+    return true;
+}
+// Whether surfel s is drawn, with its raster record and tiles.
+__device__ __forceinline__ bool disc_record(const carg<DiscRenderItem>& a, int s, DiscRaster& rec, TileBox& b) {
 #pragma clang fp contract(off)
+    // every load before the first test (one round trip)
+    const uint32_t fl = a.flags[s];
+    const double cx = (double)a.ux[s], cy = (double)a.uy[s];
+    const double n0 = a.nx[s], n1 = a.ny[s], n2 = a.nz[s], ids = a.inv_depth[s];
+    if (fl & (F_DEGENERATE | F_UNINIT)) return false;
+    if (!disc_box(a, s, b)) return false;
+    const double rs0 = (cx - a.cx) / a.fx, rs1 = (cy - a.cy) / a.fy;
+    if (fabs(n0 * rs0 + n1 * rs1 + n2 * 1.0) < 1e-6) return false;
+    const double ps0 = rs0 / ids, ps1 = rs1 / ids, ps2 = 1.0 / ids;
+    rec = DiscRaster{cx, cy, n0, n1, n2, ps0 * n0 + ps1 * n1 + ps2 * n2};
+    return true;
+}
+
+__global__ __launch_bounds__(256) void disc_count_kernel(DiscRenderItem, const DiscRenderItem* __restrict__ tab_,
+                                                         int n_items, int total, DiscRaster* __restrict__ rec,
+                                                         int32_t* __restrict__ count) {
     const cptr<DiscRenderItem> tab = table_or_arg(tab_);
     const int g = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (g >= total) return;
     const carg<DiscRenderItem>& a = tab[render_item_of_surfel(tab, n_items, g)];
-    const int s = g - a.surfel_base;
-    if (a.flags[s] & (F_DEGENERATE | F_UNINIT)) return;
-    const double cx = (double)a.ux[s], cy = (double)a.uy[s], r = (double)a.radius;
-    if (!isfinite(cx) || !isfinite(cy)) return;
-    const double n0 = a.nx[s], n1 = a.ny[s], n2 = a.nz[s], ids = a.inv_depth[s];
-    const double rs0 = (cx - a.cx) / a.fx, rs1 = (cy - a.cy) / a.fy;
-    if (fabs(n0 * rs0 + n1 * rs1 + n2 * 1.0) < 1e-6) return;
-    const double xlo = fmax(0.0, ceil(cx - r)), xhi = fmin((double)(a.width - 1), floor(cx + r));
-    const double ylo = fmax(0.0, ceil(cy - r)), yhi = fmin((double)(a.height - 1), floor(cy + r));
-    if (!(xlo <= xhi) || !(ylo <= yhi)) return;
-    if (PASS == 0) {
-        const double ps0 = rs0 / ids, ps1 = rs1 / ids, ps2 = 1.0 / ids;
-        rec[g] = DiscRaster{cx, cy, n0, n1, n2, ps0 * n0 + ps1 * n1 + ps2 * n2};
-    }
-    const int tx0 = (int)xlo / kRenderTile, tx1 = (int)xhi / kRenderTile;
-    const int ty0 = (int)ylo / kRenderTile, ty1 = (int)yhi / kRenderTile;
-    for (int ty = ty0; ty <= ty1; ++ty)
-        for (int tx = tx0; tx <= tx1; ++tx) {
-            const int t = a.tile_base + ty * a.tiles_x + tx;
-            if (PASS == 0)
-                atomicAdd(count + t, 1);
-            else
-                list[start[t] + atomicSub(count + t, 1) - 1] = g;
-        }
+    DiscRaster q;
+    TileBox b;
+    const bool use = disc_record(a, g - a.surfel_base, q, b);
+    if (!use) q.cx = __builtin_nan("");          // the fill skips it
+    rec[g] = q;
+    if (!use) return;
+    for (int ty = b.ty0; ty <= b.ty1; ++ty)
+        for (int tx = b.tx0; tx <= b.tx1; ++tx) atomicAdd(count + a.tile_base + ty * a.tiles_x + tx, 1);
 }
 
-// Exclusive scan of the tile counts into start[0 .. n] (start[n] = the total):
-// blocks of 1024 scan their counts and report their sums, one block scans the
-// sums (in chunks, with a carry) and writes the total, the sums are added
-// back.
+__global__ __launch_bounds__(256) void disc_fill_kernel(DiscRenderItem, const DiscRenderItem* __restrict__ tab_,
+                                                        int n_items, int total, const DiscRaster* __restrict__ rec,
+                                                        int32_t* __restrict__ start, int32_t* __restrict__ list) {
+    const cptr<DiscRenderItem> tab = table_or_arg(tab_);
+    const int g = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (g >= total) return;
+    const carg<DiscRenderItem>& a = tab[render_item_of_surfel(tab, n_items, g)];
+    TileBox b;
+    if (isnan(rec[g].cx) || !disc_box(a, g - a.surfel_base, b)) return;
+    for (int ty = b.ty0; ty <= b.ty1; ++ty)
+        for (int tx = b.tx0; tx <= b.tx1; ++tx)
+            list[atomicSub(start + a.tile_base + ty * a.tiles_x + tx, 1) - 1] = g;
+}
+
+// Exclusive scan over a workgroup of up to 1024 threads; s_w holds 17 words.
 __device__ __forceinline__ int block_exclusive_scan(int v, int* s_w, int& block_total) {
     const int lane = threadIdx.x & (kWaveSize - 1), wave = threadIdx.x >> 6;
     int x = v;
@@ -2537,14 +2562,18 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* s_w, int& block_
     }
     if (lane == kWaveSize - 1) s_w[wave] = x;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int w = 0; w < (int)(blockDim.x / kWaveSize); ++w) {
-            const int t = s_w[w];
-            s_w[w] = acc;
-            acc += t;
+    if (wave == 0) {
+        // the wavefronts' sums, one per lane (at most sixteen)
+        const int n = (int)(blockDim.x / kWaveSize);
+        const int c = lane < n ? s_w[lane] : 0;
+        int w = c;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const int y = __shfl_up(w, o, kWaveSize);
+            if (lane >= o) w += y;
         }
-        s_w[16] = acc;
+        if (lane < n) s_w[lane] = w - c;
+        if (lane == n - 1) s_w[16] = w;
     }
     __syncthreads();
     block_total = s_w[16];
@@ -2552,91 +2581,216 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* s_w, int& block_
     __syncthreads();
     return ex;
 }
-__global__ __launch_bounds__(1024) void bin_scan_block_kernel(const int32_t* __restrict__ count,
-                                                              int32_t* __restrict__ start,
-                                                              int32_t* __restrict__ block_sum, int n) {
+// A range of the list for each tile, in no particular order: a scan within
+// each workgroup and one atomic per workgroup on the list's cursor.  start[t]
+// is the range's end; the fill counts it down to the beginning.
+__global__ __launch_bounds__(1024) void disc_range_kernel(const int32_t* __restrict__ count,
+                                                          int32_t* __restrict__ start, int32_t* __restrict__ cursor,
+                                                          int n) {
     __shared__ int s_w[17];
+    __shared__ int s_base;
     const int i = (int)(blockIdx.x * 1024 + threadIdx.x);
+    const int c = i < n ? count[i] : 0;
     int tot;
-    const int ex = block_exclusive_scan(i < n ? count[i] : 0, s_w, tot);
-    if (i < n) start[i] = ex;
-    if (threadIdx.x == 0) block_sum[blockIdx.x] = tot;
-}
-__global__ __launch_bounds__(1024) void bin_scan_top_kernel(int32_t* __restrict__ block_sum, int nb,
-                                                            int32_t* __restrict__ start, int n) {
-    __shared__ int s_w[17];
-    int carry = 0;
-    for (int c0 = 0; c0 < nb; c0 += 1024) {
-        const int i = c0 + (int)threadIdx.x;
-        int tot;
-        const int ex = block_exclusive_scan(i < nb ? block_sum[i] : 0, s_w, tot);
-        if (i < nb) block_sum[i] = carry + ex;
-        carry += tot;
-    }
-    if (threadIdx.x == 0) start[n] = carry;
-}
-__global__ __launch_bounds__(1024) void bin_scan_add_kernel(int32_t* __restrict__ start,
-                                                            const int32_t* __restrict__ block_sum, int n) {
-    const int i = (int)(blockIdx.x * 1024 + threadIdx.x);
-    if (i < n) start[i] += block_sum[blockIdx.x];
+    const int ex = block_exclusive_scan(c, s_w, tot);
+    if (threadIdx.x == 0) s_base = atomicAdd(cursor, tot);
+    __syncthreads();
+    if (i < n) start[i] = s_base + ex + c;
 }
 
-// One workgroup per tile, one thread per pixel: the largest Eq. 3 value over
-// the tile's surfels whose disc holds the pixel, and the lowest index among
-// those that reach it.  The tile's list is staged in LDS a workgroup-wide
-// chunk at a time (one list entry and its raster record per thread, all
-// loads in flight at once), so the per-pixel walk reads LDS instead of
-// waiting on a dependent pair of loads per entry.
-__global__ __launch_bounds__(kRenderTile * kRenderTile) void disc_raster_kernel(
-    DiscRenderItem, const DiscRenderItem* __restrict__ tab_, int n_items, const DiscRaster* __restrict__ rec,
-    const int32_t* __restrict__ start, const int32_t* __restrict__ list) {
+// The whole binning of one keyframe in a workgroup, its tile counts in LDS.
+// The keyframe's part of the list begins at its first surfel's entries.
+__global__ __launch_bounds__(1024) void disc_bin_lds_kernel(DiscRenderItem, const DiscRenderItem* __restrict__ tab_,
+                                                            DiscRaster* __restrict__ rec,
+                                                            int32_t* __restrict__ count, int32_t* __restrict__ start,
+                                                            int32_t* __restrict__ list) {
+    const cptr<DiscRenderItem> tab = table_or_arg(tab_);
+    const carg<DiscRenderItem>& a = tab[blockIdx.x];
+    __shared__ int s_cnt[kBinTiles];
+    __shared__ unsigned long long s_use[kBinSurfels / kWaveSize];
+    __shared__ int s_w[17];
+    const int tid = (int)threadIdx.x;
+    const int tiles = a.tiles_x * ((a.height + kRenderTile - 1) / kRenderTile);
+    for (int t = tid; t < tiles; t += 1024) s_cnt[t] = 0;
+    __syncthreads();
+    const int n64 = (a.count + kWaveSize - 1) & ~(kWaveSize - 1);       // whole wavefronts
+    for (int s = tid; s < n64; s += 1024) {
+        DiscRaster q;
+        TileBox b;
+        const bool use = s < a.count && disc_record(a, s, q, b);
+        const unsigned long long ball = __ballot(use);
+        if ((tid & (kWaveSize - 1)) == 0) s_use[s / kWaveSize] = ball;
+        if (!use) continue;
+        rec[a.surfel_base + s] = q;
+        for (int ty = b.ty0; ty <= b.ty1; ++ty)
+            for (int tx = b.tx0; tx <= b.tx1; ++tx) atomicAdd(&s_cnt[ty * a.tiles_x + tx], 1);
+    }
+    __syncthreads();
+    // each thread takes a run of tiles: one scan over the workgroup
+    const int run = (tiles + 1023) / 1024;
+    const int t0 = min(tiles, tid * run), t1 = min(tiles, t0 + run);
+    int sum = 0;
+    for (int t = t0; t < t1; ++t) sum += s_cnt[t];
+    int tot;
+    int at = kDiscMaxTilesPerSurfel * a.surfel_base + block_exclusive_scan(sum, s_w, tot);
+    for (int t = t0; t < t1; ++t) {
+        const int c = s_cnt[t];
+        s_cnt[t] = at;
+        at += c;
+    }
+    __syncthreads();
+    const int end = kDiscMaxTilesPerSurfel * a.surfel_base + tot;
+    for (int t = tid; t < tiles; t += 1024) {
+        start[a.tile_base + t] = s_cnt[t];
+        count[a.tile_base + t] = (t + 1 < tiles ? s_cnt[t + 1] : end) - s_cnt[t];
+    }
+    __syncthreads();
+    for (int s = tid; s < a.count; s += 1024) {
+        TileBox b;
+        if (!((s_use[s / kWaveSize] >> (s & (kWaveSize - 1))) & 1ull) || !disc_box(a, s, b)) continue;
+        for (int ty = b.ty0; ty <= b.ty1; ++ty)
+            for (int tx = b.tx0; tx <= b.tx1; ++tx)
+                list[atomicAdd(&s_cnt[ty * a.tiles_x + tx], 1)] = a.surfel_base + s;
+    }
+}
+
+// One wavefront per tile, four pixels of one column per lane: the largest
+// Eq. 3 value over the tile's surfels whose disc holds the pixel, and the
+// lowest index among those that reach it.  The tile's list is staged in LDS,
+// 64 entries at a time (one entry and its raster record per lane, all loads
+// in flight at once).
+//
+// Bound: the chain of dependent loads in front of the walk (keyframe, range,
+// list, records), so what counts is how many tiles a CU holds: 32 with a
+// wavefront each, where four-wavefront workgroups left eight.  The walk
+// compares num * (1 / den), the reciprocal formed once per entry and tile,
+// instead of dividing for every pixel: the product is within 4 ulp of the
+// quotient, so where the largest stands out by more than kNear it belongs to
+// the largest quotient, which is then divided out once.  Tiles with a pixel
+// where another product comes nearer (equal planes, ties), or whose products
+// leave the normal range, walk again with divisions.  16 mixed keyframes
+// (26,000 tiles): 49 us with a workgroup per tile and a division per pixel
+// and entry, 55 with the products alone, 38 with a wavefront per tile too.
+__global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
+    DiscRenderItem, const DiscRenderItem* __restrict__ tab_, int n_items, int n_tiles,
+    const DiscRaster* __restrict__ rec, const int32_t* __restrict__ count, const int32_t* __restrict__ start,
+    const int32_t* __restrict__ list) {
 #pragma clang fp contract(off)
     const cptr<DiscRenderItem> tab = table_or_arg(tab_);
-    constexpr int kChunk = kRenderTile * kRenderTile;
-    __shared__ DiscRaster s_rec[kChunk];
-    __shared__ int s_idx[kChunk];
-    const int t = (int)blockIdx.x;
+    constexpr int kPx = 4;
+    constexpr double kNear = 1e-14, kTiny = 1e-280, kHuge = 1e280;
+    static_assert(kRenderTile == 16 && kRenderTile * kRenderTile == kPx * kWaveSize, "a tile per wavefront");
+    __shared__ DiscRaster s_rec_[kBlockThreads / kWaveSize][kWaveSize];
+    __shared__ double s_rden_[kBlockThreads / kWaveSize][kWaveSize];
+    __shared__ int s_idx_[kBlockThreads / kWaveSize][kWaveSize];
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = threadIdx.x >> 6;
+    DiscRaster* const s_rec = s_rec_[wave];
+    double* const s_rden = s_rden_[wave];
+    int* const s_idx = s_idx_[wave];
+    const int t = grid_wave();
+    if (t >= n_tiles) return;
     const carg<DiscRenderItem>& a = tab[render_item_of_tile(tab, n_items, t)];
     const int lt = t - a.tile_base;
     const int ty = lt / a.tiles_x, tx = lt - ty * a.tiles_x;
-    const int x = tx * kRenderTile + (int)(threadIdx.x % kRenderTile);
-    const int y = ty * kRenderTile + (int)(threadIdx.x / kRenderTile);
-    const bool inside = x < a.width && y < a.height;
-    const double xd = (double)x, yd = (double)y, r = (double)a.radius, r2 = r * r;
-    const double ru0 = (xd - a.cx) / a.fx, ru1 = (yd - a.cy) / a.fy;
-    unsigned long long best = 0ull;
-    int who = 0x7fffffff;
-    const int k0 = start[t], k1 = start[t + 1];
-    for (int c0 = k0; c0 < k1; c0 += kChunk) {
-        const int nc = min(kChunk, k1 - c0);
-        __syncthreads();                     // the previous chunk is read
-        if ((int)threadIdx.x < nc) {
-            const int g = list[c0 + (int)threadIdx.x];
-            s_idx[threadIdx.x] = g;
-            s_rec[threadIdx.x] = rec[g];
+    const int x = tx * kRenderTile + (lane & (kRenderTile - 1));
+    const int y0 = ty * kRenderTile + lane / kRenderTile;            // rows y0, y0 + 4, ...
+    const double r = (double)a.radius, r2 = r * r;
+    const double xd = (double)x, ru0 = (xd - a.cx) / a.fx;
+    double yd[kPx], ru1[kPx], best[kPx], next[kPx];      // the two largest products
+    int who[kPx];
+#pragma unroll
+    for (int p = 0; p < kPx; ++p) {
+        yd[p] = (double)(y0 + 4 * p);
+        ru1[p] = (yd[p] - a.cy) / a.fy;
+        best[p] = 0.0;
+        next[p] = 0.0;
+        who[p] = -1;
+    }
+    const int k0 = start[t], k1 = k0 + count[t];
+    for (int c0 = k0; c0 < k1; c0 += kWaveSize) {
+        const int nc = min(kWaveSize, k1 - c0);
+        wave_sync();                          // the previous chunk is read
+        if (lane < nc) {
+            const int g = list[c0 + lane];
+            const DiscRaster q = rec[g];
+            s_idx[lane] = g - a.surfel_base;
+            s_rec[lane] = q;
+            s_rden[lane] = 1.0 / q.den;
         }
-        __syncthreads();
-        if (!inside) continue;
+        wave_sync();
         for (int e = 0; e < nc; ++e) {
-            const DiscRaster& q = s_rec[e];
-            const double dx = xd - q.cx, dy = yd - q.cy;
-            if (!(dx * dx + dy * dy < r2)) continue;
-            const double v = (ru0 * q.n0 + ru1 * q.n1 + 1.0 * q.n2) / q.den;
-            if (!(v > 0.0) || !isfinite(v)) continue;
-            const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
-            const int s = s_idx[e] - a.surfel_base;
-            if (bits > best) {
-                best = bits;
-                who = s;
-            } else if (bits == best && s < who) {
-                who = s;
+            const DiscRaster q = s_rec[e];
+            const double rden = s_rden[e];
+            const int idx = s_idx[e];
+            const double dx = xd - q.cx, dx2 = dx * dx;
+            const double nx = ru0 * q.n0;
+#pragma unroll
+            for (int p = 0; p < kPx; ++p) {
+                const double dy = yd[p] - q.cy;
+                // (a branch: most entries miss all of a row group's pixels)
+                if (!(dx2 + dy * dy < r2)) continue;
+                const double v = (nx + ru1[p] * q.n1 + 1.0 * q.n2) * rden;
+                who[p] = v > best[p] ? idx : who[p];
+                next[p] = fmax(next[p], fmin(v, best[p]));
+                best[p] = fmax(best[p], v);
             }
         }
     }
-    if (!inside) return;
-    const size_t o = (size_t)y * (size_t)a.width + (size_t)x;
-    a.inv_depth_out[o] = best ? (float)__longlong_as_double((long long)best) : 0.f;
-    if (a.index_out) a.index_out[o] = best ? who : -1;
+    double val[kPx];
+    bool again = false;
+#pragma unroll
+    for (int p = 0; p < kPx; ++p) {
+        // (a NaN product is a NaN quotient: not drawn, and passed over by the
+        // maxima; infinite and vanishing ones go to the second walk)
+        again = again || (who[p] >= 0 && (next[p] >= best[p] * (1.0 - kNear) || !(best[p] > kTiny && best[p] < kHuge)));
+        val[p] = 0.0;
+        if (who[p] >= 0) {
+            const DiscRaster q = rec[a.surfel_base + who[p]];
+            val[p] = (ru0 * q.n0 + ru1[p] * q.n1 + 1.0 * q.n2) / q.den;
+        }
+    }
+    if (__ballot(again) != 0ull) {
+#pragma unroll
+        for (int p = 0; p < kPx; ++p) {
+            val[p] = 0.0;
+            who[p] = -1;
+        }
+        for (int c0 = k0; c0 < k1; c0 += kWaveSize) {
+            const int nc = min(kWaveSize, k1 - c0);
+            wave_sync();
+            if (lane < nc) {
+                const int g = list[c0 + lane];
+                s_idx[lane] = g - a.surfel_base;
+                s_rec[lane] = rec[g];
+            }
+            wave_sync();
+            for (int e = 0; e < nc; ++e) {
+                const DiscRaster q = s_rec[e];
+                const int idx = s_idx[e];
+                const double dx = xd - q.cx;
+#pragma unroll
+                for (int p = 0; p < kPx; ++p) {
+                    const double dy = yd[p] - q.cy;
+                    if (!(dx * dx + dy * dy < r2)) continue;
+                    const double v = (ru0 * q.n0 + ru1[p] * q.n1 + 1.0 * q.n2) / q.den;
+                    if (!(v > 0.0) || !isfinite(v)) continue;
+                    if (v > val[p] || (v == val[p] && idx < who[p])) {
+                        val[p] = v;
+                        who[p] = idx;
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < kPx; ++p) {
+        const int y = y0 + 4 * p;
+        if (x >= a.width || y >= a.height) continue;
+        const size_t o = (size_t)y * (size_t)a.width + (size_t)x;
+        a.inv_depth_out[o] = (float)val[p];
+        if (a.index_out) a.index_out[o] = who[p];
+    }
 }
 
 // Placement runs over a table of keyframes: candidates and new surfels are
@@ -2660,6 +2814,28 @@ __device__ __forceinline__ int place_entry_of_init(cptr<DiscPlaceArgs> tab, int 
     return lo;
 }
 
+// Pixel k of the side x side window of pixels within `reach` of (cx, cy), its
+// place in the index map clamped to the image, so that it can be loaded
+// whether it lies inside or not (a load inside a branch is waited for there).
+// k / side is a multiplication by inv = floor(2^20 / side) + 1, exact for
+// k below 2^20 / side - side: the largest window has 97 x 97 pixels.
+struct WindowPixel {
+    int dx, dy, at;
+    bool inside;
+};
+__device__ __forceinline__ unsigned window_inv(int side) { return (1u << 20) / (unsigned)side + 1u; }
+__device__ __forceinline__ WindowPixel window_pixel(int k, int side, int reach, unsigned inv, int cx, int cy, int W,
+                                                    int H) {
+    const int row = (int)(((unsigned)k * inv) >> 20);
+    WindowPixel w;
+    w.dy = row - reach;
+    w.dx = k - row * side - reach;
+    const int x = cx + w.dx, y = cy + w.dy;
+    w.inside = x >= 0 && y >= 0 && x < W && y < H;
+    w.at = min(max(y, 0), H - 1) * W + min(max(x, 0), W - 1);
+    return w;
+}
+
 // The search for empty areas (Surfel Initialization section): one wavefront
 // per lattice candidate u_ns = (spacing/2 + i spacing, spacing/2 + j
 // spacing), its lanes sharing the window of pixels within alpha r; the
@@ -2680,16 +2856,21 @@ __global__ __launch_bounds__(kBlockThreads) void disc_search_kernel(DiscPlaceArg
     const double ar2 = ar * ar;
     const int reach = (int)floor(ar);
     const int side = 2 * reach + 1, npix = side * side;
+    const unsigned inv = window_inv(side);
     bool hit = false;
-    for (int k0 = 0; k0 < npix; k0 += kWaveSize) {
-        const int k = k0 + lane;
-        if (k < npix) {
-            const int dy = k / side - reach, dx = k % side - reach;
-            const int x = cx + dx, y = cy + dy;
-            if (x >= 0 && y >= 0 && x < a.width && y < a.height &&
-                (double)(dx * dx + dy * dy) <= ar2 && a.index_map[(size_t)y * a.width + x] >= 0)
-                hit = true;
+    // four pixels per lane in flight at a time
+    for (int k0 = 0; k0 < npix; k0 += 4 * kWaveSize) {
+        int own[4];
+        bool in[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + u * kWaveSize + lane;
+            const WindowPixel w = window_pixel(k, side, reach, inv, cx, cy, a.width, a.height);
+            in[u] = k < npix && w.inside && (double)(w.dx * w.dx + w.dy * w.dy) <= ar2;
+            own[u] = a.index_map[w.at];
         }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) hit = hit || (in[u] && own[u] >= 0);
         if (__ballot(hit) != 0ull) break;     // wave-uniform
     }
     // the vote of the whole wavefront, taken before narrowing to one lane
@@ -2743,9 +2924,15 @@ __global__ __launch_bounds__(1024) void disc_compact_kernel(DiscPlaceArgs, const
     }
 }
 
+// The minimum over the wavefront, in every lane: within DPP rows of sixteen,
+// then over the four rows through scalar registers.
 __device__ __forceinline__ int wave_min(int v) {
-    for (int m = 1; m < kWaveSize; m <<= 1) v = min(v, __shfl_xor(v, m));
-    return v;
+    v = min(v, dpp_i<0xB1>(v));      // quad_perm [1,0,3,2]
+    v = min(v, dpp_i<0x4E>(v));      // quad_perm [2,3,0,1]
+    v = min(v, dpp_i<0x141>(v));     // row_half_mirror
+    v = min(v, dpp_i<0x140>(v));     // row_mirror
+    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
 // Neighbour initialisation of the placed surfels (Surfel Initialization
@@ -2754,7 +2941,10 @@ __device__ __forceinline__ int wave_min(int v) {
 // centre, visited in index order (the wavefront finds the next smallest
 // index each round); id = mean of Eq. 3 of their planes at the new ray,
 // n = mean of their normals sign-aligned to the first, renormalised; none
-// usable: UNINIT with id 0 and n = (0, 0, -1).
+// usable: UNINIT with id 0 and n = (0, 0, -1).  The indices are found first,
+// one lane each, and all their surfels loaded together, as are the window's
+// pixels: bound by latency, a 640x480 keyframe's new surfels took 21 us with
+// the loads one after another and take 11.
 __global__ __launch_bounds__(kWaveSize) void disc_init_kernel(DiscPlaceArgs, const DiscPlaceArgs* __restrict__ tab_,
                                                               int n_items) {
     const cptr<DiscPlaceArgs> tab = table_or_arg(tab_);
@@ -2771,42 +2961,69 @@ __global__ __launch_bounds__(kWaveSize) void disc_init_kernel(DiscPlaceArgs, con
     const double br2 = br * br;
     const int reach = (int)ceil(br);
     const int side = 2 * reach + 1, npix = side * side;
-    for (int k = lane; k < npix; k += kWaveSize) {
-        const int dy = k / side - reach, dx = k % side - reach;
-        const int x = cx + dx, y = cy + dy;
-        int j = -1;
-        if (x >= 0 && y >= 0 && x < a.width && y < a.height && (double)(dx * dx + dy * dy) < br2) {
-            j = a.index_map[(size_t)y * a.width + x];
-            if (j >= a.first) j = -1;
+    const unsigned inv = window_inv(side);
+    // nine pixels per lane in flight at a time
+    for (int k0 = 0; k0 < npix; k0 += 9 * kWaveSize) {
+        int own[9];
+        bool in[9];
+#pragma unroll
+        for (int u = 0; u < 9; ++u) {
+            const WindowPixel w = window_pixel(k0 + u * kWaveSize + lane, side, reach, inv, cx, cy, a.width, a.height);
+            in[u] = w.inside && (double)(w.dx * w.dx + w.dy * w.dy) < br2;
+            own[u] = a.index_map[w.at];
         }
-        s_win[k] = j;
+#pragma unroll
+        for (int u = 0; u < 9; ++u) {
+            const int k = k0 + u * kWaveSize + lane;
+            if (k < npix) s_win[k] = in[u] && own[u] < a.first ? own[u] : -1;
+        }
     }
     wave_sync();
     const float rnx = ((float)cx - a.cx) / a.fx, rny = ((float)cy - a.cy) / a.fy;
     int last = -1, count = 0;
     float id_sum = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, rx = 0.f, ry = 0.f, rz = 0.f;
-    for (;;) {
-        // next neighbour in index order
-        int best = 0x7fffffff;
-        for (int k = lane; k < npix; k += kWaveSize) {
-            const int j = s_win[k];
-            if (j > last) best = min(best, j);
+    for (bool more = true; more;) {
+        // the next 64 neighbours in index order, one per lane
+        int mine = -1, found = 0;
+        while (found < kWaveSize) {
+            int best = 0x7fffffff;
+            for (int k = lane; k < npix; k += kWaveSize) {
+                const int j = s_win[k];
+                if (j > last) best = min(best, j);
+            }
+            best = wave_min(best);
+            if (best == 0x7fffffff) {
+                more = false;
+                break;
+            }
+            last = best;
+            if (lane == found) mine = best;
+            ++found;
         }
-        const int j = __builtin_amdgcn_readfirstlane(wave_min(best));
-        if (j == 0x7fffffff) break;
-        last = j;
-        if (a.flags[j] & (F_UNINIT | F_DEGENERATE)) continue;
-        const float njx = a.nx[j], njy = a.ny[j], njz = a.nz[j];
-        const float rjx = (a.ux[j] - a.cx) / a.fx, rjy = (a.uy[j] - a.cy) / a.fy;
-        const float cj = njx * rjx + njy * rjy + njz;
-        if (fabsf(cj) < 1e-6f) continue;
-        // Eq. 3 of plane j at the new surfel's ray
-        const float id = a.inv_depth[j] * (njx * rnx + njy * rny + njz) / cj;
-        if (count == 0) { rx = njx; ry = njy; rz = njz; }
-        const float sg = (njx * rx + njy * ry + njz * rz) < 0.f ? -1.f : 1.f;
-        id_sum += id;
-        sx += sg * njx; sy += sg * njy; sz += sg * njz;
-        ++count;
+        // every lane's neighbour at once: usable, its Eq. 3 at the new
+        // surfel's ray, its normal
+        bool use = mine >= 0;
+        float id = 0.f, njx = 0.f, njy = 0.f, njz = 0.f;
+        if (use) {
+            const uint32_t fl = a.flags[mine];
+            njx = a.nx[mine]; njy = a.ny[mine]; njz = a.nz[mine];
+            const float ujx = a.ux[mine], ujy = a.uy[mine], idj = a.inv_depth[mine];
+            const float rjx = (ujx - a.cx) / a.fx, rjy = (ujy - a.cy) / a.fy;
+            const float cj = njx * rjx + njy * rjy + njz;
+            use = !(fl & (F_UNINIT | F_DEGENERATE)) && !(fabsf(cj) < 1e-6f);
+            id = idj * (njx * rnx + njy * rny + njz) / cj;
+        }
+        // summed in index order
+        for (unsigned long long m = __ballot(use); m != 0ull; m &= m - 1ull) {
+            const int l = __builtin_ctzll(m);
+            auto of = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+            const float jx = of(njx), jy = of(njy), jz = of(njz);
+            if (count == 0) { rx = jx; ry = jy; rz = jz; }
+            const float sg = (jx * rx + jy * ry + jz * rz) < 0.f ? -1.f : 1.f;
+            id_sum += of(id);
+            sx += sg * jx; sy += sg * jy; sz += sg * jz;
+            ++count;
+        }
     }
     if (lane != 0) return;
     bool ok = count > 0;
@@ -2964,21 +3181,23 @@ hipError_t launch_disc_gn(int dtype, const DiscForm& form, const LoneBatch& one,
 }
 
 hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items,
-                              int total_surfels, int total_tiles, const DiscRenderScratch& w, hipStream_t s) {
-    const int nb = (total_tiles + 1023) / 1024;
-    fill_int_kernel<<<std::min((total_tiles + 255) / 256, 4096), 256, 0, s>>>(w.count, total_tiles, 0);
-    const int sblocks = (total_surfels + 255) / 256;
-    if (total_surfels > 0)
-        disc_bin_kernel<0><<<sblocks, 256, 0, s>>>(one, table, n_items, total_surfels, w.rec, w.count, w.start,
-                                                   w.list);
-    bin_scan_block_kernel<<<nb, 1024, 0, s>>>(w.count, w.start, w.block_sum, total_tiles);
-    bin_scan_top_kernel<<<1, 1024, 0, s>>>(w.block_sum, nb, w.start, total_tiles);
-    bin_scan_add_kernel<<<nb, 1024, 0, s>>>(w.start, w.block_sum, total_tiles);
-    if (total_surfels > 0)
-        disc_bin_kernel<1><<<sblocks, 256, 0, s>>>(one, table, n_items, total_surfels, w.rec, w.count, w.start,
-                                                   w.list);
-    disc_raster_kernel<<<total_tiles, kRenderTile * kRenderTile, 0, s>>>(one, table, n_items, w.rec, w.start,
-                                                                         w.list);
+                              int total_surfels, int total_tiles, bool bin_lds, const DiscRenderScratch& w,
+                              hipStream_t s) {
+    if (bin_lds) {
+        disc_bin_lds_kernel<<<n_items, 1024, 0, s>>>(one, table, w.rec, w.count, w.start, w.list);
+    } else {
+        // the list's cursor follows the counts
+        fill_int_kernel<<<std::min(total_tiles / 256 + 1, 4096), 256, 0, s>>>(w.count, total_tiles + 1, 0);
+        const int sblocks = (total_surfels + 255) / 256;
+        if (total_surfels > 0)
+            disc_count_kernel<<<sblocks, 256, 0, s>>>(one, table, n_items, total_surfels, w.rec, w.count);
+        disc_range_kernel<<<(total_tiles + 1023) / 1024, 1024, 0, s>>>(w.count, w.start, w.count + total_tiles, total_tiles);
+        if (total_surfels > 0)
+            disc_fill_kernel<<<sblocks, 256, 0, s>>>(one, table, n_items, total_surfels, w.rec, w.start, w.list);
+    }
+    constexpr int wpb = kBlockThreads / kWaveSize;
+    disc_raster_kernel<<<(total_tiles + wpb - 1) / wpb, kBlockThreads, 0, s>>>(one, table, n_items, total_tiles, w.rec,
+                                                                               w.count, w.start, w.list);
     return hipGetLastError();
 }
 
