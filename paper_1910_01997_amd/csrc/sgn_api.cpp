@@ -580,9 +580,8 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     }
     const std::vector<int> order = share_order(nq, work, n_nbr);
 
-    int frame_base = 0, item_base = 0, surfel_base = 0;
-    int64_t pixel_base = 0;
-    bool any_init = false, any_render = false;
+    int frame_base = 0, item_base = 0;
+    int64_t init_waves = 0, render_waves = 0;
     for (int oi = 0; oi < n; ++oi) {
         const int i = order[oi];
         const sgn_batch_item& it = items[i];
@@ -600,25 +599,25 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         const int blocks_y = (D.gh + geo.ab - 1) / geo.ab;
         D.n_items = fl.gn ? D.groups_x * blocks_y * geo.ipb : 0;
         D.item_base = item_base;
-        D.surfel_base = surfel_base;
-        D.pixel_base = pixel_base;
+        D.init_wave = (int32_t)init_waves;
+        D.render_wave = (int32_t)render_waves;
         st = describe_frames(kf, frs + frame_base);
         if (st) return st;
         frame_base += kf.n_nbr;
         item_base += D.n_items;
-        surfel_base += D.gw * D.gh;
-        if (D.inv_depth_out)     // render segments: rows x tile columns
-            pixel_base += (int64_t)D.height * ((D.width + D.patch - 1) / D.patch);
-        any_init |= D.is_new != nullptr;
-        any_render |= D.inv_depth_out != nullptr;
+        D.div_gw = fast_div(D.gw);
+        D.div_bx = fast_div((D.width + 3) / 4);
+        if (D.is_new) init_waves += ((int64_t)D.gw * D.gh + kInitSurfels - 1) / kInitSurfels;
+        if (D.inv_depth_out)
+            render_waves += ((int64_t)((D.width + 3) / 4) * ((D.height + 3) / 4) + kWaveSize - 1) / kWaveSize;
     }
     H->kfs = (KfDev*)(dev + L.kf_off);
     H->frames = (FrameDev*)(dev + L.fr_off);
     H->n_kf = n;
     H->n_frames = total_frames;
     H->total_items = item_base;
-    H->total_surfels = surfel_base;
-    H->total_pixels = pixel_base;
+    H->init_waves = (int32_t)init_waves;
+    H->render_waves = (int32_t)render_waves;
     H->iters = prm->iters;
     H->huber_k = prm->huber_k;
     H->kappa_fp64 = prm->kappa_fp64;
@@ -626,9 +625,6 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     H->beta_r = prm->beta_r;
     H->stamp = prm->stamp;
     H->lm_lambda = prm->lm_lambda;
-    H->do_init = fl.init && any_init;
-    H->do_gn = fl.gn;
-    H->do_render = fl.render && any_render;
     // fewer items than SIMDs are all in flight at once whatever their order:
     // no cut (160x120, 300 items: 32.6 us a call against 34.4)
     if (!plan.persistent && item_base < 4 * c->cus) nq = 1;
@@ -648,15 +644,13 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     }
     const int gn_grid = plan.persistent ? persistent_grid(c, var, plan) : item_blocks(nq, H->queues, item_base, kBlockThreads / kWaveSize);
     hipError_t e = hipSuccess;
-    if (H->do_init) e = launch_init(one.one, dH, std::max(1, c->cus) * 8, c->stream);
+    if (init_waves > 0) e = launch_init(one.one, dH, (int)init_waves, c->stream);
     if (e == hipSuccess && fl.gn && item_base > 0) {
         next_timing_slot(c);
         e = launch_gn(var, one, dH, c->counters, gn_grid, c->stream, c->gn_start, c->gn_end);
         if (e == hipSuccess) c->gn_timed = true;
     }
-    // one segment per thread for the larger batches (runs of 256 segments per
-    // block, so blocks past the batch's segments return at once)
-    if (e == hipSuccess && H->do_render) e = launch_render(one.one, dH, std::max(1, c->cus) * 32, c->stream);
+    if (e == hipSuccess && render_waves > 0) e = launch_render(one.one, dH, (int)render_waves, c->stream);
     return e == hipSuccess ? SGN_OK : hip_fail(e, "kernel launch");
 }
 
@@ -774,7 +768,7 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
         n_nbr[i] = items[i].kf.n_nbr;
     }
     const std::vector<int> order = share_order(nq, work, n_nbr);
-    int frame_base = 0, surfel_base = 0, item_base = 0;
+    int frame_base = 0, item_base = 0;
     for (int oi = 0; oi < n; ++oi) {
         const sgn_disc_item& it = items[order[oi]];
         const sgn_keyframe& kf = it.kf;
@@ -783,7 +777,6 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
         D.frame_base = frame_base;
         D.item_base = item_base;
         D.n_items = (it.count + disc_surfels_per_wave(dtype) - 1) / disc_surfels_per_wave(dtype);
-        D.surfel_base = surfel_base;
         D.disc_count = it.count;
         D.disc_ux = it.ux;
         D.disc_uy = it.uy;
@@ -791,7 +784,6 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
         st = describe_frames(kf, frs + frame_base);
         if (st) return st;
         frame_base += kf.n_nbr;
-        surfel_base += it.count;
         item_base += D.n_items;
     }
     H->kfs = (KfDev*)(dev + L.kf_off);
@@ -799,7 +791,6 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
     H->n_kf = n;
     H->n_frames = total_frames;
     H->total_items = item_base;
-    H->total_surfels = surfel_base;
     H->iters = prm->iters;
     H->huber_k = prm->huber_k;
     H->kappa_fp64 = prm->kappa_fp64;
@@ -807,7 +798,6 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
     H->beta_r = prm->beta_r;
     H->stamp = prm->stamp;
     H->lm_lambda = prm->lm_lambda;
-    H->do_gn = 1;
     H->n_queues = nq;
     cut_shares(nq, kfs, n, 0.5, H->queues);    // 16 mixed keyframes: 1.82 ms; 1.90 with 0, 1.96 with 1
     const BatchHeader* dH = nullptr;
@@ -1082,8 +1072,14 @@ static sgn_status transfer_impl(sgn_ctx* c, int32_t n, const sgn_grid* src_grids
         a.dst_K[3] = dst_grid->K.cy;
         for (int i = 0; i < 9; ++i) a.R[i] = pose->R[i];
         for (int i = 0; i < 3; ++i) a.t[i] = pose->t[i];
-        a.src_w = src_grid->width; a.src_h = src_grid->height; a.src_patch = src_grid->patch;
-        a.dst_w = dst_grid->width; a.dst_h = dst_grid->height; a.dst_patch = dst_grid->patch;
+        auto log2_of = [](int patch) { return patch == 4 ? 2 : patch == 8 ? 3 : 4; };
+        a.src_gw = src_grid->width / src_grid->patch;
+        a.src_shift = log2_of(src_grid->patch);
+        a.dst_gw = dst_grid->width / dst_grid->patch;
+        a.dst_gh = dst_grid->height / dst_grid->patch;
+        a.dst_shift = log2_of(dst_grid->patch);
+        a.div_src = fast_div(a.src_gw);
+        a.div_dst = fast_div(a.dst_gw);
         a.is_new = dst_is_new[k];
         a.src_index = dst_src_index ? dst_src_index[k] : nullptr;
         a.dst_base = (int32_t)total_dst;
@@ -1112,10 +1108,20 @@ static sgn_status transfer_impl(sgn_ctx* c, int32_t n, const sgn_grid* src_grids
         tab[k].best = best + tab[k].dst_base;
         tab[k].win = win + tab[k].dst_base;
     }
-    const RegridArgs* dtab;
-    st = upload_table(c, tab, n, &dtab);
-    if (st) return st;
-    hipError_t e = launch_regrid(tab[0], dtab, n, (int)src_waves, (int)dst_waves, c->stream);
+    // (as upload_table, with the copy in the call's first kernel)
+    const size_t bytes = n > 1 ? sizeof(RegridArgs) * (size_t)n : 0;
+    int slot = 0;
+    if (n > 1) {
+        st = check_table(c, bytes);
+        if (st) return st;
+        st = take_slot(c, slot);
+        if (st) return st;
+        std::memcpy(c->host_ring[slot], tab, bytes);
+    }
+    hipError_t e = launch_regrid(tab[0], c->host_ring[slot], n > 1 ? (RegridArgs*)c->dev_table : nullptr, bytes, n,
+                                 (int)src_waves, (int)dst_waves, best, win, (int)total_dst, c->stream,
+                                 n > 1 ? c->ring_ev[slot] : nullptr);
+    if (n > 1) c->ring_used[slot] = true;
     if (e != hipSuccess) return hip_fail(e, "re-gridding launch");
     return SGN_OK;
 }

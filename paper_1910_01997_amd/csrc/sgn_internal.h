@@ -13,6 +13,20 @@ constexpr int kWaveSize = 64;
 constexpr int kBlockThreads = 256;      // 4 wavefronts per workgroup
 constexpr int kNumCounters = 16;        // work-queue heads (one per XCD + spares)
 constexpr int kXcds = 8;
+constexpr int kInitSurfels = 128;       // surfels a wavefront of the initialisation looks through
+
+// Division of n < 2^24 by a divisor known on the host: m = ceil(2^(24 + l) / d)
+// with 2^l >= d, so that (n m) >> (24 + l) is exact.  Two instructions and a
+// shift; a plain 32-bit division is about thirty.
+struct FastDiv {
+    uint32_t m;
+    int32_t l;
+};
+inline FastDiv fast_div(int d) {
+    int l = 0;
+    while ((1 << l) < d) ++l;
+    return {(uint32_t)(((1ull << (24 + l)) + (uint64_t)d - 1) / (uint64_t)d), l};
+}
 
 // Per-keyframe descriptor in device memory (one per batch item).
 struct KfDev {
@@ -30,8 +44,11 @@ struct KfDev {
     int32_t* index_out;           // may be null
     int32_t width, height, kf_pitch, n_nbr;
     int32_t gw, gh, frame_base, item_base;      // frames: [frame_base, frame_base + n_nbr)
-    int32_t groups_x, n_items, surfel_base, pad_q;  // anchor blocks per row; work items
-    int64_t pixel_base;                          // prefix over render segments (row x tile column)
+    int32_t groups_x, n_items;                  // anchor blocks per row; work items
+    // first wavefront of the initialisation (kInitSurfels surfels each) and of
+    // the render (64 blocks of 4 x 4 pixels each)
+    int32_t init_wave, render_wave;
+    FastDiv div_gw, div_bx;       // by gw; by the 4-pixel blocks of a row
     int32_t patch, nbr_pitch_b;                   // neighbour-image row pitch in bytes
     double fx_d, fy_d, cx_d, cy_d;               // intrinsics as given (double)
     float fx, fy, cx, cy;                        // the same, rounded to float
@@ -100,17 +117,17 @@ struct QueueDev {
 struct BatchHeader {
     KfDev* kfs;
     FrameDev* frames;
-    int32_t n_kf, n_frames, total_items, total_surfels;
-    int64_t total_pixels;           // render segments of the batch
+    int32_t n_kf, n_frames, total_items;
+    int32_t init_waves, render_waves;   // of the batch
+    int32_t pad0;
     int32_t iters;
     float huber_k;
     float kappa_fp64;
     int32_t depth_only;
     float beta_r;
     uint32_t stamp;
-    int32_t do_init, do_gn, do_render, n_queues;
+    int32_t n_queues;
     float lm_lambda;
-    int32_t pad_lm;
     QueueDev queues[kNumCounters];
 };
 
@@ -188,7 +205,8 @@ struct RegridArgs {
     RegridSurfels src, dst;
     double src_K[4], dst_K[4];   // fx, fy, cx, cy
     double R[9], t[3];           // X_dst = R X_src + t
-    int32_t src_w, src_h, src_patch, dst_w, dst_h, dst_patch;
+    int32_t src_gw, src_shift, dst_gw, dst_gh, dst_shift;    // grids; log2 of the tile edges
+    FastDiv div_src, div_dst;      // by src_gw and dst_gw
     unsigned long long* best;    // closest landing per destination tile (bits of 1/p'_z)
     int32_t* win;                // winning source index per destination tile
     uint8_t* is_new;
@@ -208,8 +226,8 @@ struct RegridArgs {
 // memory), and the work-queue counters cleared.
 hipError_t launch_stage(const void* host, void* dev, int n16, const FrameIn* in, FrameDev* frames, int n_frames,
                         uint32_t* counters, hipStream_t s);
-hipError_t launch_init(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s);
-hipError_t launch_render(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s);
+hipError_t launch_init(const LoneKf& one, const BatchHeader* hdr, int waves, hipStream_t s);
+hipError_t launch_render(const LoneKf& one, const BatchHeader* hdr, int waves, hipStream_t s);
 // The kernel's own start and end go to the two events.
 hipError_t launch_gn(const GnVariant& v, const LoneBatch& one, const BatchHeader* hdr, uint32_t* counters,
                      int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop);
@@ -222,8 +240,12 @@ hipError_t static_scratch_on(int device, void** out);
 // wavefronts from src_wave on (surfel i at lane i % 64 of wavefront
 // src_wave + i / 64), likewise its tiles from dst_wave; src_waves and
 // dst_waves are the totals.
-hipError_t launch_regrid(const RegridArgs& one, const RegridArgs* table, int n_pairs, int src_waves,
-                         int dst_waves, hipStream_t s);
+// The first launch also copies the table (table_bytes from pinned host memory;
+// 0 for one pair) and clears the scratch of n_tiles destination tiles (best
+// and win, both padded to 16 bytes); `uploaded` (or null) is recorded after it.
+hipError_t launch_regrid(const RegridArgs& one, const void* host, RegridArgs* table, size_t table_bytes,
+                         int n_pairs, int src_waves, int dst_waves, void* best, void* win, int n_tiles,
+                         hipStream_t s, hipEvent_t uploaded);
 
 // Disc surfels (Eq. 4).
 constexpr float kDiscMaxRadius = 12.f;

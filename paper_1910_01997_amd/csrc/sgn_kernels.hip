@@ -230,6 +230,23 @@ __device__ __forceinline__ BatchView batch_view(const BatchHeader* hdr) {
     return {&a->one.hdr, &a->one.kf, a->frames};
 }
 
+__device__ __forceinline__ int divide(int n, const carg<FastDiv>& d) {
+    return (int)(__umulhi((unsigned)n << 8, d.m) >> d.l);
+}
+
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The wavefront's number among the grid's (four wavefronts per workgroup),
+// uniform for the compiler, and the grid's count of wavefronts.
+__device__ __forceinline__ int grid_wave() {
+    return __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+}
+__device__ __forceinline__ int grid_waves() { return (int)gridDim.x * 4; }
+
 // ------------------------------------------------------------- init kernel --
 
 // Surfel Initialization section.  Neighbours of new surfel s: surfels that
@@ -237,29 +254,46 @@ __device__ __forceinline__ BatchView batch_view(const BatchHeader* hdr) {
 // id_s = mean of Eq. 3 of each neighbour's plane at r_s; new n_s = mean of
 // the sign-aligned neighbour normals, renormalised.  Neighbours are visited
 // in index order.
-__global__ void init_kernel(LoneKf, const BatchHeader* __restrict__ hdr_) {
+//
+// A wavefront never spans two keyframes, so the descriptor comes through
+// scalar loads (a thread that looked its keyframe up by itself read it with
+// chains of vector loads).  Bound by latency: of a new surfel's neighbours
+// the is_new bytes come first, then the states of those that count, all in
+// flight together.  64 mixed keyframes, half of 1.67 million surfels new:
+// 55 us before, 36 now.
+__global__ __launch_bounds__(256) void init_kernel(LoneKf, const BatchHeader* __restrict__ hdr_) {
     const BatchView view = batch_view(hdr_);
     const cptr<BatchHeader> hdr = view.hdr;
     const cptr<KfDev> kfs = view.kfs;
-    const int total = hdr->total_surfels;
-    int hint = 0;
-    for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < total; s += gridDim.x * blockDim.x) {
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    __shared__ int s_new_[256 / kWaveSize][kInitSurfels];
+    int* const s_new = s_new_[threadIdx.x >> 6];
+    for (int wv = grid_wave(); wv < hdr->init_waves; wv += grid_waves()) {
+        // (keyframes without new surfels take no wavefront)
         int lo = 0, hi = hdr->n_kf - 1;
-        if (!(s >= kfs[hint].surfel_base &&
-              s < kfs[hint].surfel_base + kfs[hint].gw * kfs[hint].gh)) {
-            while (lo < hi) {
-                int mid = (lo + hi + 1) >> 1;
-                if (kfs[mid].surfel_base <= s) lo = mid; else hi = mid - 1;
-            }
-            hint = lo;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (kfs[mid].init_wave <= wv) lo = mid; else hi = mid - 1;
         }
-        const carg<KfDev>& K = kfs[hint];
-        if (!K.is_new) continue;
-        const int S = K.patch;
-        const int i = s - K.surfel_base;
-        if (!K.is_new[i]) continue;
+        const carg<KfDev>& K = kfs[lo];
         const int gw = K.gw, gh = K.gh;
-        const int tx = i % gw, ty = i / gw;
+        const int S = K.patch;
+        // the new ones of the wavefront's run of surfels, in order
+        int n_new = 0;
+        wave_sync();                                       // the previous run's list is read
+#pragma unroll
+        for (int h = 0; h < kInitSurfels / kWaveSize; ++h) {
+            const int k = (wv - K.init_wave) * kInitSurfels + h * kWaveSize + lane;
+            const bool fresh = k < gw * gh && K.is_new[min(k, gw * gh - 1)] != 0;
+            const unsigned long long ball = __ballot(fresh);
+            if (fresh) s_new[n_new + __popcll(ball & ((1ull << lane) - 1ull))] = k;
+            n_new += __popcll(ball);
+        }
+        wave_sync();
+        for (int k0 = 0; k0 < n_new; k0 += kWaveSize) {
+        if (k0 + lane >= n_new) continue;
+        const int i = s_new[k0 + lane];
+        const int ty = divide(i, K.div_gw), tx = i - ty * gw;
         const float half = 0.5f * (float)(S - 1);
         const float ux = (float)(S * tx) + half, uy = (float)(S * ty) + half;
         const float rsx = (ux - K.cx) / K.fx, rsy = (uy - K.cy) / K.fy;
@@ -309,8 +343,12 @@ __global__ void init_kernel(LoneKf, const BatchHeader* __restrict__ hdr_) {
             uint32_t fl[9];
             float idj[9], njx[9], njy[9], njz[9];
 #pragma unroll
+            for (int k = 0; k < 9; ++k) nw[k] = k == 4 ? 1 : K.is_new[js[k]];
+#pragma unroll
+            for (int k = 0; k < 9; ++k) in[k] = in[k] && !nw[k];
+#pragma unroll
             for (int k = 0; k < 9; ++k) {
-                nw[k] = K.is_new[js[k]];
+                if (!in[k]) continue;
                 fl[k] = K.flags[js[k]];
                 idj[k] = K.inv_depth[js[k]];
                 njx[k] = K.nx[js[k]];
@@ -349,6 +387,7 @@ __global__ void init_kernel(LoneKf, const BatchHeader* __restrict__ hdr_) {
         K.ny[i] = sy * il;
         K.nz[i] = sz * il;
         K.flags[i] &= ~F_UNINIT;
+        }
     }
 }
 
@@ -430,12 +469,6 @@ __device__ __forceinline__ void stage_pair_words(cptr<FrameDev> frames, int nf, 
         w[W_Y0] = __int_as_float((int)Y0);
         w[W_HZ1] = (float)hm[7];     // h7 again, beside the words the pixel step reads
     }
-}
-
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // The four bilinear taps (x0, y0), (x0+1, y0), (x0, y0+1), (x0+1, y0+1) of
@@ -1551,125 +1584,96 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
 
 // Inverse Depth Calculation section: each pixel takes Eq. 3 of its surfel,
 // id_u = id_s (1 + sigma), sigma = n . (r_u - r_s) / (n . r_s).  A thread
-// renders one segment: the up-to-S pixels of one image row that lie in one
-// tile column (segments past the grid write "no measurement"), so a surfel's
-// state is read once per segment.  Segments are numbered keyframe after
-// keyframe (only keyframes with an output).  A block takes runs of 256
-// consecutive segments: its first thread finds the run's keyframe, and only
-// threads whose segment lies past that keyframe search for their own.
-
-// The keyframe owning segment g: the last one whose base is <= g (keyframes
-// without an output add no segments, so the next base is larger than g only
-// past the owner).
-__device__ __forceinline__ int render_owner(cptr<KfDev> kfs, int n_kf, int64_t g) {
-    int lo = 0, hi = n_kf - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (kfs[mid].pixel_base <= g) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
+// renders a block of 4 x 4 pixels, which lies in one tile (blocks past the
+// grid write "no measurement"): the surfel's state is read once for four
+// 16-byte row stores.  A wavefront takes 64 blocks of one keyframe, a row of
+// them after the other, and reads the keyframe through scalar loads.
+//
+// Bound: the writes.  64 mixed keyframes (26.8 million pixels, 107 MB):
+// 72 us with one row segment per thread, each workgroup searching its
+// keyframe first and each thread reading the descriptor through vector
+// loads; 31 us now, a copy's rate 21.
 __global__ __launch_bounds__(256) void render_kernel(LoneKf, const BatchHeader* __restrict__ hdr_) {
+#pragma clang fp contract(off)
     const BatchView view = batch_view(hdr_);
     const cptr<BatchHeader> hdr = view.hdr;
     const cptr<KfDev> kfs = view.kfs;
-    const int n_kf = hdr->n_kf;
-    const int64_t total = hdr->total_pixels;           // render segments
-    __shared__ int s_kf;
-    // the loop bounds are the same for every thread of a block
-    for (int64_t g0 = (int64_t)blockIdx.x * blockDim.x; g0 < total; g0 += (int64_t)gridDim.x * blockDim.x) {
-        __syncthreads();                                // the previous run's s_kf is read
-        if (threadIdx.x == 0) s_kf = render_owner(kfs, n_kf, g0);
-        __syncthreads();
-        const int64_t g = g0 + threadIdx.x;
-        if (g >= total) continue;
-        int kidx = s_kf;
-        {
-            const cptr<KfDev> kh = kfs + kidx;
-            const int64_t nseg = (int64_t)kh->height * ((kh->width + kh->patch - 1) / kh->patch);
-            if (!(kh->inv_depth_out && g >= kh->pixel_base && g < kh->pixel_base + nseg))
-                kidx = render_owner(kfs, n_kf, g);
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    for (int wv = grid_wave(); wv < hdr->render_waves; wv += grid_waves()) {
+        // (keyframes without an output take no wavefront)
+        int lo = 0, hi = hdr->n_kf - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (kfs[mid].render_wave <= wv) lo = mid; else hi = mid - 1;
         }
-        const cptr<KfDev> K = kfs + kidx;
-        const int W = K->width, S = K->patch;
-        const int nsx = (W + S - 1) / S;
-        const int sg = (int)(g - K->pixel_base);
-        const int y = sg / nsx, tx = sg - y * nsx;
-        const int x0 = tx * S, ty = y >> __builtin_ctz(S);    // S is 4, 8 or 16
+        const carg<KfDev>& K = kfs[lo];
+        const int W = K.width, H = K.height, S = K.patch;
+        const int nbx = (W + 3) / 4, nby = (H + 3) / 4;
+        const int blk = (wv - K.render_wave) * kWaveSize + lane;
+        if (blk >= nbx * nby) continue;
+        const int by = divide(blk, K.div_bx), bx = blk - by * nbx;
+        const int x0 = 4 * bx, y0 = 4 * by;
+        const int sh = __builtin_ctz(S);                  // S is 4, 8 or 16
+        const int tx = x0 >> sh, ty = y0 >> sh;
         const float half = 0.5f * (float)(S - 1);
-        float* const out = K->inv_depth_out + (size_t)y * W + x0;
-        int32_t* const idx_out = K->index_out ? K->index_out + (size_t)y * W + x0 : nullptr;
+        const float ifx = 1.f / K.fx, ify = 1.f / K.fy;
         bool ok = false;
         int i = -1;
-        // three divisions per segment; the pixels multiply by the reciprocals
-        const float ifx = 1.f / K->fx, ify = 1.f / K->fy;
         float id = 0.f, nx = 0.f, ny = 0.f, inv_c = 1.f, usx = 0.f, usy = 0.f;
-        if (tx < K->gw && ty < K->gh) {
-            i = ty * K->gw + tx;
+        if (tx < K.gw && ty < K.gh) {
+            i = ty * K.gw + tx;
             // the state is loaded with the flags (one round trip, not two);
             // a flagged surfel's values are not used
-            const uint32_t fl = K->flags[i];
-            const float snx = K->nx[i], sny = K->ny[i], snz = K->nz[i], sid = K->inv_depth[i];
+            const uint32_t fl = K.flags[i];
+            const float snx = K.nx[i], sny = K.ny[i], snz = K.nz[i], sid = K.inv_depth[i];
             // (kept in front of the flag test, where the compiler would sink them)
             __asm__ volatile("" ::"v"(snx), "v"(sny), "v"(snz), "v"(sid));
             if (!(fl & (F_DEGENERATE | F_UNINIT))) {
                 usx = (float)(S * tx) + half;
                 usy = (float)(S * ty) + half;
-                const float rsx = (usx - K->cx) * ifx, rsy = (usy - K->cy) * ify;
+                const float rsx = (usx - K.cx) * ifx, rsy = (usy - K.cy) * ify;
                 nx = snx;
                 ny = sny;
-                const float c = nx * rsx + ny * rsy + snz;
+                const float c = fmaf(nx, rsx, ny * rsy) + snz;
                 id = sid;
                 ok = fabsf(c) >= 1e-6f;
                 inv_c = 1.f / c;
             }
         }
-        const float dry = ((float)y - usy) * ify;
-        const int n_px = min(S, W - x0);
-        // Eq. 3 at pixel x0 + j of the segment
-        auto pixel = [&](int j, float& val, int& who) {
-            val = 0.f;
-            who = -1;
-            if (ok) {
-                const float drx = ((float)(x0 + j) - usx) * ifx;
-                const float sigma = (nx * drx + ny * dry) * inv_c;
-                const float idu = fmaf(id, sigma, id);
-                if (idu > 0.f && isfinite(idu)) {
-                    val = idu;
-                    who = i;
-                }
-            }
-        };
-        if (S == 4) {
+        float drx[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) drx[j] = ((float)(x0 + j) - usx) * ifx;
+        float* const out = K.inv_depth_out;
+        int32_t* const idx_out = K.index_out;
+        // whole aligned rows of four in one store: the same for every block
+        // of the keyframe
+        const bool rows4 = (W & 3) == 0 && ((uintptr_t)out & 15u) == 0 && ((uintptr_t)idx_out & 15u) == 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int y = y0 + r;
+            if (y >= H) break;
+            const float ndy = ny * (((float)y - usy) * ify);
             float v[4];
             int w[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) pixel(j, v[j], w[j]);
-            // a whole 16-byte aligned segment in one store, else pixel by pixel
-            if (n_px == 4 && ((uintptr_t)out & 15u) == 0) {
-                *(float4*)out = make_float4(v[0], v[1], v[2], v[3]);
+            for (int j = 0; j < 4; ++j) {
+                const float sigma = fmaf(nx, drx[j], ndy) * inv_c;
+                const float idu = fmaf(id, sigma, id);
+                const bool hit = ok && idu > 0.f && isfinite(idu);
+                v[j] = hit ? idu : 0.f;
+                w[j] = hit ? i : -1;
+            }
+            const size_t o = (size_t)y * W + x0;
+            if (rows4) {
+                *(float4*)(out + o) = make_float4(v[0], v[1], v[2], v[3]);
+                if (idx_out) *(int4*)(idx_out + o) = make_int4(w[0], w[1], w[2], w[3]);
             } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (j < n_px) out[j] = v[j];
-            }
-            if (idx_out) {
-                if (n_px == 4 && ((uintptr_t)idx_out & 15u) == 0) {
-                    *(int4*)idx_out = make_int4(w[0], w[1], w[2], w[3]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (j < n_px) idx_out[j] = w[j];
+                for (int j = 0; j < 4; ++j) {
+                    if (x0 + j >= W) continue;
+                    out[o + j] = v[j];
+                    if (idx_out) idx_out[o + j] = w[j];
                 }
-            }
-        } else {
-            for (int j = 0; j < n_px; ++j) {
-                float v;
-                int w;
-                pixel(j, v, w);
-                out[j] = v;
-                if (idx_out) idx_out[j] = w;
             }
         }
     }
@@ -1686,31 +1690,45 @@ struct Land {
     int tile;
 };
 
+// (NORMAL: with the moved normal, which the landing does not depend on.)
+template <bool NORMAL>
 __device__ __forceinline__ bool regrid_land(const carg<RegridArgs>& a, int i, Land& L) {
 #pragma clang fp contract(off)
-    const int S0 = a.src_patch, gw0 = a.src_w / S0;
-    if (a.src.flags[i] & (F_DEGENERATE | F_UNINIT)) return false;
-    const double id = (double)a.src.inv_depth[i];
+    const int S0 = 1 << a.src_shift;
+    const int ty = divide(i, a.div_src), tx = i - ty * a.src_gw;
+    // every load before the first test: one round trip instead of three
+    const uint32_t fl = a.src.flags[i];
+    const float fid = a.src.inv_depth[i];
+    float fn0 = 0.f, fn1 = 0.f, fn2 = 0.f;
+    if constexpr (NORMAL) {
+        fn0 = a.src.nx[i]; fn1 = a.src.ny[i]; fn2 = a.src.nz[i];
+        __asm__ volatile("" ::"v"(fn0), "v"(fn1), "v"(fn2));
+    }
+    __asm__ volatile("" ::"v"(fl), "v"(fid));
+    if (fl & (F_DEGENERATE | F_UNINIT)) return false;
+    const double id = (double)fid;
     if (!(id > 0.0) || !isfinite(id)) return false;
-    const double usx = S0 * (i % gw0) + 0.5 * (S0 - 1), usy = S0 * (i / gw0) + 0.5 * (S0 - 1);
+    const double usx = S0 * tx + 0.5 * (S0 - 1), usy = S0 * ty + 0.5 * (S0 - 1);
     const double rs0 = (usx - a.src_K[2]) / a.src_K[0], rs1 = (usy - a.src_K[3]) / a.src_K[1];
     const double p00 = rs0 / id, p01 = rs1 / id, p02 = 1.0 / id;          // Eq. 1
-    const double n0 = a.src.nx[i], n1 = a.src.ny[i], n2 = a.src.nz[i];
+    const double n0 = fn0, n1 = fn1, n2 = fn2;
     const cptr<double> R = a.R;
     const double p10 = R[0] * p00 + R[1] * p01 + R[2] * p02 + a.t[0];
     const double p11 = R[3] * p00 + R[4] * p01 + R[5] * p02 + a.t[1];
     const double p12 = R[6] * p00 + R[7] * p01 + R[8] * p02 + a.t[2];
-    L.np0 = R[0] * n0 + R[1] * n1 + R[2] * n2;
-    L.np1 = R[3] * n0 + R[4] * n1 + R[5] * n2;
-    L.np2 = R[6] * n0 + R[7] * n1 + R[8] * n2;
+    if constexpr (NORMAL) {
+        L.np0 = R[0] * n0 + R[1] * n1 + R[2] * n2;
+        L.np1 = R[3] * n0 + R[4] * n1 + R[5] * n2;
+        L.np2 = R[6] * n0 + R[7] * n1 + R[8] * n2;
+    }
     if (!(p12 > 0.0)) return false;
     L.rp0 = p10 / p12;
     L.rp1 = p11 / p12;
     const double ux = a.dst_K[0] * L.rp0 + a.dst_K[2], uy = a.dst_K[1] * L.rp1 + a.dst_K[3];
     const double px = floor(ux + 0.5), py = floor(uy + 0.5);          // nearest pixel
-    const int S1 = a.dst_patch, gw1 = a.dst_w / S1, gh1 = a.dst_h / S1;
-    if (!(px >= 0.0 && px < (double)(gw1 * S1) && py >= 0.0 && py < (double)(gh1 * S1))) return false;
-    L.tile = ((int)py / S1) * gw1 + (int)px / S1;
+    const int sh = a.dst_shift;
+    if (!(px >= 0.0 && px < (double)(a.dst_gw << sh) && py >= 0.0 && py < (double)(a.dst_gh << sh))) return false;
+    L.tile = ((int)py >> sh) * a.dst_gw + ((int)px >> sh);
     L.idp = 1.0 / p12;
     return true;
 }
@@ -1730,25 +1748,22 @@ __device__ __forceinline__ int regrid_entry_of_wave(cptr<RegridArgs> tab, int n,
     return lo;
 }
 
-// The wavefront's number among the grid's (four wavefronts per workgroup),
-// uniform for the compiler, and the grid's count of wavefronts.
-__device__ __forceinline__ int grid_wave() {
-    return __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-}
-__device__ __forceinline__ int grid_waves() { return (int)gridDim.x * 4; }
-
-__global__ __launch_bounds__(256) void regrid_clear_kernel(RegridArgs, const RegridArgs* __restrict__ tab_, int n_pairs,
-                                                           int dst_waves) {
-    const cptr<RegridArgs> tab = table_or_arg(tab_);
-    const int lane = threadIdx.x & 63;
-    for (int wv = grid_wave(); wv < dst_waves; wv += grid_waves()) {
-        const carg<RegridArgs>& a = tab[regrid_entry_of_wave<true>(tab, n_pairs, wv)];
-        const int j = (wv - a.dst_wave) * 64 + lane;
-        if (j < a.dst_count) {
-            a.best[j] = 0ull;
-            a.win[j] = 0x7fffffff;
-        }
+// Clears the landing keys and winners of all the batch's tiles (n_tiles of
+// each) and brings the table up, in one launch: workgroups past the table's
+// words fill, 16 bytes per thread and store.
+__global__ __launch_bounds__(256) void regrid_clear_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst,
+                                                           int n16, uint4* __restrict__ best, int nb16,
+                                                           uint4* __restrict__ win, int nw16) {
+    const int copy_blocks = (n16 + 255) / 256;
+    if ((int)blockIdx.x < copy_blocks) {
+        const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+        if (i < n16) dst[i] = src[i];
+        return;
     }
+    const int step = (int)(gridDim.x - copy_blocks) * 256;
+    const int i0 = (int)((blockIdx.x - copy_blocks) * 256 + threadIdx.x);
+    for (int i = i0; i < nb16; i += step) best[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = i0; i < nw16; i += step) win[i] = make_uint4(0x7fffffffu, 0x7fffffffu, 0x7fffffffu, 0x7fffffffu);
 }
 
 // pass 0: closest landing per tile (1/p'_z > 0, so its bits order like the
@@ -1761,7 +1776,7 @@ __global__ __launch_bounds__(256) void regrid_scatter_kernel(RegridArgs, const R
         const carg<RegridArgs>& a = tab[regrid_entry_of_wave<false>(tab, n_pairs, wv)];
         const int i = (wv - a.src_wave) * 64 + lane;
         Land L;
-        if (i >= a.src_count || !regrid_land(a, i, L)) continue;
+        if (i >= a.src_count || !regrid_land<false>(a, i, L)) continue;
         const unsigned long long bits = (unsigned long long)__double_as_longlong(L.idp);
         if (pass == 0)
             atomicMax(&a.best[L.tile], bits);
@@ -1779,14 +1794,17 @@ __global__ __launch_bounds__(256) void regrid_gather_kernel(RegridArgs, const Re
         const carg<RegridArgs>& a = tab[regrid_entry_of_wave<true>(tab, n_pairs, wv)];
         const int j = (wv - a.dst_wave) * 64 + lane;
         if (j >= a.dst_count) continue;
-        const int S1 = a.dst_patch, gw1 = a.dst_w / S1;
+        const int S1 = 1 << a.dst_shift;
+        const int ty = divide(j, a.div_dst), tx = j - ty * a.dst_gw;
         const int w = a.win[j];
+        // (loaded with the winner's state, not after it)
+        const uint32_t stamp = w != 0x7fffffff ? a.src.last_update[w] : 0u;
         bool ok = false;
         double idt = 0.0, t0 = 0.0, t1 = 0.0, t2 = -1.0;
         Land L;
-        if (w != 0x7fffffff && regrid_land(a, w, L)) {
-            const double rt0 = (S1 * (j % gw1) + 0.5 * (S1 - 1) - a.dst_K[2]) / a.dst_K[0];
-            const double rt1 = (S1 * (j / gw1) + 0.5 * (S1 - 1) - a.dst_K[3]) / a.dst_K[1];
+        if (w != 0x7fffffff && regrid_land<true>(a, w, L)) {
+            const double rt0 = (S1 * tx + 0.5 * (S1 - 1) - a.dst_K[2]) / a.dst_K[0];
+            const double rt1 = (S1 * ty + 0.5 * (S1 - 1) - a.dst_K[3]) / a.dst_K[1];
             const double c1 = L.np0 * L.rp0 + L.np1 * L.rp1 + L.np2 * 1.0;
             const double ct = L.np0 * rt0 + L.np1 * rt1 + L.np2 * 1.0;
             if (fabs(c1) >= 1e-6 && fabs(ct) >= 1e-6) {
@@ -1805,18 +1823,27 @@ __global__ __launch_bounds__(256) void regrid_gather_kernel(RegridArgs, const Re
         a.dst.flags[j] = ok ? 0u : F_UNINIT;
         a.dst.cost[j] = 0.f;
         a.dst.nvalid[j] = 0u;
-        a.dst.last_update[j] = ok ? a.src.last_update[w] : 0u;
+        a.dst.last_update[j] = ok ? stamp : 0u;
         a.is_new[j] = ok ? 0 : 1;
         if (a.src_index) a.src_index[j] = ok ? w : -1;
     }
 }
 
-hipError_t launch_regrid(const RegridArgs& one, const RegridArgs* table, int n_pairs, int src_waves,
-                         int dst_waves, hipStream_t s) {
+hipError_t launch_regrid(const RegridArgs& one, const void* host, RegridArgs* table, size_t table_bytes,
+                         int n_pairs, int src_waves, int dst_waves, void* best, void* win, int n_tiles,
+                         hipStream_t s, hipEvent_t uploaded) {
     // four wavefronts per workgroup
     auto blocks = [](int waves) { return std::max(1, std::min(65536, (waves + 3) / 4)); };
-    hipLaunchKernelGGL(regrid_clear_kernel, dim3(blocks(dst_waves)), dim3(256), 0, s, one, table, n_pairs,
-                       dst_waves);
+    const int n16 = (int)((table_bytes + 15) / 16);
+    // (the scratch arrays are padded to 256 bytes)
+    const int nb16 = (int)(((size_t)n_tiles * 8 + 15) / 16), nw16 = (int)(((size_t)n_tiles * 4 + 15) / 16);
+    const int fill = std::max(1, std::min(4096, (nb16 + 255) / 256));
+    hipLaunchKernelGGL(regrid_clear_kernel, dim3((n16 + 255) / 256 + fill), dim3(256), 0, s, (const uint4*)host,
+                       (uint4*)table, n16, (uint4*)best, nb16, (uint4*)win, nw16);
+    if (uploaded) {
+        const hipError_t e = hipEventRecord(uploaded, s);
+        if (e != hipSuccess) return e;
+    }
     if (src_waves > 0) {
         hipLaunchKernelGGL(regrid_scatter_kernel, dim3(blocks(src_waves)), dim3(256), 0, s, one, table, n_pairs,
                            src_waves, 0);
@@ -1914,13 +1941,16 @@ hipError_t launch_stage(const void* host, void* dev, int n16, const FrameIn* in,
     return hipGetLastError();
 }
 
-hipError_t launch_init(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(init_kernel, dim3(grid), dim3(256), 0, s, one, hdr);
+// Workgroups of four wavefronts (the kernels stride over any that are left).
+static dim3 wave_grid(int waves) { return dim3(std::max(1, std::min(1 << 20, (waves + 3) / 4))); }
+
+hipError_t launch_init(const LoneKf& one, const BatchHeader* hdr, int waves, hipStream_t s) {
+    hipLaunchKernelGGL(init_kernel, wave_grid(waves), dim3(256), 0, s, one, hdr);
     return hipGetLastError();
 }
 
-hipError_t launch_render(const LoneKf& one, const BatchHeader* hdr, int grid, hipStream_t s) {
-    hipLaunchKernelGGL(render_kernel, dim3(grid), dim3(256), 0, s, one, hdr);
+hipError_t launch_render(const LoneKf& one, const BatchHeader* hdr, int waves, hipStream_t s) {
+    hipLaunchKernelGGL(render_kernel, wave_grid(waves), dim3(256), 0, s, one, hdr);
     return hipGetLastError();
 }
 

@@ -1,0 +1,104 @@
+"""Sizes at which the image-storage, initialisation and render kernels change
+what they do: rows with and without 16-byte alignment, runs of surfels that
+are all, partly or not new, blocks of pixels cut by the image border."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from tests.helpers import random_unit_cap
+from tests.parity import oracle_keyframe, oracle_state
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1910_01997_amd import surfgn as sg
+    c = sg.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "u8"])
+@pytest.mark.parametrize("W,H,src_pitch,dst_pitch,src_off,dst_off", [
+    (1, 1, 1, 1, 0, 0), (7, 3, 7, 7, 0, 0), (8, 5, 8, 8, 0, 0), (9, 4, 12, 16, 0, 0), (512, 3, 512, 512, 0, 0),
+    (520, 2, 520, 520, 0, 0), (513, 7, 516, 520, 0, 0), (64, 9, 64, 64, 1, 0), (64, 9, 64, 64, 0, 4),
+    (64, 9, 66, 64, 0, 0), (64, 9, 64, 68, 0, 0)])
+def test_quantize_rows_and_alignments(ctx, dtype, W, H, src_pitch, dst_pitch, src_off, dst_off):
+    from paper_1910_01997_amd import surfgn as sg
+    gen = torch.Generator().manual_seed(W * H + src_pitch)
+    src = torch.rand(H * src_pitch + src_off, generator=gen) * 1.4 - 0.2
+    src[src_off + (H * src_pitch) // 2] = float("nan") if dtype == "u8" else 3e-6
+    dev = src.cuda()
+    tdt = torch.float16 if dtype == "f16" else torch.uint8
+    out = torch.full((H * dst_pitch + dst_off,), 77, dtype=tdt, device="cuda")
+    scale = 1.0 if dtype == "f16" else 1.0 / 255.0
+    print(f"case quantize {dtype} {W}x{H} pitches {src_pitch} {dst_pitch} offsets {src_off} {dst_off}", flush=True)
+    sg.sgn_quantize(ctx.handle, dev.data_ptr() + 4 * src_off, src_pitch,
+                    sg.sgn_image(out.data_ptr() + dst_off * out.element_size(), W, H, dst_pitch,
+                                 sg.SGN_F16 if dtype == "f16" else sg.SGN_U8, scale))
+    torch.cuda.synchronize()
+    x = src[src_off:].view(H, src_pitch)[:, :W]
+    if dtype == "f16":
+        want = x.half()
+    else:
+        want = torch.nan_to_num(torch.round(x / torch.tensor(scale, dtype=torch.float32)), 0.0).clamp(0, 255).to(tdt)
+    got = out.cpu()
+    body = got[dst_off:].view(H, dst_pitch)
+    assert torch.equal(body[:, :W], want)
+    assert (body[:, W:] == 77).all() and (got[:dst_off] == 77).all()       # nothing beside the image
+
+
+def _keyframe(ctx, rng, W, H, S, new):
+    from paper_1910_01997_amd import engine
+    m = (W // S) * (H // S)
+    ids = rng.uniform(0.3, 1.5, m).astype(np.float32)
+    ns = np.array([random_unit_cap(rng, 45) for _ in range(m)], np.float32)
+    flags = np.where(rng.random(m) < 0.1, oracle.UNINIT, 0).astype(np.uint32)
+    img = torch.zeros((H, W), dtype=torch.float32)
+    K = (0.9 * W, 0.95 * W, W / 2 + 0.3, H / 2 - 0.2)
+    return engine.DeviceKeyframe(ctx, img, img[None], np.eye(3)[None], np.zeros((1, 3)), K, S, ids, ns,
+                                 is_new=new(rng, m), index_map=True, flags=flags), ids, ns, flags
+
+
+@pytest.mark.parametrize("sizes", [
+    [(4, 4, 4)], [(260, 132, 4)], [(257, 131, 4)], [(33, 47, 8), (130, 66, 8), (64, 64, 8)], [(50, 37, 16)],
+    [(66, 40, 4), (129, 33, 4), (512, 4, 4)]])
+@pytest.mark.parametrize("pattern", ["none", "all", "one", "half", "random"])
+def test_init_and_render_match_the_oracle(ctx, sizes, pattern):
+    from paper_1910_01997_amd import surfgn as sg
+
+    def new(rng, m):
+        a = {"none": np.zeros(m), "all": np.ones(m), "one": np.arange(m) == m // 2, "half": np.arange(m) % 2,
+             "random": rng.random(m) < 0.7}[pattern]
+        return a.astype(np.uint8)
+    rng = np.random.default_rng(len(sizes) * 7 + len(pattern))
+    kfs = [_keyframe(ctx, rng, *s, new) for s in sizes]
+    print(f"case init and render {sizes} {pattern}", flush=True)
+    prm = sg.params(iters=0)
+    sg.sgn_optimize_batch(ctx.handle, sg.batch_array([k[0].item() for k in kfs]), len(kfs), prm)
+    torch.cuda.synchronize()
+    for dk, ids, ns, flags in kfs:
+        okf = oracle_keyframe(dk)
+        st = oracle_state(ids, ns, flags)
+        oracle.init_from_neighbours(okf, st, dk.is_new.cpu().numpy(), oracle.OracleParams(iters=0))
+        h = dk.state.to_host()
+        uninit = (np.asarray(st["flags"]) & oracle.UNINIT) != 0
+        assert np.array_equal((h["flags"] & sg.FLAG_UNINIT) != 0, uninit)
+        # a mean of at most eight float terms of order one: a few ulp of 1e-7
+        assert np.abs(h["inv_depth"] - st["inv_depth"])[~uninit].max(initial=0) < 4e-6
+        on = np.stack([st["nx"], st["ny"], st["nz"]], 1)
+        assert np.abs(h["n"] - on)[~uninit].max(initial=0) < 4e-6
+        # the render of the device's own state
+        st = oracle_state(h["inv_depth"], h["n"], h["flags"])
+        want, index = oracle.render(okf, st)
+        got = dk.inv_depth_out.cpu().numpy()
+        same = dk.index_out.cpu().numpy() == index
+        # Eq. 3 in float: a pixel whose value crosses zero may fall on either side
+        assert same.mean() > 0.999 if same.size > 1000 else same.all()
+        assert (np.abs(got - want) <= 1e-4 * np.maximum(1.0, np.abs(want)))[same].all()
