@@ -476,39 +476,41 @@ int item_blocks(int nq, const QueueDev* queues, int items, int wpb) {
 // The form of a four-pixels-per-lane kernel (the 4x4 layout of 4x4 surfels,
 // 16 x 16 surfels) for the batch's number of work items; every form adds the
 // same terms in the same order, so results do not depend on it.  w = items
-// per SIMD:
+// per SIMD (times: 15 iterations, 6 neighbours, f16 unless another is said):
 //   w <= 0.65  a column's pixels on four lanes, four frames in flight: a lone
 //              wavefront's time is its instructions' latency, and the chip
 //              has room for four times the wavefronts.  61 us against 108 for
-//              the plain form at 300 items (6 neighbours, f16), 82 at 910.
+//              one sample at a time at 300 items, 82 against 109 at 910.
 //   w <= 1.75  on two lanes, two frames: 87 us against 113 at 1,200 items
 //              and 117 at 1,530 (four lanes: 104 and 121).
-//   w <= 3     unsplit, two frames: 100 us against 120 at 1,900, 125 against
-//              144 at 3,072 (two lanes: 103 and 151).
-//   w <= 24, or f32
-//              one frame in flight at five wavefronts per SIMD: 180 us
-//              against 200 at 4,200, 308 against 327 at 8,295, 550 against
-//              545 at 16,950 (whole calls 583 against 624: fewer resident
-//              wavefronts leave a shorter tail); on the 64-keyframe f32 batch
-//              4.25 ms against 4.79.
-//   otherwise  one sample at a time at seven wavefronts per SIMD: f16 batch
-//              4.23 ms against 4.29, u8 4.17 against 4.44.
-// The damped variant sums a candidate's cost along a column's pixels in
-// turn, so it is not split.
+//   beyond     unsplit, the workgroup's solves shared.  One frame's taps in
+//              flight at six wavefronts per SIMD to w = 3, for f32, and for
+//              f16 batches of w > 24; else one sample at a time at eight.
+//              Whole calls, one frame / one sample: 121 / 133 us at 1,900
+//              items, 141 / 147 at 2,700 (two frames without sharing 120 and
+//              147), 272 / 261 at 7,500, 507 / 491 at 16,950; f32 278 / 323 at
+//              8,295; the 64-keyframe batch (104,000 items) f16 3.76 / 3.92 ms,
+//              f32 3.91 / 4.30, u8 3.98 / 3.83.
+// 16 x 16 surfels are not split: two frames in flight to w = 1.75 (97 us
+// against 111 at 1,200 items).  The damped variant sums a candidate's cost
+// along a column's pixels in turn and steps in gn_kernel: two frames in flight
+// to w = 3, one to w = 24 or for f32, else one sample at a time.
 void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_params* prm, GnVariant& v) {
     const bool four_px = v.patch == 16 || (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4);
     if (!four_px || v.persistent) return;
     const int64_t total = count_items(items, n, item_geo(v.patch, v.tiles_x, v.tiles_y, v.groups));
     const double w = (double)total / (4.0 * std::max(1, c->cus));
-    const bool can_split = v.patch == 4 && !(prm->lm_lambda > 0.f);
-    if (can_split && w <= 0.65) {
+    if (prm->lm_lambda > 0.f) {
+        v.deep = w <= 3.0 ? 2 : w <= 24.0 || v.dtype == SGN_F32 ? 1 : 0;
+    } else if (v.patch == 4 && w <= 0.65) {
         v.split = 4; v.deep = 4; v.tiles_x = 2; v.tiles_y = 2;
-    } else if (can_split && w <= 1.75) {
+    } else if (v.patch == 4 && w <= 1.75) {
         v.split = 2; v.deep = 2; v.tiles_x = 4; v.tiles_y = 2;
-    } else if (w <= 3.0) {
+    } else if (w <= 1.75) {
         v.deep = 2;
-    } else if (w <= 24.0 || v.dtype == SGN_F32) {
-        v.deep = 1;
+    } else {
+        v.shared = 1;
+        v.deep = w <= 3.0 || v.dtype == SGN_F32 || (v.dtype == SGN_F16 && w > 24.0);
     }
 }
 
@@ -540,7 +542,7 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     // time at every measured size (300 to 104,000 items).
     plan.persistent = plan.persistent && plan.waves_per_cu > 0;
     GnVariant var{dtype, patch, plan.tiles_x, plan.tiles_y, plan.lds_stage, plan.groups,
-                  (int)rows_by_index(items, n), 0, 1, plan.persistent};
+                  (int)rows_by_index(items, n), 0, 1, plan.persistent, 0};
     if (fl.gn && !gn_variant_supported(var)) return fail(SGN_E_UNSUPPORTED, "plan not supported for this patch");
     if (fl.gn) choose_form(c, items, n, prm, var);
     plan.tiles_x = var.tiles_x;
@@ -1440,7 +1442,7 @@ sgn_status sgn_autotune(sgn_ctx* c, const sgn_batch_item* items, int32_t n, cons
     float dflt_ms = 1e30f;
     for (const sgn_plan& pl : cands) {
         GnVariant v{items[0].kf.kf.dtype, patch, pl.tiles_x, pl.tiles_y, pl.lds_stage, pl.groups,
-                    (int)rows_by_index(items, n), 0, 1, 0};
+                    (int)rows_by_index(items, n), 0, 1, 0, 0};
         if (!gn_variant_supported(v)) continue;
         float tmin = 1e30f;
         bool ok = true;

@@ -166,6 +166,7 @@ struct GnVariant {
     int deep;       // frames whose taps are in flight at once (0: one sample at a time)
     int split;      // lanes per pixel column of the 4x4 layout (1, 2 or 4)
     int persistent; // a grid of fixed size pulling items from device queues
+    int shared;     // a workgroup's wavefronts share their surfels' solves
 };
 // Row pitch (bytes) up to which neighbour images are read through a
 // structured buffer, the row as the index: the descriptor's stride field holds

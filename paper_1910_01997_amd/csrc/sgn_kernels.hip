@@ -1002,7 +1002,7 @@ __device__ __forceinline__ bool lm_accept(float cost2, int nv2, float cost_here,
 //
 // Wavefronts per SIMD each plan's kernel is compiled for (the register
 // budget: 72 VGPRs for seven, 80 for six, 96 for five).  Occupancy pays: on
-// the 64-keyframe f16 batch the 4x4 one-group kernel takes 4.69 ms at four,
+// the 64-keyframe f16 batch, undamped, the 4x4 one-group kernel takes 4.69 ms at four,
 // 4.30 at five, 3.94 at six and 3.76 at seven (its 11-12 spilled words are
 // stored and reloaded once per work item, or in the damped variant's
 // branches); at eight, with spills inside the iteration loop, 4.05 ms.
@@ -1580,6 +1580,280 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     }
 }
 
+// The Gauss-Newton kernel of large grids: gn_kernel without damping, four
+// pixels per lane, one group per wavefront, whose workgroup shares its
+// surfels' solves.  After each iteration's sums one wavefront (another each
+// time) steps the surfels of all four items, a lane each, between two
+// barriers; in gn_kernel every wavefront issues the step with most of its
+// lanes idle.  The arithmetic and the order of every sum are gn_kernel's.
+//
+// Bound: VALU issue.  The step is about 170 of the 1,450 instructions that a
+// wavefront of sixteen 4x4 surfels issues per iteration at seven neighbour
+// frames (more for one 16 x 16 surfel), and three quarters of it goes; with
+// the surfels' state in LDS and no damped branch the rest also takes fewer
+// registers: eight wavefronts per SIMD (64 VGPRs) one sample at a time, six
+// (80) with a frame's taps in flight, where gn_kernel held seven and five.
+// 64 mixed keyframes: f16 4.15 -> 3.77 ms, f32 4.13 -> 3.93, u8 4.12 -> 3.86;
+// 1920x1080 f16 415 -> 391 us.  (At the old seven and five: 4.07, 4.00 and
+// 3.91 ms.  Raising the stepping wavefront's priority gave nothing.)
+template <typename T, int S, int TX, int TY, bool BY_ROW, int DEEP>
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(DEEP ? 6 : 8, 8))) void gn_shared_kernel(
+    LoneBatch, const BatchHeader* __restrict__ hdr_) {
+    constexpr ItemGeo G = item_geo(S, TX, TY, 1);
+    constexpr int PIX = S * S;
+    constexpr int NS = TX * TY;                               // surfels per work item
+    constexpr int LANES = kWaveSize / NS;
+    constexpr int PPL = PIX / LANES;
+    constexpr float DYR = (float)(LANES / S);
+    constexpr int WPB = kBlockThreads / kWaveSize;
+    static_assert(PPL == 4 && WPB * NS <= kWaveSize, "four pixels per lane; a lane per surfel of the workgroup");
+    const BatchView view = batch_view(hdr_);
+    const cptr<BatchHeader> hdr = view.hdr;
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int r = lane / LANES;
+    const int p = lane % LANES;
+    const float half = 0.5f * (float)(S - 1);
+    const int px0 = p % S, py0 = p / S;
+    constexpr int DROW = LANES / S;
+
+    __shared__ float4 s_pairs[WPB][kMaxNbr * kPairWords / 4];
+    __shared__ float4 s_state[WPB * NS * ST_WORDS / 4];
+    __shared__ float4 s_sums[WPB * NS * SM_WORDS / 4];
+    float* const pairs = (float*)s_pairs[wave];
+    float* const lst = (float*)s_state + wave * NS * ST_WORDS;
+    float* const lsm = (float*)s_sums + wave * NS * SM_WORDS;
+
+    const int total = hdr->total_items;
+    const int iters = hdr->iters;
+    const cptr<KfDev> kfs = view.kfs;
+    // the workgroup's first item (see gn_kernel for the XCD shares)
+    int first = (int)blockIdx.x * WPB, end = total;
+    if (hdr->n_queues == kXcds) {
+        const int share = (int)(blockIdx.x % (unsigned)kXcds);
+        first = hdr->queues[share].begin + (int)(blockIdx.x / (unsigned)kXcds) * WPB;
+        end = hdr->queues[share].end;
+    }
+    if (first >= end) return;                                 // the whole workgroup
+    const int item = first + wave;
+    // a wavefront without an item keeps to the workgroup's barriers
+    int it0x = 0, it0y = 0;
+    bool work = item < end;
+    cptr<KfDev> Kd = kfs;
+    int bx = 0, by = 0;
+    if (work) {
+        Kd = kfs + find_kf(kfs, hdr->n_kf, item, 0);
+        const int blk = item - Kd->item_base;                 // one item per anchor block
+        static_assert(G.ipb == 1, "an item is an anchor block");
+        bx = blk % Kd->groups_x; by = blk / Kd->groups_x;
+        it0x = bx * G.ab; it0y = by * G.ab;
+        work = it0x < Kd->gw && it0y < Kd->gh;
+    }
+    const int gw = Kd->gw, gh = Kd->gh;
+    const int nf = Kd->n_nbr;
+    const float img_scale = Kd->img_scale;
+    const unsigned pitch_b = (unsigned)Kd->nbr_pitch_b;
+    const unsigned wm1 = (unsigned)(Kd->width - 1), hm1 = (unsigned)(Kd->height - 1);
+    const float fxk = Kd->fx, fyk = Kd->fy, cxk = Kd->cx, cyk = Kd->cy;
+    const float drx0 = ((float)px0 - half) / fxk, dry0 = ((float)py0 - half) / fyk;
+    const float dyr_f = DYR / fyk;
+    const int bpx = bx * G.ab * S, bpy = by * G.ab * S;
+    if (work)
+        stage_pair_words(view.frames + Kd->frame_base, nf, lane, (double)bpx + 0.5 * (double)(G.ab * S - 1),
+                         (double)bpy + 0.5 * (double)(G.ab * S - 1), pairs);
+    const uint64_t fr_bits = (uint64_t)(view.frames + Kd->frame_base);
+    const uint32_t fr_lo = __builtin_amdgcn_readfirstlane((uint32_t)fr_bits);
+    const uint32_t fr_hi = __builtin_amdgcn_readfirstlane((uint32_t)(fr_bits >> 32));
+    const cptr<FrameDev> fr = (cptr<FrameDev>)(((uint64_t)fr_hi << 32) | fr_lo);
+    const int tx = it0x + r % TX, ty = it0y + r / TX;
+    float ikf[PPL];
+    const gptr<T> kimg = (gptr<T>)Kd->kf_img;
+#pragma unroll
+    for (int j = 0; j < PPL; ++j) {
+        ikf[j] = 0.f;
+        if (work && tx < gw && ty < gh)
+            ikf[j] = ldg<T>(kimg + ((unsigned)(S * ty + py0 + DROW * j) * (unsigned)Kd->kf_pitch +
+                                    (unsigned)(S * tx + px0))) * Kd->kf_scale;
+    }
+    // this item's surfels, lane k < NS the k-th
+    const int otx = it0x + lane % TX, oty = it0y + lane / TX;
+    const bool own_ok = work && lane < NS && otx < gw && oty < gh;
+    const int sidx = oty * gw + otx;
+    if (lane < NS) {
+        float* o = lst + lane * ST_WORDS;
+        o[ST_ID] = own_ok ? ((gptr<float>)Kd->inv_depth)[sidx] : 0.f;
+        o[ST_NX] = own_ok ? ((gptr<float>)Kd->nx)[sidx] : 0.f;
+        o[ST_NY] = own_ok ? ((gptr<float>)Kd->ny)[sidx] : 0.f;
+        o[ST_NZ] = own_ok ? ((gptr<float>)Kd->nz)[sidx] : -1.f;
+        const float usx = (float)(S * otx) + half, usy = (float)(S * oty) + half;
+        o[ST_RSX] = (usx - cxk) / fxk; o[ST_RSY] = (usy - cyk) / fyk;
+        o[ST_ALIVE] = own_ok ? 1.f : 0.f;
+        o[ST_FLAGS] = __uint_as_float(own_ok ? ((gptr<uint32_t>)Kd->flags)[sidx] & ~F_GN_BITS : 0u);
+        o[ST_LAM] = 0.f;                                      // set once a step is accepted
+        o[ST_COSTO] = 0.f; o[ST_NVO] = __int_as_float(0);
+    }
+    // degeneracy and tangent basis of a surfel's words, before each iteration
+    auto ready = [&](float* o, float nx, float ny, float nz, bool alive, uint32_t flags) {
+        const float c = nx * o[ST_RSX] + ny * o[ST_RSY] + nz;
+        if (alive && fabsf(c) < 1e-6f) {
+            o[ST_FLAGS] = __uint_as_float(flags | F_DEGENERATE);
+            o[ST_ALIVE] = 0.f;
+            o[ST_COSTO] = 0.f;
+            o[ST_NVO] = __int_as_float(0);
+        }
+        float b1x, b1y, b1z, b2x, b2y, b2z;
+        tangent_basis(nx, ny, nz, b1x, b1y, b1z, b2x, b2y, b2z);
+        o[ST_B1X] = b1x; o[ST_B1Y] = b1y; o[ST_B1Z] = b1z;
+        o[ST_B2X] = b2x; o[ST_B2Y] = b2y; o[ST_B2Z] = b2z;
+        o[ST_INVC] = rcp_fast(c);
+    };
+    wave_sync();
+    if (iters > 0 && lane < NS) {
+        float* o = lst + lane * ST_WORDS;
+        ready(o, o[ST_NX], o[ST_NY], o[ST_NZ], o[ST_ALIVE] != 0.f, __float_as_uint(o[ST_FLAGS]));
+    }
+    wave_sync();
+    for (int it = 0; it < iters; ++it) {
+        const bool last = it == iters - 1;
+        if (work) {
+            const float* st = lst + r * ST_WORDS;
+            float ph[9], pnv, pcs;
+            {
+                const float4 sa = *(const float4*)(st + 0);      // id, nx, ny, nz
+                const float sid = sa.x, snx = sa.y, sny = sa.z;
+                const float inv_c = st[ST_INVC];
+                const bool salive = st[ST_ALIVE] != 0.f;
+                bool pix_ok[PPL];
+                const float cnx = snx * inv_c, cny = sny * inv_c;
+                const float sig0 = fmaf(cny, dry0, cnx * drx0);
+                const float dsig = cny * dyr_f;
+                const float idu0 = fmaf(sid, sig0, sid);
+                const float didu = sid * dsig;
+#pragma unroll
+                for (int j = 0; j < PPL; ++j) {
+                    const float sig = j == 0 ? sig0 : fmaf((float)j, dsig, sig0);
+                    pix_ok[j] = salive && (fmaf(sid, sig, sid) > 0.f);
+                }
+                const float bdx = (float)(S * tx + px0 - bpx) - 0.5f * (float)(G.ab * S - 1);
+                const float bdy = (float)(S * ty + py0 - bpy) - 0.5f * (float)(G.ab * S - 1);
+                float A[PPL], B[PPL], cst[PPL];
+                unsigned nvp = 0u;
+#pragma unroll
+                for (int j = 0; j < PPL; ++j) {
+                    A[j] = 0.f; B[j] = 0.f; cst[j] = 0.f;
+                }
+                const float hk = hdr->huber_k;
+                if (last)
+                    frame_loop_px<T, true, PPL, BY_ROW, DEEP, 1>(pairs, fr, nf, bdx, bdy, DYR, idu0, didu, 0, pix_ok,
+                                                                 pitch_b, wm1, hm1, ikf, hk, img_scale, A, B, cst, nvp);
+                else
+                    frame_loop_px<T, false, PPL, BY_ROW, DEEP, 1>(pairs, fr, nf, bdx, bdy, DYR, idu0, didu, 0, pix_ok,
+                                                                  pitch_b, wm1, hm1, ikf, hk, img_scale, A, B, cst, nvp);
+                __asm__ volatile("" ::: "memory");
+                const float4 sa2 = *(const float4*)(st + 0);
+                const float4 sb = *(const float4*)(st + 4);
+                const float4 sc = *(const float4*)(st + 8);
+                const float srsy = st[ST_RSY];
+                const float sb1x = sb.x, sb1y = sb.y, sb1z = sb.z;
+                const float sb2x = sb.w, sb2y = sc.x, sb2z = sc.y, srsx = sc.w;
+                const float pinv_c = sc.z;
+                const float pcnx = sa2.y * pinv_c, pcny = sa2.z * pinv_c;
+                const float psig0 = fmaf(pcny, dry0, pcnx * drx0);
+                const float pdsig = pcny * dyr_f;
+                const float kk = hdr->depth_only != 0 ? 0.f : sa2.x * pinv_c;
+                const float k1x = kk * sb1x, k1y = kk * sb1y, k2x = kk * sb2x, k2y = kk * sb2y;
+                const float q1 = kk * fmaf(sb1x, srsx, fmaf(sb1y, srsy, sb1z));
+                const float q2 = kk * fmaf(sb2x, srsx, fmaf(sb2y, srsy, sb2z));
+                const float g00 = 1.f + psig0;
+                const float g10 = fmaf(-psig0, q1, fmaf(k1y, dry0, k1x * drx0));
+                const float g20 = fmaf(-psig0, q2, fmaf(k2y, dry0, k2x * drx0));
+                const float dg1 = fmaf(-pdsig, q1, k1y * dyr_f);
+                const float dg2 = fmaf(-pdsig, q2, k2y * dyr_f);
+                const float S0 = (A[0] + A[1]) + (A[2] + A[3]);
+                const float S1 = fmaf(3.f, A[3], fmaf(2.f, A[2], A[1]));
+                const float S2 = fmaf(9.f, A[3], fmaf(4.f, A[2], A[1]));
+                const float T0 = (B[0] + B[1]) + (B[2] + B[3]);
+                const float T1 = fmaf(3.f, B[3], fmaf(2.f, B[2], B[1]));
+                const float ga[3] = {g00, g10, g20}, gb[3] = {pdsig, dg1, dg2};
+                float uu[3], vv[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    uu[a] = fmaf(S1, gb[a], S0 * ga[a]);
+                    vv[a] = fmaf(S2, gb[a], S1 * ga[a]);
+                }
+                ph[0] = fmaf(vv[0], gb[0], uu[0] * ga[0]);
+                ph[1] = fmaf(vv[0], gb[1], uu[0] * ga[1]);
+                ph[2] = fmaf(vv[0], gb[2], uu[0] * ga[2]);
+                ph[3] = fmaf(vv[1], gb[1], uu[1] * ga[1]);
+                ph[4] = fmaf(vv[1], gb[2], uu[1] * ga[2]);
+                ph[5] = fmaf(vv[2], gb[2], uu[2] * ga[2]);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) ph[6 + a] = fmaf(T1, gb[a], T0 * ga[a]);
+                pcs = (cst[0] + cst[1]) + (cst[2] + cst[3]);
+                pnv = (float)__builtin_amdgcn_sad_u8(nvp, 0u, 0u);
+            }
+            {
+#pragma clang fp contract(off)
+                const bool odd = (p & 1) != 0;
+                const float s0 = pair_sum<LANES>(ph[0], ph[1], odd);
+                const float s1 = pair_sum<LANES>(ph[2], ph[3], odd);
+                const float s2 = pair_sum<LANES>(ph[4], ph[5], odd);
+                const float s3 = pair_sum<LANES>(ph[6], ph[7], odd);
+                const float s4 = pair_sum<LANES>(ph[8], pnv, odd);
+                float* const o = lsm + r * SM_WORDS;
+                if (LANES == 4 || p < 2) {
+                    const int w = p & 1;
+                    o[w] = s0; o[w + 2] = s1; o[w + 4] = s2; o[w + 6] = s3; o[w + 8] = s4;
+                }
+                if (last) {
+                    const float cs = group_sum<LANES>(pcs);
+                    if (LANES == 4 || p == 0) o[SM_COST] = cs;
+                }
+            }
+        }
+        __syncthreads();
+        if (wave == (int)((blockIdx.x / kXcds + (unsigned)it) % WPB) && lane < WPB * NS) {
+            float* const o = (float*)s_state + lane * ST_WORDS;
+            const float* sm = (const float*)s_sums + lane * SM_WORDS;
+            const float4 w0 = *(const float4*)(o + 0);
+            const float4 w1 = *(const float4*)(o + 4);
+            const float4 w2 = *(const float4*)(o + 8);
+            const float4 w3 = *(const float4*)(o + 12);
+            const float4 w4 = *(const float4*)(o + 16);
+            const bool alive = w3.y != 0.f;
+            if (alive) {
+                uint32_t flags = __float_as_uint(w3.z);
+                float cost_out = w4.x, cost_here = 0.f, id_c = 0.f, nx_c = 0.f, ny_c = 0.f, nz_c = 0.f, lam = 0.f;
+                int nv_out = __float_as_int(w4.y), nv = 0;
+                const float kap = hdr->kappa_fp64;
+                const bool step = owner_step(sm, alive, last, hdr->depth_only != 0, false, kap * kap, lam, w0.x, w0.y,
+                                             w0.z, w0.w, w1.x, w1.y, w1.z, w1.w, w2.x, w2.y, flags, cost_out, nv_out,
+                                             nv, cost_here, id_c, nx_c, ny_c, nz_c);
+                o[ST_FLAGS] = __uint_as_float(flags);
+                o[ST_COSTO] = cost_out; o[ST_NVO] = __int_as_float(nv_out);
+                if (step) {
+                    o[ST_ID] = id_c; o[ST_NX] = nx_c; o[ST_NY] = ny_c; o[ST_NZ] = nz_c;
+                    o[ST_LAM] = 1.f;
+                }
+                if (!last)
+                    ready(o, step ? nx_c : w0.y, step ? ny_c : w0.z, step ? nz_c : w0.w, true, flags);
+            }
+        }
+        __syncthreads();
+    }
+    if (own_ok) {
+        const float* o = lst + lane * ST_WORDS;
+        ((gmut<float>)Kd->inv_depth)[sidx] = o[ST_ID];
+        ((gmut<float>)Kd->nx)[sidx] = o[ST_NX];
+        ((gmut<float>)Kd->ny)[sidx] = o[ST_NY];
+        ((gmut<float>)Kd->nz)[sidx] = o[ST_NZ];
+        ((gmut<uint32_t>)Kd->flags)[sidx] = __float_as_uint(o[ST_FLAGS]);
+        ((gmut<float>)Kd->cost)[sidx] = o[ST_COSTO];
+        ((gmut<uint32_t>)Kd->nvalid)[sidx] = __float_as_uint(o[ST_NVO]);
+        if (o[ST_LAM] != 0.f) ((gmut<uint32_t>)Kd->last_update)[sidx] = hdr->stamp;
+    }
+}
+
 // ----------------------------------------------------------- render kernel --
 
 // Inverse Depth Calculation section: each pixel takes Eq. 3 of its surfel,
@@ -2006,13 +2280,26 @@ static void* gn_pick_deep(const GnVariant& v) {
     return v.deep == 2 ? gn_ptr<T, 4, 4, 4, 1, R, false, 2>() : gn_ptr<T, 4, 4, 4, 1, R, false, 1>();
 }
 
+// the form for large grids
+template <typename T, bool R>
+static void* gn_pick_shared(const GnVariant& v) {
+    if (v.patch == 16)
+        return v.deep ? (void*)&gn_shared_kernel<T, 16, 1, 1, R, 1> : (void*)&gn_shared_kernel<T, 16, 1, 1, R, 0>;
+    return v.deep ? (void*)&gn_shared_kernel<T, 4, 4, 4, R, 1> : (void*)&gn_shared_kernel<T, 4, 4, 4, R, 0>;
+}
+
+template <typename T, bool R>
+static void* gn_pick_form(const GnVariant& v) {
+    if (v.shared) return gn_pick_shared<T, R>(v);
+    return v.deep ? gn_pick_deep<T, R>(v) : gn_pick<T, R, false>(v);
+}
+
 template <typename T>
 static void* gn_pick_rows(const GnVariant& v) {
     // a persistent grid reads rows by offset whatever the pitch (bitwise the
     // same; it exists for plans that take only part of the device)
     if (v.persistent) return gn_pick<T, false, true>(v);
-    if (v.deep) return v.by_row ? gn_pick_deep<T, true>(v) : gn_pick_deep<T, false>(v);
-    return v.by_row ? gn_pick<T, true, false>(v) : gn_pick<T, false, false>(v);
+    return v.by_row ? gn_pick_form<T, true>(v) : gn_pick_form<T, false>(v);
 }
 
 static void* gn_select(const GnVariant& v) {
@@ -2047,7 +2334,7 @@ hipError_t launch_gn(const GnVariant& v, const LoneBatch& one, const BatchHeader
                      int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
     void* f = gn_select(v);
     if (!f) return hipErrorInvalidValue;
-    void* args[] = {(void*)&one, (void*)&hdr, (void*)&counters};
+    void* args[] = {(void*)&one, (void*)&hdr, (void*)&counters};      // (a shared kernel takes the first two)
     return launch_timed(f, grid_blocks, kBlockThreads, args, s, start, stop);
 }
 
