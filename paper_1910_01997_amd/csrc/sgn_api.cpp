@@ -492,22 +492,26 @@ int item_blocks(int nq, const QueueDev* queues, int items, int wpb) {
 //              8,295; the 64-keyframe batch (104,000 items) f16 3.76 / 3.92 ms,
 //              f32 3.91 / 4.30, u8 3.98 / 3.83.
 // 16 x 16 surfels are not split: two frames in flight to w = 1.75 (97 us
-// against 111 at 1,200 items).  The damped variant sums a candidate's cost
-// along a column's pixels in turn and steps in gn_kernel: two frames in flight
-// to w = 3, one to w = 24 or for f32, else one sample at a time.
+// against 111 at 1,200 items).  The damped variant evaluates each candidate
+// besides; its lines, at the same grids: four lanes to w = 0.75 (106 us
+// against 187 for two frames unsplit at 300 items, 122 / 191 at 660), two to
+// 1.75 (130 against four lanes' 139 at 910, 151 / 211 unsplit at 1,200, but
+// 225 / 217 at 1,900); it steps in gn_kernel beyond: two frames in flight to
+// w = 3, one to w = 24 or for f32, else one sample at a time.
 void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_params* prm, GnVariant& v) {
     const bool four_px = v.patch == 16 || (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4);
     if (!four_px || v.persistent) return;
     const int64_t total = count_items(items, n, item_geo(v.patch, v.tiles_x, v.tiles_y, v.groups));
     const double w = (double)total / (4.0 * std::max(1, c->cus));
-    if (prm->lm_lambda > 0.f) {
-        v.deep = w <= 3.0 ? 2 : w <= 24.0 || v.dtype == SGN_F32 ? 1 : 0;
-    } else if (v.patch == 4 && w <= 0.65) {
+    v.damped = prm->lm_lambda > 0.f;
+    if (v.patch == 4 && w <= (v.damped ? 0.75 : 0.65)) {
         v.split = 4; v.deep = 4; v.tiles_x = 2; v.tiles_y = 2;
     } else if (v.patch == 4 && w <= 1.75) {
         v.split = 2; v.deep = 2; v.tiles_x = 4; v.tiles_y = 2;
-    } else if (w <= 1.75) {
+    } else if (w <= (v.damped ? 3.0 : 1.75)) {
         v.deep = 2;
+    } else if (v.damped) {
+        v.deep = w <= 24.0 || v.dtype == SGN_F32;
     } else {
         v.shared = 1;
         v.deep = w <= 3.0 || v.dtype == SGN_F32 || (v.dtype == SGN_F16 && w > 24.0);
@@ -542,7 +546,7 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     // time at every measured size (300 to 104,000 items).
     plan.persistent = plan.persistent && plan.waves_per_cu > 0;
     GnVariant var{dtype, patch, plan.tiles_x, plan.tiles_y, plan.lds_stage, plan.groups,
-                  (int)rows_by_index(items, n), 0, 1, plan.persistent, 0};
+                  (int)rows_by_index(items, n), 0, 1, plan.persistent, 0, 0};
     if (fl.gn && !gn_variant_supported(var)) return fail(SGN_E_UNSUPPORTED, "plan not supported for this patch");
     if (fl.gn) choose_form(c, items, n, prm, var);
     plan.tiles_x = var.tiles_x;
@@ -1442,7 +1446,7 @@ sgn_status sgn_autotune(sgn_ctx* c, const sgn_batch_item* items, int32_t n, cons
     float dflt_ms = 1e30f;
     for (const sgn_plan& pl : cands) {
         GnVariant v{items[0].kf.kf.dtype, patch, pl.tiles_x, pl.tiles_y, pl.lds_stage, pl.groups,
-                    (int)rows_by_index(items, n), 0, 1, 0, 0};
+                    (int)rows_by_index(items, n), 0, 1, 0, 0, 0};
         if (!gn_variant_supported(v)) continue;
         float tmin = 1e30f;
         bool ok = true;

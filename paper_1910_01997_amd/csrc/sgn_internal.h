@@ -167,6 +167,7 @@ struct GnVariant {
     int split;      // lanes per pixel column of the 4x4 layout (1, 2 or 4)
     int persistent; // a grid of fixed size pulling items from device queues
     int shared;     // a workgroup's wavefronts share their surfels' solves
+    int damped;     // Levenberg-Marquardt (read by the split forms)
 };
 // Row pitch (bytes) up to which neighbour images are read through a
 // structured buffer, the row as the index: the descriptor's stride field holds

@@ -977,6 +977,82 @@ __device__ __forceinline__ bool lm_accept(float cost2, int nv2, float cost_here,
     return true;
 }
 
+// The candidate's Huber cost and valid count over a column whose NP * SPLIT
+// pixels are dealt to SPLIT lanes (see frame_loop_px).  The column's cost is
+// one chain of additions, pixel by pixel and frame by frame; each lane forms
+// its pixels' terms with the taps of four frames in flight and leaves them in
+// LDS (terms: the lane's words, 64 apart; a sample that is not valid is a term
+// of zero, which changes no sum), and the lanes then add theirs in turn, the
+// running sum handed from row to row.  The column's cost ends in the lane of
+// the last row.  A lone damped 333 x 251 keyframe of five neighbours: 166 us
+// per call with two frames in flight on unsplit columns, 97 split over four
+// lanes.
+template <typename T, bool BY_ROW, int NP, int SPLIT>
+__device__ __forceinline__ void split_cost(const float* __restrict__ pc, cptr<FrameDev> fr, int nf, float dx,
+                                           const float (&dy)[NP], const float (&idu)[NP], const bool (&pix_ok)[NP],
+                                           unsigned pitch_b, unsigned wm1, unsigned hm1, const float (&ikf)[NP],
+                                           float hk, float img_scale, int row0, float4* terms, float& cst,
+                                           int& nvl) {
+    constexpr bool SCALED = std::is_same<T, uint8_t>::value;
+    constexpr int D = 4, C = kMaxNbr / D;
+    for (int f0 = 0; f0 < nf; f0 += D) {
+        Sample sm[D][NP];
+        TapWords tw[D][NP];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int f = f0 + d;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) sm[d][j].v = false;
+            if (f < nf) {                              // wave-uniform
+                const float4 c0 = *(const float4*)(pc + f * kPairWords);
+                const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
+                const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
+                const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
+                const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    const float nxq = fmaf(c0.x, dx, fmaf(c0.y, dy[j], fmaf(c0.z, idu[j], c0.w)));
+                    const float nyq = fmaf(c1.x, dx, fmaf(c1.y, dy[j], fmaf(c1.z, idu[j], c1.w)));
+                    const float qz = fmaf(h6, dx, fmaf(h7, dy[j], fmaf(k2, idu[j], c2.x)));
+                    Sample& s = sm[d][j];
+                    s = sample_warp<T>(nxq, nyq, qz, c2, pix_ok[j], wm1, hm1);
+                    if (s.v) tw[d][j] = load_words<T, BY_ROW>(rs, s.row, s.col, pitch_b);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            float t[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                t[d] = 0.f;
+                const Sample& s = sm[d][j];
+                if (s.v) {
+                    const Lerp l = lerp_words<T>(tw[d][j], s.col, __builtin_amdgcn_fractf(s.fx));
+                    const float val = fmaf(__builtin_amdgcn_fractf(s.fy), l.bot - l.top, l.top);
+                    const float r = SCALED ? fmaf(val, img_scale, -ikf[j]) : val - ikf[j];
+                    const float ar = fabsf(r);
+                    t[d] = (ar <= hk) ? 0.5f * r * r : hk * (ar - 0.5f * hk);
+                    ++nvl;
+                }
+            }
+            terms[(j * C + f0 / D) * kWaveSize] = make_float4(t[0], t[1], t[2], t[3]);
+        }
+    }
+    {
+#pragma clang fp contract(off)
+#pragma unroll
+        for (int m = 0; m < NP * SPLIT; ++m) {
+            // lane i takes the running sum of lane i -+ 4, the row before
+            if (m > 0) cst = SPLIT == 2 && m % 2 == 0 ? dpp_f<0x104>(cst) : dpp_f<0x114>(cst);
+            for (int c = 0; c < (nf + D - 1) / D; ++c) {
+                const float4 t = terms[((m / SPLIT) * C + c) * kWaveSize];
+                cst += t.x; cst += t.y; cst += t.z; cst += t.w;
+            }
+        }
+    }
+}
+
 // The fused Gauss-Newton kernel.
 //
 // Mapping.  A work item is a block of surfels inside one aligned anchor
@@ -1007,14 +1083,15 @@ __device__ __forceinline__ bool lm_accept(float cost2, int nv2, float cost_here,
 // stored and reloaded once per work item, or in the damped variant's
 // branches); at eight, with spills inside the iteration loop, 4.05 ms.
 // The DEEP forms keep more samples in registers: two frames of four pixels
-// take 144 VGPRs (three wavefronts), one frame 96 (five, 23 spilled words),
-// the SPLIT forms 102.
+// take 125 VGPRs (four wavefronts), one frame 96 (five), the SPLIT forms 92
+// and, damped, up to 129 (the two-lane form's terms leave LDS for three
+// wavefronts anyway).
 template <int S, int K, int DEEP, int SPLIT>
 constexpr int gn_waves() {
     return SPLIT > 1 ? 4 : DEEP == 2 ? 2 : DEEP == 1 ? 5 : K == 1 ? 7 : (S == 8 ? 6 : 5);
 }
 
-template <typename T, int S, int TX, int TY, int K, bool BY_ROW, int DEEP, int SPLIT, bool PERSIST>
+template <typename T, int S, int TX, int TY, int K, bool BY_ROW, int DEEP, int SPLIT, bool PERSIST, bool DAMPED>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(gn_waves<S, K, DEEP, SPLIT>(), 8))) void gn_kernel(LoneBatch,
                                                            const BatchHeader* __restrict__ hdr_,
                                                            uint32_t* __restrict__ counters) {
@@ -1065,7 +1142,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     const bool depth_only = hdr->depth_only != 0;
     const uint32_t stamp = hdr->stamp;
     const float lm0 = hdr->lm_lambda;
-    const bool lm = lm0 > 0.f;
+    const bool lm = DAMPED && lm0 > 0.f;
     const cptr<KfDev> kfs = view.kfs;
 
     __shared__ float4 s_pairs[kBlockThreads / kWaveSize][kMaxNbr * kPairWords / 4];
@@ -1074,6 +1151,9 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     float* const pairs = (float*)s_pairs[wave];
     float* const lst = (float*)s_state[wave];
     float* const lsm = (float*)s_sums[wave];
+    // a split column's candidate costs, frame by frame (split_cost)
+    constexpr int TERMS = DAMPED && SPLIT > 1 ? PPL * kMaxNbr / 4 * kWaveSize : 1;
+    __shared__ float4 s_terms[kBlockThreads / kWaveSize][TERMS];
 
     int q = PERSIST ? (int)(blockIdx.x % (unsigned)kXcds) % hdr->n_queues : 0;
     int q_left = hdr->n_queues;
@@ -1501,7 +1581,7 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                 }
                 // owner_step body end
             }
-            if (SPLIT == 1 && lm) {
+            if (lm) {
                 // Levenberg-Marquardt: the candidate's cost over the pixels,
                 // then the acceptance test (lm_accept)
                 float inv_cc = 0.f;
@@ -1534,8 +1614,24 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                     const float cnx = sa.y * inv_c, cny = sa.z * inv_c;
                     const float sig0 = fmaf(cny, dry0, cnx * drx0);
                     const float dsig = cny * dyr_f;
+                    if constexpr (SPLIT > 1) {
+                        const float bdx = (float)(S * tx + pxs[0] - bpx) - 0.5f * (float)(G.ab * S - 1);
+                        float bdy[PPL], idu_c[PPL];
+                        bool pok[PPL];
 #pragma unroll
-                    for (int j = 0; j < PPL; ++j) {
+                        for (int j = 0; j < PPL; ++j) {
+                            const int row = row0 + SPLIT * j;
+                            const float sig = row == 0 ? sig0 : fmaf((float)row, dsig, sig0);
+                            idu_c[j] = fmaf(sa.x, sig, sa.x);
+                            bdy[j] = (float)(S * ty + pys[j] - bpy) - 0.5f * (float)(G.ab * S - 1);
+                            pok[j] = calive && (idu_c[j] > 0.f);
+                        }
+                        split_cost<T, BY_ROW, PPL, SPLIT>(pairs, fr, nf, bdx, bdy, idu_c, pok, pitch_b, wm1, hm1,
+                                                          ikf[k], hk, img_scale, row0, s_terms[wave] + lane, cst2,
+                                                          nv2l);
+                    }
+#pragma unroll
+                    for (int j = 0; SPLIT == 1 && j < PPL; ++j) {
                         const float sig = j == 0 ? sig0 : fmaf((float)j, dsig, sig0);
                         const float idu_c = fmaf(sa.x, sig, sa.x);
                         float bdx = (float)(S * tx + pxs[j] - bpx) - 0.5f * (float)(G.ab * S - 1);
@@ -1546,9 +1642,10 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
                         frame_cost<T, BY_ROW, DEEP ? 4 : 0>(pairs, fr, nf, bdx, bdy, idu_c, calive && (idu_c > 0.f),
                                                            pitch_b, wm1, hm1, ikf[k][j], hk, img_scale, cst2, nv2l);
                     }
-                    const float c2 = group_sum<LANES>(cst2);
+                    // (a split column's cost stands in its last row's lanes)
+                    const float c2 = group_sum<RL>(cst2);
                     const int n2 = group_sum<LANES>(nv2l);
-                    if (p == 0) {
+                    if (p == LANES - RL) {
                         float* o = lsm + (k * SLOTS + r) * SM_WORDS;
                         o[SM_COST] = c2;
                         o[SM_NV] = __int_as_float(n2);
@@ -2240,9 +2337,9 @@ hipError_t launch_quantize(const float* src, int src_pitch, void* dst, int dst_p
     return hipGetLastError();
 }
 
-template <typename T, int S, int TX, int TY, int K, bool R, bool P, int D = 0, int SPLIT = 1>
+template <typename T, int S, int TX, int TY, int K, bool R, bool P, int D = 0, int SPLIT = 1, bool DAMPED = true>
 static void* gn_ptr() {
-    return (void*)&gn_kernel<T, S, TX, TY, K, R, D, SPLIT, P>;
+    return (void*)&gn_kernel<T, S, TX, TY, K, R, D, SPLIT, P, DAMPED>;
 }
 
 template <typename T, int S, int TX, int TY, bool R, bool P, int KMAX = 4>
@@ -2274,8 +2371,10 @@ static void* gn_pick(const GnVariant& v) {
 // per lane: the 4x4 layout of 4x4 surfels, and 16 x 16 surfels)
 template <typename T, bool R>
 static void* gn_pick_deep(const GnVariant& v) {
-    if (v.split == 4) return gn_ptr<T, 4, 2, 2, 1, R, false, 4, 4>();
-    if (v.split == 2) return gn_ptr<T, 4, 4, 2, 1, R, false, 2, 2>();
+    if (v.split == 4)
+        return v.damped ? gn_ptr<T, 4, 2, 2, 1, R, false, 4, 4, true>() : gn_ptr<T, 4, 2, 2, 1, R, false, 4, 4, false>();
+    if (v.split == 2)
+        return v.damped ? gn_ptr<T, 4, 4, 2, 1, R, false, 2, 2, true>() : gn_ptr<T, 4, 4, 2, 1, R, false, 2, 2, false>();
     if (v.patch == 16) return v.deep == 2 ? gn_ptr<T, 16, 1, 1, 1, R, false, 2>() : gn_ptr<T, 16, 1, 1, 1, R, false, 1>();
     return v.deep == 2 ? gn_ptr<T, 4, 4, 4, 1, R, false, 2>() : gn_ptr<T, 4, 4, 4, 1, R, false, 1>();
 }

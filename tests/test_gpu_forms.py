@@ -16,7 +16,8 @@ FIELDS = ("inv_depth", "nx", "ny", "nz", "flags", "cost", "nvalid", "last_update
 
 
 @pytest.mark.parametrize("storage,patch,lam,n_nbr", [
-    ("f16", 4, 0.0, 7), ("f32", 4, 0.0, 3), ("u8", 4, 0.0, 1), ("f16", 4, 1e-3, 5), ("f32", 16, 0.0, 5),
+    ("f16", 4, 0.0, 7), ("f32", 4, 0.0, 3), ("u8", 4, 0.0, 1), ("f16", 4, 1e-3, 5), ("u8", 4, 1e-3, 16), ("f32", 4, 1e-3, 2),
+    ("f32", 16, 0.0, 5),
     ("u8", 16, 1e-3, 2), ("f16", 16, 0.0, 4), ("f16", 8, 0.0, 5)])
 def test_every_form_gives_one_result(storage, patch, lam, n_nbr):
     if not torch.cuda.is_available():
