@@ -702,28 +702,34 @@ sgn_status check_disc_item(const sgn_disc_item* it, bool need_nbr) {
 //              four: 142 us at 755 items (eight 201, one with four frames in
 //              flight 271), 266 against 290 at 1,716; f32 96 against 149 at
 //              848, but 170 against 158 at 1,510.
-//   w <= 4     one, four frames in flight (four wavefronts per SIMD): 320 us
-//              at 2,267 items (one sample at a time 363).
-//   w <= 5     two frames at five per SIMD: f32 233 us at 4,533 (305 and 250).
-//   w <= 6     one sample at a time, all resident at six: 545 us at 5,192
-//              (two frames 618, four 582).
-//   w <= 8     four frames again, two full rounds: 648 us at 6,800 (753).
-//   beyond     one sample at a time (2.09 ms at 27,200; two frames 2.12, four
-//              2.25), f32 two frames (2.15 ms at 54,400; 2.20, 2.39).
-// The damped variant's cost sums run over the slots in turn: one wavefront.
+//   w <= 2.2, f32 4
+//              one, four frames in flight (four wavefronts per SIMD): 320 us
+//              at 2,267 items (one sample at a time 363); f32 198 at 3,020
+//              (shared 203).
+//   beyond     one, the workgroup's solves shared, two frames in flight at six
+//              per SIMD.  Whole calls: 360 us at 3,020 items (four frames
+//              unshared 375), 465 against 511 at 4,530, 548 / 597 at 6,040,
+//              982 / 1,088 at 12,080; f32 296 / 328 at 6,040, 512 / 607 at
+//              12,080, 1,810 / 2,001 at 48,320.
+// The damped variant's cost sums run over the slots in turn: one wavefront,
+// its solves its own.  Four frames in flight to w = 4, two to 5, one sample at
+// a time to 6 (all resident), four again to 8 (two full rounds: 648 us at
+// 6,800 items against 753), beyond that one sample (f32 two frames).
 DiscForm choose_disc_form(const sgn_ctx* c, int items, int dtype, const sgn_params* prm) {
     const bool f32 = dtype == SGN_F32;
     const double w = (double)items / (4.0 * std::max(1, c->cus));
     if (!(prm->lm_lambda > 0.f)) {
-        if (w <= 0.25) return {16, 4};
-        if (w <= 0.45) return {8, 4};
-        if (w <= (f32 ? 1.0 : 1.7)) return {4, 4};
+        if (w <= 0.25) return {16, 4, 0};
+        if (w <= 0.45) return {8, 4, 0};
+        if (w <= (f32 ? 1.0 : 1.7)) return {4, 4, 0};
+        if (w <= (f32 ? 4.0 : 2.2)) return {1, 4, 0};
+        return {1, 2, 1};
     }
-    if (w <= 4.0) return {1, 4};
-    if (w <= 5.0) return {1, 2};
-    if (w <= 6.0) return {1, 0};
-    if (w <= 8.0) return {1, 4};
-    return {1, f32 ? 2 : 0};
+    if (w <= 4.0) return {1, 4, 0};
+    if (w <= 5.0) return {1, 2, 0};
+    if (w <= 6.0) return {1, 0, 0};
+    if (w <= 8.0) return {1, 4, 0};
+    return {1, f32 ? 2 : 0, 0};
 }
 
 // Disc surfels: descriptor table (one KfDev per keyframe; its items are runs
@@ -819,14 +825,18 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
         // neighbour rows read by index unless a row pitch exceeds the
         // descriptor's stride field
         bool by_row = true;
+        float max_radius = 0.f;
+        int max_nbr = 0;
         for (int i = 0; i < n; ++i) {
             const sgn_keyframe& kf = items[i].kf;
+            max_radius = std::max(max_radius, items[i].radius);
+            max_nbr = std::max(max_nbr, kf.n_nbr);
             if (kf.n_nbr > 0 && (size_t)kf.nbr[0].pitch * dtype_size(kf.kf.dtype) >= kMaxRowStride) by_row = false;
         }
         const DiscForm form = choose_disc_form(c, item_base, dtype, prm);
         const int blocks = item_blocks(nq, H->queues, item_base, form.waves > 1 ? 1 : kBlockThreads / kWaveSize);
-        const hipError_t e = launch_disc_gn(dtype, form, one, dH, item_base, blocks, by_row, c->stream, c->gn_start,
-                                            c->gn_end);
+        const hipError_t e = launch_disc_gn(dtype, form, one, dH, item_base, blocks, by_row, max_radius,
+                                            max_nbr, c->stream, c->gn_start, c->gn_end);
         if (e != hipSuccess) return hip_fail(e, "disc Gauss-Newton launch");
         c->gn_timed = true;
     }

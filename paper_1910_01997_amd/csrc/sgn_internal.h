@@ -257,9 +257,10 @@ constexpr float kDiscMaxRadius = 12.f;
 constexpr int disc_surfels_per_wave(int dtype) { return dtype == 0 ? 1 : 2; }
 // How the disc kernel runs: wavefronts per item (1, 4, 8 or 16) and frames
 // whose taps are in flight at once (4 with several wavefronts, else 0, 2 or
-// 4).  Results do not depend on it.
+// 4), and whether a workgroup's wavefronts share their surfels' solves.
+// Results do not depend on it.
 struct DiscForm {
-    int waves, deep;
+    int waves, deep, shared;
 };
 // Gauss-Newton over the disc surfels of a batch: work items of
 // disc_surfels_per_wave(dtype) surfels of one keyframe (KfDev::n_items =
@@ -268,8 +269,8 @@ struct DiscForm {
 // several (with one share per XCD in the header, workgroup b serves share
 // b % kXcds)
 hipError_t launch_disc_gn(int dtype, const DiscForm& form, const LoneBatch& one, const BatchHeader* hdr,
-                          int total_items, int grid_blocks, bool by_row, hipStream_t s, hipEvent_t start,
-                          hipEvent_t stop);
+                          int total_items, int grid_blocks, bool by_row, float max_radius, int max_nbr, hipStream_t s,
+                          hipEvent_t start, hipEvent_t stop);
 // Depth-buffered render of the discs of several keyframes: one table entry
 // per keyframe (device memory); the scratch holds one 64-bit depth key and
 // one index per pixel of every keyframe, keyframe after keyframe.

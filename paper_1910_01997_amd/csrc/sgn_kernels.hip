@@ -1677,6 +1677,50 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(g
     }
 }
 
+// Where a workgroup shares its surfels' solves, a surfel's state lives in its
+// ST_ words.  Degeneracy and tangent basis, before each iteration (n . r_s
+// with the roundings that gn_kernel and disc_gn_kernel give it):
+template <bool DISC>
+__device__ __forceinline__ void surfel_ready(float* o, float nx, float ny, float nz, bool alive, uint32_t flags) {
+    const float rx = o[ST_RSX], ry = o[ST_RSY];
+    const float c = (DISC ? fmaf(ny, ry, nx * rx) : fmaf(nx, rx, ny * ry)) + nz;
+    if (alive && fabsf(c) < 1e-6f) {
+        o[ST_FLAGS] = __uint_as_float(flags | F_DEGENERATE);
+        o[ST_ALIVE] = 0.f;
+        o[ST_COSTO] = 0.f;
+        o[ST_NVO] = __int_as_float(0);
+    }
+    float b1x, b1y, b1z, b2x, b2y, b2z;
+    tangent_basis(nx, ny, nz, b1x, b1y, b1z, b2x, b2y, b2z);
+    o[ST_B1X] = b1x; o[ST_B1Y] = b1y; o[ST_B1Z] = b1z;
+    o[ST_B2X] = b2x; o[ST_B2Y] = b2y; o[ST_B2Z] = b2z;
+    o[ST_INVC] = rcp_fast(c);
+}
+// and the undamped step from its sums, the next iteration's basis included.
+template <bool DISC>
+__device__ __forceinline__ void shared_step(float* o, const float* sm, bool last, bool depth_only, float kap2) {
+    const float4 w0 = *(const float4*)(o + 0);
+    const float4 w1 = *(const float4*)(o + 4);
+    const float4 w2 = *(const float4*)(o + 8);
+    const float4 w3 = *(const float4*)(o + 12);
+    const float4 w4 = *(const float4*)(o + 16);
+    const bool alive = w3.y != 0.f;
+    if (!alive) return;
+    uint32_t flags = __float_as_uint(w3.z);
+    float cost_out = w4.x, cost_here = 0.f, id_c = 0.f, nx_c = 0.f, ny_c = 0.f, nz_c = 0.f, lam = 0.f;
+    int nv_out = __float_as_int(w4.y), nv = 0;
+    const bool step = owner_step(sm, alive, last, depth_only, false, kap2, lam, w0.x, w0.y, w0.z, w0.w, w1.x, w1.y,
+                                 w1.z, w1.w, w2.x, w2.y, flags, cost_out, nv_out, nv, cost_here, id_c, nx_c, ny_c,
+                                 nz_c);
+    o[ST_FLAGS] = __uint_as_float(flags);
+    o[ST_COSTO] = cost_out; o[ST_NVO] = __int_as_float(nv_out);
+    if (step) {
+        o[ST_ID] = id_c; o[ST_NX] = nx_c; o[ST_NY] = ny_c; o[ST_NZ] = nz_c;
+        o[ST_LAM] = 1.f;
+    }
+    if (!last) surfel_ready<DISC>(o, step ? nx_c : w0.y, step ? ny_c : w0.z, step ? nz_c : w0.w, true, flags);
+}
+
 // The Gauss-Newton kernel of large grids: gn_kernel without damping, four
 // pixels per lane, one group per wavefront, whose workgroup shares its
 // surfels' solves.  After each iteration's sums one wavefront (another each
@@ -1789,25 +1833,10 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(D
         o[ST_LAM] = 0.f;                                      // set once a step is accepted
         o[ST_COSTO] = 0.f; o[ST_NVO] = __int_as_float(0);
     }
-    // degeneracy and tangent basis of a surfel's words, before each iteration
-    auto ready = [&](float* o, float nx, float ny, float nz, bool alive, uint32_t flags) {
-        const float c = nx * o[ST_RSX] + ny * o[ST_RSY] + nz;
-        if (alive && fabsf(c) < 1e-6f) {
-            o[ST_FLAGS] = __uint_as_float(flags | F_DEGENERATE);
-            o[ST_ALIVE] = 0.f;
-            o[ST_COSTO] = 0.f;
-            o[ST_NVO] = __int_as_float(0);
-        }
-        float b1x, b1y, b1z, b2x, b2y, b2z;
-        tangent_basis(nx, ny, nz, b1x, b1y, b1z, b2x, b2y, b2z);
-        o[ST_B1X] = b1x; o[ST_B1Y] = b1y; o[ST_B1Z] = b1z;
-        o[ST_B2X] = b2x; o[ST_B2Y] = b2y; o[ST_B2Z] = b2z;
-        o[ST_INVC] = rcp_fast(c);
-    };
     wave_sync();
     if (iters > 0 && lane < NS) {
         float* o = lst + lane * ST_WORDS;
-        ready(o, o[ST_NX], o[ST_NY], o[ST_NZ], o[ST_ALIVE] != 0.f, __float_as_uint(o[ST_FLAGS]));
+        surfel_ready<false>(o, o[ST_NX], o[ST_NY], o[ST_NZ], o[ST_ALIVE] != 0.f, __float_as_uint(o[ST_FLAGS]));
     }
     wave_sync();
     for (int it = 0; it < iters; ++it) {
@@ -1910,31 +1939,9 @@ __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(D
         }
         __syncthreads();
         if (wave == (int)((blockIdx.x / kXcds + (unsigned)it) % WPB) && lane < WPB * NS) {
-            float* const o = (float*)s_state + lane * ST_WORDS;
-            const float* sm = (const float*)s_sums + lane * SM_WORDS;
-            const float4 w0 = *(const float4*)(o + 0);
-            const float4 w1 = *(const float4*)(o + 4);
-            const float4 w2 = *(const float4*)(o + 8);
-            const float4 w3 = *(const float4*)(o + 12);
-            const float4 w4 = *(const float4*)(o + 16);
-            const bool alive = w3.y != 0.f;
-            if (alive) {
-                uint32_t flags = __float_as_uint(w3.z);
-                float cost_out = w4.x, cost_here = 0.f, id_c = 0.f, nx_c = 0.f, ny_c = 0.f, nz_c = 0.f, lam = 0.f;
-                int nv_out = __float_as_int(w4.y), nv = 0;
-                const float kap = hdr->kappa_fp64;
-                const bool step = owner_step(sm, alive, last, hdr->depth_only != 0, false, kap * kap, lam, w0.x, w0.y,
-                                             w0.z, w0.w, w1.x, w1.y, w1.z, w1.w, w2.x, w2.y, flags, cost_out, nv_out,
-                                             nv, cost_here, id_c, nx_c, ny_c, nz_c);
-                o[ST_FLAGS] = __uint_as_float(flags);
-                o[ST_COSTO] = cost_out; o[ST_NVO] = __int_as_float(nv_out);
-                if (step) {
-                    o[ST_ID] = id_c; o[ST_NX] = nx_c; o[ST_NY] = ny_c; o[ST_NZ] = nz_c;
-                    o[ST_LAM] = 1.f;
-                }
-                if (!last)
-                    ready(o, step ? nx_c : w0.y, step ? ny_c : w0.z, step ? nz_c : w0.w, true, flags);
-            }
+            const float kap = hdr->kappa_fp64;
+            shared_step<false>((float*)s_state + lane * ST_WORDS, (const float*)s_sums + lane * SM_WORDS, last,
+                               hdr->depth_only != 0, kap * kap);
         }
         __syncthreads();
     }
@@ -2422,9 +2429,9 @@ int gn_blocks_per_cu(const GnVariant& v) {
 // A kernel between the two timing events.  Recorded events: the launch that
 // carries its own (hipExtLaunchKernel) took 6-7 us longer alone.
 static hipError_t launch_timed(void* f, int grid_blocks, int threads, void** args, hipStream_t s, hipEvent_t start,
-                               hipEvent_t stop) {
+                               hipEvent_t stop, size_t lds = 0) {
     hipError_t e = hipEventRecord(start, s);
-    if (e == hipSuccess) e = hipLaunchKernel(f, dim3(grid_blocks), dim3(threads), args, 0, s);
+    if (e == hipSuccess) e = hipLaunchKernel(f, dim3(grid_blocks), dim3(threads), args, lds, s);
     if (e == hipSuccess) e = hipEventRecord(stop, s);
     return e;
 }
@@ -2559,13 +2566,24 @@ __device__ __forceinline__ void disc_pixel(const DiscRows& d, const int* row_x0,
 // the chip has free (640x480, 1,510 discs in 755 wavefronts: 324 us for 15
 // iterations); four of them take 142 us, with the taps of four frames in
 // flight.
+//
+// SHARED (undamped, an item per wavefront): one wavefront of the workgroup
+// steps all its surfels, a lane each, as in gn_shared_kernel: the step is
+// about 230 of the 4,400 VALU instructions that a wavefront issues per
+// iteration over a disc of radius 10 and seven frames.  With the state in LDS
+// and no damped branch, two frames in flight fit six wavefronts per SIMD where
+// they held five; the pixels' and pair words' LDS is what the batch's largest
+// disc and frame count need (22 KB where the most took 25).  VALU issue bounds
+// it.  640x480, six frames: 511 -> 465 us at 9,060 discs (f16), 1,088 -> 982
+// at 24,160; f32 607 -> 512 at 12,080 and 2,001 -> 1,810 at 48,320.  (One
+// sample at a time at eight wavefronts: 481, 1,006; 533, 1,815.)
 constexpr int disc_threads(int waves) { return waves == 1 ? kBlockThreads : waves * kWaveSize; }
-template <int WAVES, int DEEP>
-constexpr int disc_waves() { return WAVES > 1 ? 4 : DEEP == 4 ? 4 : DEEP ? 5 : 6; }
+template <int WAVES, int DEEP, bool SHARED>
+constexpr int disc_waves() { return WAVES > 1 ? 4 : DEEP == 4 ? 4 : DEEP && !SHARED ? 5 : 6; }
 
-template <typename T, int SPW, bool BY_ROW, int WAVES, int DEEP>
-__global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_per_eu(disc_waves<WAVES, DEEP>(), 8))) void disc_gn_kernel(
-    LoneBatch, const BatchHeader* __restrict__ hdr_, int total) {
+template <typename T, int SPW, bool BY_ROW, int WAVES, int DEEP, bool SHARED>
+__global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_per_eu(disc_waves<WAVES, DEEP, SHARED>(), 8))) void disc_gn_kernel(
+    LoneBatch, const BatchHeader* __restrict__ hdr_, int total, int max_slots, int max_nbr) {
     constexpr int LANES = kWaveSize / SPW;        // lanes per surfel
     constexpr int PPL = kDiscPPL * SPW;           // pixel slots per lane
     constexpr int NWAVE = disc_threads(WAVES) / kWaveSize;
@@ -2584,43 +2602,60 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
         else __syncthreads();
     };
     const int h = lane / LANES, hl = lane % LANES;       // surfel of the wave, lane within it
-    int item_ = (int)blockIdx.x * WPB + wave;
+    int first = (int)blockIdx.x * WPB, end = total;
     if (hdr->n_queues == kXcds) {
         // one share of the items per XCD (workgroups go to the XCDs in turn)
         const int share = (int)(blockIdx.x % (unsigned)kXcds);
-        item_ = hdr->queues[share].begin + (int)(blockIdx.x / (unsigned)kXcds) * WPB + wave;
-        if (item_ >= hdr->queues[share].end) item_ = total;
+        first = hdr->queues[share].begin + (int)(blockIdx.x / (unsigned)kXcds) * WPB;
+        end = hdr->queues[share].end;
     }
-    const int item = __builtin_amdgcn_readfirstlane(item_);
-    if (item >= total) return;
-    __shared__ float4 s_pairs[WPB][SPW][kMaxNbr * kPairWords / 4];
+    const int item = __builtin_amdgcn_readfirstlane(first + wave);
+    const bool work = item < end;
+    if (SHARED ? first >= end : !work) return;
+    // (the shared form's pixels and pair words: as many as the batch needs)
+    extern __shared__ float4 s_dyn[];
+    __shared__ float4 s_pairs[SHARED ? 1 : WPB][SPW][kMaxNbr * kPairWords / 4];
     __shared__ float4 s_state[WPB][SPW][ST_WORDS / 4];
     __shared__ float4 s_sums[WPB][SPW][SM_WORDS / 4];
     __shared__ int s_rows[NWAVE][SPW][kDiscRowWords];
     // each lane's pixels: offsets from the anchor and keyframe values
-    __shared__ uint32_t s_pix[WPB][PPL][kWaveSize];
-    __shared__ float s_val[WPB][packed ? 1 : PPL][kWaveSize];
+    __shared__ uint32_t s_pix[SHARED ? 1 : WPB][PPL][kWaveSize];
+    __shared__ float s_val[SHARED ? 1 : WPB][packed ? 1 : PPL][kWaveSize];
     // each slot's sums over the frames, and each wavefront's valid counts
     __shared__ float2 s_ab[WAVES > 1 ? PPL : 1][WAVES > 1 ? kWaveSize : 1];
     __shared__ float s_cst[WAVES > 1 ? PPL : 1][WAVES > 1 ? kWaveSize : 1];
     __shared__ int s_nv[WAVES > 1 ? NWAVE : 1][WAVES > 1 ? kWaveSize : 1];
-    float* const pairs = (float*)s_pairs[wave][h];
+    float* pairs;
+    uint32_t (*pix)[kWaveSize];
+    float (*vals)[kWaveSize];
+    if constexpr (SHARED) {
+        pairs = (float*)s_dyn + (wave * SPW + h) * max_nbr * kPairWords;
+        uint32_t* const px = (uint32_t*)s_dyn + WPB * SPW * max_nbr * kPairWords;
+        pix = (uint32_t (*)[kWaveSize])(px + wave * max_slots * kWaveSize);
+        vals = (float (*)[kWaveSize])((float*)px + (WPB + wave) * max_slots * kWaveSize);
+    } else {
+        pairs = (float*)s_pairs[wave][h];
+        pix = s_pix[wave];
+        vals = s_val[wave];
+    }
     float* const lst = (float*)s_state[wave][h];
     float* const lsm = (float*)s_sums[wave][h];
     int* const row_x0 = s_rows[wave_][h];
     int* const row_start = s_rows[wave_][h] + kDiscMaxRows;
 
     const cptr<KfDev> kfs = view.kfs;
-    const int kidx = find_kf(kfs, hdr->n_kf, item, 0);
+    // a shared workgroup's wavefront without an item has no surfel and keeps to
+    // the barriers
+    const int kidx = !SHARED || work ? find_kf(kfs, hdr->n_kf, item, 0) : 0;
     const cptr<KfDev> Kd = kfs + kidx;
     const int sidx = (item - Kd->item_base) * SPW + h;
-    const bool have = sidx < Kd->disc_count;         // an odd count leaves the last half empty
+    const bool have = work && sidx < Kd->disc_count; // an odd count leaves the last half empty
     const int iters = hdr->iters;
     const float hk = hdr->huber_k;
     const float kap2 = hdr->kappa_fp64 * hdr->kappa_fp64;
     const bool depth_only = hdr->depth_only != 0;
     const float lm0 = hdr->lm_lambda;
-    const bool lm = lm0 > 0.f;
+    const bool lm = !SHARED && lm0 > 0.f;
     const int W = Kd->width, H = Kd->height;
     const int nf = Kd->n_nbr;
     const float img_scale = Kd->img_scale;
@@ -2635,7 +2670,7 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
     // slot count: the larger of the wavefront's surfels, so the loop is uniform
     int nslots = (d.total + LANES - 1) / LANES;
     if constexpr (SPW == 2) nslots = max(nslots, __shfl_xor(nslots, 32));
-    nslots = __builtin_amdgcn_readfirstlane(nslots);
+    nslots = __builtin_amdgcn_readfirstlane(SHARED ? min(nslots, max_slots) : nslots);
     // anchor pixel (nearest the centre; any fixed point works for the local
     // warp coordinates)
     const int ax = (int)rint(fmin(fmax((double)ux, -1e6), 1e6));
@@ -2661,8 +2696,8 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
             pk = ((uint32_t)(x - ax) & 0xffu) | (((uint32_t)(y - ay) & 0xffu) << 8) | (slot_bits(raw) << 16);
             v = (float)raw * kf_scale;
         }
-        s_pix[wave][j][lane] = pk;
-        if constexpr (!packed) s_val[wave][j][lane] = v;
+        pix[j][lane] = pk;
+        if constexpr (!packed) vals[j][lane] = v;
     }
     // r_u - r_s = (anchor offset + (anchor - u_s)) / f
     const float fox = (float)((double)ax - (double)ux), foy = (float)((double)ay - (double)uy);
@@ -2686,9 +2721,21 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
     float lam = lm0;
     float b1x = 0.f, b1y = 0.f, b1z = 0.f, b2x = 0.f, b2y = 0.f, b2z = 0.f;
 
+    if constexpr (SHARED) {
+        if (owner) {
+            lst[ST_ID] = id; lst[ST_NX] = nx; lst[ST_NY] = ny; lst[ST_NZ] = nz;
+            lst[ST_RSX] = rsx; lst[ST_RSY] = rsy;
+            lst[ST_ALIVE] = have ? 1.f : 0.f;
+            lst[ST_FLAGS] = __uint_as_float(flags);
+            lst[ST_LAM] = 0.f;                       // set once a step is accepted
+            lst[ST_COSTO] = 0.f; lst[ST_NVO] = __int_as_float(0);
+            if (iters > 0) surfel_ready<true>(lst, nx, ny, nz, have, flags);
+        }
+    }
+
     for (int it = 0; it < iters; ++it) {
         const bool last = (it == iters - 1);
-        if (owner) {
+        if (!SHARED && owner) {
             const float c = nx * rsx + ny * rsy + nz;
             if (alive && fabsf(c) < 1e-6f) {
                 flags |= F_DEGENERATE;
@@ -2704,7 +2751,8 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
             lst[ST_RSX] = rsx; lst[ST_RSY] = rsy;
             lst[ST_ALIVE] = alive ? 1.f : 0.f;
         }
-        sync();
+        if constexpr (SHARED) wave_sync();
+        else sync();
         {
             const float4 sa = *(const float4*)(lst + 0);
             const float4 sb = *(const float4*)(lst + 4);
@@ -2741,9 +2789,9 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
                 return x;
             };
             for (int j = part; j < nslots; j += WAVES) {
-                const uint32_t pk = s_pix[wave][j][lane];
+                const uint32_t pk = pix[j][lane];
                 const Pixel x = pixel(pk);
-                const float ikf[1] = {packed ? slot_value<T>(pk) * kf_scale : s_val[wave][packed ? 0 : j][lane]};
+                const float ikf[1] = {packed ? slot_value<T>(pk) * kf_scale : vals[packed ? 0 : j][lane]};
                 const bool pv = hl + LANES * j < d.total;
                 const float idu = fmaf(sid, x.sigma, sid);
                 const bool pix_ok[1] = {salive && pv && (idu > 0.f)};
@@ -2790,7 +2838,7 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
                 // b0 b1); the first also b2 and the count, the last the cost
                 float e0 = 0.f, e1 = 0.f, e2 = 0.f;
                 for (int j = 0; j < (part < 4 ? nslots : 0); ++j) {
-                    const Pixel x = pixel(s_pix[0][j][lane]);
+                    const Pixel x = pixel(pix[j][lane]);
                     const float2 ab = s_ab[j][lane];
                     // the pair's factors: u0 v0 and u1 v1, u a product A g or B
                     const float ga = part < 2 ? x.g0 : part == 2 ? x.g1 : x.g0;
@@ -2819,6 +2867,14 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
                     if (hl == 0) lsm[SM_COST] = cs;
                 }
             }
+        }
+        if constexpr (SHARED) {
+            __syncthreads();
+            if (wave == (int)((blockIdx.x / kXcds + (unsigned)it) % WPB) && lane < WPB * SPW)
+                shared_step<true>((float*)s_state + lane * ST_WORDS, (const float*)s_sums + lane * SM_WORDS, last,
+                                  depth_only, kap2);
+            __syncthreads();
+            continue;
         }
         sync();
         bool cand = false;
@@ -2853,9 +2909,9 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
                 float cst2 = 0.f;
                 int nv2l = 0;
                 for (int j = 0; j < nslots; ++j) {
-                    const uint32_t pk = s_pix[wave][j][lane];
+                    const uint32_t pk = pix[j][lane];
                     const float bdx = (float)(int8_t)(pk & 0xffu), bdy = (float)(int8_t)((pk >> 8) & 0xffu);
-                    const float ikf = packed ? slot_value<T>(pk) * kf_scale : s_val[wave][packed ? 0 : j][lane];
+                    const float ikf = packed ? slot_value<T>(pk) * kf_scale : vals[packed ? 0 : j][lane];
                     const bool pv = hl + LANES * j < d.total;
                     const float drx = (bdx + fox) * ifx, dry = (bdy + foy) * ify;
                     const float sig = fmaf(sa.z * inv_c, dry, (sa.y * inv_c) * drx);
@@ -2879,6 +2935,12 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
             nx = nx_c; ny = ny_c; nz = nz_c;
             updated = true;
         }
+    }
+    if constexpr (SHARED) {
+        id = lst[ST_ID]; nx = lst[ST_NX]; ny = lst[ST_NY]; nz = lst[ST_NZ];
+        flags = __float_as_uint(lst[ST_FLAGS]);
+        cost_out = lst[ST_COSTO]; nv_out = __float_as_int(lst[ST_NVO]);
+        updated = lst[ST_LAM] != 0.f;
     }
     if (owner && have) {
         ((gmut<float>)Kd->inv_depth)[sidx] = id;
@@ -3604,12 +3666,13 @@ hipError_t launch_disc_transfer(const DiscTransferArgs& one, const DiscTransferA
 template <typename T, bool R>
 static void* disc_gn_pick(const DiscForm& f) {
     constexpr int SPW = disc_surfels_per_wave(std::is_same<T, float>::value ? 0 : 1);
-    return f.waves == 16  ? (void*)&disc_gn_kernel<T, SPW, R, 16, 4>
-           : f.waves == 8 ? (void*)&disc_gn_kernel<T, SPW, R, 8, 4>
-           : f.waves == 4 ? (void*)&disc_gn_kernel<T, SPW, R, 4, 4>
-           : f.deep == 4  ? (void*)&disc_gn_kernel<T, SPW, R, 1, 4>
-           : f.deep == 2  ? (void*)&disc_gn_kernel<T, SPW, R, 1, 2>
-                          : (void*)&disc_gn_kernel<T, SPW, R, 1, 0>;
+    if (f.shared) return (void*)&disc_gn_kernel<T, SPW, R, 1, 2, true>;
+    return f.waves == 16  ? (void*)&disc_gn_kernel<T, SPW, R, 16, 4, false>
+           : f.waves == 8 ? (void*)&disc_gn_kernel<T, SPW, R, 8, 4, false>
+           : f.waves == 4 ? (void*)&disc_gn_kernel<T, SPW, R, 4, 4, false>
+           : f.deep == 4  ? (void*)&disc_gn_kernel<T, SPW, R, 1, 4, false>
+           : f.deep == 2  ? (void*)&disc_gn_kernel<T, SPW, R, 1, 2, false>
+                          : (void*)&disc_gn_kernel<T, SPW, R, 1, 0, false>;
 }
 template <bool R>
 static void* disc_gn_ptr(int dtype, const DiscForm& f) {
@@ -3618,12 +3681,20 @@ static void* disc_gn_ptr(int dtype, const DiscForm& f) {
 }
 
 hipError_t launch_disc_gn(int dtype, const DiscForm& form, const LoneBatch& one, const BatchHeader* hdr,
-                          int total_items, int grid_blocks, bool by_row, hipStream_t s, hipEvent_t start,
-                          hipEvent_t stop) {
+                          int total_items, int grid_blocks, bool by_row, float max_radius, int max_nbr, hipStream_t s,
+                          hipEvent_t start, hipEvent_t stop) {
     if (total_items <= 0) return hipSuccess;
-    void* args[] = {(void*)&one, (void*)&hdr, (void*)&total_items};
+    // the unit squares about a disc's pixels lie within radius r + sqrt(1/2)
+    const int spw = disc_surfels_per_wave(dtype), lanes = kWaveSize / spw;
+    const double reach = (double)max_radius + 0.7072;
+    int max_slots = std::min((int)(3.1416 * reach * reach) / lanes + 1, kDiscPPL * spw);
+    constexpr int wpb = kBlockThreads / kWaveSize;
+    const int lds = form.shared ? wpb * 4 * (spw * max_nbr * kPairWords +
+                                             max_slots * kWaveSize * (dtype != 0 ? 1 : 2))
+                                : 0;
+    void* args[] = {(void*)&one, (void*)&hdr, (void*)&total_items, (void*)&max_slots, (void*)&max_nbr};
     return launch_timed(by_row ? disc_gn_ptr<true>(dtype, form) : disc_gn_ptr<false>(dtype, form), grid_blocks,
-                        disc_threads(form.waves), args, s, start, stop);
+                        disc_threads(form.waves), args, s, start, stop, lds);
 }
 
 hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items,

@@ -75,12 +75,14 @@ def test_full_keyframe_equals_its_default_and_four_group_plans_for_8x8():
         ctx.close()
 
 
-@pytest.mark.parametrize("storage,lam,n_nbr", [("f16", 0.0, 6), ("f32", 0.0, 3), ("u8", 0.0, 1), ("f16", 1e-3, 5)])
-def test_every_disc_form_gives_one_result(storage, lam, n_nbr):
+@pytest.mark.parametrize("storage,lam,n_nbr,radius", [
+    ("f16", 0.0, 6, 10.0), ("f32", 0.0, 3, 10.0), ("u8", 0.0, 1, 2.5), ("f16", 1e-3, 5, 10.0),
+    ("f32", 0.0, 16, 12.0), ("f16", 0.0, 16, 12.0)])
+def test_every_disc_form_gives_one_result(storage, lam, n_nbr, radius):
     """Disc surfels: copies of one keyframe take the batch through every form
     (sixteen, eight, four or one wavefronts per item, taps of four, two or no
-    frames ahead).  An odd count leaves half an item empty; some discs are cut
-    by the image border."""
+    frames ahead, solves shared or not).  An odd count leaves half an item
+    empty; some discs are cut by the image border."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_1910_01997_amd import engine, surfgn as sg
@@ -90,18 +92,18 @@ def test_every_disc_form_gives_one_result(storage, lam, n_nbr):
         spec = dataclasses.replace(spec_for_config(1), width=308, height=234, n_rects=6, seed=29, n_nbr=n_nbr,
                                    half_new=False)
         kf = make_keyframe(spec, device="cuda")
-        d = engine.DiscKeyframe.from_scene(ctx, kf, make_disc_surfels(kf, radius=10.0), storage=storage)
+        d = engine.DiscKeyframe.from_scene(ctx, kf, make_disc_surfels(kf, radius=radius), storage=storage)
         d.count -= 1 - d.count % 2
         m = d.count
         per = (m + 1) // 2 if storage != "f32" else m
         prm = sg.params(iters=3, lm_lambda=lam)
         simds = 4 * sg.sgn_device_info(0)["compute_units"]
         ref = None
-        for w in (0.1, 0.35, 0.8, 1.5, 3.0, 4.5, 5.5, 7.0, 12.0):
+        for w in (0.1, 0.35, 0.8, 1.5, 2.0, 3.0, 4.5, 5.5, 7.0, 12.0):
             k = max(1, int(w * simds / per))
             print(f"case discs {storage} lambda {lam}: {k} copies of {m}, {k * per / simds:.2f} items per SIMD", flush=True)
             states = [d.state.clone() for _ in range(k)]
-            items = sg.disc_array([sg.sgn_disc_item(d.img.view.c, s.c, d.ux.data_ptr(), d.uy.data_ptr(), m, 10.0)
+            items = sg.disc_array([sg.sgn_disc_item(d.img.view.c, s.c, d.ux.data_ptr(), d.uy.data_ptr(), m, radius)
                                    for s in states])
             sg.sgn_disc_optimize(ctx.handle, items, k, prm)
             torch.cuda.synchronize()
