@@ -1466,7 +1466,7 @@ sgn_status sgn_autotune(sgn_ctx* c, const sgn_batch_item* items, int32_t n, cons
             float ms = 0.f;
             if (st == SGN_OK) st = sgn_last_kernel_ms(c, &ms);
             if (st != SGN_OK) { ok = false; result = st; break; }
-            if (rep > 0) tmin = std::min(tmin, ms);   // the first run warms up (and captures the graph)
+            if (rep > 0) tmin = std::min(tmin, ms);   // the first run warms up
         }
         if (log)
             std::fprintf(stderr, "sgn_autotune: tiles %dx%d groups %d persistent %d xcd_queues %d: %s %.3f ms\n",

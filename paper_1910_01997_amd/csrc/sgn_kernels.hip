@@ -10,16 +10,20 @@
 //   init_kernel    neighbour-plane initialisation (Surfel Initialization).
 //   gn_kernel      the fused Gauss-Newton iterations.  A work item is a set
 //                  of surfel groups inside one aligned 16 x 16-pixel block;
-//                  a group fills the 64 lanes of a wavefront with pixels (four
-//                  4x4 surfels or one 8x8 surfel).  Each lane loops over the
-//                  neighbour frames for its pixel, with the per-pixel
+//                  a group fills the 64 lanes of a wavefront with pixels (four,
+//                  eight or sixteen 4x4 surfels, one 8x8 or one 16x16).  Each
+//                  lane loops over the neighbour frames for its pixels, with the per-pixel
 //                  inverse-depth Jacobian hoisted out of the frame loop (the
 //                  paper notes it does not depend on the frame); the normal
 //                  equations are reduced across the surfel's lanes with DPP,
 //                  and one owner lane per surfel solves its 3x3 system, all
 //                  groups of the item at once.  All iterations run inside the
 //                  kernel: surfels never read each other during the
-//                  optimisation.
+//                  optimisation.  Compiled in several forms, picked by the
+//                  number of work items; gn_shared_kernel is the form of
+//                  large undamped grids.
+//   disc_*         disc surfels (Eq. 4): Gauss-Newton, depth-buffered render,
+//                  search, placement and transfer.
 //   render_kernel  per-pixel inverse depth (and owning surfel) by Eq. 3.
 //   regrid_*       surfel reference-frame change (Eq. 10) and re-gridding
 //                  into another keyframe's tiles.

@@ -616,7 +616,7 @@ def serving_benchmark(n_streams: int = 32, rate: float = 200.0, duration: float 
         ex = HipExecutor(streams, lanes=lanes, iters=iters, pixels_per_lane=pixels_per_lane) \
             if mode == "served" else PlainExecutor(streams, iters=iters, pixels_per_lane=pixels_per_lane)
         srv = Server(ex, pool_bytes=pool_bytes, max_batch=32 if mode == "served" else 1)
-        # warm the kernels and graphs on a short burst outside the measured trace
+        # warm the kernels on a short burst outside the measured trace
         for s in range(min(4, len(streams))):
             srv.submit(Request(stream=s, arrival=srv.clock(), frame_index=0))
         srv.drain()
