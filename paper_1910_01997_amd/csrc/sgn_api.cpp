@@ -481,23 +481,27 @@ int item_blocks(int nq, const QueueDev* queues, int items, int wpb) {
 //              wavefront's time is its instructions' latency, and the chip
 //              has room for four times the wavefronts.  61 us against 108 for
 //              one sample at a time at 300 items, 82 against 109 at 910.
-//   w <= 1.75  on two lanes, two frames: 87 us against 113 at 1,200 items
-//              and 117 at 1,530 (four lanes: 104 and 121).
+//   w <= 2.5   on two lanes, two frames, five wavefronts per SIMD all resident:
+//              87 us against 113 at 1,200 items and 117 at 1,530 (four lanes:
+//              104 and 121).  Whole calls against the shared form: 119 / 122
+//              us at 1,800 items, 136 / 140 at 2,520 (u8 166 / 180 at 2,000
+//              and ten neighbours), but 155 / 140 at 2,700.
 //   beyond     unsplit, the workgroup's solves shared.  One frame's taps in
 //              flight at six wavefronts per SIMD to w = 3, for f32, and for
 //              f16 batches of w > 24; else one sample at a time at eight.
-//              Whole calls, one frame / one sample: 121 / 133 us at 1,900
-//              items, 141 / 147 at 2,700 (two frames without sharing 120 and
-//              147), 272 / 261 at 7,500, 507 / 491 at 16,950; f32 278 / 323 at
+//              Whole calls, one frame / one sample: 141 / 147 us at 2,700
+//              items (two frames without sharing 147),
+//              272 / 261 at 7,500, 507 / 491 at 16,950; f32 278 / 323 at
 //              8,295; the 64-keyframe batch (104,000 items) f16 3.76 / 3.92 ms,
 //              f32 3.91 / 4.30, u8 3.98 / 3.83.
 // 16 x 16 surfels are not split: two frames in flight to w = 1.75 (97 us
 // against 111 at 1,200 items).  The damped variant evaluates each candidate
 // besides; its lines, at the same grids: four lanes to w = 0.75 (106 us
 // against 187 for two frames unsplit at 300 items, 122 / 191 at 660), two to
-// 1.75 (130 against four lanes' 139 at 910, 151 / 211 unsplit at 1,200, but
-// 225 / 217 at 1,900); it steps in gn_kernel beyond: two frames in flight to
-// w = 3, one to w = 24 or for f32, else one sample at a time.
+// 1.5, three wavefronts per SIMD by their LDS (130 against four lanes' 139 at
+// 910, 151 / 214 unsplit at 1,530, but 225 / 217 at 1,900); it steps in
+// gn_kernel beyond: two frames in flight to w = 3, one to w = 24 or for f32,
+// else one sample at a time.
 void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_params* prm, GnVariant& v) {
     const bool four_px = v.patch == 16 || (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4);
     if (!four_px || v.persistent) return;
@@ -506,7 +510,7 @@ void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn
     v.damped = prm->lm_lambda > 0.f;
     if (v.patch == 4 && w <= (v.damped ? 0.75 : 0.65)) {
         v.split = 4; v.deep = 4; v.tiles_x = 2; v.tiles_y = 2;
-    } else if (v.patch == 4 && w <= 1.75) {
+    } else if (v.patch == 4 && w <= (v.damped ? 1.5 : 2.5)) {
         v.split = 2; v.deep = 2; v.tiles_x = 4; v.tiles_y = 2;
     } else if (w <= (v.damped ? 3.0 : 1.75)) {
         v.deep = 2;
