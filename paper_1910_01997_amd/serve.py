@@ -18,8 +18,8 @@ Scheduling (host side, this module):
     head-of-line blocking of other streams behind it); among the streams
     that are free the oldest request is admitted first;
   * continuous batching: whenever an execution lane is free, every admitted
-    request is packed into one batch and launched (one persistent fused
-    kernel for the whole batch); batches on different lanes overlap on the
+    request is packed into one batch and launched (one fused kernel for
+    the whole batch); batches on different lanes overlap on the
     device;
   * a request whose execution fails is completed with its error and its
     memory released; the rest of its batch is not affected by the scheduler;
@@ -433,7 +433,8 @@ class HipExecutor(Executor):
             self.small_plan = sg.plan(4, 4, 1, 0, 0, 1, groups=1)
             self.single_plan = sg.plan(4, 4, 0, 0, 0, 0, groups=1)
             # one wavefront per work item, the items split into one share
-            # per XCD (batches of eight keyframes or more)
+            # per XCD (batches of four items per CU or more); the small
+            # plan's persistent grid, unbounded, is this grid too
             self.large_plan = sg.plan(4, 4, 0, 0, 0, 1, groups=1)
         elif pixels_per_lane == 1:
             self.small_plan = sg.plan(2, 2, 1, 0, 0, 1, groups=1)
