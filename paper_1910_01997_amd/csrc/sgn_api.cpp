@@ -473,6 +473,19 @@ int item_blocks(int nq, const QueueDev* queues, int items, int wpb) {
     return kXcds * widest;
 }
 
+// Bytes of a keyframe's images, its own and its neighbours', over the batch by
+// pixels.
+double mean_image_bytes(const sgn_batch_item* items, int n) {
+    double bytes = 0.0, pixels = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const sgn_keyframe& kf = items[i].kf;
+        const double px = (double)kf.kf.width * kf.kf.height;
+        bytes += px * px * dtype_size(kf.kf.dtype) * (kf.n_nbr + 1);
+        pixels += px;
+    }
+    return pixels > 0.0 ? bytes / pixels : 0.0;
+}
+
 // The form of a four-pixels-per-lane kernel (the 4x4 layout of 4x4 surfels,
 // 16 x 16 surfels) for the batch's number of work items; every form adds the
 // same terms in the same order, so results do not depend on it.  w = items
@@ -487,27 +500,35 @@ int item_blocks(int nq, const QueueDev* queues, int items, int wpb) {
 //              us at 1,800 items, 136 / 140 at 2,520 (u8 166 / 180 at 2,000
 //              and ten neighbours), but 155 / 140 at 2,700.
 //   beyond     unsplit, the workgroup's solves shared.  One frame's taps in
-//              flight at six wavefronts per SIMD to w = 3, for f32, and for
-//              f16 batches of w > 24; else one sample at a time at eight.
-//              Whole calls, one frame / one sample: 141 / 147 us at 2,700
-//              items (two frames without sharing 147),
-//              272 / 261 at 7,500, 507 / 491 at 16,950; f32 278 / 323 at
-//              8,295; the 64-keyframe batch (104,000 items) f16 3.76 / 3.92 ms,
-//              f32 3.91 / 4.30, u8 3.98 / 3.83.
+//              flight at six wavefronts per SIMD to w = 3, for f32, and above
+//              w = 24 for f16 keyframes whose images (8 MB and more) are well
+//              past an XCD's 4 MB L2, so that taps come from further away;
+//              else one sample at a time at eight.  Whole calls, one frame /
+//              one sample: 141 / 147 us at 2,700 items (two frames without
+//              sharing 147), 272 / 261 at 7,500, 507 / 491 at 16,950; f32
+//              278 / 323 at 8,295; f16 at 57,600 items 1.59 / 1.55 ms with
+//              640x480 images (4.3 MB a keyframe), 2.02 / 2.07 with 1280x720
+//              (16.6 MB), 16 x 16 surfels 1.54 / 1.50 with the former; the
+//              64-keyframe batch (104,000 items) f16 3.76 / 3.92, f32 3.91 /
+//              4.30, u8 3.98 / 3.83.
 // 16 x 16 surfels are not split: two frames in flight to w = 1.75 (97 us
 // against 111 at 1,200 items).  The damped variant evaluates each candidate
 // besides; its lines, at the same grids: four lanes to w = 0.75 (106 us
 // against 187 for two frames unsplit at 300 items, 122 / 191 at 660), two to
 // 1.5, three wavefronts per SIMD by their LDS (130 against four lanes' 139 at
 // 910, 151 / 214 unsplit at 1,530, but 225 / 217 at 1,900); it steps in
-// gn_kernel beyond: two frames in flight to w = 3, one to w = 24 or for f32,
-// else one sample at a time.
+// gn_kernel beyond: two frames in flight to w = 3 (f16 209 us against 246 for
+// one sample at a time at 1,900 items), one to w = 24 and for such images and
+// f32 beyond (f16 4.20 ms against 4.30 at 57,600 items of 1280x720, 16 x 16
+// surfels 3.73 / 3.93; f32 4.50 / 5.02), else one sample at a time (u8 4.32
+// against 4.39).
 void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_params* prm, GnVariant& v) {
     const bool four_px = v.patch == 16 || (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4);
     if (!four_px || v.persistent) return;
     const int64_t total = count_items(items, n, item_geo(v.patch, v.tiles_x, v.tiles_y, v.groups));
     const double w = (double)total / (4.0 * std::max(1, c->cus));
     v.damped = prm->lm_lambda > 0.f;
+    const bool far_taps = v.dtype == SGN_F32 || (v.dtype == SGN_F16 && mean_image_bytes(items, n) > 8e6);
     if (v.patch == 4 && w <= (v.damped ? 0.75 : 0.65)) {
         v.split = 4; v.deep = 4; v.tiles_x = 2; v.tiles_y = 2;
     } else if (v.patch == 4 && w <= (v.damped ? 1.5 : 2.5)) {
@@ -515,10 +536,10 @@ void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn
     } else if (w <= (v.damped ? 3.0 : 1.75)) {
         v.deep = 2;
     } else if (v.damped) {
-        v.deep = w <= 24.0 || v.dtype == SGN_F32;
+        v.deep = w <= 24.0 || far_taps;
     } else {
         v.shared = 1;
-        v.deep = w <= 3.0 || v.dtype == SGN_F32 || (v.dtype == SGN_F16 && w > 24.0);
+        v.deep = w <= 3.0 || v.dtype == SGN_F32 || (far_taps && w > 24.0);
     }
 }
 
