@@ -1395,10 +1395,12 @@ sgn_status sgn_disc_transfer_batch(sgn_ctx* c, int32_t n, const sgn_disc_item* s
         a.counts = counts_outs[k];
     }
     SGN_HIP(hipSetDevice(c->device));
-    const DiscTransferArgs* dtab;
-    sgn_status st = upload_table(c, tab.data(), n, &dtab);
-    if (st) return st;
-    hipError_t e = launch_disc_transfer(tab[0], dtab, n, c->stream);
+    const DiscTransferArgs* dtab = nullptr;
+    if (n > kDiscXferArgs) {
+        const sgn_status st = upload_table(c, tab.data(), n, &dtab);
+        if (st) return st;
+    }
+    hipError_t e = launch_disc_transfer(tab.data(), dtab, n, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc transfer launch");
     return SGN_OK;
 }

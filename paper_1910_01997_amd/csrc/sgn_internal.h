@@ -362,8 +362,10 @@ struct DiscTransferArgs {
     int32_t* src_index;           // may be null
     int32_t* counts;              // device [2]: written, landed
 };
-// One workgroup per keyframe pair.
-hipError_t launch_disc_transfer(const DiscTransferArgs& one, const DiscTransferArgs* table, int n_pairs,
+// One workgroup per keyframe pair; table (device) may be null up to
+// kDiscXferArgs pairs.
+constexpr int kDiscXferArgs = 11;
+hipError_t launch_disc_transfer(const DiscTransferArgs* pairs, const DiscTransferArgs* table, int n_pairs,
                                 hipStream_t s);
 hipError_t launch_quantize(const float* src, int src_pitch, void* dst, int dst_pitch,
                            int width, int height, int dtype, float scale, hipStream_t s);

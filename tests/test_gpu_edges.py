@@ -1,12 +1,15 @@
 """Sizes at which the image-storage, initialisation and render kernels change
 what they do: rows with and without 16-byte alignment, runs of surfels that
 are all, partly or not new, blocks of pixels cut by the image border."""
+import dataclasses
+
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
 import oracle
+from scenegen import make_disc_surfels, make_keyframe, spec_for_config
 from tests.helpers import random_unit_cap
 from tests.parity import oracle_keyframe, oracle_state
 
@@ -102,3 +105,42 @@ def test_init_and_render_match_the_oracle(ctx, sizes, pattern):
         # Eq. 3 in float: a pixel whose value crosses zero may fall on either side
         assert same.mean() > 0.999 if same.size > 1000 else same.all()
         assert (np.abs(got - want) <= 1e-4 * np.maximum(1.0, np.abs(want)))[same].all()
+
+
+@pytest.mark.parametrize("n", [2, 11, 12])
+def test_disc_transfer_tables_by_value_and_uploaded(ctx, n):
+    """Disc transfers of few pairs take their table in the kernel's arguments
+    (up to 11), more an uploaded one: each pair as if alone, bitwise."""
+    from paper_1910_01997_amd import engine, surfgn as sg
+    kf = make_keyframe(dataclasses.replace(spec_for_config(1), n_nbr=3, half_new=False), device="cuda")
+    src = engine.DiscKeyframe.from_scene(ctx, kf, make_disc_surfels(kf, radius=10.0))
+    m = src.count
+    print(f"case disc transfer of {n} pairs, {m} discs", flush=True)
+    poses = [(np.eye(3), np.array([0.01 * k, 0.0, 0.0])) for k in range(n)]
+
+    def targets(k):
+        out = []
+        for _ in range(k):
+            st = src.state.clone()
+            xy = torch.full((2, m), -1.0, device="cuda")
+            out.append((st, xy, torch.full((2,), -1, dtype=torch.int32, device="cuda")))
+        return out
+
+    def call(ts, ps):
+        items = [sg.sgn_disc_item(src.img.view.c, t[0].c, t[1][0].data_ptr(), t[1][1].data_ptr(), 0, 10.0)
+                 for t in ts]
+        sg.sgn_disc_transfer_batch(ctx.handle, [src.item()] * len(ts), [sg.pose_of(R, t) for R, t in ps], items,
+                                   [m] * len(ts), [t[2].data_ptr() for t in ts])
+        torch.cuda.synchronize()
+
+    got = targets(n)
+    call(got, poses)
+    for k in range(n):
+        ref = targets(1)
+        call(ref, poses[k:k + 1])
+        w = int(ref[0][2][0])
+        assert w > m // 2 and torch.equal(got[k][2], ref[0][2])
+        assert torch.equal(got[k][1][:, :w].view(torch.int32), ref[0][1][:, :w].view(torch.int32))
+        for f in ("inv_depth", "nx", "ny", "nz", "flags"):
+            a, b = getattr(got[k][0], f), getattr(ref[0][0], f)
+            assert torch.equal(a[:w].view(torch.int32), b[:w].view(torch.int32)), f
