@@ -26,7 +26,7 @@ def kernel_source_hash() -> str:
     """sha256 of the kernel sources and the build flags (names a build)."""
     import hashlib
     h = hashlib.sha256()
-    for src in SOURCES + ["sgn_internal.h"]:
+    for src in SOURCES + ["sgn_internal.h", "sgn_rules.h"]:
         with open(os.path.join(CSRC, src), "rb") as f:
             h.update(f.read())
     # the flags without the include path, which depends on where the tree is

@@ -162,7 +162,7 @@ struct GnVariant {
     int tiles_x, tiles_y;
     int lds;        // stage footprints in LDS
     int groups;     // surfel groups per work item (1, 2 or 4)
-    int by_row;     // neighbour rows read by index (every row pitch below kMaxRowStride)
+    int by_row;     // neighbour rows read by index (rows_by_index)
     int deep;       // frames whose taps are in flight at once (0: one sample at a time)
     int split;      // lanes per pixel column of the 4x4 layout (1, 2 or 4)
     int persistent; // a grid of fixed size pulling items from device queues

@@ -484,12 +484,14 @@ __device__ __forceinline__ void stage_pair_words(cptr<FrameDev> frames, int nf, 
 // Two addressings:
 //  - by row (BY_ROW: every row pitch of the batch below kMaxRowStride): a
 //    structured buffer whose stride is the row pitch, the row as the index
-//    (range-checked against the row count) and col as the offset, so no
-//    multiply forms the address;
-//  - raw: the byte offset row x pitch + col, range-checked against the
-//    image's bytes.
-// Either way the loads run only for samples whose corner passed the validity
-// test (x0 < W - 1, y0 < H - 1), so every tap lies inside the image.
+//    and col as the offset, so no multiply forms the address;
+//  - raw: the byte offset row x pitch + col.
+// The loads run only for samples whose corner passed the validity test
+// (x0 < W - 1, y0 < H - 1), so every tap lies inside the image; but the second
+// dword of an f16 or u8 load at the row's end can be the one after the image's
+// last.  Raw loads are checked against the image's bytes dword by dword,
+// structured ones only by row: the host takes them where that dword is mapped
+// memory (rows_by_index_safe).  Its value is not used.
 struct Taps {
     float i00, i01, i10, i11;
 };

@@ -1,0 +1,36 @@
+"""csrc/sgn_rules.h (host rules that need neither device nor runtime), compiled by itself."""
+import ctypes as C
+import functools
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1910_01997_amd", "csrc")
+
+SHIM = r"""
+#include "sgn_rules.h"
+extern "C" {
+size_t tap_reach(int w, int h, size_t pitch_b, int elem) { return sgn::tap_reach(w, h, pitch_b, elem); }
+size_t image_end(int w, int h, size_t pitch_b, int elem) { return sgn::image_end(w, h, pitch_b, elem); }
+int rows_by_index_safe(uint64_t data, int w, int h, size_t pitch_b, int elem, uint64_t next, uint64_t mapped) {
+    return sgn::rows_by_index_safe(data, w, h, pitch_b, elem, next, [&](uintptr_t) { return (uintptr_t)mapped; });
+}
+}
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def lib():
+    d = tempfile.mkdtemp(prefix="sgn_rules_")
+    src, out = os.path.join(d, "shim.cpp"), os.path.join(d, "libshim.so")
+    with open(src, "w") as f:
+        f.write(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC, src, "-o", out],
+                   check=True)
+    L = C.CDLL(out)
+    for n in ("tap_reach", "image_end"):
+        getattr(L, n).restype = C.c_size_t
+        getattr(L, n).argtypes = [C.c_int, C.c_int, C.c_size_t, C.c_int]
+    L.rows_by_index_safe.argtypes = [C.c_uint64, C.c_int, C.c_int, C.c_size_t, C.c_int, C.c_uint64, C.c_uint64]
+    return L

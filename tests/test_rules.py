@@ -1,0 +1,43 @@
+"""Host rules against plain models, without a GPU."""
+import itertools
+
+import pytest
+
+from tests.rules import lib
+
+
+@pytest.mark.parametrize("elem", [1, 2, 4])
+def test_tap_reach_is_the_last_byte_that_row_indexed_loads_touch(elem):
+    """Eight bytes from the pair's aligned dword (f32: from the pair) in rows
+    y0 and y0 + 1, over every valid corner."""
+    for w, h, pad in itertools.product(range(2, 14), (2, 3, 5), (0, 1, 2)):
+        pitch = (w * elem + 3) // 4 * 4 + 4 * pad
+        last = 0
+        for x0, y in itertools.product(range(w - 1), range(h)):
+            col = x0 * elem
+            last = max(last, y * pitch + (col if elem == 4 else col // 4 * 4) + 8)
+        assert lib().tap_reach(w, h, pitch, elem) == last
+        end = lib().image_end(w, h, pitch, elem)
+        assert end == (h - 1) * pitch + (w * elem + 3) // 4 * 4
+        assert last <= end + 4 and (elem != 4 or last <= end)
+
+
+@pytest.mark.parametrize("elem,w", [(1, 640), (1, 638), (1, 637), (1, 639), (2, 640), (2, 639), (4, 640)])
+def test_rows_are_read_by_index_only_over_mapped_memory(elem, w):
+    h = 16
+    pitch = (w * elem + 3) // 4 * 4
+    end = lib().image_end(w, h, pitch, elem)
+    past = lib().tap_reach(w, h, pitch, elem) > end
+    assert past == ((elem, w) not in [(1, 637), (2, 639), (4, 640)])
+
+    def safe(data, next_, mapped):
+        return bool(lib().rows_by_index_safe(data, w, h, pitch, elem, next_, mapped))
+    page = 1 << 32
+    at = page - end                       # the image ends with a page
+    assert safe(at, 0, page) == (not past)          # and with the mapped memory
+    assert safe(at, 0, page + 3) == (not past)
+    assert safe(at, 0, page + 4)                    # the dword past it is mapped
+    assert safe(at, page, page)                     # the next image starts there
+    assert safe(at, page + 4096, page) == (not past)
+    assert safe(at - 4, 0, page - 4)                # the dword lies in the last byte's page
+    assert safe(at + 4, 0, page + 4)
