@@ -14,7 +14,6 @@
 
 #include "../../include/surfgn.h"
 #include "sgn_internal.h"
-#include "sgn_rules.h"
 
 using namespace sgn;
 
@@ -743,44 +742,15 @@ sgn_status check_disc_item(const sgn_disc_item* it, bool need_nbr) {
     return SGN_OK;
 }
 
-// The disc kernel's form for the batch's number of work items, w = items per
-// SIMD (times: 15 iterations, 6 neighbours, f16 with two discs per item unless
-// f32 is said, with one):
-//   w <= 0.25  sixteen wavefronts per item, one workgroup per CU: 79 us at
-//              187 items against 97 with eight and 316 with one.
-//   w <= 0.45  eight: 107 us at 424 items (sixteen 152, four 131).
-//   w <= 1.7, f32 1.0
-//              four: 142 us at 755 items (eight 201, one with four frames in
-//              flight 271), 266 against 290 at 1,716; f32 96 against 149 at
-//              848, but 170 against 158 at 1,510.
-//   w <= 2.2, f32 4
-//              one, four frames in flight (four wavefronts per SIMD): 320 us
-//              at 2,267 items (one sample at a time 363); f32 198 at 3,020
-//              (shared 203).
-//   beyond     one, the workgroup's solves shared, two frames in flight at six
-//              per SIMD.  Whole calls: 360 us at 3,020 items (four frames
-//              unshared 375), 465 against 511 at 4,530, 548 / 597 at 6,040,
-//              982 / 1,088 at 12,080; f32 296 / 328 at 6,040, 512 / 607 at
-//              12,080, 1,810 / 2,001 at 48,320.
-// The damped variant's cost sums run over the slots in turn: one wavefront,
-// its solves its own.  Four frames in flight to w = 4, two to 5, one sample at
-// a time to 6 (all resident), four again to 8 (two full rounds: 648 us at
-// 6,800 items against 753), beyond that one sample (f32 two frames).
-DiscForm choose_disc_form(const sgn_ctx* c, int items, int dtype, const sgn_params* prm) {
-    const bool f32 = dtype == SGN_F32;
-    const double w = (double)items / (4.0 * std::max(1, c->cus));
-    if (!(prm->lm_lambda > 0.f)) {
-        if (w <= 0.25) return {16, 4, 0};
-        if (w <= 0.45) return {8, 4, 0};
-        if (w <= (f32 ? 1.0 : 1.7)) return {4, 4, 0};
-        if (w <= (f32 ? 4.0 : 2.2)) return {1, 4, 0};
-        return {1, 2, 1};
+// Pixel slots of a batch's discs, of the mean disc over the surfels.
+double disc_slots(const sgn_disc_item* items, int n, int dtype) {
+    double area = 0.0, surfels = 0.0;
+    for (int i = 0; i < n; ++i) {
+        area += 3.14159265 * items[i].radius * items[i].radius * items[i].count;
+        surfels += items[i].count;
     }
-    if (w <= 4.0) return {1, 4, 0};
-    if (w <= 5.0) return {1, 2, 0};
-    if (w <= 6.0) return {1, 0, 0};
-    if (w <= 8.0) return {1, 4, 0};
-    return {1, f32 ? 2 : 0, 0};
+    const int lanes = kWaveSize / disc_surfels_per_wave(dtype);
+    return surfels > 0.0 ? std::ceil(area / surfels / lanes) : 1.0;
 }
 
 // Disc surfels: descriptor table (one KfDev per keyframe; its items are runs
@@ -882,7 +852,8 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
             max_nbr = std::max(max_nbr, kf.n_nbr);
             by_row = by_row && rows_by_index(kf);
         }
-        const DiscForm form = choose_disc_form(c, item_base, dtype, prm);
+        const DiscForm form = disc_form((double)item_base / (4.0 * std::max(1, c->cus)), disc_slots(items, n, dtype),
+                                        dtype == SGN_F32, prm->lm_lambda > 0.f);
         const int blocks = item_blocks(nq, H->queues, item_base, form.waves > 1 ? 1 : kBlockThreads / kWaveSize);
         const hipError_t e = launch_disc_gn(dtype, form, one, dH, item_base, blocks, by_row, max_radius,
                                             max_nbr, c->stream, c->gn_start, c->gn_end);

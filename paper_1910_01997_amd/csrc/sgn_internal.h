@@ -6,6 +6,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "sgn_rules.h"
+
 namespace sgn {
 
 constexpr int kMaxNbr = 16;
@@ -255,13 +257,6 @@ constexpr float kDiscMaxRadius = 12.f;
 // (0 f32, 1 f16, 2 u8): two (32 lanes each) where a pixel's LDS slot packs
 // into one word, one for f32 images.
 constexpr int disc_surfels_per_wave(int dtype) { return dtype == 0 ? 1 : 2; }
-// How the disc kernel runs: wavefronts per item (1, 4, 8 or 16) and frames
-// whose taps are in flight at once (4 with several wavefronts, else 0, 2 or
-// 4), and whether a workgroup's wavefronts share their surfels' solves.
-// Results do not depend on it.
-struct DiscForm {
-    int waves, deep, shared;
-};
 // Gauss-Newton over the disc surfels of a batch: work items of
 // disc_surfels_per_wave(dtype) surfels of one keyframe (KfDev::n_items =
 // ceil(disc_count / that), item_base their prefix).

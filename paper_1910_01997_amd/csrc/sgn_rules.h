@@ -38,4 +38,61 @@ bool rows_by_index_safe(uintptr_t data, int width, int height, size_t pitch_b, i
     return reach <= mapped_end(end - 1);
 }
 
+// How the disc kernel runs: wavefronts per item (1, 4, 8 or 16) and frames
+// whose taps are in flight at once (4 with several wavefronts, else 0, 2 or
+// 4), and whether a workgroup's wavefronts share their surfels' solves.
+// Results do not depend on it.
+struct DiscForm {
+    int waves, deep, shared;
+};
+
+// The disc kernel's form for a batch of w work items per SIMD whose discs take
+// `slots` pixel slots each (32 pixels; f32 64), as several wavefronts deal the
+// slots out: without enough slots they only wait for each other.  Times: 15
+// iterations, 6 neighbours, radius 10 (ten slots, f32 five), f16 with two
+// discs per item unless f32 is said, with one.
+//   one slot   one wavefront, four frames in flight: radius 2.5 at w = 1 58 us
+//              against 63 with four wavefronts, at 1.5 60 against 106.
+//   w <= 0.25  sixteen wavefronts per item, one workgroup per CU: 79 us at
+//              187 items against 97 with eight and 316 with one.  (Two slots
+//              or four: as with four wavefronts, within 1 us.)
+//   w <= 0.45  eight: 107 us at 424 items (sixteen 152, four 131).
+//   w <= 1     four, all resident: 142 us at 755 items (eight 201, one with
+//              four frames in flight 271); two slots at w = 1 69 against 81,
+//              four 79 against 125; f32 96 against 149 at 848.
+//   w <= 1.7, four slots and more, not f32
+//              four in two rounds: 266 us against 290 at 1,716 items; four
+//              slots at w = 1.5 129 against 132, but two 109 against 84; f32
+//              170 against 158 at 1,510.
+//   w <= 2.2, f32 4
+//              one, four frames in flight (four wavefronts per SIMD): 320 us
+//              at 2,267 items (one sample at a time 363); f32 198 at 3,020
+//              (shared 203).
+//   beyond     one, the workgroup's solves shared, two frames in flight at six
+//              per SIMD.  Whole calls: 360 us at 3,020 items (four frames
+//              unshared 375), 465 against 511 at 4,530, 548 / 597 at 6,040,
+//              982 / 1,088 at 12,080; f32 296 / 328 at 6,040, 512 / 607 at
+//              12,080, 1,810 / 2,001 at 48,320.
+// The damped variant's cost sums run over the slots in turn: one wavefront,
+// its solves its own.  Four frames in flight to w = 4 (703 us against 718 with
+// two and 737 with one sample at a time at w = 3.5), two to 5 (828 / 833, four
+// 1,065, at 4.5), one sample to 6 (all resident; 1,047, two 1,177, at 5.5),
+// four again to 8 (two full rounds: 648 us at 6,800 items against 753),
+// beyond that one sample (f32 two frames: 1,062 against 1,137 at 14).
+inline DiscForm disc_form(double w, double slots, bool f32, bool damped) {
+    if (!damped) {
+        const bool deal = slots > 1.0;
+        if (deal && w <= 0.25) return {16, 4, 0};
+        if (deal && w <= 0.45) return {8, 4, 0};
+        if (deal && w <= (f32 || slots < 4.0 ? 1.0 : 1.7)) return {4, 4, 0};
+        if (w <= (f32 ? 4.0 : 2.2)) return {1, 4, 0};
+        return {1, 2, 1};
+    }
+    if (w <= 4.0) return {1, 4, 0};
+    if (w <= 5.0) return {1, 2, 0};
+    if (w <= 6.0) return {1, 0, 0};
+    if (w <= 8.0) return {1, 4, 0};
+    return {1, f32 ? 2 : 0, 0};
+}
+
 }  // namespace sgn

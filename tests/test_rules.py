@@ -41,3 +41,18 @@ def test_rows_are_read_by_index_only_over_mapped_memory(elem, w):
     assert safe(at, page + 4096, page) == (not past)
     assert safe(at - 4, 0, page - 4)                # the dword lies in the last byte's page
     assert safe(at + 4, 0, page + 4)
+
+
+@pytest.mark.parametrize("f32", [0, 1])
+def test_disc_wavefronts_have_slots_to_deal(f32):
+    """Several wavefronts share a disc only where it has several pixel slots,
+    and take a second round (w > 1) only where each has one of its own."""
+    for slots in range(1, 17):
+        for w in (0.01, 0.25, 0.26, 0.45, 0.46, 1.0, 1.01, 1.7, 1.71, 2.2, 2.3, 4.0, 4.1, 50.0):
+            f = lib().disc_form(w, slots, f32, 0)
+            waves, deep, shared = f // 100, f // 10 % 10, f % 10
+            assert (waves, deep, shared) in [(16, 4, 0), (8, 4, 0), (4, 4, 0), (1, 4, 0), (1, 2, 1)]
+            assert waves == 1 or slots > 1
+            assert waves == 1 or waves * w <= 4.0 or slots >= 4
+            damped = lib().disc_form(w, slots, f32, 1)
+            assert damped // 100 == 1 and damped % 10 == 0
