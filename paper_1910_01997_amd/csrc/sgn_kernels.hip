@@ -3176,15 +3176,11 @@ __global__ __launch_bounds__(1024) void disc_bin_lds_kernel(DiscRenderItem, cons
 //
 // Bound: the chain of dependent loads in front of the walk (keyframe, range,
 // list, records), so what counts is how many tiles a CU holds: 32 with a
-// wavefront each, where four-wavefront workgroups left eight.  The walk
-// compares num * (1 / den), the reciprocal formed once per entry and tile,
-// instead of dividing for every pixel: the product is within 4 ulp of the
-// quotient, so where the largest stands out by more than kNear it belongs to
-// the largest quotient, which is then divided out once.  Tiles with a pixel
-// where another product comes nearer (equal planes, ties), or whose products
-// leave the normal range, walk again with divisions.  16 mixed keyframes
-// (26,000 tiles): 49 us with a workgroup per tile and a division per pixel
-// and entry, 55 with the products alone, 38 with a wavefront per tile too.
+// wavefront each, where four-wavefront workgroups left eight.  Renders of 1 /
+// 8 / 32 keyframes of 1280x720 with 4,641 discs: 37 / 84 / 246 us with a
+// workgroup per tile, 29 / 63 / 159 now.  (Choosing by num * (1 / den), with
+// divisions only where two products come near each other: 29 / 65 / 165, and
+// 34 / 88 / 254 where all surfels lie on one plane.)
 __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
     DiscRenderItem, const DiscRenderItem* __restrict__ tab_, int n_items, int n_tiles,
     const DiscRaster* __restrict__ rec, const int32_t* __restrict__ count, const int32_t* __restrict__ start,
@@ -3192,15 +3188,12 @@ __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
 #pragma clang fp contract(off)
     const cptr<DiscRenderItem> tab = table_or_arg(tab_);
     constexpr int kPx = 4;
-    constexpr double kNear = 1e-14, kTiny = 1e-280, kHuge = 1e280;
     static_assert(kRenderTile == 16 && kRenderTile * kRenderTile == kPx * kWaveSize, "a tile per wavefront");
     __shared__ DiscRaster s_rec_[kBlockThreads / kWaveSize][kWaveSize];
-    __shared__ double s_rden_[kBlockThreads / kWaveSize][kWaveSize];
     __shared__ int s_idx_[kBlockThreads / kWaveSize][kWaveSize];
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = threadIdx.x >> 6;
     DiscRaster* const s_rec = s_rec_[wave];
-    double* const s_rden = s_rden_[wave];
     int* const s_idx = s_idx_[wave];
     const int t = grid_wave();
     if (t >= n_tiles) return;
@@ -3211,14 +3204,13 @@ __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
     const int y0 = ty * kRenderTile + lane / kRenderTile;            // rows y0, y0 + 4, ...
     const double r = (double)a.radius, r2 = r * r;
     const double xd = (double)x, ru0 = (xd - a.cx) / a.fx;
-    double yd[kPx], ru1[kPx], best[kPx], next[kPx];      // the two largest products
+    double yd[kPx], ru1[kPx], val[kPx];
     int who[kPx];
 #pragma unroll
     for (int p = 0; p < kPx; ++p) {
         yd[p] = (double)(y0 + 4 * p);
         ru1[p] = (yd[p] - a.cy) / a.fy;
-        best[p] = 0.0;
-        next[p] = 0.0;
+        val[p] = 0.0;
         who[p] = -1;
     }
     const int k0 = start[t], k1 = k0 + count[t];
@@ -3227,15 +3219,12 @@ __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
         wave_sync();                          // the previous chunk is read
         if (lane < nc) {
             const int g = list[c0 + lane];
-            const DiscRaster q = rec[g];
             s_idx[lane] = g - a.surfel_base;
-            s_rec[lane] = q;
-            s_rden[lane] = 1.0 / q.den;
+            s_rec[lane] = rec[g];
         }
         wave_sync();
         for (int e = 0; e < nc; ++e) {
             const DiscRaster q = s_rec[e];
-            const double rden = s_rden[e];
             const int idx = s_idx[e];
             const double dx = xd - q.cx, dx2 = dx * dx;
             const double nx = ru0 * q.n0;
@@ -3244,55 +3233,11 @@ __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
                 const double dy = yd[p] - q.cy;
                 // (a branch: most entries miss all of a row group's pixels)
                 if (!(dx2 + dy * dy < r2)) continue;
-                const double v = (nx + ru1[p] * q.n1 + 1.0 * q.n2) * rden;
-                who[p] = v > best[p] ? idx : who[p];
-                next[p] = fmax(next[p], fmin(v, best[p]));
-                best[p] = fmax(best[p], v);
-            }
-        }
-    }
-    double val[kPx];
-    bool again = false;
-#pragma unroll
-    for (int p = 0; p < kPx; ++p) {
-        // (a NaN product is a NaN quotient: not drawn, and passed over by the
-        // maxima; infinite and vanishing ones go to the second walk)
-        again = again || (who[p] >= 0 && (next[p] >= best[p] * (1.0 - kNear) || !(best[p] > kTiny && best[p] < kHuge)));
-        val[p] = 0.0;
-        if (who[p] >= 0) {
-            const DiscRaster q = rec[a.surfel_base + who[p]];
-            val[p] = (ru0 * q.n0 + ru1[p] * q.n1 + 1.0 * q.n2) / q.den;
-        }
-    }
-    if (__ballot(again) != 0ull) {
-#pragma unroll
-        for (int p = 0; p < kPx; ++p) {
-            val[p] = 0.0;
-            who[p] = -1;
-        }
-        for (int c0 = k0; c0 < k1; c0 += kWaveSize) {
-            const int nc = min(kWaveSize, k1 - c0);
-            wave_sync();
-            if (lane < nc) {
-                const int g = list[c0 + lane];
-                s_idx[lane] = g - a.surfel_base;
-                s_rec[lane] = rec[g];
-            }
-            wave_sync();
-            for (int e = 0; e < nc; ++e) {
-                const DiscRaster q = s_rec[e];
-                const int idx = s_idx[e];
-                const double dx = xd - q.cx;
-#pragma unroll
-                for (int p = 0; p < kPx; ++p) {
-                    const double dy = yd[p] - q.cy;
-                    if (!(dx * dx + dy * dy < r2)) continue;
-                    const double v = (ru0 * q.n0 + ru1[p] * q.n1 + 1.0 * q.n2) / q.den;
-                    if (!(v > 0.0) || !isfinite(v)) continue;
-                    if (v > val[p] || (v == val[p] && idx < who[p])) {
-                        val[p] = v;
-                        who[p] = idx;
-                    }
+                const double v = (nx + ru1[p] * q.n1 + 1.0 * q.n2) / q.den;
+                if (!(v > 0.0) || !isfinite(v)) continue;
+                if (v > val[p] || (v == val[p] && idx < who[p])) {
+                    val[p] = v;
+                    who[p] = idx;
                 }
             }
         }
