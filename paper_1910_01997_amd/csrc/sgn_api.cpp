@@ -1214,7 +1214,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     if (n > SGN_MAX_BATCH) return fail(SGN_E_UNSUPPORTED, "more keyframes than SGN_MAX_BATCH");
     std::vector<DiscRenderItem> tab(n);
     int64_t total_surfels = 0, total_pixels = 0, total_tiles = 0;
-    bool bin_lds = true;
+    int64_t most_tiles = 0, most_surfels = 0;
     for (int i = 0; i < n; ++i) {
         const sgn_disc_item* it = &items[i];
         sgn_status st = check_disc_item(it, false);
@@ -1239,7 +1239,8 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
         total_pixels += (int64_t)r.width * r.height;
         const int64_t tiles = (int64_t)r.tiles_x * ((r.height + kRenderTile - 1) / kRenderTile);
         total_tiles += tiles;
-        bin_lds &= tiles <= kBinTiles && it->count <= kBinSurfels;
+        most_tiles = std::max(most_tiles, tiles);
+        most_surfels = std::max(most_surfels, (int64_t)it->count);
     }
     if (total_surfels > (int64_t)INT32_MAX / (2 * kDiscMaxTilesPerSurfel) || total_tiles > (int64_t)INT32_MAX / 2)
         return fail(SGN_E_UNSUPPORTED, "too many surfels or pixels in one batch");
@@ -1256,7 +1257,8 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     w.count = (int32_t*)((char*)ws + lw.count_off);
     w.start = (int32_t*)((char*)ws + lw.start_off);
     w.list = (int32_t*)((char*)ws + lw.list_off);
-    hipError_t e = launch_disc_render(tab[0], dtab, n, (int)total_surfels, (int)total_tiles, bin_lds, w, c->stream);
+    const hipError_t e = launch_disc_render(tab[0], dtab, n, (int)total_surfels, (int)total_tiles,
+                                            bin_in_lds(n, most_tiles, most_surfels), w, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc render launch");
     return SGN_OK;
 }

@@ -302,9 +302,6 @@ struct DiscRenderScratch {
     int32_t* start;
     int32_t* list;
 };
-// Largest keyframe that one workgroup bins in LDS.
-constexpr int kBinTiles = 15360;
-constexpr int kBinSurfels = 16384;
 hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items, int total_surfels,
                               int total_tiles, bool bin_lds, const DiscRenderScratch& w, hipStream_t s);
 // The search for empty areas on the lattice (spacing/2 + i spacing, ...),

@@ -2968,18 +2968,17 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
 //
 // The render works in screen tiles of kRenderTile x kRenderTile pixels.  The
 // usable surfels are binned to the tiles their disc's bounding box meets (a
-// count per tile, a range of the list for each, a fill); then one workgroup
-// per tile gives each pixel to a thread, which walks the tile's list keeping
-// the largest value and the lowest index that reaches it.  The outcome does
-// not depend on the list order, so the fill's atomics leave it
-// deterministic, and the depth test needs no atomics.
+// count per tile, a range of the list for each, a fill); then a wavefront per
+// tile, four pixels per lane, walks the tile's list keeping the largest value
+// and the lowest index that reaches it.  The outcome does not depend on the
+// list order, so the fill's atomics leave it deterministic, and the depth test
+// needs no atomics.
 //
-// Binning takes one launch where a workgroup's LDS holds a keyframe's tile
-// counts (disc_bin_lds_kernel: up to kBinTiles tiles and kBinSurfels surfels,
-// images to about 2000 x 2000), else four (clear, count, ranges, fill).  The
-// work is a few microseconds either way; what counts is the launches, about
-// 4.7 us each: a 640x480 keyframe's render took 35 us with seven (three of
-// them a scan of the counts) and takes 17 with two.
+// Binning takes one launch, a workgroup per keyframe (disc_bin_lds_kernel,
+// where bin_in_lds says so), else four over the whole device (clear, count,
+// ranges, fill).  For few surfels the launches count, about 4.7 us each: a
+// 640x480 keyframe's render took 35 us with seven (three of them a scan of
+// the counts) and takes 17 with two.
 
 // Table entry of global surfel g (largest surfel_base <= g among entries
 // with surfels) or of global tile t (by tile_base).
@@ -3121,7 +3120,7 @@ __global__ __launch_bounds__(1024) void disc_bin_lds_kernel(DiscRenderItem, cons
     const cptr<DiscRenderItem> tab = table_or_arg(tab_);
     const carg<DiscRenderItem>& a = tab[blockIdx.x];
     __shared__ int s_cnt[kBinTiles];
-    __shared__ unsigned long long s_use[kBinSurfels / kWaveSize];
+    __shared__ unsigned long long s_use[(kBinSurfels + kWaveSize - 1) / kWaveSize];
     __shared__ int s_w[17];
     const int tid = (int)threadIdx.x;
     const int tiles = a.tiles_x * ((a.height + kRenderTile - 1) / kRenderTile);

@@ -95,4 +95,19 @@ inline DiscForm disc_form(double w, double slots, bool f32, bool damped) {
     return {1, f32 ? 2 : 0, 0};
 }
 
+// Whether the disc render bins each keyframe in one workgroup's LDS: its tile
+// counts have to fit, and the largest keyframe's surfels, which one CU then
+// works through, must not take longer than the launches that are saved.  Few
+// keyframes leave the other CUs idle; many share the device either way, and
+// spare the atomics in memory.  Whole renders, LDS / memory: 1 keyframe of
+// 1,564 discs 17 / 23 us, 2,304 24 / 25, 3,072 25 / 29 (640x480), 3,108 28 /
+// 26 (1920x1080), 4,641 29 / 26, 15,252 108 / 40; 8 keyframes of 4,641
+// 64 / 63, of 10,549 124 / 105; 12 of 4,641 79 / 80; 16 of 3,600 96 / 94, of
+// 4,641 94 / 98, of 6,279 108 / 125, of 8,040 208 / 186; 64 of 4,641 276 / 306.
+constexpr int kBinTiles = 15360;
+constexpr int kBinSurfels = 6400;
+inline bool bin_in_lds(int keyframes, int64_t most_tiles, int64_t most_surfels) {
+    return most_tiles <= kBinTiles && most_surfels <= (keyframes >= 12 ? kBinSurfels : 3072);
+}
+
 }  // namespace sgn

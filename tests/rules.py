@@ -16,6 +16,7 @@ size_t image_end(int w, int h, size_t pitch_b, int elem) { return sgn::image_end
 int rows_by_index_safe(uint64_t data, int w, int h, size_t pitch_b, int elem, uint64_t next, uint64_t mapped) {
     return sgn::rows_by_index_safe(data, w, h, pitch_b, elem, next, [&](uintptr_t) { return (uintptr_t)mapped; });
 }
+int bin_in_lds(int keyframes, int64_t tiles, int64_t surfels) { return sgn::bin_in_lds(keyframes, tiles, surfels); }
 int disc_form(double w, double slots, int f32, int damped) {
     const sgn::DiscForm f = sgn::disc_form(w, slots, f32, damped);
     return f.waves * 100 + f.deep * 10 + f.shared;
@@ -37,5 +38,6 @@ def lib():
         getattr(L, n).restype = C.c_size_t
         getattr(L, n).argtypes = [C.c_int, C.c_int, C.c_size_t, C.c_int]
     L.rows_by_index_safe.argtypes = [C.c_uint64, C.c_int, C.c_int, C.c_size_t, C.c_int, C.c_uint64, C.c_uint64]
+    L.bin_in_lds.argtypes = [C.c_int, C.c_int64, C.c_int64]
     L.disc_form.argtypes = [C.c_double, C.c_double, C.c_int, C.c_int]
     return L

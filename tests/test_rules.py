@@ -56,3 +56,11 @@ def test_disc_wavefronts_have_slots_to_deal(f32):
             assert waves == 1 or waves * w <= 4.0 or slots >= 4
             damped = lib().disc_form(w, slots, f32, 1)
             assert damped // 100 == 1 and damped % 10 == 0
+
+
+def test_one_workgroup_bins_a_keyframe_only_where_that_is_little_work():
+    def lds(*a):
+        return bool(lib().bin_in_lds(*a))
+    assert lds(1, 1200, 1564) and lds(1, 15360, 3072) and not lds(1, 15361, 10)
+    assert not lds(1, 8160, 3073) and not lds(8, 15252, 15252) and not lds(11, 3600, 4641)
+    assert lds(12, 3600, 4641) and lds(64, 1200, 6400) and not lds(64, 1200, 6401) and not lds(12, 15361, 1)
