@@ -2247,42 +2247,52 @@ __device__ __forceinline__ uint8_t stored_u8(float v, float scale) {
     return (uint8_t)fminf(fmaxf(rintf(v / scale), 0.f), 255.f);
 }
 
-// f32 images to f16 or u8.  A thread takes eight pixels of a row, with two
-// 16-byte loads and one store where the rows allow it (VEC: every row starts
-// on 16 bytes of the source and 16 (f16) or 8 (u8) of the destination), else
-// pixel by pixel.  Bound: memory; 1920x1080 to f16 moves 12.4 MB.  One pixel
-// per thread, its row found by a 64-bit division, took 6.4 us a call, most of
-// it beyond the launch; now 4.8.
+// f32 images to f16 or u8, eight pixels of a row per thread.  Where every row
+// starts on 16 bytes of the source and 16 (f16) or 8 (u8) of the destination
+// (VEC) they are neighbours, two 16-byte loads and one store; else they lie 64
+// apart, so that the wavefront's loads and stores join up.  Bound: memory;
+// 1920x1080 to f16 moves 12.4 MB.  One pixel per thread, its row found by a
+// 64-bit division, took 5.2 us a call back to back, 15.3 at 3840x2160; VEC
+// 4.1 and 8.7.  Rows that allow no wide loads: 4095x2159 to f16 16.5 us with a
+// pixel per thread, 26.2 with eight neighbours, 11.1 now.
 template <int DTYPE, bool VEC>
 __global__ __launch_bounds__(256) void quantize_kernel(const float* __restrict__ src, int src_pitch,
                                                        void* __restrict__ dst, int dst_pitch, int width, int height,
                                                        float scale) {
-    const int x0 = 8 * (int)(blockIdx.x * 64 + (threadIdx.x & 63));
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int x0 = 8 * kWaveSize * (int)blockIdx.x + (VEC ? 8 * lane : lane);
     if (x0 >= width) return;
-    const int n = min(8, width - x0);
     for (int y = (int)(blockIdx.y * 4 + (threadIdx.x >> 6)); y < height; y += (int)gridDim.y * 4) {
-        const float* const in = src + (size_t)y * src_pitch + x0;
-        const size_t o = (size_t)y * dst_pitch + x0;
-        if (VEC && n == 8) {
-            const float4 a = *(const float4*)in, b = *(const float4*)(in + 4);
+        const float* const in = src + (size_t)y * src_pitch;
+        const size_t o = (size_t)y * dst_pitch;
+        auto put = [&](int x, float v) {
+            if constexpr (DTYPE == 1) ((_Float16*)dst)[o + x] = stored_f16(v, scale);
+            else ((uint8_t*)dst)[o + x] = stored_u8(v, scale);
+        };
+        if constexpr (!VEC) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = in[min(x0 + kWaveSize * k, width - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (x0 + kWaveSize * k < width) put(x0 + kWaveSize * k, v[k]);
+        } else if (x0 + 8 <= width) {
+            const float4 a = *(const float4*)(in + x0), b = *(const float4*)(in + x0 + 4);
             const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
             if constexpr (DTYPE == 1) {
                 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
                 half8 h;
 #pragma unroll
                 for (int k = 0; k < 8; ++k) h[k] = stored_f16(v[k], scale);
-                *(half8*)((_Float16*)dst + o) = h;
+                *(half8*)((_Float16*)dst + o + x0) = h;
             } else {
                 unsigned w[2] = {0u, 0u};
 #pragma unroll
                 for (int k = 0; k < 8; ++k) w[k / 4] |= (unsigned)stored_u8(v[k], scale) << (8 * (k % 4));
-                *(uint2*)((uint8_t*)dst + o) = make_uint2(w[0], w[1]);
+                *(uint2*)((uint8_t*)dst + o + x0) = make_uint2(w[0], w[1]);
             }
         } else {
-            for (int k = 0; k < n; ++k) {
-                if constexpr (DTYPE == 1) ((_Float16*)dst)[o + k] = stored_f16(in[k], scale);
-                else ((uint8_t*)dst)[o + k] = stored_u8(in[k], scale);
-            }
+            for (int x = x0; x < width; ++x) put(x, in[x]);
         }
     }
 }
