@@ -170,9 +170,10 @@ typedef struct {
     int32_t waves_per_cu;       /* persistent grid size per compute unit (0: not bounded) */
     int32_t lds_stage;          /* 1: stage neighbour-frame footprints in LDS */
     int32_t xcd_queues;         /* 1: the work items cut into one run of equal work per
-                                   XCD: in a persistent grid, one device queue per XCD;
-                                   else the workgroups the hardware gives XCD x (every
-                                   eighth, from x) take XCD x's run in order */
+                                   XCD, which the workgroups the hardware gives XCD x
+                                   (every eighth, from x) take in order; in a persistent
+                                   grid, one device queue of whole keyframes per XCD (no
+                                   more queues than keyframes) */
     int32_t groups;             /* tiles_x x tiles_y groups per work item: 1, 2 or 4; 1 or
                                    2 for the 4x2 and 2x4 blocks; 1 for 4x4 and S = 16 (0:
                                    as many as fit, at most four).  A work item lies in one

@@ -438,9 +438,12 @@ int persistent_grid(sgn_ctx* c, const GnVariant& v, const sgn_plan& plan) {
 // Keyframe order of a batch: bound to nq shares by greedy load balance (the
 // biggest work to the least loaded share), share after share, and within one
 // by neighbour count, longest first, so the short items fill the tail.
-std::vector<int> share_order(int nq, const std::vector<int64_t>& work, const std::vector<int>& n_nbr) {
+// share_of[i] is keyframe i's share.
+std::vector<int> share_order(int nq, const std::vector<int64_t>& work, const std::vector<int>& n_nbr,
+                             std::vector<int>& share_of) {
     const int n = (int)work.size();
-    std::vector<int> order(n), share_of(n, 0);
+    std::vector<int> order(n);
+    share_of.assign(n, 0);
     for (int i = 0; i < n; ++i) order[i] = i;
     if (nq > 1) {
         std::vector<int> bysize(order);
@@ -592,7 +595,7 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     if (plan.tiles_x == 0 && plan.tiles_y == 0) plan = default_plan_for(c, items, n);
     if (plan.groups == 0) plan.groups = default_groups(patch, plan.tiles_x, plan.tiles_y);
     // A grid of fixed size runs only where the plan bounds it: handing the
-    // items out from device queues took 1.6-4 times the hardware dispatcher's
+    // items out from device queues took 1.2-4 times the hardware dispatcher's
     // time at every measured size (300 to 104,000 items).
     plan.persistent = plan.persistent && plan.waves_per_cu > 0;
     GnVariant var{dtype, patch, plan.tiles_x, plan.tiles_y, plan.lds_stage, plan.groups,
@@ -626,7 +629,10 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     // keyframe order: longest work items first, grouped by XCD queue
     const ItemGeo geo = fl.gn ? item_geo(patch, plan.tiles_x, plan.tiles_y, plan.groups)
                               : item_geo(patch, patch == 4 ? 4 : 1, 1, 1);
-    int nq = fl.gn && plan.xcd_queues ? kXcds : 1;
+    // (a persistent grid: no more queues than keyframes, as every wavefront
+    // goes through all of them at the end: 640x480 alone, 20 wavefronts per CU,
+    // 180 us with one queue, 567 with eight)
+    int nq = !(fl.gn && plan.xcd_queues) ? 1 : plan.persistent ? std::min(kXcds, n) : kXcds;
     std::vector<int64_t> work(n);
     std::vector<int> n_nbr(n);
     for (int i = 0; i < n; ++i) {
@@ -634,7 +640,8 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         work[i] = (int64_t)(kf.kf.width / kf.patch) * (kf.kf.height / kf.patch) * std::max(1, kf.n_nbr);
         n_nbr[i] = kf.n_nbr;
     }
-    const std::vector<int> order = share_order(nq, work, n_nbr);
+    std::vector<int> share_of;
+    const std::vector<int> order = share_order(nq, work, n_nbr, share_of);
 
     int frame_base = 0, item_base = 0;
     int64_t init_waves = 0, render_waves = 0;
@@ -687,7 +694,18 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     H->n_queues = nq;
     // (64 mixed f16 keyframes: 4.18 ms with 0.5-1.5 frames, 4.23 with 2;
     // f32 4.13 with 1, 4.20 with 0.5 and 1.5)
-    cut_shares(nq, kfs, n, 1.0, H->queues);
+    if (!plan.persistent) {
+        cut_shares(nq, kfs, n, 1.0, H->queues);
+    } else {
+        // whole keyframes per queue: a queue that is empty early is no loss
+        // here, the wavefronts go on to the next (16 mixed keyframes, f16, 20
+        // wavefronts per CU: 1,332 us, with items cut into equal runs 1,432)
+        for (int oi = 0; oi < n; ++oi) {
+            QueueDev& q = H->queues[share_of[order[oi]]];
+            if (q.end == q.begin) q.begin = kfs[oi].item_base;
+            q.end = kfs[oi].item_base + kfs[oi].n_items;
+        }
+    }
 
     const BatchHeader* dH = nullptr;
     if (lone) {
@@ -800,7 +818,8 @@ sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const s
         work[i] = (int64_t)items[i].count * std::max(1, items[i].kf.n_nbr);
         n_nbr[i] = items[i].kf.n_nbr;
     }
-    const std::vector<int> order = share_order(nq, work, n_nbr);
+    std::vector<int> share_of;
+    const std::vector<int> order = share_order(nq, work, n_nbr, share_of);
     int frame_base = 0, item_base = 0;
     for (int oi = 0; oi < n; ++oi) {
         const sgn_disc_item& it = items[order[oi]];
