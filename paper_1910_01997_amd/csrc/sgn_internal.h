@@ -14,7 +14,6 @@ constexpr int kMaxNbr = 16;
 constexpr int kWaveSize = 64;
 constexpr int kBlockThreads = 256;      // 4 wavefronts per workgroup
 constexpr int kNumCounters = 16;        // work-queue heads (one per XCD + spares)
-constexpr int kXcds = 8;
 constexpr int kInitSurfels = 128;       // surfels a wavefront of the initialisation looks through
 
 // Division of n < 2^24 by a divisor known on the host: m = ceil(2^(24 + l) / d)
@@ -108,11 +107,6 @@ __host__ __device__ inline void frame_constants(const FrameIn& in, FrameDev& F) 
     F.zrow[3] = 0.f;
     F.img = in.img;
 }
-
-// Work queue q covers the global item range [begin, end).
-struct QueueDev {
-    int32_t begin, end;
-};
 
 // Header of one batch: every per-call value of the kernels, in device memory
 // for a batch, in the kernel arguments for a lone keyframe.

@@ -10,7 +10,14 @@ CSRC = os.path.join(ROOT, "paper_1910_01997_amd", "csrc")
 
 SHIM = r"""
 #include "sgn_rules.h"
+struct Kf { int32_t n_items, n_nbr, item_base; };
 extern "C" {
+void cut_shares(int nq, const Kf* kfs, int n, double fixed, int32_t* out) {
+    sgn::cut_shares(nq, kfs, n, fixed, (sgn::QueueDev*)out);
+}
+int item_blocks(int nq, const int32_t* queues, int items, int wpb) {
+    return sgn::item_blocks(nq, (const sgn::QueueDev*)queues, items, wpb);
+}
 size_t tap_reach(int w, int h, size_t pitch_b, int elem) { return sgn::tap_reach(w, h, pitch_b, elem); }
 size_t image_end(int w, int h, size_t pitch_b, int elem) { return sgn::image_end(w, h, pitch_b, elem); }
 int rows_by_index_safe(uint64_t data, int w, int h, size_t pitch_b, int elem, uint64_t next, uint64_t mapped) {
@@ -38,6 +45,9 @@ def lib():
         getattr(L, n).restype = C.c_size_t
         getattr(L, n).argtypes = [C.c_int, C.c_int, C.c_size_t, C.c_int]
     L.rows_by_index_safe.argtypes = [C.c_uint64, C.c_int, C.c_int, C.c_size_t, C.c_int, C.c_uint64, C.c_uint64]
+    L.cut_shares.argtypes = [C.c_int, C.c_void_p, C.c_int, C.c_double, C.c_void_p]
+    L.cut_shares.restype = None
+    L.item_blocks.argtypes = [C.c_int, C.c_void_p, C.c_int, C.c_int]
     L.bin_in_lds.argtypes = [C.c_int, C.c_int64, C.c_int64]
     L.disc_form.argtypes = [C.c_double, C.c_double, C.c_int, C.c_int]
     return L

@@ -1,6 +1,8 @@
 """Host rules against plain models, without a GPU."""
 import itertools
+import random
 
+import numpy as np
 import pytest
 
 from tests.rules import lib
@@ -64,3 +66,41 @@ def test_one_workgroup_bins_a_keyframe_only_where_that_is_little_work():
     assert lds(1, 1200, 1564) and lds(1, 15360, 3072) and not lds(1, 15361, 10)
     assert not lds(1, 8160, 3073) and not lds(8, 15252, 15252) and not lds(11, 3600, 4641)
     assert lds(12, 3600, 4641) and lds(64, 1200, 6400) and not lds(64, 1200, 6401) and not lds(12, 15361, 1)
+
+
+def _cut(nq, items, nbr, fixed):
+    base = np.concatenate([[0], np.cumsum(items)])
+    kfs = np.ascontiguousarray(np.stack([items, nbr, base[:-1]], 1).astype(np.int32))
+    out = np.full(2 * nq, -1, np.int32)
+    lib().cut_shares(nq, kfs.ctypes.data, len(items), fixed, out.ctypes.data)
+    return out, int(base[-1])
+
+
+@pytest.mark.parametrize("nq", [1, 8])
+@pytest.mark.parametrize("fixed", [0.5, 1.0])
+def test_item_runs_cover_every_item_once_in_equal_work(nq, fixed):
+    """Runs are ordered, meet and cover the items; none is heavier than its
+    part of the work by more than one item; the grid of workgroups takes every
+    item exactly once."""
+    rng = random.Random(nq)
+    lists = [[1], [0], [7], [8], [0, 0, 0], [5, 0, 0, 3], [1] * 9, [3000, 1, 1, 1], [1, 1, 3000], [5000] * 3]
+    lists += [[rng.randint(0, 10 ** rng.randint(1, 3)) for _ in range(rng.randint(1, 40))] for _ in range(40)]
+    for items in lists:
+        nbr = [rng.randint(1, 16) for _ in items]
+        out, total = _cut(nq, items, nbr, fixed)
+        begin, end = out[::2], out[1::2]
+        assert begin[0] == 0 and end[-1] == total and (begin[1:] == end[:-1]).all() and (begin <= end).all()
+        work = np.repeat(np.array(nbr, float) + fixed, items)
+        at = np.concatenate([[0.0], np.cumsum(work)])
+        heavy = np.max(work, initial=0.0)
+        assert (at[end] - at[begin] <= at[-1] / nq + heavy + 1e-6 * at[-1]).all()
+        for wpb in (1, 4):
+            blocks = lib().item_blocks(nq, out.ctypes.data, total, wpb)
+            seen = np.zeros(total + wpb, int)
+            for b in range(blocks):
+                if nq == 8:
+                    first, last = begin[b % 8] + b // 8 * wpb, end[b % 8]
+                else:
+                    first, last = b * wpb, total
+                seen[first:max(first, min(first + wpb, last))] += 1
+            assert (seen[:total] == 1).all() and (seen[total:] == 0).all()
