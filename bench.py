@@ -73,9 +73,9 @@ def parse():
     ap.add_argument("--no-autotune", action="store_true",
                     help="time the library's default plan instead of the autotuned one")
     ap.add_argument("--plan", default="",
-                    help="GN mapping TXxTY:K[:P[:X]] (surfels per group, groups per work item, "
-                         "persistent grid 0/1, XCD queues or shares 0/1; P and X default to 1), "
-                         "e.g. 2x4:2 or 4x4:1:0:1")
+                    help="GN mapping TXxTY:K[:W[:X]] (surfels per group, groups per work item, wavefronts per "
+                         "CU of a persistent grid or 0 for one per work item, XCD shares 0/1; W defaults "
+                         "to 0, X to 1), e.g. 2x4:2 or 4x4:1:0:1")
     ap.add_argument("--calibrate-copy-mib", type=int, default=0,
                     help="run one device-to-device copy of this many MiB first (a kernel of "
                          "known traffic for scaling the HBM counters)")
@@ -379,12 +379,12 @@ def main():
     if args.plan:
         fields = args.plan.split(":")
         tx, ty = (int(v) for v in fields[0].split("x"))
-        pers = int(fields[2]) if len(fields) > 2 else 1
+        waves = int(fields[2]) if len(fields) > 2 else 0
         xq = int(fields[3]) if len(fields) > 3 else 1
-        plan = sg.plan(tx, ty, pers, 0, 0, xq, groups=int(fields[1]))
+        plan = sg.plan(tx, ty, int(waves > 0), waves, 0, xq, groups=int(fields[1]))
     elif not args.no_autotune:
         # the mapping the autotuner picks for this batch (every tile layout,
-        # groups per item, persistent grid or not, XCD queues or shares or not)
+        # groups per item, XCD shares or not)
         items = sg.batch_array([d.item(render=False, init=False) for d in dks])
         plan = engine.autotune(ctx, items, len(dks), prm)
         log("autotuned plan", plan.as_dict())

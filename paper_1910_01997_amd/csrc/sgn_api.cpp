@@ -196,7 +196,6 @@ void describe_keyframe(const sgn_keyframe& kf, const sgn_surfels& s, KfDev& D) {
     D.n_nbr = kf.n_nbr;
     D.nbr_pitch_b = kf.n_nbr > 0 ? kf.nbr[0].pitch * (int32_t)dtype_size(kf.kf.dtype) : 0;
     D.fx = (float)kf.K.fx; D.fy = (float)kf.K.fy; D.cx = (float)kf.K.cx; D.cy = (float)kf.K.cy;
-    D.fx_d = kf.K.fx; D.fy_d = kf.K.fy; D.cx_d = kf.K.cx; D.cy_d = kf.K.cy;
     D.kf_scale = kf.kf.scale;
     D.img_scale = kf.n_nbr > 0 ? kf.nbr[0].scale : 1.f;
 }
@@ -429,10 +428,9 @@ bool rows_by_index(const sgn_batch_item* items, int n) {
     return true;
 }
 
-int persistent_grid(sgn_ctx* c, const GnVariant& v, const sgn_plan& plan) {
-    int per_cu = plan.waves_per_cu > 0 ? std::max(1, plan.waves_per_cu / 4) : gn_blocks_per_cu(v);
-    if (per_cu < 1) per_cu = 1;
-    return std::max(1, c->cus) * per_cu;
+// Workgroups of a bounded persistent grid (four wavefronts each).
+int persistent_grid(const sgn_ctx* c, const sgn_plan& plan) {
+    return std::max(1, c->cus) * std::max(1, plan.waves_per_cu / 4);
 }
 
 // Keyframe order of a batch: bound to nq shares by greedy load balance (the
@@ -677,7 +675,7 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
         if (st) return st;
         dH = (const BatchHeader*)(dev + L.hdr_off);
     }
-    const int gn_grid = plan.persistent ? persistent_grid(c, var, plan) : item_blocks(nq, H->queues, item_base, kBlockThreads / kWaveSize);
+    const int gn_grid = plan.persistent ? persistent_grid(c, plan) : item_blocks(nq, H->queues, item_base, kBlockThreads / kWaveSize);
     hipError_t e = hipSuccess;
     if (init_waves > 0) e = launch_init(one.one, dH, (int)init_waves, c->stream);
     if (e == hipSuccess && fl.gn && item_base > 0) {
@@ -1193,7 +1191,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     if (n < 1 || !items || !inv_depth_outs) return fail(SGN_E_INVALID, "empty batch or null array");
     if (n > SGN_MAX_BATCH) return fail(SGN_E_UNSUPPORTED, "more keyframes than SGN_MAX_BATCH");
     std::vector<DiscRenderItem> tab(n);
-    int64_t total_surfels = 0, total_pixels = 0, total_tiles = 0;
+    int64_t total_surfels = 0, total_tiles = 0;
     int64_t most_tiles = 0, most_surfels = 0;
     for (int i = 0; i < n; ++i) {
         const sgn_disc_item* it = &items[i];
@@ -1210,13 +1208,11 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
         r.count = it->count;
         r.width = it->kf.kf.width; r.height = it->kf.kf.height;
         r.surfel_base = (int32_t)total_surfels;
-        r.pixel_base = total_pixels;
         r.radius = it->radius;
         r.fx = it->kf.K.fx; r.fy = it->kf.K.fy; r.cx = it->kf.K.cx; r.cy = it->kf.K.cy;
         r.tiles_x = (r.width + kRenderTile - 1) / kRenderTile;
         r.tile_base = (int32_t)total_tiles;
         total_surfels += it->count;
-        total_pixels += (int64_t)r.width * r.height;
         const int64_t tiles = (int64_t)r.tiles_x * ((r.height + kRenderTile - 1) / kRenderTile);
         total_tiles += tiles;
         most_tiles = std::max(most_tiles, tiles);

@@ -51,8 +51,7 @@ struct KfDev {
     int32_t init_wave, render_wave;
     FastDiv div_gw, div_bx;       // by gw; by the 4-pixel blocks of a row
     int32_t patch, nbr_pitch_b;                   // neighbour-image row pitch in bytes
-    double fx_d, fy_d, cx_d, cy_d;               // intrinsics as given (double)
-    float fx, fy, cx, cy;                        // the same, rounded to float
+    float fx, fy, cx, cy;                        // intrinsics, rounded to float
     float kf_scale, img_scale, pad0, pad1;
     // disc surfels (Eq. 4): centres of the surfels, radius in pixels; null
     // and 0 for tiles
@@ -226,7 +225,7 @@ hipError_t launch_stage(const void* host, void* dev, int n16, const FrameIn* in,
                         uint32_t* counters, hipStream_t s);
 hipError_t launch_init(const LoneKf& one, const BatchHeader* hdr, int waves, hipStream_t s);
 hipError_t launch_render(const LoneKf& one, const BatchHeader* hdr, int waves, hipStream_t s);
-// The kernel's own start and end go to the two events.
+// The two events are recorded on the stream before and after the kernel.
 hipError_t launch_gn(const GnVariant& v, const LoneBatch& one, const BatchHeader* hdr, uint32_t* counters,
                      int grid_blocks, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 // Device address of the static scratch array on `device` (which must be the
@@ -261,8 +260,7 @@ hipError_t launch_disc_gn(int dtype, const DiscForm& form, const LoneBatch& one,
                           int total_items, int grid_blocks, bool by_row, float max_radius, int max_nbr, hipStream_t s,
                           hipEvent_t start, hipEvent_t stop);
 // Depth-buffered render of the discs of several keyframes: one table entry
-// per keyframe (device memory); the scratch holds one 64-bit depth key and
-// one index per pixel of every keyframe, keyframe after keyframe.
+// per keyframe (device memory; null for one keyframe, `one`).
 struct DiscRenderItem {
     const float* inv_depth;
     const float* nx;
@@ -274,7 +272,6 @@ struct DiscRenderItem {
     float* inv_depth_out;         // [width * height]
     int32_t* index_out;           // [width * height] or null
     int32_t count, width, height, surfel_base;
-    int64_t pixel_base;
     float radius;
     int32_t tiles_x;              // render tiles per row (kRenderTile pixels square)
     double fx, fy, cx, cy;
@@ -355,8 +352,6 @@ hipError_t launch_disc_transfer(const DiscTransferArgs* pairs, const DiscTransfe
                                 hipStream_t s);
 hipError_t launch_quantize(const float* src, int src_pitch, void* dst, int dst_pitch,
                            int width, int height, int dtype, float scale, hipStream_t s);
-// Workgroups of 256 threads of the chosen GN variant that fit on one CU.
-int gn_blocks_per_cu(const GnVariant& v);
 bool gn_variant_supported(const GnVariant& v);
 
 }  // namespace sgn

@@ -597,12 +597,6 @@ __device__ __forceinline__ Lerp lerp_words(const TapWords& w, unsigned col, floa
     return l;
 }
 
-template <typename T, bool BY_ROW>
-__device__ __forceinline__ Lerp sample_rows(__amdgpu_buffer_rsrc_t rs, unsigned row, unsigned col,
-                                            unsigned pitch_b, float ax) {
-    return lerp_words<T>(load_words<T, BY_ROW>(rs, row, col, pitch_b), col, ax);
-}
-
 // floor(x) converted to int in one instruction (v_cvt_flr_i32_f32).
 __device__ __forceinline__ int cvt_floor(float x) {
     int r;
@@ -2399,12 +2393,13 @@ static void* gn_pick_deep(const GnVariant& v) {
     return v.deep == 2 ? gn_ptr<T, 4, 4, 4, 1, R, false, 2>() : gn_ptr<T, 4, 4, 4, 1, R, false, 1>();
 }
 
-// the form for large grids
+// the form for large grids (f32 always has a frame's taps in flight)
 template <typename T, bool R>
 static void* gn_pick_shared(const GnVariant& v) {
-    if (v.patch == 16)
-        return v.deep ? (void*)&gn_shared_kernel<T, 16, 1, 1, R, 1> : (void*)&gn_shared_kernel<T, 16, 1, 1, R, 0>;
-    return v.deep ? (void*)&gn_shared_kernel<T, 4, 4, 4, R, 1> : (void*)&gn_shared_kernel<T, 4, 4, 4, R, 0>;
+    if constexpr (!std::is_same<T, float>::value)
+        if (!v.deep)
+            return v.patch == 16 ? (void*)&gn_shared_kernel<T, 16, 1, 1, R, 0> : (void*)&gn_shared_kernel<T, 4, 4, 4, R, 0>;
+    return v.patch == 16 ? (void*)&gn_shared_kernel<T, 16, 1, 1, R, 1> : (void*)&gn_shared_kernel<T, 4, 4, 4, R, 1>;
 }
 
 template <typename T, bool R>
@@ -2428,14 +2423,6 @@ static void* gn_select(const GnVariant& v) {
 }
 
 bool gn_variant_supported(const GnVariant& v) { return gn_select(v) != nullptr; }
-
-int gn_blocks_per_cu(const GnVariant& v) {
-    void* f = gn_select(v);
-    if (!f) return 0;
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, kBlockThreads, 0) != hipSuccess) return 0;
-    return n;
-}
 
 // A kernel between the two timing events.  Recorded events: the launch that
 // carries its own (hipExtLaunchKernel) took 6-7 us longer alone.

@@ -430,16 +430,16 @@ class HipExecutor(Executor):
         # pixel, or 4 lanes of four pixels), so a request's result is the
         # same, bitwise, alone and in any mix
         if pixels_per_lane == 4:
-            self.small_plan = sg.plan(4, 4, 1, 0, 0, 1, groups=1)
             self.single_plan = sg.plan(4, 4, 0, 0, 0, 0, groups=1)
             # one wavefront per work item, the items split into one share
-            # per XCD (batches of four items per CU or more); the small
-            # plan's persistent grid, unbounded, is this grid too
-            self.large_plan = sg.plan(4, 4, 0, 0, 0, 1, groups=1)
+            # per XCD (batches of four items per CU or more)
+            self.small_plan = self.large_plan = sg.plan(4, 4, 0, 0, 0, 1, groups=1)
         elif pixels_per_lane == 1:
-            self.small_plan = sg.plan(2, 2, 1, 0, 0, 1, groups=1)
+            # a small batch cannot fill the device with four groups per
+            # work item
+            self.small_plan = sg.plan(2, 2, 0, 0, 0, 1, groups=1)
             self.single_plan = sg.plan(2, 2, 0, 0, 0, 0, groups=1)
-            self.large_plan = sg.plan(2, 2, 1, 0, 0, 1, groups=4)
+            self.large_plan = sg.plan(2, 2, 0, 0, 0, 1, groups=4)
         else:
             raise ValueError("pixels_per_lane is 1 or 4")
         self.small_batch_surfels = 200_000
@@ -494,8 +494,6 @@ class HipExecutor(Executor):
             else:
                 plan = self.plan
                 if plan is None:
-                    # a small batch cannot fill the device with four groups per
-                    # work item: use one group per wavefront there
                     total = sum(self.streams[r.stream].dk.n_surfels for r in batch)
                     plan = self.small_plan if total < self.small_batch_surfels else self.large_plan
                 arr = self.sg.batch_array(items)
