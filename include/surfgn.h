@@ -38,8 +38,9 @@
  *     per call; about 2 MB on the device and four times that in pinned host
  *     staging memory), the work-queue counters and timing events.  sgn_create
  *     allocates all of it; no other call allocates device or pinned memory.
- *     A call for one keyframe (or keyframe pair) passes its descriptors in
- *     its kernels' arguments and uses no table.
+ *     A call for one keyframe (or keyframe pair, or up to eleven pairs of a
+ *     disc transfer) passes its descriptors in its kernels' arguments and uses
+ *     no table, unless its plan bounds a persistent grid.
  *   - Calls that need scratch memory (re-gridding, disc render and
  *     placement, the autotuner's state snapshot) take a caller-provided
  *     workspace `ws` of `ws_bytes` bytes: device memory, 256-byte aligned, at
@@ -240,12 +241,10 @@ sgn_status sgn_render_inverse_depth(sgn_ctx* ctx, const sgn_keyframe* kf,
                                     int32_t* index_out);
 
 /* The whole per-keyframe update for many keyframes at once: initialisation
- * of new surfels, the Gauss-Newton iterations in one fused kernel launch,
- * and the
- * inverse-depth render.  All
- * items must share patch and image dtype.  Results equal those of the
- * per-keyframe calls for the same plan (each surfel is reduced in a fixed
- * order that does not depend on the batch). */
+ * of new surfels, the Gauss-Newton iterations in one fused kernel launch and
+ * the inverse-depth render.  All items must share patch and image dtype.
+ * Results equal those of the per-keyframe calls for the same plan (each surfel
+ * is reduced in a fixed order that does not depend on the batch). */
 sgn_status sgn_optimize_batch(sgn_ctx* ctx, const sgn_batch_item* items, int32_t n_items,
                               const sgn_params* params, const sgn_plan* plan /* NULL: default */);
 

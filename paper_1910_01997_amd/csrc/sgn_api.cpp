@@ -497,7 +497,11 @@ double mean_image_bytes(const sgn_batch_item* items, int n) {
 //              640x480 images (4.3 MB a keyframe), 2.02 / 2.07 with 1280x720
 //              (16.6 MB), 16 x 16 surfels 1.54 / 1.50 with the former; the
 //              64-keyframe batch (104,000 items) f16 3.76 / 3.92, f32 3.91 /
-//              4.30, u8 3.98 / 3.83.
+//              4.30, u8 3.98 / 3.83.  (Uniform batches of six sizes from
+//              4.3 to 24.7 MB, w 8 to 110: one frame is ahead by 1-4 % from
+//              w = 55 at 9.4 MB and more, behind by 1-4 % at 4.3 MB at every
+//              w; from w = 24 to 48 by 2-4 % with eight neighbours and behind
+//              by 1-3 % with five to seven.)
 // 16 x 16 surfels are not split: two frames in flight to w = 1.75 (97 us
 // against 111 at 1,200 items).  The damped variant evaluates each candidate
 // besides; its lines, at the same grids: four lanes to w = 0.75 (106 us
@@ -688,7 +692,11 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
 }
 
 // Upload of a caller's table of n entries: *dev is its device copy, or null
-// for a single entry, which travels with the launch.
+// for a single entry, which travels with the launch.  (By a kernel, not a copy
+// command: waited for one at a time, disc transfers of 12 to 48 pairs take 20.5
+// to 21.9 us of 160x120 against 22.6-23.8; queued back to back, where the host
+// bounds small ones, 11.9-12.7 against 11.6-12.0, and of 640x480 12.3-13.0
+// against 13.3-13.9.)
 template <typename T>
 sgn_status upload_table(sgn_ctx* c, const T* tab, int n, const T** dev) {
     *dev = nullptr;
@@ -731,8 +739,8 @@ double disc_slots(const sgn_disc_item* items, int n, int dtype) {
 }
 
 // Disc surfels: descriptor table (one KfDev per keyframe; its items are runs
-// of disc_surfels_per_wave(dtype) surfels), frame constants, then one
-// wavefront per item.
+// of disc_surfels_per_wave(dtype) surfels), frame constants, then one launch of
+// the form that disc_form picks.
 sgn_status run_disc_batch(sgn_ctx* c, const sgn_disc_item* items, int n, const sgn_params* prm) {
     if (n < 1) return fail(SGN_E_INVALID, "empty batch");
     if (!items) return fail(SGN_E_INVALID, "null items");

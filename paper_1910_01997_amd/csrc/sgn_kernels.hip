@@ -1074,11 +1074,13 @@ __device__ __forceinline__ void split_cost(const float* __restrict__ pc, cptr<Fr
 // reads the neighbour rows by index (row pitches below kMaxRowStride).
 //
 // Wavefronts per SIMD each plan's kernel is compiled for (the register
-// budget: 72 VGPRs for seven, 80 for six, 96 for five).  Occupancy pays: on
-// the 64-keyframe f16 batch, undamped, the 4x4 one-group kernel takes 4.69 ms at four,
-// 4.30 at five, 3.94 at six and 3.76 at seven (its 11-12 spilled words are
-// stored and reloaded once per work item, or in the damped variant's
-// branches); at eight, with spills inside the iteration loop, 4.05 ms.
+// budget: 72 VGPRs for seven, 80 for six, 96 for five).  One sample at a time
+// and one group, four pixels per lane, is the form of large damped batches: 64
+// mixed u8 keyframes take 8.00 ms at five, 8.07 at six, 7.92 at seven and 8.65
+// at eight, where it spills inside the iteration loop; 32 of 16 x 16 surfels
+// 2.72, 2.71, 2.65, 2.71.  Undamped, in the plans of fewer pixels per lane, and
+// in bounded persistent grids occupancy pays more (f16 4x4 one group 4.69 ms at
+// four, 4.30 at five, 3.94 at six, 3.76 at seven, 4.05 at eight).
 // The DEEP forms keep more samples in registers: two frames of four pixels
 // take 125 VGPRs (four wavefronts), one frame 96 (five), the SPLIT forms 92
 // and, damped, up to 129 (the two-lane form's terms leave LDS for three
