@@ -2,6 +2,7 @@
 // the HIP kernels (sgn_kernels.hip).  Not part of the public interface.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include <hip/hip_runtime.h>
@@ -51,8 +52,11 @@ struct KfDev {
     int32_t init_wave, render_wave;
     FastDiv div_gw, div_bx;       // by gw; by the 4-pixel blocks of a row
     int32_t patch, nbr_pitch_b;                   // neighbour-image row pitch in bytes
+    // what follows in one cache line, the entry in four (16 mixed disc
+    // keyframes: 2.04 ms, 2.06 packed to 216 bytes)
+    int32_t pad[10];
     float fx, fy, cx, cy;                        // intrinsics, rounded to float
-    float kf_scale, img_scale, pad0, pad1;
+    float kf_scale, img_scale;
     // disc surfels (Eq. 4): centres of the surfels, radius in pixels; null
     // and 0 for tiles
     const float* disc_ux;
@@ -60,6 +64,7 @@ struct KfDev {
     float disc_r;
     int32_t disc_count;           // surfels of the keyframe (an item is a run of them)
 };
+static_assert(sizeof(KfDev) == 256 && offsetof(KfDev, fx) >= 192, "cache lines");
 
 // Per-neighbour-frame constants of Eq. 6, in device memory or in a lone
 // keyframe's kernel arguments.
