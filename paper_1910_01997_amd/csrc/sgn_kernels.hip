@@ -486,9 +486,10 @@ __device__ __forceinline__ void stage_pair_words(cptr<FrameDev> frames, int nf, 
 // The loads run only for samples whose corner passed the validity test
 // (x0 < W - 1, y0 < H - 1), so every tap lies inside the image; but the second
 // dword of an f16 or u8 load at the row's end can be the one after the image's
-// last.  Raw loads are checked against the image's bytes dword by dword,
-// structured ones only by row: the host takes them where that dword is mapped
-// memory (rows_by_index_safe).  Its value is not used.
+// last.  Raw loads are checked dword by dword against the image's bytes (of its
+// last row the width, not the pitch: the memory may end there), structured
+// ones only by row: the host takes them where that dword is mapped memory
+// (rows_by_index_safe).  Its value is not used.
 struct Taps {
     float i00, i01, i10, i11;
 };
@@ -498,11 +499,12 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t image_rsrc(const void* img, unsigned nbytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(img), (short)0, (int)nbytes, 0x00020000);
 }
-template <bool BY_ROW>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t image_rsrc_for(const void* img, unsigned pitch_b,
-                                                                 unsigned rows) {
-    if constexpr (BY_ROW) return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(img), (short)pitch_b, (int)rows, 0x00020000);
-    else return image_rsrc(img, pitch_b * rows);
+template <typename T, bool BY_ROW>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t image_rsrc_for(const void* img, unsigned pitch_b, unsigned wm1,
+                                                                 unsigned hm1) {
+    if constexpr (BY_ROW)
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(img), (short)pitch_b, (int)(hm1 + 1), 0x00020000);
+    else return image_rsrc(img, (unsigned)image_end((int)wm1 + 1, (int)hm1 + 1, pitch_b, (int)sizeof(T)));
 }
 // buffer_load_dwordx2 ... idxen offen: base + index x stride + offset + soffset
 __device__ u32x2 struct_buffer_load_b64(__amdgpu_buffer_rsrc_t rsrc, int vindex, int voffset, int soffset,
@@ -704,7 +706,7 @@ __device__ __forceinline__ void frame_loop_px(const float* __restrict__ pc, cptr
             const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
             const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
             const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
-            const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
+            const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<T, BY_ROW>(fr[f].img, pitch_b, wm1, hm1);
             // Eq. 6 in local coordinates
             float nxq = fmaf(c0.x, dx, fmaf(c0.y, dy, fmaf(c0.z, idu0, c0.w)));
             float nyq = fmaf(c1.x, dx, fmaf(c1.y, dy, fmaf(c1.z, idu0, c1.w)));
@@ -794,7 +796,7 @@ __device__ __forceinline__ void frame_cost(const float* __restrict__ pc, cptr<Fr
             const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
             const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
             const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
-            const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
+            const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<T, BY_ROW>(fr[f].img, pitch_b, wm1, hm1);
             const float nxq = fmaf(c0.x, dx, fmaf(c0.y, dy, fmaf(c0.z, idu, c0.w)));
             const float nyq = fmaf(c1.x, dx, fmaf(c1.y, dy, fmaf(c1.z, idu, c1.w)));
             const float qz = fmaf(h6, dx, fmaf(h7, dy, fmaf(k2, idu, c2.x)));
@@ -1005,7 +1007,7 @@ __device__ __forceinline__ void split_cost(const float* __restrict__ pc, cptr<Fr
                 const float4 c1 = *(const float4*)(pc + f * kPairWords + 4);
                 const float4 c2 = *(const float4*)(pc + f * kPairWords + 8);
                 const float h6 = fr[f].zrow[0], h7 = fr[f].zrow[1], k2 = fr[f].zrow[2];
-                const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<BY_ROW>(fr[f].img, pitch_b, hm1 + 1);
+                const __amdgpu_buffer_rsrc_t rs = image_rsrc_for<T, BY_ROW>(fr[f].img, pitch_b, wm1, hm1);
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
                     const float nxq = fmaf(c0.x, dx, fmaf(c0.y, dy[j], fmaf(c0.z, idu[j], c0.w)));

@@ -19,8 +19,9 @@ inline size_t tap_reach(int width, int height, size_t pitch_b, int elem_bytes) {
     const size_t col = (size_t)(width - 2) * elem_bytes;
     return (size_t)(height - 1) * pitch_b + (elem_bytes == 4 ? col : col & ~size_t(3)) + 8;
 }
-// One past the image's last dword.
-inline size_t image_end(int width, int height, size_t pitch_b, int elem_bytes) {
+// One past the image's last dword (the size that loads by byte offset are
+// checked against).
+constexpr size_t image_end(int width, int height, size_t pitch_b, int elem_bytes) {
     return (size_t)(height - 1) * pitch_b + (((size_t)width * elem_bytes + 3) & ~size_t(3));
 }
 

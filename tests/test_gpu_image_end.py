@@ -15,9 +15,11 @@ MB = 1 << 20
 FIELDS = ("inv_depth", "nx", "ny", "nz", "flags", "cost", "nvalid", "last_update")
 
 
-def _at_end_of_memory(images):
-    """The images copied to the end of a memory segment."""
-    n, size = images.numel() * images.element_size(), 12 * MB
+def _at_end_of_memory(images, pitch):
+    """The images copied to rows of `pitch` elements of which the last ends
+    with its width, at the end of a memory segment."""
+    k, h, w = images.shape
+    n, size = (((k * h) - 1) * pitch + w) * images.element_size(), 12 * MB
     assert n <= size
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
@@ -29,14 +31,15 @@ def _at_end_of_memory(images):
         kept.append(buf)
     else:
         raise AssertionError("no allocation ends its segment")
-    out = buf[size - n:].view(images.dtype).view(images.shape)
+    out = buf[size - n:].view(images.dtype).as_strided((k, h, w), (h * pitch, pitch, 1))
     out.copy_(images)
     return out
 
 
 @pytest.mark.parametrize("storage", ["f16", "u8"])
-@pytest.mark.parametrize("disc,lam", [(False, 0.0), (False, 1e-3), (True, 0.0)])
-def test_images_at_the_end_of_their_memory(storage, disc, lam):
+@pytest.mark.parametrize("disc,lam,pad", [(False, 0.0, 0), (False, 1e-3, 0), (True, 0.0, 0), (False, 0.0, 16),
+                                          (False, 1e-3, 64), (True, 0.0, 16)])
+def test_images_at_the_end_of_their_memory(storage, disc, lam, pad):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_1910_01997_amd import engine, surfgn as sg
@@ -47,14 +50,14 @@ def test_images_at_the_end_of_their_memory(storage, disc, lam):
         prm = sg.params(iters=8, lm_lambda=lam)
         got = []
         for end in (False, True):
-            print(f"case image end {storage} disc {disc} lambda {lam} at the end {end}", flush=True)
+            print(f"case image end {storage} disc {disc} lambda {lam} pitch + {pad} at the end {end}", flush=True)
             if disc:
                 d = engine.DiscKeyframe.from_scene(ctx, kf, make_disc_surfels(kf, radius=10.0), storage=storage)
                 img = d.img
             else:
                 d = img = engine.DeviceKeyframe.from_scene(ctx, kf, storage=storage, render=False)
             if end:
-                img.nbr_imgs = _at_end_of_memory(img.nbr_imgs)
+                img.nbr_imgs = _at_end_of_memory(img.nbr_imgs, img.width + pad)
                 img.view = sg.KeyframeView(img.kf_img, [img.nbr_imgs[i] for i in range(img.n_nbr)], img.R, img.t,
                                            img.K, img.patch, img.scale)
             if disc:
