@@ -74,7 +74,7 @@ def parse():
                     help="time the library's default plan instead of the autotuned one")
     ap.add_argument("--plan", default="",
                     help="GN mapping TXxTY:K[:W[:X]] (surfels per group, groups per work item, wavefronts per "
-                         "CU of a persistent grid or 0 for one per work item, XCD shares 0/1; W defaults "
+                         "CU of a persistent grid, below four one per work item, XCD shares 0/1; W defaults "
                          "to 0, X to 1), e.g. 2x4:2 or 4x4:1:0:1")
     ap.add_argument("--calibrate-copy-mib", type=int, default=0,
                     help="run one device-to-device copy of this many MiB first (a kernel of "
@@ -381,6 +381,7 @@ def main():
         tx, ty = (int(v) for v in fields[0].split("x"))
         waves = int(fields[2]) if len(fields) > 2 else 0
         xq = int(fields[3]) if len(fields) > 3 else 1
+        waves = waves if waves >= 4 else 0       # a workgroup is four wavefronts
         plan = sg.plan(tx, ty, int(waves > 0), waves, 0, xq, groups=int(fields[1]))
     elif not args.no_autotune:
         # the mapping the autotuner picks for this batch (every tile layout,
