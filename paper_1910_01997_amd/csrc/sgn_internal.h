@@ -15,7 +15,7 @@ constexpr int kMaxNbr = 16;
 constexpr int kWaveSize = 64;
 constexpr int kBlockThreads = 256;      // 4 wavefronts per workgroup
 constexpr int kNumCounters = 16;        // work-queue heads (one per XCD + spares)
-constexpr int kInitSurfels = 128;       // surfels a wavefront of the initialisation looks through
+constexpr int kInitSurfels = 128;       // most surfels that a wavefront of the initialisation looks through
 
 // Division of n < 2^24 by a divisor known on the host: m = ceil(2^(24 + l) / d)
 // with 2^l >= d, so that (n m) >> (24 + l) is exact.  Two instructions and a
@@ -47,7 +47,7 @@ struct KfDev {
     int32_t width, height, kf_pitch, n_nbr;
     int32_t gw, gh, frame_base, item_base;      // frames: [frame_base, frame_base + n_nbr)
     int32_t groups_x, n_items;                  // anchor blocks per row; work items
-    // first wavefront of the initialisation (kInitSurfels surfels each) and of
+    // first wavefront of the initialisation (init_run surfels each) and of
     // the render (64 blocks of 4 x 4 pixels each)
     int32_t init_wave, render_wave;
     FastDiv div_gw, div_bx;       // by gw; by the 4-pixel blocks of a row
@@ -119,7 +119,7 @@ struct BatchHeader {
     FrameDev* frames;
     int32_t n_kf, n_frames, total_items;
     int32_t init_waves, render_waves;   // of the batch
-    int32_t pad0;
+    int32_t init_run;                   // surfels per wavefront of the initialisation (a multiple of 64)
     int32_t iters;
     float huber_k;
     float kappa_fp64;

@@ -269,6 +269,7 @@ __global__ __launch_bounds__(256) void init_kernel(LoneKf, const BatchHeader* __
     const int lane = threadIdx.x & (kWaveSize - 1);
     __shared__ int s_new_[256 / kWaveSize][kInitSurfels];
     int* const s_new = s_new_[threadIdx.x >> 6];
+    const int run = hdr->init_run;
     for (int wv = grid_wave(); wv < hdr->init_waves; wv += grid_waves()) {
         // (keyframes without new surfels take no wavefront)
         int lo = 0, hi = hdr->n_kf - 1;
@@ -284,7 +285,8 @@ __global__ __launch_bounds__(256) void init_kernel(LoneKf, const BatchHeader* __
         wave_sync();                                       // the previous run's list is read
 #pragma unroll
         for (int h = 0; h < kInitSurfels / kWaveSize; ++h) {
-            const int k = (wv - K.init_wave) * kInitSurfels + h * kWaveSize + lane;
+            if (h * kWaveSize >= run) break;               // uniform
+            const int k = (wv - K.init_wave) * run + h * kWaveSize + lane;
             const bool fresh = k < gw * gh && K.is_new[min(k, gw * gh - 1)] != 0;
             const unsigned long long ball = __ballot(fresh);
             if (fresh) s_new[n_new + __popcll(ball & ((1ull << lane) - 1ull))] = k;
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(256) void init_kernel(LoneKf, const BatchHeader* __
         const float br2 = br * br;
         // a tile dx columns away has its nearest pixel at |dx| S - half from
         // u_s: none beyond floor((br + half) / S) can be closer than br
-        const int reach = (int)floorf((br + half) / (float)S);
+        const int reach = (int)fminf(floorf((br + half) / (float)S), (float)(gw + gh));
         float id_sum = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, rx = 0.f, ry = 0.f, rz = 0.f;
         int count = 0;
         // one neighbour tile (row ny, column nxt) in visiting order, with its
@@ -360,13 +362,21 @@ __global__ __launch_bounds__(256) void init_kernel(LoneKf, const BatchHeader* __
             for (int k = 0; k < 9; ++k)
                 if (in[k]) visit(ty - 1 + k / 3, tx - 1 + k % 3, nw[k], fl[k], idj[k], njx[k], njy[k], njz[k]);
         } else {
-            for (int ny = ty - reach; ny <= ty + reach; ++ny) {
-                if (ny < 0 || ny >= gh) continue;
-                for (int nxt = tx - reach; nxt <= tx + reach; ++nxt) {
-                    if (nxt < 0 || nxt >= gw) continue;
-                    const int j = ny * gw + nxt;
-                    if (j == i) continue;
-                    visit(ny, nxt, K.is_new[j], K.flags[j], K.inv_depth[j], K.nx[j], K.ny[j], K.nz[j]);
+            // one trip to memory per neighbour: its state at once, beside the
+            // next one's is_new byte
+            const int x0 = max(tx - reach, 0), x1 = min(tx + reach, gw - 1);
+            for (int ny = max(ty - reach, 0); ny <= min(ty + reach, gh - 1); ++ny) {
+                const int row = ny * gw;
+                uint8_t ahead = K.is_new[row + x0];
+                for (int nxt = x0; nxt <= x1; ++nxt) {
+                    const uint8_t nw = ahead;
+                    ahead = K.is_new[row + min(nxt + 1, x1)];
+                    if (nw) continue;                  // (so is the surfel itself)
+                    const int j = row + nxt;
+                    const uint32_t fl = K.flags[j];
+                    const float idj = K.inv_depth[j], njx = K.nx[j], njy = K.ny[j], njz = K.nz[j];
+                    __asm__ volatile("" ::"v"(fl), "v"(idj), "v"(njx), "v"(njy), "v"(njz));
+                    visit(ny, nxt, nw, fl, idj, njx, njy, njz);
                 }
             }
         }

@@ -42,6 +42,12 @@ bool rows_by_index_safe(uintptr_t data, int width, int height, size_t pitch_b, i
     return reach <= mapped_end(end - 1);
 }
 
+// Tiles to either side of its own that a new surfel's initialisation looks at.
+inline int init_reach(float beta_r, int patch) {
+    const float br = beta_r > 0.f ? beta_r : (float)patch;
+    return (int)std::min((br + 0.5f * (float)(patch - 1)) / (float)patch, 1e6f);
+}
+
 // Work queue (or run) q covers the global item range [begin, end).
 struct QueueDev {
     int32_t begin, end;

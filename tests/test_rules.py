@@ -104,3 +104,13 @@ def test_item_runs_cover_every_item_once_in_equal_work(nq, fixed):
                     first, last = b * wpb, total
                 seen[first:max(first, min(first + wpb, last))] += 1
             assert (seen[:total] == 1).all() and (seen[total:] == 0).all()
+
+
+def test_init_reach_counts_the_tiles_that_a_radius_meets():
+    for s in (4, 8, 16):
+        assert lib().init_reach(0.0, s) == 1 == lib().init_reach(float(s), s) and lib().init_reach(0.1, s) == 0
+        for br in (0.7 * s, 1.4 * s, 2.6 * s, 5.1 * s):
+            centre = (s - 1) / 2
+            met = max(t for t in range(9) if max(0.0, t * s - centre) < br)          # the tile t's nearest pixel
+            assert lib().init_reach(br, s) == met
+        assert lib().init_reach(3e38, s) > 16384
