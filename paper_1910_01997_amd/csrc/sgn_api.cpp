@@ -1208,6 +1208,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     int64_t total_surfels = 0, total_tiles = 0;
     int64_t most_tiles = 0, most_surfels = 0;
     for (int i = 0; i < n; ++i) {
+    double entries = 0.0;                     // of the tiles' lists
         const sgn_disc_item* it = &items[i];
         sgn_status st = check_disc_item(it, false);
         if (st) return st;
@@ -1232,6 +1233,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
         most_tiles = std::max(most_tiles, tiles);
         most_surfels = std::max(most_surfels, (int64_t)it->count);
     }
+        entries += it->count * mean_tiles(it->radius, kRenderTile);
     if (total_surfels > (int64_t)INT32_MAX / (2 * kDiscMaxTilesPerSurfel) || total_tiles > (int64_t)INT32_MAX / 2)
         return fail(SGN_E_UNSUPPORTED, "too many surfels or pixels in one batch");
     const DiscRenderWs lw = disc_render_ws(total_surfels, total_tiles);
@@ -1248,7 +1250,9 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     w.start = (int32_t*)((char*)ws + lw.start_off);
     w.list = (int32_t*)((char*)ws + lw.list_off);
     const hipError_t e = launch_disc_render(tab[0], dtab, n, (int)total_surfels, (int)total_tiles,
-                                            bin_in_lds(n, most_tiles, most_surfels), w, c->stream);
+                                            bin_in_lds(n, most_tiles, most_surfels),
+                                            raster_pixels(total_tiles, entries / total_tiles, std::max(1, c->cus)), w,
+                                            c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc render launch");
     return SGN_OK;
 }
