@@ -460,19 +460,17 @@ std::vector<int> share_order(int nq, const std::vector<int64_t>& work, const std
     return order;
 }
 
-// A keyframe's pixels and the bytes of its images, its own and its
-// neighbours', over the batch by pixels.
-void mean_images(const sgn_batch_item* items, int n, double* pixels, double* bytes) {
-    double p = 0.0, p2 = 0.0, b = 0.0;
+// Bytes of a keyframe's images, its own and its neighbours', over the batch by
+// pixels.
+double mean_image_bytes(const sgn_batch_item* items, int n) {
+    double bytes = 0.0, pixels = 0.0;
     for (int i = 0; i < n; ++i) {
         const sgn_keyframe& kf = items[i].kf;
         const double px = (double)kf.kf.width * kf.kf.height;
-        p += px;
-        p2 += px * px;
-        b += px * px * dtype_size(kf.kf.dtype) * (kf.n_nbr + 1);
+        bytes += px * px * dtype_size(kf.kf.dtype) * (kf.n_nbr + 1);
+        pixels += px;
     }
-    *pixels = p > 0.0 ? p2 / p : 0.0;
-    *bytes = p > 0.0 ? b / p : 0.0;
+    return pixels > 0.0 ? bytes / pixels : 0.0;
 }
 
 // The form of a four-pixels-per-lane kernel (the 4x4 layout of 4x4 surfels,
@@ -511,16 +509,17 @@ void mean_images(const sgn_batch_item* items, int n, double* pixels, double* byt
 // 1.5, three wavefronts per SIMD by their LDS (130 against four lanes' 139 at
 // 910, 151 / 214 unsplit at 1,530, but 225 / 217 at 1,900); it steps in
 // gn_kernel beyond: two frames in flight to w = 3 (f16 209 us against 246 for
-// one sample at a time at 1,900 items), then one or none (damped_one_frame).
+// one sample at a time at 1,900 items), one to w = 24 and for such images and
+// f32 beyond (f16 4.20 ms against 4.30 at 57,600 items of 1280x720, 16 x 16
+// surfels 3.73 / 3.93; f32 4.50 / 5.02), else one sample at a time (u8 4.32
+// against 4.39).
 void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_params* prm, GnVariant& v) {
     const bool four_px = v.patch == 16 || (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4);
     if (!four_px || v.persistent) return;
     const int64_t total = count_items(items, n, item_geo(v.patch, v.tiles_x, v.tiles_y, v.groups));
     const double w = (double)total / (4.0 * std::max(1, c->cus));
     v.damped = prm->lm_lambda > 0.f;
-    double pixels, bytes;
-    mean_images(items, n, &pixels, &bytes);
-    const bool far_taps = v.dtype == SGN_F32 || (v.dtype == SGN_F16 && bytes > 8e6);
+    const bool far_taps = v.dtype == SGN_F32 || (v.dtype == SGN_F16 && mean_image_bytes(items, n) > 8e6);
     if (v.patch == 4 && w <= (v.damped ? 0.75 : 0.65)) {
         v.split = 4; v.deep = 4; v.tiles_x = 2; v.tiles_y = 2;
     } else if (v.patch == 4 && w <= (v.damped ? 1.5 : 2.5)) {
@@ -528,7 +527,7 @@ void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn
     } else if (w <= (v.damped ? 3.0 : 1.75)) {
         v.deep = 2;
     } else if (v.damped) {
-        v.deep = damped_one_frame(w, v.patch, pixels, bytes, bytes / (pixels * dtype_size(v.dtype)) - 1.0, far_taps);
+        v.deep = w <= 24.0 || far_taps;
     } else {
         v.shared = 1;
         v.deep = w <= 3.0 || v.dtype == SGN_F32 || (far_taps && w > 24.0);
@@ -607,12 +606,12 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     std::vector<int> share_of;
     const std::vector<int> order = share_order(nq, work, n_nbr, share_of);
 
+    int frame_base = 0, item_base = 0;
     // Each wavefront of the initialisation compacts its run's new surfels to a
     // lane each.  Where the radius reaches past the adjacent tiles a surfel's chain
     // of neighbours is long, and a second round of lanes doubles it: 640x480, 4x4
     // surfels, half of them new, radius 5.1 S 121 us with runs of 128, 50 with 64.
     const int init_run = init_reach(prm->beta_r, patch) > 1 ? kWaveSize : kInitSurfels;
-    int frame_base = 0, item_base = 0;
     int64_t init_waves = 0, render_waves = 0;
     for (int oi = 0; oi < n; ++oi) {
         const int i = order[oi];
@@ -649,8 +648,8 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     H->n_frames = total_frames;
     H->total_items = item_base;
     H->init_waves = (int32_t)init_waves;
-    H->init_run = init_run;
     H->render_waves = (int32_t)render_waves;
+    H->init_run = init_run;
     H->iters = prm->iters;
     H->huber_k = prm->huber_k;
     H->kappa_fp64 = prm->kappa_fp64;
@@ -1208,7 +1207,6 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     std::vector<DiscRenderItem> tab(n);
     int64_t total_surfels = 0, total_tiles = 0;
     int64_t most_tiles = 0, most_surfels = 0;
-    double entries = 0.0;                     // of the tiles' lists
     for (int i = 0; i < n; ++i) {
         const sgn_disc_item* it = &items[i];
         sgn_status st = check_disc_item(it, false);
@@ -1233,7 +1231,6 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
         total_tiles += tiles;
         most_tiles = std::max(most_tiles, tiles);
         most_surfels = std::max(most_surfels, (int64_t)it->count);
-        entries += it->count * mean_tiles(it->radius, kRenderTile);
     }
     if (total_surfels > (int64_t)INT32_MAX / (2 * kDiscMaxTilesPerSurfel) || total_tiles > (int64_t)INT32_MAX / 2)
         return fail(SGN_E_UNSUPPORTED, "too many surfels or pixels in one batch");
@@ -1251,9 +1248,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     w.start = (int32_t*)((char*)ws + lw.start_off);
     w.list = (int32_t*)((char*)ws + lw.list_off);
     const hipError_t e = launch_disc_render(tab[0], dtab, n, (int)total_surfels, (int)total_tiles,
-                                            bin_in_lds(n, most_tiles, most_surfels),
-                                            raster_pixels(total_tiles, entries / total_tiles, std::max(1, c->cus)), w,
-                                            c->stream);
+                                            bin_in_lds(n, most_tiles, most_surfels), w, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc render launch");
     return SGN_OK;
 }
