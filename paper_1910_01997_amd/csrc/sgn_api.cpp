@@ -606,12 +606,12 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     std::vector<int> share_of;
     const std::vector<int> order = share_order(nq, work, n_nbr, share_of);
 
-    int frame_base = 0, item_base = 0;
     // Each wavefront of the initialisation compacts its run's new surfels to a
     // lane each.  Where the radius reaches past the adjacent tiles a surfel's chain
     // of neighbours is long, and a second round of lanes doubles it: 640x480, 4x4
     // surfels, half of them new, radius 5.1 S 121 us with runs of 128, 50 with 64.
     const int init_run = init_reach(prm->beta_r, patch) > 1 ? kWaveSize : kInitSurfels;
+    int frame_base = 0, item_base = 0;
     int64_t init_waves = 0, render_waves = 0;
     for (int oi = 0; oi < n; ++oi) {
         const int i = order[oi];
@@ -648,8 +648,8 @@ sgn_status run_batch(sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_p
     H->n_frames = total_frames;
     H->total_items = item_base;
     H->init_waves = (int32_t)init_waves;
-    H->render_waves = (int32_t)render_waves;
     H->init_run = init_run;
+    H->render_waves = (int32_t)render_waves;
     H->iters = prm->iters;
     H->huber_k = prm->huber_k;
     H->kappa_fp64 = prm->kappa_fp64;
@@ -1207,6 +1207,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     std::vector<DiscRenderItem> tab(n);
     int64_t total_surfels = 0, total_tiles = 0;
     int64_t most_tiles = 0, most_surfels = 0;
+    double entries = 0.0;                     // of the tiles' lists
     for (int i = 0; i < n; ++i) {
         const sgn_disc_item* it = &items[i];
         sgn_status st = check_disc_item(it, false);
@@ -1231,6 +1232,7 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
         total_tiles += tiles;
         most_tiles = std::max(most_tiles, tiles);
         most_surfels = std::max(most_surfels, (int64_t)it->count);
+        entries += it->count * mean_tiles(it->radius, kRenderTile);
     }
     if (total_surfels > (int64_t)INT32_MAX / (2 * kDiscMaxTilesPerSurfel) || total_tiles > (int64_t)INT32_MAX / 2)
         return fail(SGN_E_UNSUPPORTED, "too many surfels or pixels in one batch");
@@ -1248,7 +1250,9 @@ sgn_status sgn_disc_render_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t
     w.start = (int32_t*)((char*)ws + lw.start_off);
     w.list = (int32_t*)((char*)ws + lw.list_off);
     const hipError_t e = launch_disc_render(tab[0], dtab, n, (int)total_surfels, (int)total_tiles,
-                                            bin_in_lds(n, most_tiles, most_surfels), w, c->stream);
+                                            bin_in_lds(n, most_tiles, most_surfels),
+                                            raster_pixels(total_tiles, entries / total_tiles, std::max(1, c->cus)), w,
+                                            c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc render launch");
     return SGN_OK;
 }

@@ -298,8 +298,9 @@ struct DiscRenderScratch {
     int32_t* start;
     int32_t* list;
 };
+// px: pixels per lane of the raster (raster_pixels).
 hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items, int total_surfels,
-                              int total_tiles, bool bin_lds, const DiscRenderScratch& w, hipStream_t s);
+                              int total_tiles, bool bin_lds, int px, const DiscRenderScratch& w, hipStream_t s);
 // The search for empty areas on the lattice (spacing/2 + i spacing, ...),
 // placement of the qualifying candidates as surfels first .. and their
 // neighbour initialisation from the index map.

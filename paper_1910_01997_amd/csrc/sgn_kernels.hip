@@ -2974,8 +2974,8 @@ __global__ __launch_bounds__(disc_threads(WAVES)) __attribute__((amdgpu_waves_pe
 //
 // The render works in screen tiles of kRenderTile x kRenderTile pixels.  The
 // usable surfels are binned to the tiles their disc's bounding box meets (a
-// count per tile, a range of the list for each, a fill); then a wavefront per
-// tile, four pixels per lane, walks the tile's list keeping the largest value
+// count per tile, a range of the list for each, a fill); then a wavefront or
+// four per tile walk the tile's list keeping, for each pixel, the largest value
 // and the lowest index that reaches it.  The outcome does not depend on the
 // list order, so the fill's atomics leave it deterministic, and the depth test
 // needs no atomics.
@@ -3173,11 +3173,11 @@ __global__ __launch_bounds__(1024) void disc_bin_lds_kernel(DiscRenderItem, cons
     }
 }
 
-// One wavefront per tile, four pixels of one column per lane: the largest
-// Eq. 3 value over the tile's surfels whose disc holds the pixel, and the
-// lowest index among those that reach it.  The tile's list is staged in LDS,
-// 64 entries at a time (one entry and its raster record per lane, all loads
-// in flight at once).
+// A wavefront per tile with four pixels of one column per lane (PX = 4), or
+// four wavefronts with one (see raster_pixels): the largest Eq. 3 value over
+// the tile's surfels whose disc holds the pixel, and the lowest index among
+// those that reach it.  The tile's list is staged in LDS, 64 entries at a time
+// (one entry and its raster record per lane, all loads in flight at once).
 //
 // Bound: the chain of dependent loads in front of the walk (keyframe, range,
 // list, records), so what counts is how many tiles a CU holds: 32 with a
@@ -3186,33 +3186,34 @@ __global__ __launch_bounds__(1024) void disc_bin_lds_kernel(DiscRenderItem, cons
 // workgroup per tile, 29 / 63 / 159 now.  (Choosing by num * (1 / den), with
 // divisions only where two products come near each other: 29 / 65 / 165, and
 // 34 / 88 / 254 where all surfels lie on one plane.)
+template <int PX>
 __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
     DiscRenderItem, const DiscRenderItem* __restrict__ tab_, int n_items, int n_tiles,
     const DiscRaster* __restrict__ rec, const int32_t* __restrict__ count, const int32_t* __restrict__ start,
     const int32_t* __restrict__ list) {
 #pragma clang fp contract(off)
     const cptr<DiscRenderItem> tab = table_or_arg(tab_);
-    constexpr int kPx = 4;
-    static_assert(kRenderTile == 16 && kRenderTile * kRenderTile == kPx * kWaveSize, "a tile per wavefront");
+    constexpr int kParts = kRenderTile * kRenderTile / (PX * kWaveSize);      // wavefronts per tile
+    static_assert(kRenderTile == 16 && kParts * PX * kWaveSize == kRenderTile * kRenderTile, "tiles in whole wavefronts");
     __shared__ DiscRaster s_rec_[kBlockThreads / kWaveSize][kWaveSize];
     __shared__ int s_idx_[kBlockThreads / kWaveSize][kWaveSize];
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = threadIdx.x >> 6;
     DiscRaster* const s_rec = s_rec_[wave];
     int* const s_idx = s_idx_[wave];
-    const int t = grid_wave();
+    const int t = grid_wave() / kParts, part = grid_wave() % kParts;
     if (t >= n_tiles) return;
     const carg<DiscRenderItem>& a = tab[render_item_of_tile(tab, n_items, t)];
     const int lt = t - a.tile_base;
     const int ty = lt / a.tiles_x, tx = lt - ty * a.tiles_x;
     const int x = tx * kRenderTile + (lane & (kRenderTile - 1));
-    const int y0 = ty * kRenderTile + lane / kRenderTile;            // rows y0, y0 + 4, ...
+    const int y0 = ty * kRenderTile + 4 * PX * part + lane / kRenderTile;      // rows y0, y0 + 4, ...
     const double r = (double)a.radius, r2 = r * r;
     const double xd = (double)x, ru0 = (xd - a.cx) / a.fx;
-    double yd[kPx], ru1[kPx], val[kPx];
-    int who[kPx];
+    double yd[PX], ru1[PX], val[PX];
+    int who[PX];
 #pragma unroll
-    for (int p = 0; p < kPx; ++p) {
+    for (int p = 0; p < PX; ++p) {
         yd[p] = (double)(y0 + 4 * p);
         ru1[p] = (yd[p] - a.cy) / a.fy;
         val[p] = 0.0;
@@ -3234,7 +3235,7 @@ __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
             const double dx = xd - q.cx, dx2 = dx * dx;
             const double nx = ru0 * q.n0;
 #pragma unroll
-            for (int p = 0; p < kPx; ++p) {
+            for (int p = 0; p < PX; ++p) {
                 const double dy = yd[p] - q.cy;
                 // (a branch: most entries miss all of a row group's pixels)
                 if (!(dx2 + dy * dy < r2)) continue;
@@ -3248,7 +3249,7 @@ __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
         }
     }
 #pragma unroll
-    for (int p = 0; p < kPx; ++p) {
+    for (int p = 0; p < PX; ++p) {
         const int y = y0 + 4 * p;
         if (x >= a.width || y >= a.height) continue;
         const size_t o = (size_t)y * (size_t)a.width + (size_t)x;
@@ -3680,7 +3681,7 @@ hipError_t launch_disc_gn(int dtype, const DiscForm& form, const LoneBatch& one,
 }
 
 hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* table, int n_items,
-                              int total_surfels, int total_tiles, bool bin_lds, const DiscRenderScratch& w,
+                              int total_surfels, int total_tiles, bool bin_lds, int px, const DiscRenderScratch& w,
                               hipStream_t s) {
     if (bin_lds) {
         disc_bin_lds_kernel<<<n_items, 1024, 0, s>>>(one, table, w.rec, w.count, w.start, w.list);
@@ -3695,8 +3696,9 @@ hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* t
             disc_fill_kernel<<<sblocks, 256, 0, s>>>(one, table, n_items, total_surfels, w.rec, w.start, w.list);
     }
     constexpr int wpb = kBlockThreads / kWaveSize;
-    disc_raster_kernel<<<(total_tiles + wpb - 1) / wpb, kBlockThreads, 0, s>>>(one, table, n_items, total_tiles, w.rec,
-                                                                               w.count, w.start, w.list);
+    const int waves = total_tiles * (4 / px);
+    auto* f = px == 1 ? disc_raster_kernel<1> : disc_raster_kernel<4>;
+    f<<<(waves + wpb - 1) / wpb, kBlockThreads, 0, s>>>(one, table, n_items, total_tiles, w.rec, w.count, w.start, w.list);
     return hipGetLastError();
 }
 

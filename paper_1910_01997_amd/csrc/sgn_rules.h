@@ -165,4 +165,22 @@ inline bool bin_in_lds(int keyframes, int64_t most_tiles, int64_t most_surfels) 
     return most_tiles <= kBinTiles && most_surfels <= (keyframes >= 12 ? kBinSurfels : 3072);
 }
 
+// Pixels per lane of the disc raster's wavefronts, for render tiles of 16 x 16
+// whose lists hold `mean` surfels by their discs' boxes.  Four, a wavefront per
+// tile, unless there are so few tiles that each SIMD has one wavefront or two
+// and each of those a long list to walk: then one, four wavefronts per tile.
+// Whole renders, one pixel per lane / four: 640x480 (1,200 tiles) 1,536 discs
+// of radius 12 (8 per list) 18.5 / 21.1 us, 12,288 (64) 67 / 80, 24,576 (128)
+// 114 / 133; two such keyframes (2,400) 25.4 / 26.1, 87 / 96, 152 / 157;
+// 1280x720 (3,600) 31.8 / 31.2, 105 / 102, 192 / 182.  With shorter lists both
+// are within about 2 us of each other either way.
+inline int raster_pixels(int64_t tiles, double mean, int cus) {
+    return mean >= 8.0 && tiles <= 5 * (int64_t)cus ? 1 : 4;
+}
+// Render tiles that a disc's box meets, on average over where its centre lies.
+inline double mean_tiles(double radius, int tile) {
+    const double m = 1.0 + 2.0 * radius / tile;
+    return m * m;
+}
+
 }  // namespace sgn

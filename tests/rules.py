@@ -25,6 +25,8 @@ int rows_by_index_safe(uint64_t data, int w, int h, size_t pitch_b, int elem, ui
 }
 int bin_in_lds(int keyframes, int64_t tiles, int64_t surfels) { return sgn::bin_in_lds(keyframes, tiles, surfels); }
 int init_reach(float beta_r, int patch) { return sgn::init_reach(beta_r, patch); }
+int raster_pixels(int64_t tiles, double mean, int cus) { return sgn::raster_pixels(tiles, mean, cus); }
+double mean_tiles(double radius, int tile) { return sgn::mean_tiles(radius, tile); }
 int disc_form(double w, double slots, int f32, int damped) {
     const sgn::DiscForm f = sgn::disc_form(w, slots, f32, damped);
     return f.waves * 100 + f.deep * 10 + f.shared;
@@ -51,5 +53,8 @@ def lib():
     L.item_blocks.argtypes = [C.c_int, C.c_void_p, C.c_int, C.c_int]
     L.bin_in_lds.argtypes = [C.c_int, C.c_int64, C.c_int64]
     L.init_reach.argtypes = [C.c_float, C.c_int]
+    L.raster_pixels.argtypes = [C.c_int64, C.c_double, C.c_int]
+    L.mean_tiles.argtypes = [C.c_double, C.c_int]
+    L.mean_tiles.restype = C.c_double
     L.disc_form.argtypes = [C.c_double, C.c_double, C.c_int, C.c_int]
     return L

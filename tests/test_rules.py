@@ -114,3 +114,14 @@ def test_init_reach_counts_the_tiles_that_a_radius_meets():
             met = max(t for t in range(9) if max(0.0, t * s - centre) < br)          # the tile t's nearest pixel
             assert lib().init_reach(br, s) == met
         assert lib().init_reach(3e38, s) > 16384
+
+
+def test_raster_takes_a_pixel_per_lane_for_few_tiles_with_long_lists():
+    """The expected list is the surfels' boxes over the tiles, counted here for
+    centres spread evenly over a plane of whole tiles."""
+    for r in (0.5, 2.5, 6.0, 12.0):
+        at = (np.arange(1600) + 0.5) / 100.0                    # a tile's width of centres
+        met = np.floor((at + r) / 16.0) - np.floor((at - r) / 16.0) + 1
+        assert abs(met.mean() ** 2 - lib().mean_tiles(r, 16)) < 0.01 * lib().mean_tiles(r, 16)
+    assert lib().raster_pixels(1280, 8.0, 256) == 1 and lib().raster_pixels(1, 9.0, 256) == 1
+    assert lib().raster_pixels(1281, 500.0, 256) == 4 and lib().raster_pixels(1, 7.9, 256) == 4
