@@ -460,17 +460,19 @@ std::vector<int> share_order(int nq, const std::vector<int64_t>& work, const std
     return order;
 }
 
-// Bytes of a keyframe's images, its own and its neighbours', over the batch by
-// pixels.
-double mean_image_bytes(const sgn_batch_item* items, int n) {
-    double bytes = 0.0, pixels = 0.0;
+// A keyframe's pixels and the bytes of its images, its own and its
+// neighbours', over the batch by pixels.
+void mean_images(const sgn_batch_item* items, int n, double* pixels, double* bytes) {
+    double p = 0.0, p2 = 0.0, b = 0.0;
     for (int i = 0; i < n; ++i) {
         const sgn_keyframe& kf = items[i].kf;
         const double px = (double)kf.kf.width * kf.kf.height;
-        bytes += px * px * dtype_size(kf.kf.dtype) * (kf.n_nbr + 1);
-        pixels += px;
+        p += px;
+        p2 += px * px;
+        b += px * px * dtype_size(kf.kf.dtype) * (kf.n_nbr + 1);
     }
-    return pixels > 0.0 ? bytes / pixels : 0.0;
+    *pixels = p > 0.0 ? p2 / p : 0.0;
+    *bytes = p > 0.0 ? b / p : 0.0;
 }
 
 // The form of a four-pixels-per-lane kernel (the 4x4 layout of 4x4 surfels,
@@ -509,17 +511,16 @@ double mean_image_bytes(const sgn_batch_item* items, int n) {
 // 1.5, three wavefronts per SIMD by their LDS (130 against four lanes' 139 at
 // 910, 151 / 214 unsplit at 1,530, but 225 / 217 at 1,900); it steps in
 // gn_kernel beyond: two frames in flight to w = 3 (f16 209 us against 246 for
-// one sample at a time at 1,900 items), one to w = 24 and for such images and
-// f32 beyond (f16 4.20 ms against 4.30 at 57,600 items of 1280x720, 16 x 16
-// surfels 3.73 / 3.93; f32 4.50 / 5.02), else one sample at a time (u8 4.32
-// against 4.39).
+// one sample at a time at 1,900 items), then one or none (damped_one_frame).
 void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn_params* prm, GnVariant& v) {
     const bool four_px = v.patch == 16 || (v.patch == 4 && v.tiles_x == 4 && v.tiles_y == 4);
     if (!four_px || v.persistent) return;
     const int64_t total = count_items(items, n, item_geo(v.patch, v.tiles_x, v.tiles_y, v.groups));
     const double w = (double)total / (4.0 * std::max(1, c->cus));
     v.damped = prm->lm_lambda > 0.f;
-    const bool far_taps = v.dtype == SGN_F32 || (v.dtype == SGN_F16 && mean_image_bytes(items, n) > 8e6);
+    double pixels, bytes;
+    mean_images(items, n, &pixels, &bytes);
+    const bool far_taps = v.dtype == SGN_F32 || (v.dtype == SGN_F16 && bytes > 8e6);
     if (v.patch == 4 && w <= (v.damped ? 0.75 : 0.65)) {
         v.split = 4; v.deep = 4; v.tiles_x = 2; v.tiles_y = 2;
     } else if (v.patch == 4 && w <= (v.damped ? 1.5 : 2.5)) {
@@ -527,7 +528,7 @@ void choose_form(const sgn_ctx* c, const sgn_batch_item* items, int n, const sgn
     } else if (w <= (v.damped ? 3.0 : 1.75)) {
         v.deep = 2;
     } else if (v.damped) {
-        v.deep = w <= 24.0 || far_taps;
+        v.deep = damped_one_frame(w, v.patch, pixels, bytes, bytes / (pixels * dtype_size(v.dtype)) - 1.0, far_taps);
     } else {
         v.shared = 1;
         v.deep = w <= 3.0 || v.dtype == SGN_F32 || (far_taps && w > 24.0);

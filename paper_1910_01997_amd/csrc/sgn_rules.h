@@ -150,6 +150,39 @@ inline DiscForm disc_form(double w, double slots, bool f32, bool damped) {
     return {1, f32 ? 2 : 0, 0};
 }
 
+// Damped four-pixels-per-lane batches of w > 3 items per SIMD: one frame's taps
+// in flight, five wavefronts per SIMD, or one sample at a time, seven (whole
+// calls, one frame / one sample, us).  A keyframe has `pixels` pixels, `frames`
+// neighbours and `bytes` of images.
+//   w <= 5     one frame, all resident: 291 / 303 (320x240 f16, six neighbours, w
+//              = 3.2); small keyframes of many neighbours to 4.1 only: 704 / 676
+//              f16, 642 / 615 f32 (320x240, twelve, w = 4.7).
+//   w <= 7     one sample, all resident at seven only, for 16 x 16 surfels (270 /
+//              251 f16, 261 / 237 f32, 640x480, w = 5.9) and small keyframes (421
+//              / 390 f16, 399 / 354 f32, 320x240); else to w = 6.2 where L2 holds
+//              much of the images: 315 / 303 u8, but 551 / 622 f16 with twelve
+//              neighbours (8 MB), 293 / 379 f32 (640x480, w = 5.9); 388 / 428 f16
+//              (480x360, nine, w = 6.7).
+//   w <= 9     one frame: one sample's second round is nearly empty: 562 / 578 and,
+//              twelve neighbours, 1,172 / 1,266 (320x240 f16, w = 8.2), 397 / 413
+//              (640x480); 16 x 16 ones 436 / 454 f32 (320x240, twelve, w = 8.8).
+//   beyond     one frame to w = 24, and further where taps come from far (4x4
+//              surfels 2,541 / 3,178 f16 of 24 MB, 1,346 / 1,770 f32 of 26 MB, w =
+//              28); one sample for small images: 4x4 surfels of few neighbours
+//              988 / 936 f16, 912 / 873 f32 (320x240, six, w = 16; twelve equal,
+//              400x304, nine, 899 / 925), 16 x 16 ones 847 / 793 f16 (320x240), 438 /
+//              415 u8 (480x360), but 795 / 826 f32 of 4.9 MB (400x304).
+inline bool damped_one_frame(double w, int patch, double pixels, double bytes, double frames, bool far_taps) {
+    const bool tiny = pixels < 100e3;
+    if (w <= (patch == 4 && tiny && frames >= 8.0 ? 4.1 : 5.0)) return true;
+    if (w <= 7.0 && (patch == 16 || tiny)) return false;
+    if (w <= 6.2 && bytes < 4.5e6) return false;
+    if (w <= 9.0) return true;
+    const bool near = patch == 16 ? tiny || (pixels < 250e3 && bytes < 2.4e6)
+                                  : pixels < 150e3 && bytes < 2.2e6 && frames < 8.0;
+    return !near && (w <= 24.0 || far_taps);
+}
+
 // Whether the disc render bins each keyframe in one workgroup's LDS: its tile
 // counts have to fit, and the largest keyframe's surfels, which one CU then
 // works through, must not take longer than the launches that are saved.  Few

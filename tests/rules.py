@@ -24,6 +24,9 @@ int rows_by_index_safe(uint64_t data, int w, int h, size_t pitch_b, int elem, ui
     return sgn::rows_by_index_safe(data, w, h, pitch_b, elem, next, [&](uintptr_t) { return (uintptr_t)mapped; });
 }
 int bin_in_lds(int keyframes, int64_t tiles, int64_t surfels) { return sgn::bin_in_lds(keyframes, tiles, surfels); }
+int damped_one_frame(double w, int patch, double pixels, double bytes, double frames, int far_taps) {
+    return sgn::damped_one_frame(w, patch, pixels, bytes, frames, far_taps != 0);
+}
 int init_reach(float beta_r, int patch) { return sgn::init_reach(beta_r, patch); }
 int raster_pixels(int64_t tiles, double mean, int cus) { return sgn::raster_pixels(tiles, mean, cus); }
 double mean_tiles(double radius, int tile) { return sgn::mean_tiles(radius, tile); }
@@ -52,6 +55,7 @@ def lib():
     L.cut_shares.restype = None
     L.item_blocks.argtypes = [C.c_int, C.c_void_p, C.c_int, C.c_int]
     L.bin_in_lds.argtypes = [C.c_int, C.c_int64, C.c_int64]
+    L.damped_one_frame.argtypes = [C.c_double, C.c_int, C.c_double, C.c_double, C.c_double, C.c_int]
     L.init_reach.argtypes = [C.c_float, C.c_int]
     L.raster_pixels.argtypes = [C.c_int64, C.c_double, C.c_int]
     L.mean_tiles.argtypes = [C.c_double, C.c_int]

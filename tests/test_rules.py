@@ -125,3 +125,22 @@ def test_raster_takes_a_pixel_per_lane_for_few_tiles_with_long_lists():
         assert abs(met.mean() ** 2 - lib().mean_tiles(r, 16)) < 0.01 * lib().mean_tiles(r, 16)
     assert lib().raster_pixels(1280, 8.0, 256) == 1 and lib().raster_pixels(1, 9.0, 256) == 1
     assert lib().raster_pixels(1281, 500.0, 256) == 4 and lib().raster_pixels(1, 7.9, 256) == 4
+
+
+@pytest.mark.parametrize("patch", [4, 16])
+def test_damped_batches_that_only_seven_wavefronts_per_simd_hold_take_that_form(patch):
+    """Between five and seven items per SIMD one round of one sample at a time
+    against two of one frame in flight; large images' taps outweigh it for 4x4
+    surfels."""
+    def one(w, width, height, elem, frames):
+        px = width * height
+        b = px * elem * (frames + 1)
+        return bool(lib().damped_one_frame(w, patch, px, b, frames, elem == 4 or elem == 2 and b > 8e6))
+    for w in (5.01, 6.0, 6.2, 6.9, 7.0):
+        assert not one(w, 320, 240, 2, 6) and not one(w, 320, 240, 4, 12)
+        assert one(w, 640, 480, 4, 6) == (patch == 4) and one(w, 640, 480, 1, 6) == (patch == 4 and w > 6.2)
+    for w in (3.01, 4.0, 7.01, 9.0):
+        assert one(w, 320, 240, 2, 12) and one(w, 640, 480, 4, 6)
+    assert one(5.0, 320, 240, 2, 6) and one(5.0, 320, 240, 2, 12) == (patch == 16)
+    for w in (9.01, 24.0, 24.1, 100.0):
+        assert not one(w, 320, 240, 2, 6) and one(w, 640, 480, 4, 6) and one(w, 640, 480, 2, 6) == (w <= 24.0)
