@@ -1323,10 +1323,12 @@ sgn_status sgn_disc_place_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t 
     if (!c) return fail(SGN_E_INVALID, "null context");
     SGN_HIP(hipSetDevice(c->device));
     for (int i = 0; i < n; ++i) tab[i].cand_flag = (uint8_t*)ws + tab[i].cand_base;
-    const DiscPlaceArgs* dtab;
-    st = upload_table(c, tab.data(), n, &dtab);
-    if (st) return st;
-    hipError_t e = launch_disc_place(tab[0], dtab, n, (int)total_cands, (int)total_init, c->stream);
+    const DiscPlaceArgs* dtab = nullptr;
+    if (n > kDiscPlaceArgs) {
+        st = upload_table(c, tab.data(), n, &dtab);
+        if (st) return st;
+    }
+    hipError_t e = launch_disc_place(tab.data(), dtab, n, (int)total_cands, (int)total_init, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc placement launch");
     return SGN_OK;
 }

@@ -325,10 +325,11 @@ struct DiscPlaceArgs {
     int32_t cand_base;            // candidates of the table's earlier keyframes
     int32_t init_base;            // new-surfel slots (min(room, candidates)) of earlier keyframes
 };
-// Placement for a device table of n_items keyframes: search (one wavefront
-// per candidate), compaction (one workgroup per keyframe), initialisation
-// (one wavefront per new-surfel slot).
-hipError_t launch_disc_place(const DiscPlaceArgs& one, const DiscPlaceArgs* table, int n_items,
+// Placement for n_items keyframes: search (one wavefront per candidate),
+// compaction (one workgroup per keyframe), initialisation (one wavefront per
+// new-surfel slot).  table (device) may be null up to kDiscPlaceArgs keyframes.
+constexpr int kDiscPlaceArgs = 16;
+hipError_t launch_disc_place(const DiscPlaceArgs* items, const DiscPlaceArgs* table, int n_items,
                              int total_cands, int total_init, hipStream_t s);
 // Eq. 10 for disc surfels: each usable source surfel moves to p' = R p + t,
 // n' = R n, and is re-centred at K_dst pi(p'); those landing in the

@@ -3258,10 +3258,15 @@ __global__ __launch_bounds__(kBlockThreads) void disc_raster_kernel(
     }
 }
 
-// Placement runs over a table of keyframes: candidates and new surfels are
+// Placement runs over a table of keyframes (up to kDiscPlaceArgs of them in the
+// kernels' arguments, as in the disc transfer): candidates and new surfels are
 // numbered keyframe after keyframe (cand_base, init_base); the entry owning
 // number g is the last whose base is <= g (entries with none share the next
 // base and are never the last).
+template <int N>
+struct DiscPlaceTab {
+    DiscPlaceArgs item[N];
+};
 __device__ __forceinline__ int place_entry_of_cand(cptr<DiscPlaceArgs> tab, int n, int g) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
@@ -3306,7 +3311,8 @@ __device__ __forceinline__ WindowPixel window_pixel(int k, int side, int reach, 
 // spacing), its lanes sharing the window of pixels within alpha r; the
 // candidate qualifies when no non-empty pixel of the index map lies within
 // alpha r (integer squared distance against (alpha r)^2 in double).
-__global__ __launch_bounds__(kBlockThreads) void disc_search_kernel(DiscPlaceArgs, const DiscPlaceArgs* __restrict__ tab_,
+template <int N>
+__global__ __launch_bounds__(kBlockThreads) void disc_search_kernel(DiscPlaceTab<N>, const DiscPlaceArgs* __restrict__ tab_,
                                                                     int n_items, int total) {
     const cptr<DiscPlaceArgs> tab = table_or_arg(tab_);
     const int lane = threadIdx.x & (kWaveSize - 1);
@@ -3356,7 +3362,8 @@ __global__ __launch_bounds__(kBlockThreads) void disc_search_kernel(DiscPlaceArg
 // first, first + 1, ... (as many as there is room for); counts[0] = placed,
 // counts[1] = qualifying.  One workgroup per keyframe scans its flags in
 // chunks.
-__global__ __launch_bounds__(1024) void disc_compact_kernel(DiscPlaceArgs, const DiscPlaceArgs* __restrict__ tab_) {
+template <int N>
+__global__ __launch_bounds__(1024) void disc_compact_kernel(DiscPlaceTab<N>, const DiscPlaceArgs* __restrict__ tab_) {
     const cptr<DiscPlaceArgs> tab = table_or_arg(tab_);
     const carg<DiscPlaceArgs>& a = tab[blockIdx.x];
     __shared__ int s_wave[1024 / kWaveSize + 1];
@@ -3419,7 +3426,8 @@ __device__ __forceinline__ int wave_min(int v) {
 // one lane each, and all their surfels loaded together, as are the window's
 // pixels: bound by latency, a 640x480 keyframe's new surfels took 21 us with
 // the loads one after another and take 11.
-__global__ __launch_bounds__(kWaveSize) void disc_init_kernel(DiscPlaceArgs, const DiscPlaceArgs* __restrict__ tab_,
+template <int N>
+__global__ __launch_bounds__(kWaveSize) void disc_init_kernel(DiscPlaceTab<N>, const DiscPlaceArgs* __restrict__ tab_,
                                                               int n_items) {
     const cptr<DiscPlaceArgs> tab = table_or_arg(tab_);
     // the window's surfel indices (those within beta r, below `first`), or -1
@@ -3702,15 +3710,27 @@ hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* t
     return hipGetLastError();
 }
 
-hipError_t launch_disc_place(const DiscPlaceArgs& one, const DiscPlaceArgs* table, int n_items,
-                             int total_cands, int total_init, hipStream_t s) {
+template <int N>
+static hipError_t launch_place(const DiscPlaceTab<N>& by_value, const DiscPlaceArgs* table, int n_items,
+                               int total_cands, int total_init, hipStream_t s) {
     const int waves = kBlockThreads / kWaveSize;
     if (total_cands > 0)
-        disc_search_kernel<<<(total_cands + waves - 1) / waves, kBlockThreads, 0, s>>>(one, table, n_items,
-                                                                                        total_cands);
-    disc_compact_kernel<<<n_items, 1024, 0, s>>>(one, table);
-    if (total_init > 0) disc_init_kernel<<<total_init, kWaveSize, 0, s>>>(one, table, n_items);
+        disc_search_kernel<N><<<(total_cands + waves - 1) / waves, kBlockThreads, 0, s>>>(by_value, table, n_items,
+                                                                                           total_cands);
+    disc_compact_kernel<N><<<n_items, 1024, 0, s>>>(by_value, table);
+    if (total_init > 0) disc_init_kernel<N><<<total_init, kWaveSize, 0, s>>>(by_value, table, n_items);
     return hipGetLastError();
+}
+
+hipError_t launch_disc_place(const DiscPlaceArgs* items, const DiscPlaceArgs* table, int n_items,
+                             int total_cands, int total_init, hipStream_t s) {
+    static_assert(sizeof(DiscPlaceTab<kDiscPlaceArgs>) + sizeof(table) + 8 <= 4096, "kernel arguments");
+    if (table || n_items == 1)
+        return launch_place(DiscPlaceTab<1>{{items[0]}}, table, n_items, total_cands, total_init, s);
+    DiscPlaceTab<kDiscPlaceArgs> t;
+    std::copy(items, items + n_items, t.item);
+    std::fill(t.item + n_items, t.item + kDiscPlaceArgs, DiscPlaceArgs{});
+    return launch_place(t, nullptr, n_items, total_cands, total_init, s);
 }
 
 }  // namespace sgn
