@@ -1282,6 +1282,7 @@ sgn_status sgn_disc_place_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t 
     if (pp->spacing < 1 || pp->spacing > 1024) return fail(SGN_E_INVALID, "spacing must be in [1, 1024]");
     std::vector<DiscPlaceArgs> tab(n);
     int64_t total_cands = 0, total_init = 0;
+    int widest = 0;                          // side of the neighbour windows
     for (int i = 0; i < n; ++i) {
         const sgn_disc_item* item = &items[i];
         sgn_status st = check_disc_item(item, false);
@@ -1310,6 +1311,7 @@ sgn_status sgn_disc_place_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t 
         a.radius = item->radius; a.alpha = pp->alpha; a.beta = pp->beta;
         a.fx = (float)item->kf.K.fx; a.fy = (float)item->kf.K.fy;
         a.cx = (float)item->kf.K.cx; a.cy = (float)item->kf.K.cy;
+        widest = std::max(widest, 2 * (int)std::ceil((double)pp->beta * (double)item->radius) + 1);
         a.counts = counts_outs[i];
         a.cand_base = (int32_t)total_cands;
         a.init_base = (int32_t)total_init;
@@ -1328,7 +1330,8 @@ sgn_status sgn_disc_place_batch(sgn_ctx* c, const sgn_disc_item* items, int32_t 
         st = upload_table(c, tab.data(), n, &dtab);
         if (st) return st;
     }
-    hipError_t e = launch_disc_place(tab.data(), dtab, n, (int)total_cands, (int)total_init, c->stream);
+    hipError_t e = launch_disc_place(tab.data(), dtab, n, (int)total_cands, (int)total_init,
+                                           widest * widest <= 2 * kWaveSize, c->stream);
     if (e != hipSuccess) return hip_fail(e, "disc placement launch");
     return SGN_OK;
 }

@@ -327,10 +327,11 @@ struct DiscPlaceArgs {
 };
 // Placement for n_items keyframes: search (one wavefront per candidate),
 // compaction (one workgroup per keyframe), initialisation (one wavefront per
-// new-surfel slot).  table (device) may be null up to kDiscPlaceArgs keyframes.
+// new-surfel slot; small: no window of theirs has more than two pixels per lane).
+// table (device) may be null up to kDiscPlaceArgs keyframes.
 constexpr int kDiscPlaceArgs = 16;
 hipError_t launch_disc_place(const DiscPlaceArgs* items, const DiscPlaceArgs* table, int n_items,
-                             int total_cands, int total_init, hipStream_t s);
+                             int total_cands, int total_init, bool small, hipStream_t s);
 // Eq. 10 for disc surfels: each usable source surfel moves to p' = R p + t,
 // n' = R n, and is re-centred at K_dst pi(p'); those landing in the
 // destination image are written in source order.

@@ -3425,8 +3425,11 @@ __device__ __forceinline__ int wave_min(int v) {
 // usable: UNINIT with id 0 and n = (0, 0, -1).  The indices are found first,
 // one lane each, and all their surfels loaded together, as are the window's
 // pixels: bound by latency, a 640x480 keyframe's new surfels took 21 us with
-// the loads one after another and take 11.
-template <int N>
+// the loads one after another and take 11.  SLOTS pixels per lane: nine, or two
+// where that covers every window, which a placement of many small discs pays
+// for (4 empty 640x480 maps, radius 1.5: 672 us one at a time, 798 with nine,
+// 577 with two).
+template <int N, int SLOTS>
 __global__ __launch_bounds__(kWaveSize) void disc_init_kernel(DiscPlaceTab<N>, const DiscPlaceArgs* __restrict__ tab_,
                                                               int n_items) {
     const cptr<DiscPlaceArgs> tab = table_or_arg(tab_);
@@ -3444,18 +3447,18 @@ __global__ __launch_bounds__(kWaveSize) void disc_init_kernel(DiscPlaceTab<N>, c
     const int reach = (int)ceil(br);
     const int side = 2 * reach + 1, npix = side * side;
     const unsigned inv = window_inv(side);
-    // nine pixels per lane in flight at a time
-    for (int k0 = 0; k0 < npix; k0 += 9 * kWaveSize) {
-        int own[9];
-        bool in[9];
+    // SLOTS pixels per lane in flight at a time
+    for (int k0 = 0; k0 < npix; k0 += SLOTS * kWaveSize) {
+        int own[SLOTS];
+        bool in[SLOTS];
 #pragma unroll
-        for (int u = 0; u < 9; ++u) {
+        for (int u = 0; u < SLOTS; ++u) {
             const WindowPixel w = window_pixel(k0 + u * kWaveSize + lane, side, reach, inv, cx, cy, a.width, a.height);
             in[u] = w.inside && (double)(w.dx * w.dx + w.dy * w.dy) < br2;
             own[u] = a.index_map[w.at];
         }
 #pragma unroll
-        for (int u = 0; u < 9; ++u) {
+        for (int u = 0; u < SLOTS; ++u) {
             const int k = k0 + u * kWaveSize + lane;
             if (k < npix) s_win[k] = in[u] && own[u] < a.first ? own[u] : -1;
         }
@@ -3712,25 +3715,26 @@ hipError_t launch_disc_render(const DiscRenderItem& one, const DiscRenderItem* t
 
 template <int N>
 static hipError_t launch_place(const DiscPlaceTab<N>& by_value, const DiscPlaceArgs* table, int n_items,
-                               int total_cands, int total_init, hipStream_t s) {
+                               int total_cands, int total_init, bool small, hipStream_t s) {
     const int waves = kBlockThreads / kWaveSize;
     if (total_cands > 0)
         disc_search_kernel<N><<<(total_cands + waves - 1) / waves, kBlockThreads, 0, s>>>(by_value, table, n_items,
                                                                                            total_cands);
     disc_compact_kernel<N><<<n_items, 1024, 0, s>>>(by_value, table);
-    if (total_init > 0) disc_init_kernel<N><<<total_init, kWaveSize, 0, s>>>(by_value, table, n_items);
+    auto* init = small ? disc_init_kernel<N, 2> : disc_init_kernel<N, 9>;
+    if (total_init > 0) init<<<total_init, kWaveSize, 0, s>>>(by_value, table, n_items);
     return hipGetLastError();
 }
 
 hipError_t launch_disc_place(const DiscPlaceArgs* items, const DiscPlaceArgs* table, int n_items,
-                             int total_cands, int total_init, hipStream_t s) {
+                             int total_cands, int total_init, bool small, hipStream_t s) {
     static_assert(sizeof(DiscPlaceTab<kDiscPlaceArgs>) + sizeof(table) + 8 <= 4096, "kernel arguments");
     if (table || n_items == 1)
-        return launch_place(DiscPlaceTab<1>{{items[0]}}, table, n_items, total_cands, total_init, s);
+        return launch_place(DiscPlaceTab<1>{{items[0]}}, table, n_items, total_cands, total_init, small, s);
     DiscPlaceTab<kDiscPlaceArgs> t;
     std::copy(items, items + n_items, t.item);
     std::fill(t.item + n_items, t.item + kDiscPlaceArgs, DiscPlaceArgs{});
-    return launch_place(t, nullptr, n_items, total_cands, total_init, s);
+    return launch_place(t, nullptr, n_items, total_cands, total_init, small, s);
 }
 
 }  // namespace sgn
