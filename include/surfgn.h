@@ -38,9 +38,10 @@
  *     per call; about 2 MB on the device and four times that in pinned host
  *     staging memory), the work-queue counters and timing events.  sgn_create
  *     allocates all of it; no other call allocates device or pinned memory.
- *     A call for one keyframe (or keyframe pair, or up to eleven pairs of a
- *     disc transfer) passes its descriptors in its kernels' arguments and uses
- *     no table, unless its plan bounds a persistent grid.
+ *     A call for one keyframe (or keyframe pair, up to eleven pairs of a disc
+ *     transfer, up to sixteen keyframes of a disc placement) passes its
+ *     descriptors in its kernels' arguments and uses no table, unless its plan
+ *     bounds a persistent grid.
  *   - Calls that need scratch memory (re-gridding, disc render and
  *     placement, the autotuner's state snapshot) take a caller-provided
  *     workspace `ws` of `ws_bytes` bytes: device memory, 256-byte aligned, at
